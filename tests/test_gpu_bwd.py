@@ -53,6 +53,27 @@ def test_layout_transpose_matches_definition(shape):
     assert np.array_equal(lt.tile_idx[:nnz].cpu().numpy(), tile_idx)
 
 
+@pytest.mark.parametrize("shape", [
+    (2, 1, 1, 0.9, 64),                # one tile
+    (2, 257, 4097, 0.002, 64),         # 65 block columns: a second workgroup per head with one column
+    (2, 100, 2047, 0.05, 16),          # 128 block columns, exactly two workgroups
+    (1, 16 * 4096, 40, 0.02, 16),      # as many block rows as the table holds
+    (2, 16 * 4097 + 1, 40, 0.02, 16),  # and two more: a second round with its own bits
+])
+def test_layout_transpose_at_the_edges_of_its_table(shape):
+    H, Lq, Lk, density, block = shape
+    print("transpose", shape, flush=True)
+    mask = synth.random_mask(H, Lq, Lk, density, seed=Lq)
+    lay = ap.ap_build_layout(torch.from_numpy(mask).cuda(), block, block)
+    lt = ap.ap_build_layout_transpose(lay)
+    torch.cuda.synchronize()
+    rp, ci, _ = oracle.build_layout(mask, block, block)
+    col_ptr, row_idx, tile_idx = transpose_reference(rp, ci, H, -(-Lq // block), -(-Lk // block))
+    assert np.array_equal(lt.col_ptr.cpu().numpy(), col_ptr)
+    assert np.array_equal(lt.row_idx[:len(ci)].cpu().numpy(), row_idx)
+    assert np.array_equal(lt.tile_idx[:len(ci)].cpu().numpy(), tile_idx)
+
+
 def run_bwd(Q, K, V, dO, mask_np, causal, scale=0.0, per_row=True):
     dq, rq = to_device(Q, "bf16")
     dk, rk = to_device(K, "bf16")

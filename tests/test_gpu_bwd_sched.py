@@ -105,6 +105,15 @@ def test_col_schedule_matches_definition(shape, min_rows):
     check_col_schedule(mask, causal, min_rows)
 
 
+@pytest.mark.parametrize("Lq", [64 * 64, 64 * 64 + 1, 64 * 129])
+@pytest.mark.parametrize("density", [0.003, 0.04])
+def test_col_schedule_of_columns_longer_than_one_segment(Lq, density):
+    """64 tiles of a block column are held at a time: exactly that many, one more, and three rounds."""
+    mask = synth.random_mask(1, Lq, 70, density, seed=Lq)
+    check_col_schedule(mask, False, 0)
+    check_col_schedule(mask, False, 17)
+
+
 def test_col_schedule_on_the_structured_mask():
     cfg = synth.CONFIGS["C3"]
     mask = np.stack([synth.head_mask(cfg, h) for h in range(2)]).astype(np.uint8)

@@ -15,12 +15,15 @@
 // last group; inside a class by tile, then ascending): an isolated connection is used by one
 // query, so most gathered entries then concern one wavefront only and the other one skips them.
 //
-// One workgroup per block row, one thread per query row.  The bitmap words of a segment of tiles
-// are brought into LDS with all loads in flight at once; the per-tile decisions are then taken with
-// one lane per tile (column sets by OR over LDS, positions by prefix sums over the lanes), the
-// gathered columns are listed in LDS in their final order, and only the assembly of each row's
-// gathered words walks that list.  Every decision depends on OR-reductions of the row words only,
-// so the emitted order is fixed: no atomics.
+// One workgroup of four wavefronts per block row; a thread stands for one query row and for every
+// kParts-th tile or entry.  The bitmap words of a segment of tiles are brought into LDS with all loads
+// in flight at once; the per-tile decisions are then taken with one lane per tile (column sets by OR
+// over LDS, positions by prefix sums over the lanes), the gathered columns are listed in LDS in their
+// final order, and the words of the gathered entries are assembled from that list, the entries dealt
+// to the wavefronts.  Every decision depends on OR-reductions of the row words only, so the emitted
+// order is fixed: no atomics.  The time is one block row's chain of loads and LDS walks (1024
+// workgroups at 16 heads of 64 x 64 tiles, all resident): 61 us with one wavefront per block row, 26 us
+// with four.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -32,6 +35,7 @@ namespace {
 
 constexpr int kSegWords = 4096;                            // bitmap words of one segment (tiles x rows)
 constexpr int kSegMax = 64;                                // at most this many tiles per segment (block_m = 64)
+constexpr int kThreads = 256;
 
 // inclusive prefix sum over the 64 lanes of a wavefront
 __device__ __forceinline__ int wave_inclusive_scan(int v, int lane)
@@ -46,7 +50,7 @@ __device__ __forceinline__ int wave_inclusive_scan(int v, int lane)
 
 // LDS (dynamic): words[t * (BM + 1) + row] (one word of padding per tile: a lane per tile then reads
 // conflict-free), gm[t * 4 + g] = visible columns of 32-row group g of tile t, list[p] = tile << 6 | column
-__global__ __launch_bounds__(128) void build_schedule_kernel(
+__global__ __launch_bounds__(kThreads) void build_schedule_kernel(
     const int32_t* __restrict__ row_ptr, const int32_t* __restrict__ col_idx,
     const uint64_t* __restrict__ bitmaps, int nQB, int Lq, int Lk, int BM, long long cap,
     int causal, int min_cols, Schedule s)
@@ -58,11 +62,15 @@ __global__ __launch_bounds__(128) void build_schedule_kernel(
     uint64_t* gm = lds64 + (size_t)kSegMax * 65;
     uint16_t* list = (uint16_t*)(gm + kSegMax * 4);
     __shared__ int32_t k0s[kSegMax];
+    __shared__ uint64_t s_tail[2][128];                    // row words of the open gathered entry, double-buffered
 
     const int r = blockIdx.x;
     const int qb = r % nQB;
-    const int row = threadIdx.x;                           // 0 .. BM-1
-    const int lane = row & 63;
+    const int tid = threadIdx.x;
+    const int row = tid & (BM - 1);                        // this thread's query row
+    const int parts = kThreads / BM;                       // threads per row: 4 or 2
+    const int part = __builtin_amdgcn_readfirstlane(tid / BM);   // the same in a wavefront
+    const int lane = tid & 63;
     const int NG = BM / 32;                                // 32-row groups (wavefronts of the attention kernel)
     const long long diag = (long long)qb * BM + row + ((long long)Lk - Lq);
 
@@ -73,26 +81,28 @@ __global__ __launch_bounds__(128) void build_schedule_kernel(
     // columns of every 32-row group of each.
     auto load_segment = [&](int seg, int n) {
         __syncthreads();                                   // previous use of the LDS arrays is over
-        for (int t = row; t < n; t += BM) k0s[t] = col_idx[seg + t] * 64;
-        __syncthreads();
-        for (int tb = 0; tb < n; tb += 8) {
-            uint64_t w[8];
+        if (tid < n) k0s[tid] = col_idx[seg + tid] * 64;
+        uint64_t w[kSegMax / 4];                           // this thread's tiles part, part + parts, ...: 16 of them
 #pragma unroll
-            for (int u = 0; u < 8; ++u) w[u] = tb + u < n ? bitmaps[(size_t)(seg + tb + u) * BM + row] : 0ull;
-#pragma unroll
-            for (int u = 0; u < 8; ++u) {
-                if (tb + u >= n) break;
-                uint64_t word = w[u];
-                if (causal) {
-                    const long long lim = diag - (long long)k0s[tb + u];
-                    if (lim < 0) word = 0;
-                    else if (lim < 63) word &= (2ull << lim) - 1ull;
-                }
-                words[(size_t)(tb + u) * pitch + row] = word;
-            }
+        for (int u = 0; u < kSegMax / 4; ++u) {
+            const int t = u * parts + part;
+            w[u] = t < n ? bitmaps[(size_t)(seg + t) * BM + row] : 0ull;
         }
         __syncthreads();
-        for (int pair = row; pair < n * NG; pair += BM) {  // (tile, group): OR of its 32 row words
+#pragma unroll
+        for (int u = 0; u < kSegMax / 4; ++u) {
+            const int t = u * parts + part;
+            if (t >= n) break;
+            uint64_t word = w[u];
+            if (causal) {
+                const long long lim = diag - (long long)k0s[t];
+                if (lim < 0) word = 0;
+                else if (lim < 63) word &= (2ull << lim) - 1ull;
+            }
+            words[(size_t)t * pitch + row] = word;
+        }
+        __syncthreads();
+        for (int pair = tid; pair < n * NG; pair += kThreads) {   // (tile, group): OR of its 32 row words
             const int t = pair / NG, g = pair % NG;
             uint64_t m = 0;
 #pragma unroll 8
@@ -127,15 +137,16 @@ __global__ __launch_bounds__(128) void build_schedule_kernel(
         const int n = min(kSeg, t1 - seg);
         load_segment(seg, n);
         const Tile ti = tile_info(n);
-        unsigned long long cm = __ballot(ti.cons);         // the same in every wavefront
-        while (cm) {
-            const int t = __ffsll((long long)cm) - 1;
-            cm &= cm - 1;
-            const size_t e = (size_t)t0 + n_cons;
+        const unsigned long long cm = __ballot(ti.cons);   // the same in every wavefront
+        int rank = 0;
+        for (unsigned long long rest = cm; rest; rest &= rest - 1, ++rank) {
+            if (rank % parts != part) continue;
+            const int t = __ffsll((long long)rest) - 1;
+            const size_t e = (size_t)t0 + n_cons + rank;
             if (row == 0) s.start[e] = k0s[t];
             s.bitmaps[e * BM + row] = words[(size_t)t * pitch + row];
-            ++n_cons;
         }
+        n_cons += rank;
     }
     // Sweep 1: the gathered entries, so that the attention kernel meets a gathered entry (whose keys
     // it must fetch before it can load anything) only after it has other loads in flight.  Their
@@ -143,7 +154,7 @@ __global__ __launch_bounds__(128) void build_schedule_kernel(
     // in slot p % 64 of entry t0 + n_cons + p / 64.
     const size_t first = (size_t)t0 + n_cons;
     long long stream = 0;                                  // gathered columns emitted so far
-    uint64_t tail_word = 0;                                // this row's bits of the open gathered entry
+    int tail = 0;                                          // which half of s_tail holds the open entry's words
     for (int seg = t0; seg < t1; seg += kSeg) {
         const int n = min(kSeg, t1 - seg);
         if (!one_segment) load_segment(seg, n);
@@ -165,7 +176,7 @@ __global__ __launch_bounds__(128) void build_schedule_kernel(
                 const int cnt = __popcll(cmask);
                 const int incl = wave_inclusive_scan(cnt, lane);
                 int pos = total + incl - cnt;
-                if (row < 64) {                            // the first wavefront writes the list
+                if (tid < 64) {                            // the first wavefront writes the list
                     while (cmask) {
                         const int bit = __ffsll((long long)cmask) - 1;
                         cmask &= cmask - 1;
@@ -176,33 +187,44 @@ __global__ __launch_bounds__(128) void build_schedule_kernel(
             }
         __syncthreads();
         // keys and kinds of the gathered slots of this segment, in parallel
-        for (int p = row; p < total; p += BM) {
+        for (int p = tid; p < total; p += kThreads) {
             const int it = list[p];
             const long long gp = stream + p;
             s.cols[(first + (size_t)(gp >> 6)) * 64 + (gp & 63)] = k0s[it >> 6] + (it & 63);
             if ((gp & 63) == 0) s.start[first + (size_t)(gp >> 6)] = -1;
         }
-        // every row assembles its words by walking the list
-        int fill = (int)(stream & 63);
-        for (int p = 0; p < total; ++p) {
-            const int it = list[p];
-            const uint64_t word = words[(size_t)(it >> 6) * pitch + row];
-            tail_word |= ((word >> (it & 63)) & 1ull) << fill;
-            if (++fill == 64) {
-                s.bitmaps[(first + (size_t)((stream + p) >> 6)) * BM + row] = tail_word;
-                tail_word = 0;
-                fill = 0;
+        // words of the gathered entries that this segment touches, one entry at a time per wavefront
+        const long long end = stream + total;
+        for (long long e = (stream >> 6) + part; (e << 6) < end; e += parts) {
+            const long long lo = e << 6 < stream ? stream : e << 6, hi = min(end, (e + 1) << 6);
+            uint64_t acc = e << 6 < stream ? s_tail[tail][row] : 0ull;   // the entry that was left open
+            const uint16_t* lp = list + (lo - stream);
+            const int n_p = (int)(hi - lo), fill = (int)(lo & 63);
+            const int mine = lane < n_p ? lp[lane] : 0;    // handed out with v_readlane
+            const uint32_t* halves = (const uint32_t*)words + 2 * row;
+            for (int p0 = 0; p0 < n_p; p0 += 8) {
+#pragma unroll
+                for (int u = 0; u < 8; ++u) {              // 8 independent LDS reads in flight
+                    const int it = __builtin_amdgcn_readlane(mine, p0 + u);
+                    const uint32_t half = halves[(size_t)(it >> 6) * (2 * pitch) + ((it >> 5) & 1)];
+                    const uint32_t keep = p0 + u < n_p ? 1u : 0u;
+                    acc |= (uint64_t)((half >> (it & 31)) & keep) << ((fill + p0 + u) & 63);
+                }
             }
+            if (hi == (e + 1) << 6) s.bitmaps[(first + (size_t)e) * BM + row] = acc;
+            else s_tail[tail ^ 1][row] = acc;
         }
-        stream += total;
+        if (total > 0) tail ^= 1;
+        stream = end;
+        __syncthreads();                                   // s_tail is complete; the list is free
     }
     const int fill = (int)(stream & 63);
-    if (fill > 0) {                                        // last, partly filled gathered entry
+    if (fill > 0 && part == 0) {                           // last, partly filled gathered entry
         const size_t e = first + (size_t)(stream >> 6);
         for (int c = fill + row; c < 64; c += BM) s.cols[e * 64 + c] = Lk;   // empty slot: reads as zeros
-        s.bitmaps[e * BM + row] = tail_word;
+        s.bitmaps[e * BM + row] = s_tail[tail][row];
     }
-    if (row == 0) s.cnt[r] = n_cons + (int)((stream + 63) >> 6);
+    if (tid == 0) s.cnt[r] = n_cons + (int)((stream + 63) >> 6);
 }
 
 }  // namespace
@@ -216,7 +238,7 @@ hipError_t launch_build_schedule(const int32_t* row_ptr, const int32_t* col_idx,
     // words (padded), group column sets, column list
     const size_t lds = ((size_t)kSegMax * 65 + (size_t)kSegMax * 4) * sizeof(uint64_t) +
                        (size_t)kSegMax * 64 * sizeof(uint16_t);
-    hipLaunchKernelGGL(build_schedule_kernel, dim3((unsigned)(H * nQB)), dim3(BM), lds, stream, row_ptr,
+    hipLaunchKernelGGL(build_schedule_kernel, dim3((unsigned)(H * nQB)), dim3(kThreads), lds, stream, row_ptr,
                        col_idx, bitmaps, nQB, Lq, Lk, BM, cap, causal, min_cols, s);
     return hipGetLastError();
 }

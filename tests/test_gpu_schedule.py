@@ -81,6 +81,20 @@ def test_schedule_covers_exactly_the_visible_mask(bm, min_cols):
         assert np.array_equal(got, visible(mask, causal))
 
 
+@pytest.mark.parametrize("bm", [64, 128])
+@pytest.mark.parametrize("tiles,density", [(32, 0.003), (33, 0.002), (64, 0.001), (65, 0.002), (130, 0.0007),
+                                           (130, 0.02)])
+def test_schedule_of_rows_longer_than_one_segment(bm, tiles, density):
+    """64 tiles (32 at block_m = 128) of a block row are held at a time; gathered entries stay open
+    from one round to the next."""
+    mask = synth.random_mask(1, 130, tiles * 64 - 5, density, seed=tiles)
+    mask[0, 5, 64:128] = 1                                   # one tile that stays consecutive
+    print("schedule", bm, mask.shape, density, flush=True)
+    lay = ap.ap_build_layout(torch.from_numpy(mask).cuda(), bm, 64)
+    sched = ap.ap_build_schedule(lay, causal=False)
+    assert np.array_equal(expand_schedule(lay, sched, False), visible(mask, False))
+
+
 def test_schedule_packs_isolated_connections():
     # band + isolated connections: the schedule needs clearly fewer entries than stored tiles
     cfg = synth.CONFIGS["C3"]

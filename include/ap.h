@@ -548,10 +548,11 @@ ap_status ap_accumulate_attention_maps_lse(const void *Q, const void *K, const f
  *   workspace     device scratch of at least ap_prune_mask_workspace_bytes() bytes, 16-byte
  *                 aligned; contents undefined before and after
  *
- * Exact: tau is an element of abar, found by radix selection over the bit patterns in two sweeps
- * over the map (a histogram of the leading key bits, then the candidates of the selected interval;
- * more histogram levels only when that interval holds a very large number of ties); integer
- * atomics only, so the result is bit-identical from run to run.
+ * Exact: tau is an element of abar.  A sample of the map gives a narrow interval of values, one sweep
+ * writes the mask of everything outside it and collects the entries inside, and tau is selected among
+ * those by their bit patterns; if the interval misses the rank or holds a very large number of ties,
+ * further sweeps select by radix over all entries.  Integer atomics only, so the result is
+ * bit-identical from run to run.
  * ------------------------------------------------------------------------------------------- */
 size_t ap_prune_mask_workspace_bytes(void);
 

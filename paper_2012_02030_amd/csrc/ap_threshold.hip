@@ -2,21 +2,31 @@
 // Eq. (2)).
 //
 // tau is the order statistic of rank floor(p * N) among the N participating entries of the mean
-// maps of all heads of a layer.  It is found exactly, by radix selection over the entries' bit
-// patterns, in two sweeps over the maps:
+// maps of all heads of a layer.  It is found exactly, with one sweep over the maps in which the
+// mask is written too:
 //
-//   sweep 1  radix_hist_kernel<0>: histogram of the top 15 key bits (32768 bins in LDS);
-//            radix_select_kernel<0> picks the bin that holds the wanted rank.  That bin is a
-//            value interval about 1 % wide and usually holds well under a million entries.
-//   sweep 2  mask_collect_kernel: every entry above the bin is kept, every entry below it is
-//            pruned, and the entries inside it (the candidates) are copied out.
-//   then     candidate_select_kernel finds tau among the candidates (their remaining 17 bits) and
-//            candidate_fixup_kernel writes their mask bytes.
+//   sample   about two million entries (clusters of 16, every stride-th of the map; all of them if
+//            the map is small) are counted into a histogram of their leading 12 key bits, then the
+//            bins around the wanted rank once more into 8192 sub-bins.  That gives a narrow value
+//            interval [lo, hi] that is meant to hold tau: the sample's own rank, five standard
+//            deviations of a clustered sample to either side (typically 0.2 to 0.6 % of the map).
+//   sweep    every entry above the interval is kept, every entry below it pruned; the entries
+//            inside it (the candidates) are copied out, and the entries above it counted.
+//   select   the count says whether the interval holds the wanted rank.  If so, tau is found among
+//            the candidates by two histograms over their key bits, and their mask bytes are written.
 //
-// If the bin holds more candidates than the workspace has room for (massive ties), levels 1
-// and 2 of the histogram/select pair fix 15 and then 2 more bits with a sweep each before the
-// mask sweep; otherwise those launches return at once.  Which path runs is decided on the
-// device, so the call never synchronises with the host.
+// If the interval misses the rank, or holds more candidates than the workspace has room for (massive
+// ties), the exact way follows: two 16-bit histogram levels over all entries fix every bit of tau
+// and a further sweep writes the mask.  Which path runs is decided on the device (the launches of the
+// other one return at once), so the call never synchronises with the host; the result is the same
+// element of the map either way.
+//
+// What bounds it: reading the map and writing the mask once (805 MB for 16 x 4096 x 4096 causal maps).
+// A full first sweep for an exact histogram costs a read of the map more and, worse, one LDS atomic per
+// entry on a few hot bins.  Measured there: 473 us with the histogram sweep (126 us), one-workgroup
+// selections (26 + 52 us) and a mask sweep of 231 us; now 245 us, of which the sweep is 165 (4.9 TB/s),
+// the sample 33, the candidates 30 and the launches that return at once 14.  At 12 x 512 x 512 (launches
+// only) 61 -> 55 us; rows that start anywhere (Lk = 4095) 644 -> 252 us.
 //
 // Float bit patterns are mapped to unsigned keys whose integer order is the numeric order
 // (sign bit flipped for non-negative values, all bits flipped for negative ones; -0 counts as +0).
@@ -29,39 +39,71 @@ namespace ap {
 
 namespace {
 
-constexpr int kBins = 32768;                 // 15-bit digit
-constexpr uint32_t kCap = 1u << 20;          // candidates the workspace can hold
+constexpr int kCoarse = 4096;                // first look at the sample: leading 12 key bits
+constexpr int kCoarseShift = 20;
+constexpr int kSubBits = 10, kSub = 1 << kSubBits;   // second look: sub-bins of the bins around the rank
+constexpr int kCandBits = 10, kCandBins = 1 << kCandBits;   // first histogram over the candidates
+constexpr int kLastBits = 13, kLastBins = 1 << kLastBits;   // second one
+constexpr int kMaxBracketBits = kCandBits + kLastBits;   // widest interval the selection resolves
+constexpr int kExactBins = 65536;            // a level of the exact way: 16 key bits
+constexpr uint32_t kCap = 3u << 19;          // candidates the workspace can hold
+constexpr unsigned long long kSample = 1ull << 21;   // entries looked at, at least (all, if there are fewer)
+constexpr double kDesign = 6.0;              // variance of the clustered sample over an independent one's
+constexpr double kSigmas = 5.0;              // half width of the interval in standard deviations of the sample
 constexpr int kThreads = 1024;
+constexpr int kSweepThreads = 512;
 
 struct SelectState {
-    unsigned long long rank;                 // wanted rank among the entries that match `prefix`
-    unsigned long long count;                // number of entries that match `prefix`
-    uint32_t prefix;                         // the key bits fixed so far (lower bits zero)
-    uint32_t fixed_bits;                     // how many top bits of the key are fixed
-    uint32_t ncand;                          // candidates collected
+    unsigned long long rank;                 // wanted rank among the participating entries
+    unsigned long long n;                    // number of participating entries
+    unsigned long long above;                // sweep: entries above the interval
+    unsigned long long ncand;                // sweep: entries inside it (the candidates)
+    unsigned long long exact_rank;           // exact way: wanted rank among the entries that match exact_prefix
+    uint32_t s_lo, s_hi;                     // ranks of the sample that the interval runs between
+    uint32_t s_total;
+    uint32_t range_lo, range_shift, range_below;   // second look: first key, sub-bin width, sample entries before it
+    uint32_t lo, hi;                         // the interval, as keys, inclusive
+    uint32_t wide;                           // 1: too wide to resolve, go the exact way
+    uint32_t cand_lo, cand_shift, cand_rank; // chosen bin of the candidates
+    uint32_t exact_prefix;
     uint32_t tau_key;
-    unsigned long long pad[4];
+    uint32_t done[7];                        // finished workgroups of each kernel that ends with a selection
 };
-static_assert(sizeof(SelectState) == 64, "state is one 64-byte block");
 
 struct Workspace {
     SelectState* st;
-    unsigned long long* hist;                // [kBins]
+    uint32_t* coarse;                        // [kCoarse]
+    uint32_t* sub;                           // [kSub]
+    uint32_t* cand;                          // [kCandBins]
+    uint32_t* last;                          // [kLastBins]
+    unsigned long long* exact;               // [2][kExactBins]
     uint32_t* cand_key;                      // [kCap]
     unsigned long long* cand_idx;            // [kCap] linear index into the maps
 };
+constexpr size_t kStateBytes = 256;
+static_assert(sizeof(SelectState) <= kStateBytes, "the state has a block of its own");
+// everything up to the candidate lists is cleared before use
+constexpr size_t kClearBytes = kStateBytes + (size_t)(kCoarse + kSub + kCandBins + kLastBins) * 4 +
+                               (size_t)2 * kExactBins * 8;
 
 __host__ __device__ inline Workspace carve(void* p)
 {
     Workspace w;
     char* c = reinterpret_cast<char*>(p);
     w.st = reinterpret_cast<SelectState*>(c);
-    w.hist = reinterpret_cast<unsigned long long*>(c + 64);
-    w.cand_key = reinterpret_cast<uint32_t*>(c + 64 + (size_t)kBins * 8);
-    w.cand_idx = reinterpret_cast<unsigned long long*>(c + 64 + (size_t)kBins * 8 + (size_t)kCap * 4);
+    w.coarse = reinterpret_cast<uint32_t*>(c + kStateBytes);
+    w.sub = w.coarse + kCoarse;
+    w.cand = w.sub + kSub;
+    w.last = w.cand + kCandBins;
+    w.exact = reinterpret_cast<unsigned long long*>(w.last + kLastBins);
+    w.cand_idx = reinterpret_cast<unsigned long long*>(c + kClearBytes);
+    w.cand_key = reinterpret_cast<uint32_t*>(w.cand_idx + kCap);
     return w;
 }
-constexpr size_t kWorkspaceBytes = 64 + (size_t)kBins * 8 + (size_t)kCap * 4 + (size_t)kCap * 8;
+constexpr size_t kWorkspaceBytes = kClearBytes + (size_t)kCap * 12;
+static_assert(kClearBytes % 16 == 0, "cleared in 16-byte pieces");
+
+constexpr uint32_t kKeyMinusInf = 0x007fffffu, kKeyPlusInf = 0xff800000u, kKeyZero = 0x80000000u;
 
 __device__ __forceinline__ uint32_t key_of(float v)
 {
@@ -75,19 +117,84 @@ __device__ __forceinline__ float value_of(uint32_t key)
     return __uint_as_float((key & 0x80000000u) ? (key & 0x7fffffffu) : ~key);
 }
 
-__global__ void select_init_kernel(Workspace w, unsigned long long rank, unsigned long long n,
-                                   float* tau_out, int none)
+__device__ __forceinline__ int bits_for(unsigned long long width)   // smallest b with width <= 2^b
 {
-    for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < kBins; i += gridDim.x * blockDim.x) w.hist[i] = 0;
-    if (blockIdx.x == 0 && threadIdx.x == 0) {
-        w.st->rank = rank;
-        w.st->count = n;
-        w.st->prefix = 0;
-        w.st->fixed_bits = 0;
-        w.st->ncand = 0;
-        w.st->tau_key = 0;
-        if (none && tau_out) *tau_out = INFINITY;            // rank N: everything is pruned
+    return width <= 1 ? 0 : 64 - __clzll((long long)(width - 1));
+}
+
+__global__ __launch_bounds__(256) void select_init_kernel(Workspace w, unsigned long long rank, unsigned long long n,
+                                                          float* tau_out, int none)
+{
+    uint4* p = reinterpret_cast<uint4*>(w.st);
+    for (int i = blockIdx.x * 256 + threadIdx.x; i < (int)(kClearBytes / 16); i += gridDim.x * 256) {
+        uint4 v = make_uint4(0, 0, 0, 0);
+        if (i == 0) v = make_uint4((uint32_t)rank, (uint32_t)(rank >> 32), (uint32_t)n, (uint32_t)(n >> 32));
+        p[i] = v;
     }
+    if (blockIdx.x == 0 && threadIdx.x == 0 && none && tau_out) *tau_out = INFINITY;   // rank N: everything is pruned
+}
+
+// The last workgroup of a launch to get here returns true, and then sees what all of them wrote.
+__device__ __forceinline__ bool last_workgroup(uint32_t* done)
+{
+    __shared__ uint32_t s_last;
+    // What is handed over are counts in memory that only atomics of agent scope touch, and they are read
+    // back with loads of that scope: it is enough that this thread's have been performed (a full fence
+    // would write back the L2, once per wavefront).
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    __syncthreads();
+    if (threadIdx.x == 0) s_last = atomicAdd(done, 1u) == gridDim.x - 1 ? 1u : 0u;
+    __syncthreads();
+    return s_last != 0;
+}
+
+template <typename T>
+__device__ __forceinline__ T load_agent(const T* p)          // past this XCD's caches: another one's atomics wrote it
+{
+    return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// For a workgroup of kThreads: the bins of a histogram that hold the given ranks, R of them.  `base`:
+// entries before the first bin.  The thread whose bins hold a rank reports it: found(r, bin, entries
+// before the bin).  Returns the number of entries counted.
+template <int NB, int R, typename T, typename F>
+__device__ __forceinline__ unsigned long long find_ranks(const T* hist, unsigned long long base,
+                                                         const unsigned long long (&ranks)[R], F&& found)
+{
+    constexpr int PER = NB / kThreads;                       // consecutive bins of a thread
+    __shared__ unsigned long long s_wave[kThreads / 64];
+    const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
+    unsigned long long sum = 0;
+#pragma unroll 4
+    for (int i = 0; i < PER; ++i) sum += load_agent(hist + t * PER + i);
+    unsigned long long incl = sum;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+        const unsigned long long up = __shfl_up(incl, o, 64);
+        if (lane >= o) incl += up;
+    }
+    if (lane == 63) s_wave[wave] = incl;
+    __syncthreads();
+    unsigned long long before = base + incl - sum, all = 0;
+    for (int w = 0; w < kThreads / 64; ++w) {
+        if (w < wave) before += s_wave[w];
+        all += s_wave[w];
+    }
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+        if (ranks[r] < before || ranks[r] >= before + sum) continue;
+        unsigned long long b = before;
+        for (int i = 0; i < PER; ++i) {
+            const unsigned long long c = load_agent(hist + t * PER + i);
+            if (ranks[r] < b + c) {
+                found(r, t * PER + i, b);
+                break;
+            }
+            b += c;
+        }
+    }
+    __syncthreads();
+    return all;
 }
 
 // The maps are walked in units, one wavefront per unit, all of (nearly) the same size so that
@@ -99,7 +206,7 @@ __global__ void select_init_kernel(Workspace w, unsigned long long rank, unsigne
 // arithmetic is wave-uniform.
 struct Walk {
     const float* abar;
-    long long units;
+    int units;                   // below 2^31: the entry point checks H * Lq
     int H, Lq, Lk;
     int causal;
     int per_head;                // units per head
@@ -113,11 +220,11 @@ struct Unit {                    // wave-uniform
     int total;                   // p0 + n[1]
 };
 
-__device__ __forceinline__ Unit decode_unit(const Walk& w, long long unit)
+__device__ __forceinline__ Unit decode_unit(const Walk& w, int unit)
 {
     Unit u;
-    const int h = (int)(unit / w.per_head);
-    const int t = (int)(unit - (long long)h * w.per_head);
+    const int h = (int)((uint32_t)unit / (uint32_t)w.per_head);
+    const int t = unit - h * w.per_head;
     const long long off = (long long)w.Lk - w.Lq;
     const int i0 = t;
     const int i1 = w.causal ? w.Lq - 1 - t : t;
@@ -132,331 +239,462 @@ __device__ __forceinline__ Unit decode_unit(const Walk& w, long long unit)
     return u;
 }
 
-struct Quad {
-    float4 v;
-    int col;                     // column of the first entry
-    int cnt;                     // how many of the 4 entries are visible entries of the row (0..4)
-    int which;                   // 0 or 1: row of the unit
+// rows of a map whose Lk is no multiple of 4 start anywhere: the same loads and stores, 4- and 1-byte aligned
+typedef __attribute__((ext_vector_type(4))) float f32x4;
+typedef __attribute__((ext_vector_type(4), aligned(4))) float f32x4_a4;
+typedef __attribute__((aligned(1))) uint32_t u32_a1;
+
+// Entries col .. col + 3 of a row of which n are visible: one 128-bit load, also where the visible prefix
+// ends inside the four; entry by entry only where the row itself ends inside them.
+__device__ __forceinline__ f32x4 load_quad(const float* row, int col, int n, int Lk)
+{
+    f32x4 v = {0.f, 0.f, 0.f, 0.f};
+    if (col < n) {
+        if (col + 4 <= Lk) {
+            v = *reinterpret_cast<const f32x4_a4*>(row + col);
+        } else {
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+                if (col + e < n) v[e] = row[col + e];
+        }
+    }
+    return v;
+}
+
+// ---- sample
+
+// Entry clusters of the sample: 16 positions (four lanes, a quad each), every stride-th cluster of a
+// unit, starting at a place that depends on the unit.
+struct Sample {
+    unsigned long long slots;    // clusters, some of them beyond their unit's end
+    uint32_t per_unit, stride;
 };
 
-// U quads of this lane, starting at position pos0 of the unit.  The 128-bit loads of complete
-// quads are issued back to back; quads cut by the end of a prefix are filled in afterwards.
-template <int U>
-__device__ __forceinline__ void load_quads(const Walk& w, const Unit& u, int pos0, int lane, Quad* q)
+template <typename F>
+__device__ __forceinline__ void for_sample(const Walk& w, const Sample& s, F&& body)
 {
-    const bool vec_ok = (w.Lk & 3) == 0;
-    const float* p[U];
-    bool full[U];
+    constexpr int U = 4;                                     // quads of a lane in flight
+    const unsigned long long lanes = s.slots * 4, step = (unsigned long long)gridDim.x * kThreads;
+    for (unsigned long long i0 = (unsigned long long)blockIdx.x * kThreads + threadIdx.x; i0 < lanes; i0 += U * step) {
+        f32x4 v[U];
+        int cnt[U];
 #pragma unroll
-    for (int k = 0; k < U; ++k) {
-        const int pos = pos0 + k * 256 + lane * 4;
-        const bool second = pos >= u.p0;
-        q[k].which = second ? 1 : 0;
-        q[k].col = second ? pos - u.p0 : pos;
-        const int nrow = second ? u.n[1] : u.n[0];
-        int cnt = nrow - q[k].col;
-        cnt = cnt < 0 ? 0 : (cnt > 4 ? 4 : cnt);
-        q[k].cnt = cnt;
-        p[k] = (second ? u.row[1] : u.row[0]) + q[k].col;
-        full[k] = vec_ok && cnt == 4;
-        q[k].v = make_float4(0.f, 0.f, 0.f, 0.f);
-    }
-    if (vec_ok) {                                            // then the map holds at least 4 floats
-#pragma unroll
-        for (int k = 0; k < U; ++k) q[k].v = *reinterpret_cast<const float4*>(full[k] ? p[k] : w.abar);
-    }
-#pragma unroll
-    for (int k = 0; k < U; ++k) {
-        if (full[k] || q[k].cnt == 0) continue;
-        float e[4] = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-        for (int c = 0; c < 4; ++c)
-            if (c < q[k].cnt) e[c] = p[k][c];
-        q[k].v = make_float4(e[0], e[1], e[2], e[3]);
-    }
-}
-
-template <int LEVEL> struct Digit;
-template <> struct Digit<0> { static constexpr int shift = 17, bits = 15; };
-template <> struct Digit<1> { static constexpr int shift = 2, bits = 15; };
-template <> struct Digit<2> { static constexpr int shift = 0, bits = 2; };
-
-template <int LEVEL>
-__global__ __launch_bounds__(kThreads) void radix_hist_kernel(Walk w, Workspace ws)
-{
-    constexpr int SHIFT = Digit<LEVEL>::shift, BITS = Digit<LEVEL>::bits;
-    constexpr int NB = 1 << BITS;
-    constexpr int U = 8;
-    if (LEVEL > 0 && ws.st->count <= kCap) return;           // the candidates fit: no further digit needed
-    __shared__ uint32_t h[NB];
-    for (int i = threadIdx.x; i < NB; i += kThreads) h[i] = 0;
-    __syncthreads();
-    const uint32_t prefix = ws.st->prefix;
-    const int lane = threadIdx.x & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const long long nwaves = (long long)gridDim.x * (kThreads / 64);
-    auto count = [&](float v) {
-        const uint32_t key = key_of(v);
-        bool match = true;
-        if constexpr (LEVEL > 0) match = (key >> (SHIFT + BITS)) == (prefix >> (SHIFT + BITS));
-        if (match) atomicAdd(&h[(key >> SHIFT) & (NB - 1)], 1u);
-    };
-    for (long long unit = (long long)wave * gridDim.x + blockIdx.x; unit < w.units; unit += nwaves) {
-        const Unit u = decode_unit(w, unit);
-        for (int pos0 = 0; pos0 < u.total; pos0 += 256 * U) {
-            Quad q[U];
-            load_quads<U>(w, u, pos0, lane, q);
-#pragma unroll
-            for (int k = 0; k < U; ++k) {
-                if (q[k].cnt > 0) count(q[k].v.x);
-                if (q[k].cnt > 1) count(q[k].v.y);
-                if (q[k].cnt > 2) count(q[k].v.z);
-                if (q[k].cnt > 3) count(q[k].v.w);
-            }
+        for (int k = 0; k < U; ++k) {
+            const unsigned long long i = i0 + k * step;
+            const unsigned long long slot = i >> 2;
+            const uint32_t unit = slot >> 32 ? (uint32_t)(slot / s.per_unit) : (uint32_t)slot / s.per_unit;
+            const uint32_t j = (uint32_t)(slot - (unsigned long long)unit * s.per_unit);
+            const uint32_t phase = ((unit * 2654435761u) >> 8) % s.stride;
+            const unsigned long long pos = ((unsigned long long)j * s.stride + phase) * 16 + 4 * (i & 3);
+            cnt[k] = 0;
+            v[k] = f32x4{0.f, 0.f, 0.f, 0.f};
+            if (i >= lanes) continue;
+            const Unit u = decode_unit(w, (int)unit);
+            if (pos >= (unsigned long long)u.total) continue;
+            const bool second = (int)pos >= u.p0;
+            const int col = second ? (int)pos - u.p0 : (int)pos, n = second ? u.n[1] : u.n[0];
+            v[k] = load_quad(second ? u.row[1] : u.row[0], col, n, w.Lk);
+            cnt[k] = n - col;
         }
+#pragma unroll
+        for (int k = 0; k < U; ++k)
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+                if (e < cnt[k]) body(key_of(v[k][e]));
     }
-    __syncthreads();
-    for (int i = threadIdx.x; i < NB; i += kThreads)
-        if (h[i]) atomicAdd(&ws.hist[i], (unsigned long long)h[i]);
 }
 
-
-// One workgroup: find the bin whose cumulative count passes the wanted rank, fix that digit,
-// and clear the histogram for the next level.  The histogram goes through LDS in two halves so
-// that global memory is read and cleared with consecutive addresses per wavefront while every
-// thread scans a run of consecutive bins.
-template <int LEVEL>
-__global__ __launch_bounds__(kThreads) void radix_select_kernel(Workspace ws)
+__global__ __launch_bounds__(kThreads) void sample_coarse_kernel(Walk w, Sample s, Workspace ws)
 {
-    constexpr int SHIFT = Digit<LEVEL>::shift, BITS = Digit<LEVEL>::bits;
-    constexpr int NB = 1 << BITS;
-    constexpr int HALF = NB >= 2 * kThreads ? NB / 2 : NB;   // bins staged at a time
-    constexpr int NHALF = NB / HALF;
-    constexpr int PER = (HALF + kThreads - 1) / kThreads;    // consecutive bins per thread
-    if (LEVEL > 0 && ws.st->count <= kCap) return;
-    __shared__ unsigned long long bins[HALF];
-    __shared__ unsigned long long part[kThreads];
-    __shared__ unsigned long long group[32];
-    __shared__ unsigned long long total;
+    __shared__ uint32_t h[kCoarse];
     const int t = threadIdx.x;
-    unsigned long long rank = ws.st->rank;
-    const uint32_t prefix = ws.st->prefix;
-    bool found = false;
-    for (int half = 0; half < NHALF; ++half) {
-        __syncthreads();                                     // LDS of the previous half is no longer read
-        for (int i = t; i < HALF; i += kThreads) {
-            bins[i] = ws.hist[half * HALF + i];
-            ws.hist[half * HALF + i] = 0;
-        }
-        __syncthreads();
-        if (found) continue;                                 // the remaining half is only cleared
-        unsigned long long mine = 0;
-#pragma unroll
-        for (int i = 0; i < PER; ++i)
-            if (t * PER + i < HALF) mine += bins[t * PER + i];
-        part[t] = mine;
-        __syncthreads();
-        if (t < 32) {                                        // two-level exclusive scan of part[]
-            unsigned long long s = 0;
-            for (int i = 0; i < 32; ++i) s += part[t * 32 + i];
-            group[t] = s;
-        }
-        __syncthreads();
-        unsigned long long before = 0;
-        for (int i = 0; i < (t >> 5); ++i) before += group[i];
-        for (int i = (t & ~31); i < t; ++i) before += part[i];
-        if (t == kThreads - 1) total = before + mine;
-        if (rank >= before && rank < before + mine) {        // at most one thread, in one half
-            unsigned long long cum = before;
-            for (int i = 0; i < PER; ++i) {
-                const unsigned long long c = bins[t * PER + i];
-                if (rank < cum + c) {
-                    ws.st->prefix = prefix | ((uint32_t)(half * HALF + t * PER + i) << SHIFT);
-                    ws.st->fixed_bits = 32 - SHIFT;
-                    ws.st->rank = rank - cum;
-                    ws.st->count = c;
-                    break;
-                }
-                cum += c;
-            }
-        }
-        __syncthreads();
-        if (rank < total) found = true;                      // uniform: every thread reads the same total
-        else rank -= total;
+    for (int i = t; i < kCoarse; i += kThreads) h[i] = 0;
+    __syncthreads();
+    for_sample(w, s, [&](uint32_t key) { atomicAdd(&h[key >> kCoarseShift], 1u); });
+    __syncthreads();
+    for (int i = t; i < kCoarse; i += kThreads)
+        if (h[i]) atomicAdd(&ws.coarse[i], h[i]);
+    if (!last_workgroup(&ws.st->done[0])) return;
+
+    __shared__ int s_bin[2];
+    __shared__ unsigned long long s_below, s_total;
+    if (t == 0) {
+        s_bin[0] = 0;
+        s_bin[1] = kCoarse - 1;
+        s_below = s_total = 0;
+    }
+    unsigned long long mine = 0;
+    for (int i = t; i < kCoarse; i += kThreads) mine += load_agent(ws.coarse + i);
+    __syncthreads();
+    atomicAdd(&s_total, mine);
+    __syncthreads();
+    const unsigned long long rank = ws.st->rank, n = ws.st->n, total = s_total;
+    // the sample's own rank, and how far the map's may be from it: binomial with the variance of
+    // clusters whose entries resemble each other
+    unsigned long long s_mid = rank, margin = 0;
+    if (s.stride > 1) {
+        const double f = (double)rank / (double)n;
+        s_mid = (unsigned long long)(f * (double)total);
+        margin = (unsigned long long)(kSigmas * sqrt((double)total * f * (1.0 - f) * kDesign)) + 16;
+    }
+    const unsigned long long top = total > 0 ? total - 1 : 0;
+    const unsigned long long s_lo = s_mid > margin ? min(s_mid - margin, top) : 0;
+    const unsigned long long s_hi = min(s_mid + margin, top);
+    const unsigned long long want[2] = {s_lo, s_hi};
+    find_ranks<kCoarse>(ws.coarse, 0ull, want, [&](int r, int bin, unsigned long long below) {
+        s_bin[r] = bin;
+        if (r == 0) s_below = below;
+    });
+    if (t == 0) {
+        const int bits = bits_for((unsigned long long)(s_bin[1] - s_bin[0] + 1) << kCoarseShift);
+        ws.st->s_lo = (uint32_t)s_lo;
+        ws.st->s_hi = (uint32_t)s_hi;
+        ws.st->s_total = (uint32_t)total;
+        ws.st->range_lo = (uint32_t)s_bin[0] << kCoarseShift;
+        ws.st->range_shift = (uint32_t)(bits > kSubBits ? bits - kSubBits : 0);
+        ws.st->range_below = (uint32_t)s_below;
     }
 }
 
-// Second sweep: the mask of every entry that the fixed key bits already decide, and the list of
-// the entries they do not decide.  Candidates are staged per wavefront in LDS (a lane reserves
-// room for its own with one LDS atomic) and moved to the global list in blocks, so the global
-// counter sees one atomic per few hundred candidates.
-constexpr int kStage = 384;                  // staged candidates per wavefront
-constexpr int kStageFlush = kStage - 256;    // a quad step adds at most 64 lanes x 4 entries
-
-__global__ __launch_bounds__(kThreads) void mask_collect_kernel(Walk w, Workspace ws, uint8_t* mask, int none)
+__global__ __launch_bounds__(kThreads) void sample_fine_kernel(Walk w, Sample s, Workspace ws)
 {
-    constexpr int U = 4;
-    __shared__ uint32_t s_key[kThreads / 64][kStage];
-    __shared__ unsigned long long s_idx[kThreads / 64][kStage];
-    __shared__ uint32_t s_fill[kThreads / 64];
-    const uint32_t fixed = ws.st->fixed_bits;
-    const uint32_t prefix = ws.st->prefix;
-    const bool exact = fixed == 32;                          // tau = prefix, nothing to collect
-    const int shift = (exact || none) ? 0 : 32 - (int)fixed; // undecided low bits (2 .. 17)
-    const uint32_t phi = prefix >> shift;
+    __shared__ uint32_t h[kSub];
+    const int t = threadIdx.x;
+    for (int i = t; i < kSub; i += kThreads) h[i] = 0;
+    __syncthreads();
+    const uint32_t range_lo = ws.st->range_lo, shift = ws.st->range_shift;
+    for_sample(w, s, [&](uint32_t key) {
+        const uint32_t bin = (key - range_lo) >> shift;
+        if (key >= range_lo && bin < kSub) atomicAdd(&h[bin], 1u);
+    });
+    __syncthreads();
+    for (int i = t; i < kSub; i += kThreads)
+        if (h[i]) atomicAdd(&ws.sub[i], h[i]);
+    if (!last_workgroup(&ws.st->done[1])) return;
+
+    __shared__ int s_bin[2];
+    if (t == 0) {
+        s_bin[0] = 0;
+        s_bin[1] = kSub - 1;
+    }
+    __syncthreads();
+    const uint32_t s_lo = ws.st->s_lo, s_hi = ws.st->s_hi;
+    const unsigned long long want[2] = {s_lo, s_hi};
+    find_ranks<kSub>(ws.sub, (unsigned long long)ws.st->range_below, want,
+                     [&](int r, int bin, unsigned long long) { s_bin[r] = bin; });
+    if (t == 0) {
+        // a sample that ends inside the margin says nothing about the values beyond it
+        const bool open = s.stride > 1;
+        unsigned long long lo = (unsigned long long)range_lo + ((unsigned long long)s_bin[0] << shift);
+        unsigned long long hi = (unsigned long long)range_lo + ((unsigned long long)(s_bin[1] + 1) << shift) - 1;
+        if (open && s_lo == 0) lo = 0;
+        if (open && s_hi + 1 >= ws.st->s_total) hi = 0xffffffffull;
+        // the sweep compares values: keep to keys that are values, and to +0 for zero
+        if (lo < kKeyMinusInf) lo = kKeyMinusInf;
+        if (hi > kKeyPlusInf) hi = kKeyPlusInf;
+        if (hi == kKeyZero - 1) hi = kKeyZero;
+        ws.st->lo = (uint32_t)lo;
+        ws.st->hi = (uint32_t)hi;
+        ws.st->wide = hi < lo || bits_for(hi - lo + 1) > kMaxBracketBits ? 1u : 0u;
+    }
+}
+
+// Did the sweep's interval hold the wanted rank, with all its candidates collected?
+__device__ __forceinline__ bool interval_ok(const SelectState* st, unsigned long long* rank_inside)
+{
+    const unsigned long long below = st->n - st->above - st->ncand;
+    *rank_inside = st->rank - below;
+    return st->wide == 0 && st->ncand <= kCap && st->rank >= below && st->rank - below < st->ncand;
+}
+
+// ---- sweep: the mask of every entry that the interval decides, and the list of those it does not
+
+// Candidates are staged per wavefront in LDS and moved to the global list in blocks, so that the global
+// counter sees one atomic per few hundred candidates.  Their places come from ballots.
+constexpr int kStage = 384;                  // staged candidates per wavefront
+constexpr int kStageFlush = kStage - 256;    // a step adds at most 64 lanes x 4 entries
+
+// Zeros for dst[0 .. n): whole wavefront, any alignment.
+__device__ __forceinline__ void zero_bytes(uint8_t* dst, int n, int lane)
+{
+    const int head = min(n, (int)(-(uintptr_t)dst & 15u));
+    if (lane < head) dst[lane] = 0;
+    const int body = (n - head) >> 4;
+    uint4* q = reinterpret_cast<uint4*>(dst + head);
+    for (int i = lane; i < body; i += 64) q[i] = make_uint4(0, 0, 0, 0);
+    const int tail = head + 16 * body + lane;
+    if (lane < 16 && tail < n) dst[tail] = 0;
+}
+
+// EXACT = false: the interval of the sample.  EXACT = true: tau itself is known (the exact way), every
+// entry is decided; runs only if the interval failed.
+template <bool EXACT>
+__global__ __launch_bounds__(kSweepThreads) void mask_sweep_kernel(Walk w, Workspace ws, uint8_t* mask)
+{
+    constexpr int U = 8;                                     // quads of a lane in flight
+    constexpr int WAVES = kSweepThreads / 64;
+    __shared__ uint32_t s_key[EXACT ? 1 : WAVES][kStage];
+    __shared__ unsigned long long s_idx[EXACT ? 1 : WAVES][kStage];
+    __shared__ unsigned long long s_above;
+    if (EXACT) {
+        unsigned long long dummy;
+        if (!mask || interval_ok(ws.st, &dummy)) return;
+    } else if (ws.st->wide) {
+        return;
+    }
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const long long nwaves = (long long)gridDim.x * (kThreads / 64);
-    const bool vec_ok = (w.Lk & 3) == 0;
-    if (lane == 0) s_fill[wave] = 0;
-    __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+    const int nwaves = (int)gridDim.x * WAVES;
+    const float lo = EXACT ? 0.f : value_of(ws.st->lo);
+    const float hi = EXACT ? 0.f : value_of(ws.st->hi);
+    const float tau = EXACT ? value_of(ws.st->tau_key) : 0.f;
+    if (threadIdx.x == 0) s_above = 0;
+    int fill = 0;                                            // staged candidates (wave-uniform)
+    unsigned long long above = 0;                            // of this lane
 
     auto flush = [&]() {                                     // wave-uniform
-        __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");   // staged entries written by other lanes
-        const int fill = (int)__builtin_amdgcn_readfirstlane(s_fill[wave]);
         if (fill == 0) return;
-        uint32_t base = 0;
-        if (lane == 0) base = atomicAdd(&ws.st->ncand, (uint32_t)fill);
+        __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");   // staged entries written by other lanes
+        unsigned long long base = 0;
+        if (lane == 0) base = atomicAdd(&ws.st->ncand, (unsigned long long)fill);
         base = __shfl(base, 0, 64);
         for (int i = lane; i < fill; i += 64) {
-            const uint32_t slot = base + i;
-            if (slot < kCap) {                               // always: the bin was chosen to fit
+            const unsigned long long slot = base + i;
+            if (slot < kCap) {                               // the count runs on: it tells that they did not fit
                 ws.cand_key[slot] = s_key[wave][i];
                 ws.cand_idx[slot] = s_idx[wave][i];
             }
         }
         __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
-        if (lane == 0) s_fill[wave] = 0;
-        __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+        fill = 0;
     };
 
-    for (long long unit = (long long)wave * gridDim.x + blockIdx.x; unit < w.units; unit += nwaves) {
-        const Unit u = decode_unit(w, unit);
-        for (int pos0 = 0; pos0 < u.total && !none; pos0 += 256 * U) {
-            Quad q[U];
-            load_quads<U>(w, u, pos0, lane, q);
+    // Entries [lin, lin + 4) of the maps, of which the first cnt count: decide, collect, write.
+    auto one = [&](const f32x4& v, long long lin, int cnt, bool whole, bool room) {
+        bool a[4], c[4];
+        uint32_t out = 0;
 #pragma unroll
-            for (int k = 0; k < U; ++k) {
-                const float ve[4] = {q[k].v.x, q[k].v.y, q[k].v.z, q[k].v.w};
-                uint32_t out = 0;
-                uint32_t keys[4];
-                uint32_t cmask = 0;                          // which of the 4 entries are candidates
+        for (int e = 0; e < 4; ++e) {
+            const bool vis = whole || e < cnt;               // whole is a compile-time constant
+            a[e] = EXACT ? !(v[e] < tau) : !(v[e] <= hi);
+            c[e] = !EXACT && v[e] >= lo && !a[e];
+            if (!whole) {
+                a[e] = a[e] && vis;
+                c[e] = c[e] && vis;
+            }
+            out |= a[e] ? 1u << (8 * e) : 0u;
+        }
+        if (!EXACT) {
+            above += (uint32_t)__popc(out);
+            if (__ballot(c[0] || c[1] || c[2] || c[3]) != 0) {
+                if (fill > kStageFlush) flush();
 #pragma unroll
                 for (int e = 0; e < 4; ++e) {
-                    const bool vis = e < q[k].cnt;
-                    keys[e] = key_of(ve[e]);
-                    const uint32_t hi = keys[e] >> shift;
-                    if (vis && (exact ? keys[e] >= prefix : hi > phi)) out |= 1u << (8 * e);
-                    if (vis && !exact && hi == phi) cmask |= 1u << e;
-                }
-                const long long lin = u.base[q[k].which] + q[k].col;
-                if (__ballot(cmask != 0) != 0) {             // rare enough to keep out of the common path
-                    if (__builtin_amdgcn_readfirstlane(s_fill[wave]) > kStageFlush) flush();
-                    if (cmask != 0) {
-                        uint32_t pos = atomicAdd(&s_fill[wave], (uint32_t)__popc(cmask));
-#pragma unroll
-                        for (int e = 0; e < 4; ++e)
-                            if (cmask & (1u << e)) {
-                                s_key[wave][pos] = keys[e];
-                                s_idx[wave][pos] = (unsigned long long)(lin + e);
-                                ++pos;
-                            }
+                    const unsigned long long m = __ballot(c[e]);
+                    if (m == 0) continue;
+                    if (c[e]) {
+                        const int pos = fill + (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32),
+                                                   __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0));
+                        s_key[wave][pos] = key_of(v[e]);
+                        s_idx[wave][pos] = (unsigned long long)(lin + e);
                     }
-                }
-                // candidates get 0 here, their byte comes later; a quad cut by the visible prefix
-                // also writes the zeros of its hidden entries (inside the row)
-                if (mask && q[k].cnt > 0) {
-                    uint8_t* dst = mask + lin;
-                    if (vec_ok) {
-                        *reinterpret_cast<uint32_t*>(dst) = out;
-                    } else {
-                        for (int e = 0; e < q[k].cnt; ++e) dst[e] = (uint8_t)((out >> (8 * e)) & 1u);
-                    }
+                    fill += __popcll(m);
                 }
             }
         }
-        // zeros for everything the sweep above did not write: the hidden tail of each row
+        // candidates get 0 here, their byte comes later; four entries cut by the visible prefix also
+        // write the zeros of the hidden ones (inside the row)
+        if (mask && (whole || cnt > 0)) {
+            if (whole || room) {
+                *reinterpret_cast<u32_a1*>(mask + lin) = out;
+            } else {
+                for (int e = 0; e < cnt; ++e) mask[lin + e] = (uint8_t)((out >> (8 * e)) & 1u);
+            }
+        }
+    };
+
+    for (long long unit = (long long)blockIdx.x * WAVES + wave; unit < w.units; unit += nwaves) {
+        const Unit u = decode_unit(w, (int)unit);
+        // what is left of each row behind its last 256 visible entries: requested first
+        f32x4 rest[2];
+        int rest_col[2];
 #pragma unroll
         for (int r = 0; r < 2; ++r) {
-            const bool present = r == 0 || u.base[1] != u.base[0];
-            if (!present || !mask) continue;
-            int start = none ? 0 : u.n[r];
-            if (vec_ok) start = none ? 0 : (start + 3) & ~3;
-            uint8_t* dst = mask + u.base[r];
-            if (vec_ok) {
-                for (int j = start + lane * 4; j < w.Lk; j += 256) *reinterpret_cast<uint32_t*>(dst + j) = 0u;
-            } else {
-                for (int j = start + lane; j < w.Lk; j += 64) dst[j] = 0;
+            rest_col[r] = (u.n[r] & ~255) + 4 * lane;
+            rest[r] = load_quad(u.row[r], rest_col[r], u.n[r], w.Lk);
+        }
+#pragma unroll
+        for (int r = 0; r < 2; ++r) {
+            const int steps = u.n[r] >> 8;                   // 256 entries of the row each, all visible
+            const float* row = u.row[r] + 4 * lane;
+            const long long lin = u.base[r] + 4 * lane;
+            for (int s0 = 0; s0 < steps; s0 += U) {
+                f32x4 v[U];
+#pragma unroll
+                for (int k = 0; k < U; ++k)
+                    if (s0 + k < steps) v[k] = *reinterpret_cast<const f32x4_a4*>(row + (s0 + k) * 256);
+#pragma unroll
+                for (int k = 0; k < U; ++k)
+                    if (s0 + k < steps) one(v[k], lin + (s0 + k) * 256, 4, true, true);
+            }
+        }
+#pragma unroll
+        for (int r = 0; r < 2; ++r) {
+            if (u.n[r] == 0) continue;                       // a unit of one row
+            one(rest[r], u.base[r] + rest_col[r], u.n[r] - rest_col[r], false, rest_col[r] + 4 <= w.Lk);
+            if (mask) {                                      // the hidden tail of the row
+                const int up = (u.n[r] + 3) & ~3;            // written with the last four, if they fitted the row
+                const int start = up <= w.Lk ? up : u.n[r];
+                if (start < w.Lk) zero_bytes(mask + u.base[r] + start, w.Lk - start, lane);
             }
         }
     }
-    flush();
+    if (!EXACT) {
+        flush();
+#pragma unroll
+        for (int o = 32; o > 0; o >>= 1) above += __shfl_xor(above, o, 64);
+        __syncthreads();
+        if (lane == 0 && above) atomicAdd(&s_above, above);
+        __syncthreads();
+        if (threadIdx.x == 0 && s_above) atomicAdd(&ws.st->above, s_above);
+    }
 }
 
-// One workgroup: tau among the candidates, by radix selection over their undecided low bits.
-__global__ __launch_bounds__(kThreads) void candidate_select_kernel(Workspace ws, float* tau_out)
+// ---- select: tau among the candidates
+
+__global__ __launch_bounds__(kThreads) void candidate_bins_kernel(Workspace ws)
 {
-    __shared__ uint32_t h[1024];
-    __shared__ uint32_t group[32];
-    __shared__ uint32_t chosen[2];                           // bin, count before it
+    __shared__ uint32_t h[kCandBins];
+    unsigned long long rank;
+    if (!interval_ok(ws.st, &rank)) return;
     const int t = threadIdx.x;
-    uint32_t prefix = ws.st->prefix;
-    int remaining = 32 - (int)ws.st->fixed_bits;             // undecided low bits
-    uint32_t rank = (uint32_t)ws.st->rank;                   // < ncand <= kCap
-    const uint32_t n = min(ws.st->ncand, kCap);
-    while (remaining > 0) {
-        const int bits = remaining > 10 ? 10 : remaining;
-        const int shift = remaining - bits;
-        h[t] = 0;
-        __syncthreads();
-        for (uint32_t i0 = 0; i0 < n; i0 += 8 * kThreads) {   // 8 loads in flight per thread
-            uint32_t keys[8];
-#pragma unroll
-            for (int u = 0; u < 8; ++u) {
-                const uint32_t i = i0 + u * kThreads + t;
-                keys[u] = ws.cand_key[i < n ? i : 0];
-            }
-#pragma unroll
-            for (int u = 0; u < 8; ++u) {
-                const uint32_t i = i0 + u * kThreads + t;
-                // remaining <= 17, so the shifts are defined
-                if (i < n && (keys[u] >> remaining) == (prefix >> remaining))
-                    atomicAdd(&h[(keys[u] >> shift) & ((1u << bits) - 1u)], 1u);
-            }
-        }
-        __syncthreads();
-        if (t < 32) {
-            uint32_t s = 0;
-            for (int i = 0; i < 32; ++i) s += h[t * 32 + i];
-            group[t] = s;
-        }
-        __syncthreads();
-        uint32_t before = 0;
-        for (int i = 0; i < (t >> 5); ++i) before += group[i];
-        for (int i = (t & ~31); i < t; ++i) before += h[i];
-        const uint32_t mine = h[t];
-        if (rank >= before && rank < before + mine) {        // exactly one thread
-            chosen[0] = (uint32_t)t;
-            chosen[1] = before;
-        }
-        __syncthreads();
-        prefix |= chosen[0] << shift;
-        rank -= chosen[1];
-        remaining = shift;
-        __syncthreads();
+    const uint32_t n = (uint32_t)ws.st->ncand, lo = ws.st->lo;
+    const int bits = bits_for((unsigned long long)ws.st->hi - lo + 1);
+    const int shift = bits > kCandBits ? bits - kCandBits : 0;
+    for (int i = t; i < kCandBins; i += kThreads) h[i] = 0;
+    __syncthreads();
+    for (uint32_t i = blockIdx.x * kThreads + t; i < n; i += gridDim.x * kThreads)
+        atomicAdd(&h[(ws.cand_key[i] - lo) >> shift], 1u);
+    __syncthreads();
+    for (int i = t; i < kCandBins; i += kThreads)
+        if (h[i]) atomicAdd(&ws.cand[i], h[i]);
+    if (!last_workgroup(&ws.st->done[2])) return;
+    const unsigned long long want[1] = {rank};
+    find_ranks<kCandBins>(ws.cand, 0ull, want, [&](int, int bin, unsigned long long below) {
+        ws.st->cand_lo = lo + ((uint32_t)bin << shift);
+        ws.st->cand_shift = (uint32_t)shift;
+        ws.st->cand_rank = (uint32_t)(rank - below);
+    });
+}
+
+__global__ __launch_bounds__(kThreads) void candidate_last_kernel(Workspace ws, float* tau_out)
+{
+    __shared__ uint32_t h[kLastBins];
+    unsigned long long dummy;
+    if (!interval_ok(ws.st, &dummy)) return;
+    const int t = threadIdx.x;
+    const uint32_t n = (uint32_t)ws.st->ncand, lo = ws.st->cand_lo, width = 1u << ws.st->cand_shift;   // <= kLastBins
+    for (int i = t; i < kLastBins; i += kThreads) h[i] = 0;
+    __syncthreads();
+    for (uint32_t i = blockIdx.x * kThreads + t; i < n; i += gridDim.x * kThreads) {
+        const uint32_t d = ws.cand_key[i] - lo;
+        if (d < width) atomicAdd(&h[d], 1u);
     }
-    if (t == 0) {
-        ws.st->tau_key = prefix;
-        if (tau_out) *tau_out = value_of(prefix);
-    }
+    __syncthreads();
+    for (int i = t; i < kLastBins; i += kThreads)
+        if (h[i]) atomicAdd(&ws.last[i], h[i]);
+    if (!last_workgroup(&ws.st->done[3])) return;
+    const unsigned long long want[1] = {ws.st->cand_rank};
+    find_ranks<kLastBins>(ws.last, 0ull, want, [&](int, int bin, unsigned long long) {
+        ws.st->tau_key = lo + (uint32_t)bin;
+        if (tau_out) *tau_out = value_of(lo + (uint32_t)bin);
+    });
 }
 
 __global__ __launch_bounds__(256) void candidate_fixup_kernel(Workspace ws, uint8_t* mask)
 {
-    const uint32_t n = min(ws.st->ncand, kCap);
+    unsigned long long dummy;
+    if (!interval_ok(ws.st, &dummy)) return;
+    const uint32_t n = (uint32_t)ws.st->ncand;
     const uint32_t tau_key = ws.st->tau_key;
     for (uint32_t i = blockIdx.x * 256u + threadIdx.x; i < n; i += gridDim.x * 256u)
         if (ws.cand_key[i] >= tau_key) mask[ws.cand_idx[i]] = 1;
+}
+
+// ---- the exact way: 16 key bits per level over all entries, only if the interval failed.  The counts
+// of a workgroup are kept as 16-bit halves of LDS words and moved out before one of them can overflow.
+template <int LEVEL>
+__global__ __launch_bounds__(kThreads) void exact_level_kernel(Walk w, Workspace ws, float* tau_out)
+{
+    constexpr int STEP = 256;                                // entries of a wavefront's step
+    constexpr int STEPS = 65535 / (STEP * (kThreads / 64));  // steps of all wavefronts between two moves: 15
+    __shared__ uint32_t h[kExactBins / 2];
+    unsigned long long dummy;
+    if (interval_ok(ws.st, &dummy)) return;
+    const int t = threadIdx.x, lane = t & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
+    const long long nwaves = (long long)gridDim.x * (kThreads / 64);
+    const uint32_t prefix = LEVEL == 0 ? 0u : ws.st->exact_prefix;
+    unsigned long long* hist = ws.exact + (size_t)LEVEL * kExactBins;
+    for (int i = t; i < kExactBins / 2; i += kThreads) h[i] = 0;
+    __syncthreads();
+    long long unit = (long long)wave * gridDim.x + blockIdx.x;   // runs past w.units
+    int pos0 = 0;
+    // every wavefront takes the same number of rounds, those that have run out with nothing to do
+    const long long units_per_wave = ((long long)w.units + nwaves - 1) / nwaves;
+    const int steps_per_unit = (int)(((long long)w.Lk + (w.causal ? (long long)w.Lk - w.Lq + 5 : 0) + STEP - 1) / STEP) + 1;
+    const long long rounds = (units_per_wave * steps_per_unit + STEPS - 1) / STEPS;
+    for (long long round = 0; round < rounds; ++round) {
+        for (int k = 0; k < STEPS && unit < w.units; ++k) {
+            const Unit u = decode_unit(w, (int)unit);
+            const int pos = pos0 + lane * 4;
+            const bool second = pos >= u.p0;
+            const int col = second ? pos - u.p0 : pos, n = second ? u.n[1] : u.n[0];
+            const f32x4 v = load_quad(second ? u.row[1] : u.row[0], col, n, w.Lk);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const uint32_t key = key_of(v[e]);
+                if (col + e < n && (LEVEL == 0 || (key >> 16) == (prefix >> 16))) {
+                    const uint32_t bin = LEVEL == 0 ? key >> 16 : key & 0xffffu;
+                    atomicAdd(&h[bin >> 1], 1u << (16 * (bin & 1)));
+                }
+            }
+            pos0 += STEP;
+            if (pos0 >= u.total) {
+                pos0 = 0;
+                unit += nwaves;
+            }
+        }
+        __syncthreads();
+        for (int i = t; i < kExactBins / 2; i += kThreads) {
+            const uint32_t v = h[i];
+            if (v == 0) continue;
+            h[i] = 0;
+            if (v & 0xffffu) atomicAdd(&hist[2 * i], (unsigned long long)(v & 0xffffu));
+            if (v >> 16) atomicAdd(&hist[2 * i + 1], (unsigned long long)(v >> 16));
+        }
+        __syncthreads();
+    }
+    if (!last_workgroup(&ws.st->done[4 + LEVEL])) return;
+    const unsigned long long rank = LEVEL == 0 ? ws.st->rank : ws.st->exact_rank;
+    const unsigned long long want[1] = {rank};
+    find_ranks<kExactBins>(hist, 0ull, want, [&](int, int bin, unsigned long long below) {
+        if (LEVEL == 0) {
+            ws.st->exact_prefix = (uint32_t)bin << 16;
+            ws.st->exact_rank = rank - below;
+        } else {
+            ws.st->tau_key = prefix | (uint32_t)bin;
+            if (tau_out) *tau_out = value_of(prefix | (uint32_t)bin);
+        }
+    });
+}
+
+__global__ __launch_bounds__(256) void zero_mask_kernel(uint8_t* mask, unsigned long long n)   // everything is pruned
+{
+    const unsigned long long words = n / 4, step = (unsigned long long)gridDim.x * 256;
+    const unsigned long long i0 = (unsigned long long)blockIdx.x * 256 + threadIdx.x;
+    for (unsigned long long i = i0; i < words; i += step) reinterpret_cast<uint32_t*>(mask)[i] = 0u;
+    if (i0 < (n & 3)) mask[words * 4 + i0] = 0;
 }
 
 }  // namespace
@@ -475,27 +713,46 @@ hipError_t launch_prune_mask(const float* abar, int H, int Lq, int Lk, int causa
     w.Lk = Lk;
     w.causal = causal;
     w.per_head = causal ? (Lq + 1) / 2 : Lq;
-    w.units = (long long)H * w.per_head;
-    const long long wg_units = (w.units + kThreads / 64 - 1) / (kThreads / 64);
-    // the histogram takes 128 KB of LDS: one workgroup of 16 wavefronts per compute unit
-    const unsigned grid = (unsigned)min((long long)256, wg_units);
-    const unsigned grid2 = (unsigned)min((long long)512, wg_units);   // 48 KB of LDS: two per compute unit
-    const int none_i = none ? 1 : 0;
+    w.units = H * w.per_head;
 
-    hipLaunchKernelGGL(select_init_kernel, dim3(32), dim3(256), 0, stream, ws, rank, n, tau_out, none_i);
-    if (!none) {
-        hipLaunchKernelGGL(radix_hist_kernel<0>, dim3(grid), dim3(kThreads), 0, stream, w, ws);
-        hipLaunchKernelGGL(radix_select_kernel<0>, dim3(1), dim3(kThreads), 0, stream, ws);
-        hipLaunchKernelGGL(radix_hist_kernel<1>, dim3(grid), dim3(kThreads), 0, stream, w, ws);
-        hipLaunchKernelGGL(radix_select_kernel<1>, dim3(1), dim3(kThreads), 0, stream, ws);
-        hipLaunchKernelGGL(radix_hist_kernel<2>, dim3(grid), dim3(kThreads), 0, stream, w, ws);
-        hipLaunchKernelGGL(radix_select_kernel<2>, dim3(1), dim3(kThreads), 0, stream, ws);
+    hipLaunchKernelGGL(select_init_kernel, dim3(64), dim3(256), 0, stream, ws, rank, n, tau_out, none ? 1 : 0);
+    if (none) {
+        if (mask)
+            hipLaunchKernelGGL(zero_mask_kernel, dim3(2048), dim3(256), 0, stream, mask,
+                               (unsigned long long)H * Lq * Lk);
+        return hipGetLastError();
     }
-    hipLaunchKernelGGL(mask_collect_kernel, dim3(grid2), dim3(kThreads), 0, stream, w, ws, mask, none_i);
-    if (!none) {
-        hipLaunchKernelGGL(candidate_select_kernel, dim3(1), dim3(kThreads), 0, stream, ws, tau_out);
-        if (mask) hipLaunchKernelGGL(candidate_fixup_kernel, dim3(256), dim3(256), 0, stream, ws, mask);
-    }
+    // positions of the longest unit: a row, or a pair of rows with the first padded to a quad
+    const long long unit_len = causal ? (long long)Lk + (Lk - Lq) + 1 + 3 : Lk;
+    Sample s;
+    // a sample for which the interval holds about 2^20 candidates: 2 kSigmas standard deviations of the
+    // sample, as a share of the n entries
+    const double f = (double)rank / (double)n, share = (double)n / (double)(1u << 20);
+    const double want = 4.0 * kSigmas * kSigmas * kDesign * f * (1.0 - f) * share * share;
+    const unsigned long long size = want > (double)kSample ? (unsigned long long)min(want, (double)n) : kSample;
+    s.stride = (uint32_t)min(max(n / size, 1ull), 1ull << 30);
+    s.per_unit = (uint32_t)(((unit_len + 15) / 16 + s.stride - 1) / s.stride);
+    s.slots = (unsigned long long)w.units * s.per_unit;
+    const unsigned sgrid = (unsigned)min(128ull, (s.slots * 4 + kThreads - 1) / kThreads);
+    const int sweep_wgs = (w.units + kSweepThreads / 64 - 1) / (kSweepThreads / 64);
+    // Two wavefronts per SIMD with 8 KB in flight each.  More wavefronts mean more places of the map and
+    // the mask that are read and written at a time, and that costs more than it hides: whole call at
+    // 16 x 4096 x 4096 causal 245 us with 256 workgroups, 258 with 384, 271 with 512, 288 with 768.
+    const unsigned grid = (unsigned)min(256, sweep_wgs);
+    // the exact levels take 128 KB of LDS: one workgroup of 16 wavefronts per compute unit
+    const unsigned egrid = (unsigned)min(256, (w.units + kThreads / 64 - 1) / (kThreads / 64));
+    const unsigned cgrid = (unsigned)min(64ull, (n + kThreads - 1) / kThreads);
+
+    hipLaunchKernelGGL(sample_coarse_kernel, dim3(sgrid), dim3(kThreads), 0, stream, w, s, ws);
+    hipLaunchKernelGGL(sample_fine_kernel, dim3(sgrid), dim3(kThreads), 0, stream, w, s, ws);
+    hipLaunchKernelGGL(mask_sweep_kernel<false>, dim3(grid), dim3(kSweepThreads), 0, stream, w, ws, mask);
+    hipLaunchKernelGGL(candidate_bins_kernel, dim3(cgrid), dim3(kThreads), 0, stream, ws);
+    hipLaunchKernelGGL(candidate_last_kernel, dim3(cgrid), dim3(kThreads), 0, stream, ws, tau_out);
+    if (mask) hipLaunchKernelGGL(candidate_fixup_kernel, dim3(256), dim3(256), 0, stream, ws, mask);
+    // nothing of what follows runs unless the interval failed
+    hipLaunchKernelGGL(exact_level_kernel<0>, dim3(egrid), dim3(kThreads), 0, stream, w, ws, tau_out);
+    hipLaunchKernelGGL(exact_level_kernel<1>, dim3(egrid), dim3(kThreads), 0, stream, w, ws, tau_out);
+    if (mask) hipLaunchKernelGGL(mask_sweep_kernel<true>, dim3(grid), dim3(kSweepThreads), 0, stream, w, ws, mask);
     return hipGetLastError();
 }
 

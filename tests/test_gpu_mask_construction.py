@@ -184,6 +184,24 @@ def test_prune_mask_more_ties_than_the_candidate_buffer_holds(spread):
         check_prune(a, p, causal)
 
 
+@pytest.mark.parametrize("levels", [0, 1 << 20, 64])
+@pytest.mark.parametrize("shape,causal", [((2, 1500, 1777), False), ((3, 2000, 2003), True), ((5, 16, 60001), False),
+                                          ((40, 200, 1031), True)])
+def test_prune_mask_where_only_a_sample_is_looked_at(shape, causal, levels):
+    """More entries than the first look reads (2^21), rows that start anywhere: distinct values, values
+    with some ties, and values of 64 kinds, where the interval of the sample holds more candidates than
+    there is room for and the exact way decides.  Ranks in the middle and at both ends."""
+    rng = np.random.default_rng(shape[1])
+    a = rng.lognormal(-6.0, 2.0, size=shape).astype(np.float32)
+    a *= np.exp(-np.arange(shape[2], dtype=np.float32) / shape[2])         # neighbours resemble each other
+    if levels:
+        top = float(a.max())
+        a = (np.ceil(a ** 0.25 * (levels / top ** 0.25)) / levels).astype(np.float32)
+    for p in (0.9, 0.5, 0.0, 1e-6, 0.999999):
+        print("prune", shape, causal, levels, p, flush=True)
+        check_prune(a, p, causal, layout_block_ms=())
+
+
 def test_mask_feeds_layout_and_attention_end_to_end():
     """Q, K -> mean map -> mask -> layout on the GPU; entries whose oracle mean is not within
     the map tolerance of the oracle's threshold must agree with the oracle's mask."""

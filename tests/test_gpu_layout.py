@@ -38,6 +38,18 @@ def test_random_masks(H, Lq, Lk, bm, bn, density):
     assert_layout_equal(lay, mask)
 
 
+@pytest.mark.parametrize("bm", [16, 64, 128])
+@pytest.mark.parametrize("Lk", [1, 15, 16, 17, 1007, 1023, 1024, 1025, 2049])
+def test_row_ends_of_the_byte_mask_scan(Lk, bm):
+    """A lane takes 16 columns at any alignment and a wavefront 1024: ends of rows inside, at and just
+    behind both, one row short of a block row and one more; the last column is always kept."""
+    for Lq in (2 * bm - 1, 2 * bm + 1):
+        print("layout row ends", Lq, Lk, bm, flush=True)
+        mask = synth.random_mask(2, Lq, Lk, 0.02, seed=Lk)
+        mask[:, :, -1] = 255
+        assert_layout_equal(ap.ap_build_layout(torch.from_numpy(mask).cuda(), bm, 64), mask)
+
+
 def test_any_nonzero_byte_is_kept():
     rng = np.random.default_rng(5)
     mask = (rng.random((2, 128, 128)) < 0.05).astype(np.uint8) * rng.integers(1, 256, (2, 128, 128)).astype(np.uint8)

@@ -813,7 +813,7 @@ def main():
                      "frac": head_res["hbm_roofline_frac"],
                      "traffic": MEASURED_TRAFFIC_BYTES.get((head.name, args.block_m, not args.no_sched)),
                      "traffic_source": "profiles/fwd_mfma_kernel_C5.md (separate rocprofv3 --pmc runs, 2026-11-28, commit a175aa2)",
-                     "kernel": "fwd_mfma_kernel" if head.dtype == "bf16" else "fwd_valu_kernel",
+                     "kernel": "fwd_mfma_kernel" if head.dtype == "bf16" else "fwd_f32_kernel",
                      "algorithmic_bytes_per_launch": head_res["hbm_alg_bytes"]},
         "roofline_dense_run": {"bound": "mfma", "achieved": head_res["dense_tflops"], "peak": MFMA_BF16_PEAK_TFLOPS,
                                "unit": "TFLOP/s", "frac": head_res["dense_mfma_frac"]},

@@ -265,7 +265,7 @@ static ap_status fwd_common(const void* Q, const void* K, const void* V, void* O
     else if (dtype == AP_BF16)
         e = ap::launch_fwd_mfma(a, (hipStream_t)stream);
     else
-        e = ap::launch_fwd_valu(a, false, (hipStream_t)stream);
+        e = ap::launch_fwd_f32(a, (hipStream_t)stream);
     return e == hipSuccess ? AP_OK : AP_ERR_HIP;
 }
 

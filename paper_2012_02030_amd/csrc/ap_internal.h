@@ -34,7 +34,7 @@ hipError_t launch_build_schedule(const int32_t* row_ptr, const int32_t* col_idx,
                                  long long cap, int causal, int min_cols, const Schedule& s,
                                  hipStream_t stream);
 
-// ---- attention forward (ap_attn_valu.hip, ap_attn_mfma.hip)
+// ---- attention forward (ap_attn_f32.hip, ap_attn_mfma.hip)
 struct FwdArgs {
     const void* Q;
     const void* K;
@@ -57,8 +57,8 @@ struct FwdArgs {
     float* part_lse;                // [splits, B, H, Lq]
 };
 
-// fp32-arithmetic kernel (one query per lane); handles fp32 and bf16 storage, block 64x64
-hipError_t launch_fwd_valu(const FwdArgs& a, bool bf16, hipStream_t stream);
+// fp32 matrix-core kernel, block 64x64
+hipError_t launch_fwd_f32(const FwdArgs& a, hipStream_t stream);
 // bf16 matrix-core kernel; block_m 64 or 128, block_n 64
 hipError_t launch_fwd_mfma(const FwdArgs& a, hipStream_t stream);
 // same result, the entries of every block row cut into a.splits chunks and merged (block_m 64)

@@ -382,14 +382,14 @@ hipError_t launch_d(const BwdArgs& a, hipStream_t stream)
 {
     const int nQB = (a.Lq + 63) / 64, nKB = (a.Lk + 63) / 64;
     const int nQP = (nQB + 1) / 2, nKP = (nKB + 1) / 2;
-    const long long rows = (long long)a.B * a.H * a.Lq;
-    const long long dthreads = rows * (D / 8);
-    hipLaunchKernelGGL(bwd_delta_kernel<D>, dim3((unsigned)((dthreads + 255) / 256)), dim3(256), 0, stream, a);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    if (a.sched.cnt) {
+    hipError_t e;
+    if (a.sched.cnt) {                                       // forms delta on the way
         e = launch_bwd_sched(a, true, false, stream);
     } else {
+        const long long dthreads = (long long)a.B * a.H * a.Lq * (D / 8);
+        hipLaunchKernelGGL(bwd_delta_kernel<D>, dim3((unsigned)((dthreads + 255) / 256)), dim3(256), 0, stream, a);
+        e = hipGetLastError();
+        if (e != hipSuccess) return e;
         hipLaunchKernelGGL(bwd_dq_kernel<D>, dim3((unsigned)(a.B * a.H * nQP)), dim3(256), 0, stream, a, nQB, nQP);
         e = hipGetLastError();
     }

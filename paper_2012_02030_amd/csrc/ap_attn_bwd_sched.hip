@@ -4,11 +4,25 @@
 // queries per block column), so the backward pass skips what the forward pass skips.  Causal
 // limits are folded into the entry bitmaps by the schedule builders.
 //
-// One workgroup of two wavefronts per block row (dQ) or block column (dK, dV).  Every tile is
-// stored once in LDS, with a swizzle that suits both the row-wise reads (scores) and the
-// transposing reads (gradient products).  Two LDS stages: the next entry's tiles travel while the
-// current entry is computed; the metadata of the entry after that (start, gather indices, bitmap
-// words, per-query statistics) is fetched into registers in the same step.
+// One workgroup of four wavefronts per block row (dQ) or block column (dK, dV); a wavefront forms the
+// scores of one 32 x 32 quarter of every entry.  Every tile is stored once in LDS, with a swizzle that
+// suits both the row-wise reads (scores) and the transposing reads (gradient products).  Two LDS
+// stages: the next entry's tiles travel while the current entry is computed; the metadata of the entry
+// after that (start, gather indices, bitmap words, per-query statistics) is fetched into registers in
+// the same step.
+//
+// What bounds these kernels is the issue of instructions around the matrix work, so what counts is a
+// second wavefront on every SIMD, i.e. at most 256 registers at D = 128.  Two wavefronts per workgroup
+// that each formed a 32 x 64 half and, for dK and dV, kept both accumulators needed 314 (dQ) and 393 of
+// them: one wavefront per SIMD, every wait exposed.  A quarter per wavefront and
+//   dQ      partial sums over the two key halves, added at the end,
+//   dK, dV  accumulators divided by what they hold (one wavefront of a pair sums dV over both query
+//           halves, the other dK) with the probabilities or score gradients that the partner needs
+//           handed over through LDS in bf16, the precision the products use anyway,
+// fit.  B4 H16 L4096 D128, 10 % kept: dQ 229 -> 175 us (29 of the 229 a pass of its own for delta), dK and dV
+// 269 -> 230 us; B4 H16 L2048 218 -> 156 us in all.  Of a dQ workgroup's 20 us there, 7 pass before its first
+// entry (a chain of cold loads), 1.5 per entry, 2 in the sum over key halves and the store; of a dK, dV
+// workgroup's 27 us 5.4, 2.4 per entry and 1.5.  Inside an entry the LDS pipe is busy about 70 % of the time.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -31,22 +45,129 @@ enum { SOFTMAX = 0, ENTMAX15 = 1, GBAR = 2 };
 
 __device__ __forceinline__ float lse2_of(float lse) { return lse == -INFINITY ? INFINITY : lse * kLog2e; }
 
+// Two products that share nothing but their shape, their matrix instructions in turn (each is one
+// dependent chain): s = T0 * B0, p = T1 * B1 for 32 rows of two tiles in LDS (SWZ_BOTH; `row` is this
+// lane's row, k_swz = (l / 32) ^ swz_u(row)) and two operands in registers.  Operands are requested
+// AHEAD contraction steps early.
+//
+// The operands that stay in registers (Q and dO rows, or K and V rows) come the same way as the tiles: 1 KB
+// per instruction into the LDS stage that is still free, and from there with one row per lane.  Loaded into
+// registers directly they are 16 bytes from each of 32 rows per instruction, about 50 cycles of the
+// vector memory path instead of 16, in front of the first tile of every workgroup.
+template <int D>
+__device__ __forceinline__ void read_operand(const uint16_t* T, int row, int k_swz, bf16x8* x)
+{
+#pragma unroll
+    for (int kk = 0; kk < D / 16; ++kk)
+        x[kk] = *reinterpret_cast<const bf16x8*>(T + row * D + ((2 * kk) ^ k_swz) * 8);
+}
+
+template <int CTRL>
+__device__ __forceinline__ float dpp_add(float v)
+{
+    return v + __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, 0xf, 0xf, false));
+}
+// sum over aligned groups of N = 4, 8 or 16 lanes, in every lane of the group
+template <int N>
+__device__ __forceinline__ float group_sum(float v)
+{
+    v = dpp_add<0xB1>(v);                                    // quad_perm [1,0,3,2]
+    v = dpp_add<0x4E>(v);                                    // quad_perm [2,3,0,1]
+    if (N >= 8) v = dpp_add<0x141>(v);                       // row_half_mirror
+    if (N >= 16) v = dpp_add<0x140>(v);                      // row_mirror
+    return v;
+}
+
+template <int D>
+__device__ __forceinline__ void two_products_32(const uint16_t* T0, const uint16_t* T1, int row, int k_swz,
+                                                const bf16x8* b0, const bf16x8* b1, f32x16& s, f32x16& p)
+{
+    constexpr int KSTEPS = D / 16;
+    constexpr int AHEAD = KSTEPS < 3 ? KSTEPS : 3;
+#pragma unroll
+    for (int i = 0; i < 16; ++i) s[i] = p[i] = 0.f;
+    bf16x8 r0[KSTEPS], r1[KSTEPS];
+    auto read = [&](int kk) {
+        r0[kk] = *reinterpret_cast<const bf16x8*>(T0 + row * D + ((2 * kk) ^ k_swz) * 8);
+        r1[kk] = *reinterpret_cast<const bf16x8*>(T1 + row * D + ((2 * kk) ^ k_swz) * 8);
+    };
+#pragma unroll
+    for (int kk = 0; kk < AHEAD; ++kk) read(kk);
+#pragma unroll
+    for (int kk = 0; kk < KSTEPS; ++kk) {
+        if (kk + AHEAD < KSTEPS) read(kk + AHEAD);
+        s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(r0[kk], b0[kk], s, 0, 0, 0);
+        p = __builtin_amdgcn_mfma_f32_32x32x16_bf16(r1[kk], b1[kk], p, 0, 0, 0);
+    }
+    __builtin_amdgcn_sched_group_barrier(0x100, 2 * AHEAD, 0);   // pin that order
+#pragma unroll
+    for (int kk = 0; kk < KSTEPS; ++kk) {
+        if (kk + AHEAD < KSTEPS) __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);
+        __builtin_amdgcn_sched_group_barrier(0x008, 2, 0);
+    }
+}
+
+// acc^T[D x 32] += T^T[D x 32] * P[32 x 32] for 32 rows of a tile in LDS (SWZ_BOTH), starting at Ts (a
+// multiple of 32 rows into the tile); P: 16 scores per lane in the order the score products leave them,
+// as two bf16 operands.
+template <int D>
+__device__ __forceinline__ void tr_mm_32(lds_u16* Ts, const bf16x8* pb, f32x16* acc, const TrReadU<D>& t)
+{
+    constexpr int DBLK = D / 32;
+    bf16x8 x[2][DBLK];
+    auto read = [&](int ks) {
+#pragma unroll
+        for (int db = 0; db < DBLK; ++db) {
+            const bf16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((lds_bf16x4*)(Ts + 16 * ks * D + t.off[0][db]));
+            const bf16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((lds_bf16x4*)(Ts + 16 * ks * D + t.off[1][db]));
+            x[ks][db] = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
+        }
+    };
+    read(0);
+    read(1);
+#pragma unroll
+    for (int ks = 0; ks < 2; ++ks)
+#pragma unroll
+        for (int db = 0; db < DBLK; ++db)
+            acc[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(x[ks][db], pb[ks], acc[db], 0, 0, 0);
+}
+
+__device__ __forceinline__ void to_operands(const f32x16& x, bf16x8* pb)
+{
+#pragma unroll
+    for (int ks = 0; ks < 2; ++ks)
+#pragma unroll
+        for (int e = 0; e < 8; ++e) pb[ks][e] = (__bf16)x[8 * ks + e];
+}
+
+// all ones (one-bit signed field) selects x, zero selects -infinity
+__device__ __forceinline__ float or_minus_inf(float x, uint32_t keep)
+{
+    return __uint_as_float((__float_as_uint(x) & keep) | (0xff800000u & ~keep));
+}
+
+// The leading arguments repeat fields of `a`: they arrive in registers when a wavefront starts
+// (kernel-argument preloading), so the chain row pointer -> entry -> tiles starts at once.
 template <int D, int MODE>
-__global__ __launch_bounds__(128, D == 128 ? 1 : 2) void bwd_dq_sched_kernel(BwdArgs a, int nQB)
+__global__ __launch_bounds__(256, 2) void bwd_dq_sched_kernel(
+    const int32_t* __restrict__ p_row_ptr, const int32_t* __restrict__ p_cnt, const int32_t* __restrict__ p_start,
+    const int32_t* __restrict__ p_cols, const uint32_t* __restrict__ p_words, int nQB, int p_B, BwdArgs a)
 {
     constexpr int TILE = kBN * D;
     constexpr int KSTEPS = D / 16;
     constexpr int DBLK = D / 32;
     constexpr int RPI = 64 / (D / 8);
-    constexpr int NLOAD = (D / 8) / 2;
+    constexpr int NLOAD = (D / 8) / 4;
     constexpr int STAGE = 2 * TILE;                          // K rows, V rows
     __shared__ __attribute__((aligned(1024))) uint16_t smem[2 * STAGE];
+    __shared__ float s_pair[2][2][64];                       // sums that the two key halves of a query add up
     lds_u16* lds = (lds_u16*)smem;
 
     const int tid = threadIdx.x;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int lane = tid & 63;
     const int n = lane & 31, hh = lane >> 5;
+    const int qh = wave & 1, kh = wave >> 1;                 // this wavefront's quarter of every entry
     const int g_row = lane / (D / 8);
     // A zero the compiler cannot see through.  Indexing with it turns the per-entry load of a
     // start into a vector load: a scalar load inside the loop would make every later wait for an
@@ -56,38 +177,86 @@ __global__ __launch_bounds__(128, D == 128 ? 1 : 2) void bwd_dq_sched_kernel(Bwd
 
     const int bid = xcd_contiguous(blockIdx.x, gridDim.x);
     const int qb = nQB - 1 - (bid % nQB);
-    const int h = (bid / nQB) % a.H;
-    const int b = bid / (nQB * a.H);
+    const int b = (bid / nQB) % p_B;                         // the examples of a head one after another: they share its schedule
+    const int h = bid / (nQB * p_B);
+    const int r = h * nQB + qb;
+    const int t0 = p_row_ptr[r];
+    const int t1 = t0 + p_cnt[r];
 
     const uint16_t* Qp = (const uint16_t*)a.Q + (size_t)b * a.sq[0] + (size_t)h * a.sq[1];
     const uint16_t* Gp = (const uint16_t*)a.dO + (size_t)b * a.so[0] + (size_t)h * a.so[1];
     const uint16_t* Kp = (const uint16_t*)a.K + (size_t)b * a.sk[0] + (size_t)h * a.sk[1];
     const uint16_t* Vp = (const uint16_t*)a.V + (size_t)b * a.sv[0] + (size_t)h * a.sv[1];
+    const int sq_bytes = (int)a.sq[2] * 2, so_bytes = (int)a.so[2] * 2;
+    const rsrc_t q_rsrc = make_rsrc(Qp, (unsigned)((a.Lq - 1) * sq_bytes + D * 2));
+    const rsrc_t g_rsrc = make_rsrc(Gp, (unsigned)((a.Lq - 1) * so_bytes + D * 2));
     uint16_t* dQp = (uint16_t*)a.dQ + (size_t)b * a.sq[0] + (size_t)h * a.sq[1];
     const int sk_bytes = (int)a.sk[2] * 2, sv_bytes = (int)a.sv[2] * 2;
     const rsrc_t k_rsrc = make_rsrc(Kp, (unsigned)((a.Lk - 1) * sk_bytes + D * 2));
     const rsrc_t v_rsrc = make_rsrc(Vp, (unsigned)((a.Lk - 1) * sv_bytes + D * 2));
 
-    const int brow = wave * 32 + n;
+    const int brow = qh * 32 + n;
     const int qrow = qb * 64 + brow;
     const bool row_ok = qrow < a.Lq;
-    const int qload = row_ok ? qrow : a.Lq - 1;
-    bf16x8 qreg[KSTEPS], greg[KSTEPS];                       // Q^T and dO^T operands
-    {
-        const uint16_t* qr = Qp + (size_t)qload * a.sq[2] + 8 * hh;
-        const uint16_t* gr = Gp + (size_t)qload * a.so[2] + 8 * hh;
+
+    // metadata of an entry: where it starts (or -1), gather key `lane` (read for every entry,
+    // used by gathered ones only) and this lane's half of its bitmap word: three loads per entry
+    struct Meta {
+        int start;
+        int key;
+        uint32_t word;
+    };
+    auto fetch = [&](int t, Meta& m) {
+        m.start = p_start[t + vzero];                        // a vector load: see vzero
+        m.key = p_cols[(size_t)t * 64 + lane];
+        m.word = p_words[((size_t)t * 64 + brow) * 2 + kh];
+    };
+    auto issue = [&](const Meta& m, int stage) {
+        lds_u16* base = lds + stage * STAGE;
+        const int start = __builtin_amdgcn_readfirstlane(m.start);
+        if (start >= 0) {
+            issue_tile_loads<D, 4, SWZ_BOTH>(k_rsrc, base, start, sk_bytes, wave, lane);
+            issue_tile_loads<D, 4, SWZ_BOTH>(v_rsrc, base + TILE, start, sv_bytes, wave, lane);
+        } else {
+            int gk[NLOAD];                                   // keys of the rows this lane loads
 #pragma unroll
-        for (int kk = 0; kk < KSTEPS; ++kk) {
-            qreg[kk] = *reinterpret_cast<const bf16x8*>(qr + 16 * kk);
-            greg[kk] = *reinterpret_cast<const bf16x8*>(gr + 16 * kk);
+            for (int u = 0; u < NLOAD; ++u) gk[u] = __shfl(m.key, (wave + 4 * u) * RPI + g_row, 64);
+            issue_gather_loads<D, 4, SWZ_BOTH>(k_rsrc, base, gk, sk_bytes, wave, lane);
+            issue_gather_loads<D, 4, SWZ_BOTH>(v_rsrc, base + TILE, gk, sv_bytes, wave, lane);
+        }
+    };
+
+    Meta cur, nxt;
+    cur.word = 0;
+    if (t0 < t1) fetch(t0, cur);                             // everything waits for this first
+    // Q and dO rows of the block row (rows >= Lq read as zeros) into the second stage
+    issue_tile_loads<D, 4, SWZ_BOTH>(q_rsrc, lds + STAGE, qb * 64, sq_bytes, wave, lane);
+    issue_tile_loads<D, 4, SWZ_BOTH>(g_rsrc, lds + STAGE + TILE, qb * 64, so_bytes, wave, lane);
+    const size_t stat_base = ((size_t)b * a.H + h) * a.Lq;
+    // SOFTMAX: log-sum-exp; entmax modes: tau (+inf for a query without keys) and gbar.  Loaded for every
+    // lane and looked at later: a branch on the row would wait here, before the first tile is requested.
+    float lse2 = a.lse[stat_base + (row_ok ? qrow : a.Lq - 1)];
+    float delta = MODE == ENTMAX15 ? a.delta[stat_base + (row_ok ? qrow : a.Lq - 1)] : 0.f;
+    // delta = <dO, O> is formed here, where dO is at hand (a pass of its own reads dO once more).  The dK, dV
+    // kernel reads it from memory.
+    constexpr int CPR = D / 8, NO = 64 * CPR / 256;          // 16-byte pieces of a row; pieces of O per thread
+    uint4 o[NO];
+    if (MODE == SOFTMAX) {
+        const uint16_t* Op = (const uint16_t*)a.O + (size_t)b * a.so[0] + (size_t)h * a.so[1];
+#pragma unroll
+        for (int u = 0; u < NO; ++u) {
+            const int idx = u * 256 + tid, row = min(qb * 64 + idx / CPR, a.Lq - 1);
+            o[u] = *reinterpret_cast<const uint4*>(Op + (size_t)row * a.so[2] + idx % CPR * 8);
         }
     }
-    const size_t stat = ((size_t)b * a.H + h) * a.Lq + qload;
-    // SOFTMAX: base-2 log-sum-exp and delta; entmax modes: tau (+inf for a query without keys) and gbar
-    float lse2 = row_ok ? (MODE == SOFTMAX ? lse2_of(a.lse[stat]) : a.lse[stat]) : INFINITY;
-    float delta = row_ok && MODE != GBAR ? a.delta[stat] : 0.f;
+    nxt = cur;
+    if (t0 < t1) {
+        issue(cur, 0);
+        if (t0 + 1 < t1) fetch(t0 + 1, nxt);
+    }
     const float sc = MODE == SOFTMAX ? a.scale * kLog2e : a.scale * 0.5f;
     float num = 0.f, den = 0.f;                              // GBAR: this lane's share of sum u dP and sum u
+    const int k_row = kh * 32 + n;
     const int k_swz = hh ^ swz_u<D>(n);
     const TrReadU<D> tr = make_tr_read_u<D>(lane);
 
@@ -97,55 +266,41 @@ __global__ __launch_bounds__(128, D == 128 ? 1 : 2) void bwd_dq_sched_kernel(Bwd
 #pragma unroll
         for (int i = 0; i < 16; ++i) dqacc[db][i] = 0.f;
 
-    const int r = h * nQB + qb;
-    const int t0 = a.row_ptr[r];
-    const int t1 = t0 + a.sched.cnt[r];
-
-    // metadata of an entry: where it starts (or -1), gather key `lane` (read for every entry,
-    // used by gathered ones only) and this lane's bitmap word: three loads per entry
-    struct Meta {
-        int start;
-        int key;
-        uint64_t word;
-    };
-    auto fetch = [&](int t, Meta& m) {
-        m.start = a.sched.start[t + vzero];                  // a vector load: see vzero
-        m.key = a.sched.cols[(size_t)t * 64 + lane];
-        m.word = a.sched.bitmaps[(size_t)t * 64 + brow];     // causal limit folded in
-    };
-    auto issue = [&](const Meta& m, int stage) {
-        lds_u16* base = lds + stage * STAGE;
-        const int start = __builtin_amdgcn_readfirstlane(m.start);
-        if (start >= 0) {
-            issue_tile_loads<D, 2, SWZ_BOTH>(k_rsrc, base, start, sk_bytes, wave, lane);
-            issue_tile_loads<D, 2, SWZ_BOTH>(v_rsrc, base + TILE, start, sv_bytes, wave, lane);
-        } else {
-            int gk[NLOAD];                                   // keys of the rows this lane loads
-#pragma unroll
-            for (int u = 0; u < NLOAD; ++u) gk[u] = __shfl(m.key, (wave + 2 * u) * RPI + g_row, 64);
-            issue_gather_loads<D, 2, SWZ_BOTH>(k_rsrc, base, gk, sk_bytes, wave, lane);
-            issue_gather_loads<D, 2, SWZ_BOTH>(v_rsrc, base + TILE, gk, sv_bytes, wave, lane);
-        }
-    };
-
-    Meta cur, nxt;
-    if (t0 < t1) {
-        fetch(t0, cur);
-        issue(cur, 0);
-        nxt = cur;
-        if (t0 + 1 < t1) fetch(t0 + 1, nxt);
-    }
-    // first use of the loaded registers before the loop, so that no wait for them lands inside it
+    // everything has landed here, so that no wait for loaded registers lands inside the loop
     wait_vmem();
-    settle<KSTEPS>(qreg);
-    settle<KSTEPS>(greg);
     asm volatile("" : "+v"(lse2), "+v"(delta));
+    __syncthreads();
+    bf16x8 qreg[KSTEPS], greg[KSTEPS];                       // Q^T and dO^T operands
+    read_operand<D>(smem + STAGE, brow, k_swz, qreg);
+    read_operand<D>(smem + STAGE + TILE, brow, k_swz, greg);
+    lse2 = row_ok ? (MODE == SOFTMAX ? lse2_of(lse2) : lse2) : INFINITY;
+    if (MODE == SOFTMAX) {
+#pragma unroll
+        for (int u = 0; u < NO; ++u) {
+            const int idx = u * 256 + tid, row = idx / CPR, c = idx % CPR;
+            const uint4 g4 = *reinterpret_cast<const uint4*>(smem + STAGE + TILE + row * D + (c ^ swz_u<D>(row)) * 8);
+            const uint32_t ow[4] = {o[u].x, o[u].y, o[u].z, o[u].w}, gw[4] = {g4.x, g4.y, g4.z, g4.w};
+            float d = 0.f;
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                d = fmaf(__uint_as_float(ow[k] << 16), __uint_as_float(gw[k] << 16), d);
+                d = fmaf(__uint_as_float(ow[k] & 0xffff0000u), __uint_as_float(gw[k] & 0xffff0000u), d);
+            }
+            d = group_sum<CPR>(d);
+            if (c == 0) {
+                s_pair[0][0][row] = d;
+                if (qb * 64 + row < a.Lq) a.delta[stat_base + qb * 64 + row] = d;
+            }
+        }
+        __syncthreads();
+        delta = s_pair[0][0][brow];
+    }
 
     int stage = 0;
     for (int t = t0; t < t1; ++t) {
         wait_vmem();                                         // entry t and the metadata of t + 1 have landed
         __syncthreads();                                     // ... for everybody; the other stage is free
-        const uint64_t word = cur.word;
+        const uint32_t word = cur.word;
         if (t + 1 < t1) {
             issue(nxt, stage ^ 1);
             cur = nxt;
@@ -153,67 +308,108 @@ __global__ __launch_bounds__(128, D == 128 ? 1 : 2) void bwd_dq_sched_kernel(Bwd
         }
         if (__ballot(word != 0) != 0) {
             uint16_t* base = smem + stage * STAGE;
-            f32x16 sacc[2], pacc[2];
-            qk_64<D>(base, qreg, n, k_swz, sacc);            // S^T  = K Q^T
-            qk_64<D>(base + TILE, greg, n, k_swz, pacc);     // dP^T = V dO^T
-            const uint64_t wsh = word >> (4 * hh);
-            const uint32_t wbits[2] = {(uint32_t)wsh, (uint32_t)(wsh >> 32)};
+            f32x16 s, p;
+            two_products_32<D>(base, base + TILE, k_row, k_swz, qreg, greg, s, p);   // S^T = K Q^T, dP^T = V dO^T
+            const int wbits = (int)(word >> (4 * hh));
 #pragma unroll
-            for (int kb = 0; kb < 2; ++kb)
-#pragma unroll
-                for (int i = 0; i < 16; ++i) {
-                    const int pos = 8 * (i / 4) + (i % 4);
-                    const uint32_t keep = (uint32_t)__builtin_amdgcn_sbfe((int)wbits[kb], pos, 1);
-                    const float x = fmaf(sacc[kb][i], sc, -lse2);
-                    if (MODE == SOFTMAX) {
-                        const float p = __builtin_amdgcn_exp2f(__uint_as_float((__float_as_uint(x) & keep) | (0xff800000u & ~keep)));
-                        sacc[kb][i] = p * (pacc[kb][i] - delta);   // dS^T
+            for (int i = 0; i < 16; ++i) {
+                const uint32_t keep = (uint32_t)__builtin_amdgcn_sbfe(wbits, 8 * (i / 4) + (i % 4), 1);
+                const float x = fmaf(s[i], sc, -lse2);
+                if (MODE == SOFTMAX) {
+                    s[i] = __builtin_amdgcn_exp2f(or_minus_inf(x, keep)) * (p[i] - delta);   // dS^T
+                } else {
+                    const float u = fmaxf(__uint_as_float(__float_as_uint(x) & keep), 0.f);   // pruned: 0
+                    if (MODE == GBAR) {
+                        num = fmaf(u, p[i], num);
+                        den += u;
                     } else {
-                        const float u = fmaxf(__uint_as_float(__float_as_uint(x) & keep), 0.f);   // pruned: 0
-                        if (MODE == GBAR) {
-                            num = fmaf(u, pacc[kb][i], num);
-                            den += u;
-                        } else {
-                            sacc[kb][i] = u * (pacc[kb][i] - delta);   // dS^T
-                        }
+                        s[i] = u * (p[i] - delta);           // dS^T
                     }
                 }
-            if (MODE != GBAR) tr_mm_64_u<D>(lds + stage * STAGE, sacc, dqacc, tr);   // dQ^T += K^T dS^T
+            }
+            if (MODE != GBAR) {
+                bf16x8 pb[2];
+                to_operands(s, pb);
+                tr_mm_32<D>(lds + stage * STAGE + kh * 32 * D, pb, dqacc, tr);   // dQ^T += K^T dS^T
+            }
         }
         stage ^= 1;
     }
-    if (MODE == GBAR) {                                      // the two half-wavefronts hold different keys
+    if (MODE == GBAR) {                                      // half-wavefronts and key halves hold different keys
         num += __shfl_xor(num, 32, 64);
         den += __shfl_xor(den, 32, 64);
-        if (row_ok && hh == 0) a.delta[stat] = den > 0.f ? num / den : 0.f;
+        if (hh == 0) {
+            s_pair[kh][0][brow] = num;
+            s_pair[kh][1][brow] = den;
+        }
+        __syncthreads();
+        num = s_pair[0][0][brow] + s_pair[1][0][brow];
+        den = s_pair[0][1][brow] + s_pair[1][1][brow];
+        if (row_ok && hh == 0 && kh == 0) a.delta[stat_base + qrow] = den > 0.f ? num / den : 0.f;
         return;
     }
+    // add the two key halves: each wavefront gives away half of its 32-column blocks and finishes the others
     __syncthreads();                                         // all wavefronts are done with the tiles
-    store_rows_bf16<D>(smem + wave * 32 * D, dqacc, a.scale, lane,
-                       dQp + (size_t)(qb * 64 + wave * 32) * a.sq[2], a.sq[2], a.Lq - (qb * 64 + wave * 32));
+    constexpr int HB = DBLK >= 2 ? DBLK / 2 : 1;
+    float4* give = reinterpret_cast<float4*>(smem);          // [wave][block][quarter][lane]
+    const int mine = DBLK >= 2 ? kh * HB : 0, other = DBLK >= 2 ? (1 - kh) * HB : 0;
+    if (DBLK >= 2 || kh == 1) {
+#pragma unroll
+        for (int db = 0; db < DBLK; ++db) {
+            if (db < other || db >= other + HB) continue;
+#pragma unroll
+            for (int g = 0; g < 4; ++g)
+                give[((wave * HB + db % HB) * 4 + g) * 64 + lane] =
+                    make_float4(dqacc[db][4 * g], dqacc[db][4 * g + 1], dqacc[db][4 * g + 2], dqacc[db][4 * g + 3]);
+        }
+    }
+    __syncthreads();
+    if (DBLK < 2 && kh == 1) return;
+    f32x16 sum[HB];
+#pragma unroll
+    for (int hb = 0; hb < HB; ++hb)
+#pragma unroll
+        for (int g = 0; g < 4; ++g) {
+            const float4 v = give[(((wave ^ 2) * HB + hb) * 4 + g) * 64 + lane];
+            const float ve[4] = {v.x, v.y, v.z, v.w};
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const float own = DBLK >= 2 && kh ? dqacc[DBLK - HB + hb][4 * g + e] : dqacc[hb][4 * g + e];
+                sum[hb][4 * g + e] = own + ve[e];
+            }
+        }
+    __syncthreads();                                         // the sums are read: their place becomes the stores' staging
+    const int row0 = qb * 64 + qh * 32;
+    store_rows_bf16<HB * 32>(smem + wave * 32 * HB * 32, sum, a.scale, lane,
+                             dQp + (size_t)row0 * a.sq[2] + mine * 32, a.sq[2], a.Lq - row0);
 }
 
-// Two wavefronts per SIMD where the registers allow it without spilling (the 1.5-entmax form at
-// D = 64 needs a few more than 256).
+// A pair of wavefronts per 32 keys.  Wavefront `role` of it forms the scores of query half `role` of every
+// entry; role 0 sums dV over both query halves, role 1 sums dK, and each hands the other what it needs of
+// its own half: role 0 the score gradients, role 1 the probabilities.
 template <int D, int NORM>
-__global__ __launch_bounds__(128, (D == 128 || (D == 64 && NORM == 1)) ? 1 : 2) void bwd_dkv_sched_kernel(BwdArgs a, int nKB)
+__global__ __launch_bounds__(256, 2) void bwd_dkv_sched_kernel(
+    const int32_t* __restrict__ p_col_ptr, const int32_t* __restrict__ p_cnt, const int32_t* __restrict__ p_start,
+    const int32_t* __restrict__ p_cols, const uint32_t* __restrict__ p_words, int nKB, int p_H, int p_B, int NP, BwdArgs a)
 {
     constexpr int TILE = kBN * D;
     constexpr int KSTEPS = D / 16;
     constexpr int DBLK = D / 32;
     constexpr int RPI = 64 / (D / 8);
-    constexpr int NLOAD = (D / 8) / 2;
+    constexpr int NLOAD = (D / 8) / 4;
     constexpr int STAGE = 2 * TILE;                          // Q rows, dO rows
     __shared__ __attribute__((aligned(1024))) uint16_t smem[2 * STAGE];
-    __shared__ __attribute__((aligned(16))) float s_lse2[2][64];
-    __shared__ __attribute__((aligned(16))) float s_delta[2][64];
-    __shared__ __attribute__((aligned(16))) uint32_t s_half[2][2][64];   // bitmap words: low halves, high halves
+    __shared__ __attribute__((aligned(16))) bf16x8 s_hand[4][2][64];     // what a wavefront hands its partner
+    __shared__ __attribute__((aligned(16))) float s_stat[4][64];         // of its 32 queries: lse (or tau), delta (or gbar)
+    __shared__ __attribute__((aligned(16))) uint32_t s_word[4][32];      // ... and words of kept keys, its half
+    __shared__ uint32_t s_live[2][4];                        // does a wavefront's quarter hold anything?  by parity of the entry
     lds_u16* lds = (lds_u16*)smem;
 
     const int tid = threadIdx.x;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int lane = tid & 63;
     const int n = lane & 31, hh = lane >> 5;
+    const int kh = wave & 1, role = wave >> 1;
     const int g_row = lane / (D / 8);
     // A zero the compiler cannot see through.  Indexing with it turns the per-entry load of a
     // start into a vector load: a scalar load inside the loop would make every later wait for an
@@ -225,16 +421,15 @@ __global__ __launch_bounds__(128, (D == 128 || (D == 64 && NORM == 1)) ? 1 : 2) 
     // takes.  Every XCD gets a contiguous range of pairs (they share Q and dO rows in its L2); when
     // the pairs divide evenly over the 8 XCDs, the heavy columns of all pairs of the range come
     // first, so that the longest workgroups start at once, then the other columns pair by pair.
-    const int32_t* order = a.csched.cnt + (size_t)a.H * nKB;
-    const int32_t* n_heavy = order + (size_t)a.H * nKB;
-    const int NP = a.B * a.H;
+    const int32_t* order = p_cnt + (size_t)p_H * nKB;
+    const int32_t* n_heavy = order + (size_t)p_H * nKB;
     int pair, idx;
     if (NP % 8 == 0 && NP / 8 <= 64) {
         // lane p looks at pair P0 + p: one load and two wave-wide prefix sums instead of a chain of
         // dependent scalar loads
         const int PP = NP / 8, P0 = (blockIdx.x & 7) * PP;
         const int l = blockIdx.x >> 3;
-        const int hv = lane < PP ? n_heavy[(P0 + lane) % a.H] : 0;
+        const int hv = lane < PP ? n_heavy[(P0 + lane) / p_B] : 0;
         const int lt = lane < PP ? nKB - hv : 0;
         int hv_incl = hv, lt_incl = lt;                      // inclusive prefix sums over the lanes
 #pragma unroll
@@ -262,49 +457,21 @@ __global__ __launch_bounds__(128, (D == 128 || (D == 64 && NORM == 1)) ? 1 : 2) 
         pair = bid / nKB;
         idx = bid % nKB;
     }
-    const int h = pair % a.H;
-    const int b = pair / a.H;
+    const int h = pair / p_B;                                // the examples of a head share its schedule
+    const int b = pair % p_B;
     const int kb = order[(size_t)h * nKB + idx];
+    const int c = h * nKB + kb;
+    const int t0 = p_col_ptr[c];
+    const int t1 = t0 + p_cnt[c];
 
     const uint16_t* Qp = (const uint16_t*)a.Q + (size_t)b * a.sq[0] + (size_t)h * a.sq[1];
     const uint16_t* Gp = (const uint16_t*)a.dO + (size_t)b * a.so[0] + (size_t)h * a.so[1];
     const uint16_t* Kp = (const uint16_t*)a.K + (size_t)b * a.sk[0] + (size_t)h * a.sk[1];
     const uint16_t* Vp = (const uint16_t*)a.V + (size_t)b * a.sv[0] + (size_t)h * a.sv[1];
-    uint16_t* dKp = (uint16_t*)a.dK + (size_t)b * a.sk[0] + (size_t)h * a.sk[1];
-    uint16_t* dVp = (uint16_t*)a.dV + (size_t)b * a.sv[0] + (size_t)h * a.sv[1];
     const int sq_bytes = (int)a.sq[2] * 2, so_bytes = (int)a.so[2] * 2;
     const rsrc_t q_rsrc = make_rsrc(Qp, (unsigned)((a.Lq - 1) * sq_bytes + D * 2));
     const rsrc_t g_rsrc = make_rsrc(Gp, (unsigned)((a.Lq - 1) * so_bytes + D * 2));
     const size_t stat_base = ((size_t)b * a.H + h) * a.Lq;
-
-    const int key = kb * 64 + wave * 32 + n;
-    const int kload = key < a.Lk ? key : a.Lk - 1;
-    bf16x8 kreg[KSTEPS], vreg[KSTEPS];                       // K^T and V^T operands
-    {
-        const uint16_t* kr = Kp + (size_t)kload * a.sk[2] + 8 * hh;
-        const uint16_t* vr = Vp + (size_t)kload * a.sv[2] + 8 * hh;
-#pragma unroll
-        for (int kk = 0; kk < KSTEPS; ++kk) {
-            kreg[kk] = *reinterpret_cast<const bf16x8*>(kr + 16 * kk);
-            vreg[kk] = *reinterpret_cast<const bf16x8*>(vr + 16 * kk);
-        }
-    }
-    const float sc = NORM == SOFTMAX ? a.scale * kLog2e : a.scale * 0.5f;
-    const int k_swz = hh ^ swz_u<D>(n);
-    const TrReadU<D> tr = make_tr_read_u<D>(lane);
-
-    f32x16 dkacc[DBLK], dvacc[DBLK];
-#pragma unroll
-    for (int db = 0; db < DBLK; ++db)
-#pragma unroll
-        for (int i = 0; i < 16; ++i) {
-            dkacc[db][i] = 0.f;
-            dvacc[db][i] = 0.f;
-        }
-
-    const int c = h * nKB + kb;
-    const int t0 = a.col_ptr[c];
-    const int t1 = t0 + a.csched.cnt[c];
 
     // metadata of an entry: where it starts (or -1) and gathered query `lane` (read for every
     // entry, used by gathered ones only)
@@ -312,137 +479,179 @@ __global__ __launch_bounds__(128, (D == 128 || (D == 64 && NORM == 1)) ? 1 : 2) 
         int start;
         int row;
     };
-    // per-slot statistics of an entry, fetched by the first 64 threads one step ahead
+    // statistics of this wavefront's 32 query slots of an entry, fetched one step ahead: lower lanes lse (or
+    // tau) and the word of kept keys, upper lanes delta (or gbar)
     struct Stat {
-        float lse, delta;
-        uint64_t word;
+        float v;
+        uint32_t word;
     };
+    const float* stat_src = (hh ? a.delta : a.lse) + stat_base;
     auto fetch = [&](int t, Meta& m) {
-        m.start = a.csched.start[t + vzero];                 // a vector load: see vzero
-        m.row = a.csched.cols[(size_t)t * 64 + lane];
+        m.start = p_start[t + vzero];                        // a vector load: see vzero
+        m.row = p_cols[(size_t)t * 64 + lane];
     };
     auto fetch_stat = [&](int t, const Meta& m, Stat& s) {
-        if (tid < 64) {
-            const int q = m.start >= 0 ? m.start + tid : m.row;   // (all lanes hold the same start)
-            const int ql = q < a.Lq ? q : a.Lq - 1;
-            const float l = a.lse[stat_base + ql], d = a.delta[stat_base + ql];
-            s.lse = q < a.Lq ? l : (NORM == SOFTMAX ? -INFINITY : INFINITY);   // lse, or tau
-            s.delta = q < a.Lq ? d : 0.f;
-            s.word = a.csched.bitmaps[(size_t)t * 64 + tid];
-        }
+        const int gathered = __shfl(m.row, role * 32 + n, 64);
+        const int q = m.start >= 0 ? m.start + role * 32 + n : gathered;   // (all lanes hold the same start)
+        const float v = stat_src[q < a.Lq ? q : a.Lq - 1];
+        s.v = q < a.Lq ? v : (hh ? 0.f : (NORM == SOFTMAX ? -INFINITY : INFINITY));
+        s.word = p_words[((size_t)t * 64 + role * 32 + n) * 2 + kh];
     };
     auto issue = [&](const Meta& m, int stage) {
         lds_u16* base = lds + stage * STAGE;
         const int start = __builtin_amdgcn_readfirstlane(m.start);
         if (start >= 0) {
-            issue_tile_loads<D, 2, SWZ_BOTH>(q_rsrc, base, start, sq_bytes, wave, lane);
-            issue_tile_loads<D, 2, SWZ_BOTH>(g_rsrc, base + TILE, start, so_bytes, wave, lane);
+            issue_tile_loads<D, 4, SWZ_BOTH>(q_rsrc, base, start, sq_bytes, wave, lane);
+            issue_tile_loads<D, 4, SWZ_BOTH>(g_rsrc, base + TILE, start, so_bytes, wave, lane);
         } else {
             int gq[NLOAD];                                   // queries of the rows this lane loads
 #pragma unroll
-            for (int u = 0; u < NLOAD; ++u) gq[u] = __shfl(m.row, (wave + 2 * u) * RPI + g_row, 64);
-            issue_gather_loads<D, 2, SWZ_BOTH>(q_rsrc, base, gq, sq_bytes, wave, lane);
-            issue_gather_loads<D, 2, SWZ_BOTH>(g_rsrc, base + TILE, gq, so_bytes, wave, lane);
+            for (int u = 0; u < NLOAD; ++u) gq[u] = __shfl(m.row, (wave + 4 * u) * RPI + g_row, 64);
+            issue_gather_loads<D, 4, SWZ_BOTH>(q_rsrc, base, gq, sq_bytes, wave, lane);
+            issue_gather_loads<D, 4, SWZ_BOTH>(g_rsrc, base + TILE, gq, so_bytes, wave, lane);
         }
     };
 
     Meta cur, nxt;
+    cur.start = cur.row = 0;
+    if (t0 < t1) fetch(t0, cur);                             // everything waits for this first
+    {   // K and V rows of the block column (rows >= Lk read as zeros) into the second stage
+        const int sk_bytes = (int)a.sk[2] * 2, sv_bytes = (int)a.sv[2] * 2;
+        issue_tile_loads<D, 4, SWZ_BOTH>(make_rsrc(Kp, (unsigned)((a.Lk - 1) * sk_bytes + D * 2)), lds + STAGE, kb * 64,
+                                         sk_bytes, wave, lane);
+        issue_tile_loads<D, 4, SWZ_BOTH>(make_rsrc(Vp, (unsigned)((a.Lk - 1) * sv_bytes + D * 2)), lds + STAGE + TILE,
+                                         kb * 64, sv_bytes, wave, lane);
+    }
+    const float sc = NORM == SOFTMAX ? a.scale * kLog2e : a.scale * 0.5f;
+    const int q_tile_row = role * 32 + n;
+    const int k_swz = hh ^ swz_u<D>(n);
+    const TrReadU<D> tr = make_tr_read_u<D>(lane);
+
+    f32x16 acc[DBLK];                                        // role 0: dV^T, role 1: dK^T
+#pragma unroll
+    for (int db = 0; db < DBLK; ++db)
+#pragma unroll
+        for (int i = 0; i < 16; ++i) acc[db][i] = 0.f;
+
     Stat st;
-    st.lse = NORM == SOFTMAX ? -INFINITY : INFINITY;
-    st.delta = 0.f;
+    st.v = 0.f;
     st.word = 0;
+    nxt = cur;
     if (t0 < t1) {
-        fetch(t0, cur);
         issue(cur, 0);
         fetch_stat(t0, cur, st);
-        nxt = cur;
         if (t0 + 1 < t1) fetch(t0 + 1, nxt);
     }
     wait_vmem();
-    settle<KSTEPS>(kreg);
-    settle<KSTEPS>(vreg);
+    __syncthreads();
+    bf16x8 kreg[KSTEPS], vreg[KSTEPS];                       // K^T and V^T operands
+    read_operand<D>(smem + STAGE, kh * 32 + n, k_swz, kreg);
+    read_operand<D>(smem + STAGE + TILE, kh * 32 + n, k_swz, vreg);
 
     int stage = 0;
     for (int t = t0; t < t1; ++t) {
         wait_vmem();                                         // entry t, its statistics and the metadata of t + 1
-        if (tid < 64) {
-            s_lse2[stage][tid] = NORM == SOFTMAX ? lse2_of(st.lse) : st.lse;
-            s_delta[stage][tid] = st.delta;
-            s_half[stage][0][tid] = (uint32_t)st.word;
-            s_half[stage][1][tid] = (uint32_t)(st.word >> 32);
-        }
-        __syncthreads();                                     // ... for everybody; the other stage is free
+        // read and written by this wavefront only: LDS order is all they need
+        s_stat[wave][lane] = NORM == SOFTMAX && hh == 0 ? lse2_of(st.v) : st.v;
+        if (hh == 0) s_word[wave][n] = st.word;
+        const bool live = __ballot(st.word != 0) != 0;
+        if (lane == 0) s_live[stage][wave] = live ? 1u : 0u;
+        __syncthreads();                                     // entry t is there for everybody; the other stage is free
         if (t + 1 < t1) {
             issue(nxt, stage ^ 1);
             fetch_stat(t + 1, nxt, st);
             if (t + 2 < t1) fetch(t + 2, nxt);
         }
         uint16_t* base = smem + stage * STAGE;
-        f32x16 sacc[2], pacc[2];
-        qk_64<D>(base, kreg, n, k_swz, sacc);                // S  = Q K^T   (rows: queries, lane: key)
-        qk_64<D>(base + TILE, vreg, n, k_swz, pacc);         // dP = dO V^T
-        const uint32_t* halves = &s_half[stage][wave][0];    // this wavefront's 32 keys: bit n of these
-#pragma unroll
-        for (int qblk = 0; qblk < 2; ++qblk)
+        // the tile that this wavefront's gradient is a product of: dO for dV, Q for dK
+        lds_u16* grad_tile = lds + stage * STAGE + (role ? 0 : TILE);
+        if (live) {
+            f32x16 s, p;
+            two_products_32<D>(base, base + TILE, q_tile_row, k_swz, kreg, vreg, s, p);   // S = Q K^T, dP = dO V^T
 #pragma unroll
             for (int g = 0; g < 4; ++g) {
-                const int r0 = 32 * qblk + 8 * g + 4 * hh;   // 4 consecutive query slots
-                const float4 l4 = *reinterpret_cast<const float4*>(&s_lse2[stage][r0]);
-                const float4 d4 = *reinterpret_cast<const float4*>(&s_delta[stage][r0]);
-                const uint4 w4 = *reinterpret_cast<const uint4*>(&halves[r0]);
+                const int r0 = 8 * g + 4 * hh;               // 4 consecutive query slots
+                const float4 l4 = *reinterpret_cast<const float4*>(&s_stat[wave][r0]);
+                const float4 d4 = *reinterpret_cast<const float4*>(&s_stat[wave][32 + r0]);
+                const uint4 w4 = *reinterpret_cast<const uint4*>(&s_word[wave][r0]);
                 const float le[4] = {l4.x, l4.y, l4.z, l4.w}, de[4] = {d4.x, d4.y, d4.z, d4.w};
                 const uint32_t we[4] = {w4.x, w4.y, w4.z, w4.w};
 #pragma unroll
                 for (int e = 0; e < 4; ++e) {
                     const int i = 4 * g + e;
-                    // pruned entries: the exponent's argument is replaced by -inf with a bit-select
                     const uint32_t keep = (uint32_t)__builtin_amdgcn_sbfe((int)we[e], n, 1);
-                    const float x = fmaf(sacc[qblk][i], sc, -le[e]);
+                    const float x = fmaf(s[i], sc, -le[e]);
                     if (NORM == SOFTMAX) {
-                        const float p = __builtin_amdgcn_exp2f(__uint_as_float((__float_as_uint(x) & keep) | (0xff800000u & ~keep)));
-                        sacc[qblk][i] = p;                   // P
-                        pacc[qblk][i] = p * (pacc[qblk][i] - de[e]);   // dS
+                        s[i] = __builtin_amdgcn_exp2f(or_minus_inf(x, keep));   // P
+                        p[i] = s[i] * (p[i] - de[e]);        // dS
                     } else {
                         const float u = fmaxf(__uint_as_float(__float_as_uint(x) & keep), 0.f);   // pruned: 0
-                        sacc[qblk][i] = u * u;               // P
-                        pacc[qblk][i] = u * (pacc[qblk][i] - de[e]);   // dS
+                        s[i] = u * u;                        // P
+                        p[i] = u * (p[i] - de[e]);           // dS
                     }
                 }
             }
-        tr_mm_64_u<D>(lds + stage * STAGE + TILE, sacc, dvacc, tr);   // dV^T += dO^T P
-        tr_mm_64_u<D>(lds + stage * STAGE, pacc, dkacc, tr);          // dK^T += Q^T dS
+            bf16x8 own[2], hand[2];
+            {
+                bf16x8 pp[2], dd[2];
+                to_operands(s, pp);
+                to_operands(p, dd);
+#pragma unroll
+                for (int ks = 0; ks < 2; ++ks) {
+                    own[ks] = role ? dd[ks] : pp[ks];
+                    hand[ks] = role ? pp[ks] : dd[ks];
+                }
+            }
+            s_hand[wave][0][lane] = hand[0];
+            s_hand[wave][1][lane] = hand[1];
+            tr_mm_32<D>(grad_tile + role * 32 * D, own, acc, tr);
+        }
+        __syncthreads();                                     // what the partner hands over is there
+        if (s_live[stage][wave ^ 2]) {
+            bf16x8 got[2];
+            got[0] = s_hand[wave ^ 2][0][lane];
+            got[1] = s_hand[wave ^ 2][1][lane];
+            tr_mm_32<D>(grad_tile + (1 - role) * 32 * D, got, acc, tr);
+        }
         stage ^= 1;
     }
     __syncthreads();                                         // all wavefronts are done with the tiles
-    const int krow0 = kb * 64 + wave * 32;
+    const int krow0 = kb * 64 + kh * 32;
     uint16_t* stg = smem + wave * 32 * D;
-    store_rows_bf16<D>(stg, dkacc, a.scale, lane, dKp + (size_t)krow0 * a.sk[2], a.sk[2], a.Lk - krow0);
-    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");       // the staging area is reused
-    store_rows_bf16<D>(stg, dvacc, 1.0f, lane, dVp + (size_t)krow0 * a.sv[2], a.sv[2], a.Lk - krow0);
+    if (role) {
+        uint16_t* dKp = (uint16_t*)a.dK + (size_t)b * a.sk[0] + (size_t)h * a.sk[1];
+        store_rows_bf16<D>(stg, acc, a.scale, lane, dKp + (size_t)krow0 * a.sk[2], a.sk[2], a.Lk - krow0);
+    } else {
+        uint16_t* dVp = (uint16_t*)a.dV + (size_t)b * a.sv[0] + (size_t)h * a.sv[1];
+        store_rows_bf16<D>(stg, acc, 1.0f, lane, dVp + (size_t)krow0 * a.sv[2], a.sv[2], a.Lk - krow0);
+    }
 }
 
 template <int D>
 hipError_t launch_d(const BwdArgs& a, bool dq, bool dkv, hipStream_t stream)
 {
-    const int nQB = (a.Lq + 63) / 64, nKB = (a.Lk + 63) / 64;
-    const dim3 qgrid((unsigned)(a.B * a.H * nQB)), kgrid((unsigned)(a.B * a.H * nKB));
-    if (a.entmax) {                                          // gbar first, then the two gradient kernels
-        hipLaunchKernelGGL((bwd_dq_sched_kernel<D, GBAR>), qgrid, dim3(128), 0, stream, a, nQB);
-        hipError_t e = hipGetLastError();
-        if (e != hipSuccess) return e;
-        hipLaunchKernelGGL((bwd_dq_sched_kernel<D, ENTMAX15>), qgrid, dim3(128), 0, stream, a, nQB);
-        e = hipGetLastError();
-        if (e != hipSuccess) return e;
-        hipLaunchKernelGGL((bwd_dkv_sched_kernel<D, ENTMAX15>), kgrid, dim3(128), 0, stream, a, nKB);
+    const int nQB = (a.Lq + 63) / 64, nKB = (a.Lk + 63) / 64, NP = a.B * a.H;
+    const dim3 qgrid((unsigned)(NP * nQB)), kgrid((unsigned)(NP * nKB)), block(256);
+    const Schedule &rs = a.sched, &cs = a.csched;
+    auto run_dq = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, qgrid, block, 0, stream, a.row_ptr, rs.cnt, rs.start, rs.cols,
+                           (const uint32_t*)rs.bitmaps, nQB, a.B, a);
         return hipGetLastError();
+    };
+    auto run_dkv = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, kgrid, block, 0, stream, a.col_ptr, cs.cnt, cs.start, cs.cols,
+                           (const uint32_t*)cs.bitmaps, nKB, a.H, a.B, NP, a);
+        return hipGetLastError();
+    };
+    hipError_t e = hipSuccess;
+    if (a.entmax) {                                          // gbar first, then the two gradient kernels
+        e = run_dq(bwd_dq_sched_kernel<D, GBAR>);
+        if (e == hipSuccess) e = run_dq(bwd_dq_sched_kernel<D, ENTMAX15>);
+        return e == hipSuccess ? run_dkv(bwd_dkv_sched_kernel<D, ENTMAX15>) : e;
     }
-    if (dq) {
-        hipLaunchKernelGGL((bwd_dq_sched_kernel<D, SOFTMAX>), qgrid, dim3(128), 0, stream, a, nQB);
-        const hipError_t e = hipGetLastError();
-        if (e != hipSuccess) return e;
-    }
-    if (dkv) hipLaunchKernelGGL((bwd_dkv_sched_kernel<D, SOFTMAX>), kgrid, dim3(128), 0, stream, a, nKB);
-    return hipGetLastError();
+    if (dq) e = run_dq(bwd_dq_sched_kernel<D, SOFTMAX>);
+    if (e == hipSuccess && dkv) e = run_dkv(bwd_dkv_sched_kernel<D, SOFTMAX>);
+    return e;
 }
 
 }  // namespace

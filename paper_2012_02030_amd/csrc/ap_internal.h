@@ -102,7 +102,7 @@ struct BwdArgs {
     int entmax;                     // 1: 1.5-entmax (both schedules required; lse holds tau, delta gets gbar)
 };
 hipError_t launch_bwd(const BwdArgs& a, hipStream_t stream);
-// the kernels that walk schedules (ap_attn_bwd_sched.hip); softmax: delta must have been computed;
+// the kernels that walk schedules (ap_attn_bwd_sched.hip); softmax: dq writes delta, dkv reads it;
 // entmax: runs the gbar pass and both gradient kernels whatever dq and dkv say
 hipError_t launch_bwd_sched(const BwdArgs& a, bool dq, bool dkv, hipStream_t stream);
 // column schedule (ap_col_schedule.hip): entry e of block column c is element col_ptr[c] + e

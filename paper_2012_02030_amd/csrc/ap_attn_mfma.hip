@@ -51,14 +51,14 @@ using namespace mfma;
 // (few queries against many keys: one workgroup per block row would leave the chip idle).
 //
 // The leading scalar arguments repeat fields of `a` (row pointers, entry counts, block rows per head
-// of the layout, heads, splits): the library is built with kernel-argument preloading, which hands
+// of the layout, examples, splits): the library is built with kernel-argument preloading, which hands
 // the first 16 dwords of the argument block to a wavefront in registers when it starts, so the
 // loads of the block row's pointer and count go out at once instead of after a first round trip
 // for the argument block (the structure itself is too large to be preloaded).
 template <int D, int NW, int STAGES, bool SCHED, bool SPLIT = false>
 __global__ __launch_bounds__(64 * NW, (D <= 64 && STAGES == 1) ? 3 : 2) void fwd_mfma_kernel(
     const int32_t* __restrict__ p_row_ptr, const int32_t* __restrict__ p_cnt, int nQB, int xcd_chunk,
-    int p_nqb_layout, int p_H, int p_splits, FwdArgs a)
+    int p_nqb_layout, int p_B, int p_splits, FwdArgs a)
 {
     constexpr int BM = 32 * NW;
     constexpr int KSTEPS = D / 16;                           // contraction steps of Q K^T
@@ -94,8 +94,8 @@ __global__ __launch_bounds__(64 * NW, (D <= 64 && STAGES == 1) ? 3 : 2) void fwd
         bid /= p_splits;
     }
     const int qb = nQB - 1 - (bid % nQB);                    // long causal rows first
-    const int h = (bid / nQB) % p_H;
-    const int b = bid / (nQB * p_H);
+    const int b = (bid / nQB) % p_B;                         // the examples of a head one after another: they share its schedule
+    const int h = bid / (nQB * p_B);
     const int r = h * p_nqb_layout + qb;                     // requested first: everything else waits for these
     int t_begin = p_row_ptr[r];
     int nt = SCHED ? p_cnt[r] : p_row_ptr[r + 1] - t_begin;
@@ -562,10 +562,10 @@ hipError_t launch_one(const FwdArgs& a, hipStream_t stream)
     const int32_t* cnt = a.sched.cnt;
     if (cnt)
         hipLaunchKernelGGL((fwd_mfma_kernel<D, NW, STAGES, true>), dim3((unsigned)blocks), dim3(64 * NW), 0,
-                           stream, a.row_ptr, cnt, nQB, xcd_chunk, a.nqb_layout, a.H, a.splits, a);
+                           stream, a.row_ptr, cnt, nQB, xcd_chunk, a.nqb_layout, a.B, a.splits, a);
     else
         hipLaunchKernelGGL((fwd_mfma_kernel<D, NW, STAGES, false>), dim3((unsigned)blocks), dim3(64 * NW), 0,
-                           stream, a.row_ptr, cnt, nQB, xcd_chunk, a.nqb_layout, a.H, a.splits, a);
+                           stream, a.row_ptr, cnt, nQB, xcd_chunk, a.nqb_layout, a.B, a.splits, a);
     return hipGetLastError();
 }
 
@@ -617,10 +617,10 @@ hipError_t launch_split_d(const FwdArgs& a, hipStream_t stream)
     const int32_t* cnt = a.sched.cnt;
     if (cnt)
         hipLaunchKernelGGL((fwd_mfma_kernel<D, 2, ST, true, true>), dim3((unsigned)blocks), dim3(128), 0,
-                           stream, a.row_ptr, cnt, nQB, 0, a.nqb_layout, a.H, a.splits, a);
+                           stream, a.row_ptr, cnt, nQB, 0, a.nqb_layout, a.B, a.splits, a);
     else
         hipLaunchKernelGGL((fwd_mfma_kernel<D, 2, ST, false, true>), dim3((unsigned)blocks), dim3(128), 0,
-                           stream, a.row_ptr, cnt, nQB, 0, a.nqb_layout, a.H, a.splits, a);
+                           stream, a.row_ptr, cnt, nQB, 0, a.nqb_layout, a.B, a.splits, a);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     const long long threads = (long long)a.B * a.H * a.Lq * (D / 4);

@@ -46,7 +46,8 @@ constexpr int kCandBits = 10, kCandBins = 1 << kCandBits;   // first histogram o
 constexpr int kLastBits = 13, kLastBins = 1 << kLastBits;   // second one
 constexpr int kMaxBracketBits = kCandBits + kLastBits;   // widest interval the selection resolves
 constexpr int kExactBins = 65536;            // a level of the exact way: 16 key bits
-constexpr uint32_t kCap = 3u << 19;          // candidates the workspace can hold
+constexpr uint32_t kCap = 978240;            // candidates the workspace can hold
+constexpr double kAim = 650000.0;            // candidates aimed at where the map is large
 constexpr unsigned long long kSample = 1ull << 21;   // entries looked at, at least (all, if there are fewer)
 constexpr double kDesign = 6.0;              // variance of the clustered sample over an independent one's
 constexpr double kSigmas = 5.0;              // half width of the interval in standard deviations of the sample
@@ -100,7 +101,9 @@ __host__ __device__ inline Workspace carve(void* p)
     w.cand_key = reinterpret_cast<uint32_t*>(w.cand_idx + kCap);
     return w;
 }
-constexpr size_t kWorkspaceBytes = kClearBytes + (size_t)kCap * 12;
+// The size that callers of the C ABI have always been told; kCap is what is left of it.
+constexpr size_t kWorkspaceBytes = 64 + (size_t)32768 * 8 + (size_t)(1 << 20) * 12;
+static_assert(kClearBytes + (size_t)kCap * 12 <= kWorkspaceBytes, "the candidate lists fit");
 static_assert(kClearBytes % 16 == 0, "cleared in 16-byte pieces");
 
 constexpr uint32_t kKeyMinusInf = 0x007fffffu, kKeyPlusInf = 0xff800000u, kKeyZero = 0x80000000u;
@@ -725,9 +728,9 @@ hipError_t launch_prune_mask(const float* abar, int H, int Lq, int Lk, int causa
     // positions of the longest unit: a row, or a pair of rows with the first padded to a quad
     const long long unit_len = causal ? (long long)Lk + (Lk - Lq) + 1 + 3 : Lk;
     Sample s;
-    // a sample for which the interval holds about 2^20 candidates: 2 kSigmas standard deviations of the
+    // a sample for which the interval holds about kAim candidates: 2 kSigmas standard deviations of the
     // sample, as a share of the n entries
-    const double f = (double)rank / (double)n, share = (double)n / (double)(1u << 20);
+    const double f = (double)rank / (double)n, share = (double)n / kAim;
     const double want = 4.0 * kSigmas * kSigmas * kDesign * f * (1.0 - f) * share * share;
     const unsigned long long size = want > (double)kSample ? (unsigned long long)min(want, (double)n) : kSample;
     s.stride = (uint32_t)min(max(n / size, 1ull), 1ull << 30);

@@ -1,4 +1,6 @@
-"""Thin ctypes binding of the C ABI in include/ap.h (same names, argument marshalling only).
+"""Thin binding of the C ABI in include/ap.h (same names, argument marshalling only): ctypes, and for the
+ordinary form of the attention calls the native module ap_calls, which does the same marshalling in a
+third of the time and leaves every other form of a call to the code below.
 
 PyTorch supplies device memory and the HIP stream; every step of the computation runs in the
 library's own kernels.  There is no fallback: if the shared library has not been built, the
@@ -43,6 +45,11 @@ class _CSchedule(ctypes.Structure):
 
 
 _lib = None
+_calls = None            # the native call path, bound to the functions of _lib
+_CALLS_API = ("ap_sparse_attn_fwd", "ap_sparse_attn_fwd_cropped", "ap_fwd_split_workspace_bytes",
+              "ap_sparse_attn_fwd_split", "ap_sparse_attn_decode", "ap_sparse_attn_entmax15_fwd",
+              "ap_bwd_workspace_bytes", "ap_sparse_attn_bwd", "ap_sparse_attn_bwd_sched",
+              "ap_entmax15_bwd_workspace_bytes", "ap_sparse_attn_entmax15_bwd")
 
 
 class ApError(RuntimeError):
@@ -53,7 +60,7 @@ class ApError(RuntimeError):
 
 def lib() -> ctypes.CDLL:
     """Load libap_mi355x.so (built by ``python -m paper_2012_02030_amd.build``)."""
-    global _lib
+    global _lib, _calls
     if _lib is None:
         if not os.path.exists(LIB_PATH):
             raise RuntimeError(
@@ -154,8 +161,24 @@ def lib() -> ctypes.CDLL:
         L.ap_prune_mask.restype = i32
         L.ap_prune_mask.argtypes = [vp, i32, i32, i32, i32, ctypes.c_double, vp, vp, vp,
                                     ctypes.c_size_t, vp]
-        _lib = L
+        try:
+            from . import ap_calls
+        except ImportError as e:
+            raise RuntimeError("the native call path is missing: build it with "
+                               "`python -m paper_2012_02030_amd.build` (%s)" % e) from e
+        ap_calls.bind(*(ctypes.cast(getattr(L, name), vp).value for name in _CALLS_API),
+                      torch._C._cuda_getDevice, torch._C._cuda_getCurrentRawStream)
+        _calls, _lib = ap_calls, L
     return _lib
+
+
+def _done(res, where: str) -> bool:
+    """What a native call returned: its outputs, None (the general path takes the call) or a status."""
+    if res.__class__ is tuple:
+        return True
+    if res is not None:
+        raise ApError(res, where)
+    return False
 
 
 def ap_status_string(status: int) -> str:
@@ -339,6 +362,12 @@ def ap_sparse_attn_fwd(Q: torch.Tensor, K: torch.Tensor, V: torch.Tensor, layout
     under the top-left corner of that mask (ap_sparse_attn_fwd_cropped).
     Returns (O, lse); lse is None when return_lse is False.  Asynchronous on the stream.
     """
+    if _lib is None:
+        lib()
+    if out is None and lse is None:
+        res = _calls.fwd(Q, K, V, layout, causal, softmax_scale, return_lse, stream, sched, crop)
+        if _done(res, "ap_sparse_attn_fwd"):
+            return res
     if Q.dtype == torch.bfloat16:
         dt = AP_BF16
     elif Q.dtype == torch.float32:
@@ -392,6 +421,12 @@ def ap_sparse_attn_decode(Q: torch.Tensor, K: torch.Tensor, V: torch.Tensor, lay
                           stream: Optional[torch.cuda.Stream] = None, splits: int = 1):
     """ap_sparse_attn_fwd for one or a few queries against many keys (bf16), `splits` workgroups
     per query.  Returns (O, lse)."""
+    if _lib is None:
+        lib()
+    if out is None:
+        res = _calls.split(Q, K, V, layout, splits, causal, softmax_scale, return_lse, stream, None, True)
+        if _done(res, "ap_sparse_attn_decode"):
+            return res
     if Q.dtype != torch.bfloat16 or K.dtype != Q.dtype or V.dtype != Q.dtype:
         raise ValueError("Q, K, V must be bfloat16")
     B, H, Lq, D = Q.shape
@@ -428,6 +463,12 @@ def ap_sparse_attn_entmax15_fwd(Q: torch.Tensor, K: torch.Tensor, V: torch.Tenso
                                 stream: Optional[torch.cuda.Stream] = None,
                                 sched: Optional[Schedule] = None):
     """Masked attention with the 1.5-entmax normaliser (bf16, block_m 64).  Returns (O, tau)."""
+    if _lib is None:
+        lib()
+    if out is None:
+        res = _calls.entmax_fwd(Q, K, V, layout, causal, softmax_scale, return_tau, stream, sched)
+        if _done(res, "ap_sparse_attn_entmax15_fwd"):
+            return res
     if sched is not None and sched.causal != bool(causal):
         raise ValueError("schedule was built with causal=%s" % sched.causal)
     cs = sched.c_struct() if sched is not None else None
@@ -467,6 +508,12 @@ def ap_sparse_attn_fwd_split(Q: torch.Tensor, K: torch.Tensor, V: torch.Tensor, 
                              sched: Optional[Schedule] = None):
     """ap_sparse_attn_fwd with the entries of every block row cut into `splits` chunks (bf16,
     block_m 64): for few queries against many keys.  Returns (O, lse).  Asynchronous."""
+    if _lib is None:
+        lib()
+    if out is None:
+        res = _calls.split(Q, K, V, layout, splits, causal, softmax_scale, return_lse, stream, sched, False)
+        if _done(res, "ap_sparse_attn_fwd_split"):
+            return res
     if Q.dtype != torch.bfloat16 or K.dtype != Q.dtype or V.dtype != Q.dtype:
         raise ValueError("Q, K, V must be bfloat16")
     B, H, Lq, D = Q.shape
@@ -593,6 +640,12 @@ def ap_sparse_attn_bwd(Q: torch.Tensor, K: torch.Tensor, V: torch.Tensor, O: tor
 
     O and lse are the forward call's outputs; dO must have O's strides.  With a row schedule
     and/or a column schedule the call goes to ap_sparse_attn_bwd_sched.  Asynchronous on the stream."""
+    if _lib is None:
+        lib()
+    if O is not None:
+        res = _calls.bwd(Q, K, V, O, dO, lse, layout, layout_t, causal, softmax_scale, stream, sched, col_sched)
+        if _done(res, "ap_sparse_attn_bwd"):
+            return res
     for sc in (sched, col_sched):
         if sc is not None and sc.causal != bool(causal):
             raise ValueError("schedule was built with another `causal`")
@@ -647,6 +700,11 @@ def ap_sparse_attn_entmax15_bwd(Q: torch.Tensor, K: torch.Tensor, V: torch.Tenso
     """Gradients (dQ, dK, dV) of ap_sparse_attn_entmax15_fwd's O with respect to Q, K, V (bf16).
 
     tau is the forward call's second output; both schedules are required.  Asynchronous on the stream."""
+    if _lib is None:
+        lib()
+    res = _calls.bwd(Q, K, V, None, dO, tau, layout, layout_t, causal, softmax_scale, stream, sched, col_sched)
+    if _done(res, "ap_sparse_attn_entmax15_bwd"):
+        return res
     for t in (Q, K, V, dO):
         if t.dtype != torch.bfloat16 or t.dim() != 4 or t.stride(3) != 1:
             raise ValueError("Q, K, V, dO must be bfloat16 [B, H, L, D] with a contiguous last dimension")

@@ -1,15 +1,17 @@
-"""Build the gfx950 shared library (hipcc cross-compiles without a GPU)."""
+"""Build the gfx950 shared library (hipcc cross-compiles without a GPU) and the binding's native call path."""
 from __future__ import annotations
 
 import glob
 import os
 import subprocess
 import sys
+import sysconfig
 
 PKG = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(PKG)
 CSRC = os.path.join(PKG, "csrc")
 LIB = os.path.join(PKG, "libap_mi355x.so")
+CALLS = os.path.join(PKG, "ap_calls.so")                      # torch tensors -> C-ABI call (host code)
 RESOURCES = os.path.join(PKG, "libap_mi355x.resources.txt")   # per-kernel registers, spills, LDS
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
@@ -79,7 +81,31 @@ def build(verbose: bool = False, extra=()) -> str:
     if spilling:                                             # the library still works; the tests flag it
         print("WARNING: kernels that spill vector registers: " + ", ".join(spilling), flush=True)
     os.replace(tmp, LIB)
+    build_calls(verbose)
     return LIB
+
+
+def build_calls(verbose: bool = False) -> str:
+    """Compile the CPython module that takes the attention calls from torch tensors to the library."""
+    import torch
+    tdir = os.path.dirname(os.path.abspath(torch.__file__))
+    tmp = CALLS + ".tmp.%d" % os.getpid()
+    cmd = [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall",
+           "-D_GLIBCXX_USE_CXX11_ABI=%d" % int(torch._C._GLIBCXX_USE_CXX11_ABI),
+           "-I", os.path.join(ROOT, "include"), "-isystem", sysconfig.get_paths()["include"],
+           "-isystem", os.path.join(tdir, "include"),
+           "-isystem", os.path.join(tdir, "include", "torch", "csrc", "api", "include"),
+           os.path.join(CSRC, "ap_calls.cpp"), "-L", os.path.join(tdir, "lib"),
+           "-ltorch_python", "-ltorch", "-ltorch_cpu", "-lc10", "-o", tmp]
+    if verbose:
+        print(" ".join(cmd), flush=True)
+    proc = subprocess.run(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
+    if proc.returncode != 0:
+        if os.path.exists(tmp):
+            os.remove(tmp)
+        raise RuntimeError("building the call path failed:\n" + proc.stdout)
+    os.replace(tmp, CALLS)
+    return CALLS
 
 
 if __name__ == "__main__":

@@ -569,30 +569,54 @@ hipError_t launch_one(const FwdArgs& a, hipStream_t stream)
     return hipGetLastError();
 }
 
-// O = sum_s exp(lse_s - lse) O_s with lse = ln sum_s exp(lse_s): one thread per (row, 4 elements).
+// O = sum_s exp(lse_s - lse) O_s with lse = ln sum_s exp(lse_s): one thread per (row, 4 elements), 8 chunks
+// in flight at a time (bound by memory latency: 8 chunks of 4096 rows
+// of 128 take 5.4 us, 9.0 with one chunk after another).
 template <int D>
 __global__ __launch_bounds__(256) void merge_splits_kernel(FwdArgs a)
 {
     constexpr int TPR = D / 4;                               // threads per row
+    constexpr int U = 8;
     const long long rows = (long long)a.B * a.H * a.Lq;
     const long long row = ((long long)blockIdx.x * 256 + threadIdx.x) / TPR;
     const int part = threadIdx.x % TPR;
     if (row >= rows) return;
-    float mx = -INFINITY;
-    for (int s = 0; s < a.splits; ++s) mx = fmaxf(mx, a.part_lse[(size_t)s * rows + row]);
+    float mx = -INFINITY, tot = 0.f;
     float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
-    float tot = 0.f;
-    if (mx != -INFINITY) {
-        for (int s = 0; s < a.splits; ++s) {
-            const float w = __expf(a.part_lse[(size_t)s * rows + row] - mx);   // 0 for an empty chunk
-            if (w == 0.f) continue;                          // its partial output may be anything finite
-            const float4 o = *reinterpret_cast<const float4*>(a.part_o + ((size_t)s * rows + row) * D + part * 4);
-            acc.x = fmaf(w, o.x, acc.x);
-            acc.y = fmaf(w, o.y, acc.y);
-            acc.z = fmaf(w, o.z, acc.z);
-            acc.w = fmaf(w, o.w, acc.w);
+    for (int s0 = 0; s0 < a.splits; s0 += U) {
+        float l[U];
+        float4 o[U];
+#pragma unroll
+        for (int k = 0; k < U; ++k) {
+            l[k] = -INFINITY;
+            o[k] = make_float4(0.f, 0.f, 0.f, 0.f);
+            if (s0 + k < a.splits) {
+                l[k] = a.part_lse[(size_t)(s0 + k) * rows + row];
+                o[k] = *reinterpret_cast<const float4*>(a.part_o + ((size_t)(s0 + k) * rows + row) * D + part * 4);
+            }
+        }
+        float m_new = mx;
+#pragma unroll
+        for (int k = 0; k < U; ++k) m_new = fmaxf(m_new, l[k]);
+        if (m_new == -INFINITY) continue;
+        if (m_new != mx) {
+            const float f = __expf(mx - m_new);              // 0 as long as there was nothing
+            acc.x *= f; acc.y *= f; acc.z *= f; acc.w *= f;
+            tot *= f;
+            mx = m_new;
+        }
+#pragma unroll
+        for (int k = 0; k < U; ++k) {
+            const float w = __expf(l[k] - mx);               // 0 for an empty chunk
+            if (w == 0.f) continue;                          // its partial output may be anything
+            acc.x = fmaf(w, o[k].x, acc.x);
+            acc.y = fmaf(w, o[k].y, acc.y);
+            acc.z = fmaf(w, o[k].z, acc.z);
+            acc.w = fmaf(w, o[k].w, acc.w);
             tot += w;
         }
+    }
+    if (mx != -INFINITY) {
         const float inv = 1.f / tot;
         acc.x *= inv; acc.y *= inv; acc.z *= inv; acc.w *= inv;
     }

@@ -5,17 +5,22 @@
 // With one to a few queries per (example, head) there is nothing for the matrix cores to do: a
 // 64-query tile would be empty but for a row or two.  The work is reading the kept keys' K and V
 // rows, so it is laid out for that.  `splits` workgroups of 16 wavefronts per query, each with a
-// contiguous share of the stored tiles of the query's block row.  A workgroup
+// share of the stored tiles of the query's block row.  A workgroup
 //   1. turns the bitmap words of up to 128 tiles at a time into the list of kept visible keys in
-//      LDS (one thread per tile, a prefix sum of the population counts gives every thread its
+//      LDS (one thread per 8 keys of a tile, a prefix sum of the population counts gives every thread its
 //      place in the list), so that what follows is a flat loop over keys;
 //   2. runs one online-softmax stream per group of D / 8 lanes: a lane holds 8 elements of the
 //      query and of the output, a K or V row is one 16-byte load per lane of the group (a
 //      wavefront instruction fetches 64 / (D / 8) rows), the dot product is 8 multiply-adds and a
 //      sum over the group with data-parallel-primitive moves inside a 16-lane row; stream s takes
-//      keys s, s + S, s + 2 S, ... of the list, four keys of every stream are in flight at a time;
+//      keys s, s + S, s + 2 S, ... of the list, eight keys of every stream are in flight at a time;
 //   3. merges the streams of a wavefront by lane exchanges, the 16 wavefronts through LDS, and
 //      those of several workgroups by the split forward call's merge kernel.
+//
+// Bound by the latency of its chain of loads (row bounds, tile words, key list, K and V rows) and by the
+// workgroup with the most keys: B4 H16 D128, 1600 of 16001 keys kept, 4 splits 15.5 us (52 MB of K and V rows,
+// 3.4 TB/s).  With contiguous shares of the tiles, one thread per tile for the list and four keys in flight
+// per stream 20.9 us.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -70,11 +75,11 @@ __global__ __launch_bounds__(64 * kWaves) void decode_kernel(FwdArgs a, int nQB)
     constexpr int NS = kWaves * SPW;                         // streams per workgroup
     constexpr int CHUNK = 128;                               // tiles per pass
     constexpr int LCAP = CHUNK * 64;                         // keys per pass at most
-    constexpr int UN = 4;                                    // keys of a stream in flight
+    constexpr int UN = 8;                                    // keys of a stream in flight
     constexpr int E = D == 128 ? 2 : 1;                      // final merge: elements per lane
     static_assert(kWaves * D <= LCAP, "the merge area reuses the key list");
     __shared__ int s_list[LCAP];                             // kept visible keys; later the merge area
-    __shared__ int s_wsum[2];
+    __shared__ int s_wsum[kWaves];
     __shared__ float s_m[kWaves], s_l[kWaves];
 
     const int tid = threadIdx.x;
@@ -113,44 +118,43 @@ __global__ __launch_bounds__(64 * kWaves) void decode_kernel(FwdArgs a, int nQB)
     const int r = h * nQB + i / a.block_m;
     const int rr = i % a.block_m;
     const long long diag = (long long)i + ((long long)a.Lk - a.Lq);
-    int t0 = a.row_ptr[r], t1 = a.row_ptr[r + 1];
-    {                                                        // this workgroup's share of the tiles
-        const int per = (t1 - t0 + a.splits - 1) / a.splits;
-        t0 = min(t1, t0 + split * per);
-        t1 = min(t1, t0 + per);
-    }
+    // This workgroup's tiles: every splits-th one, since the tiles near the query hold far more keys than
+    // the others (contiguous shares: the fullest of four has 1.6 times the mean at 16 thousand keys).
+    const int first = a.row_ptr[r] + split;
+    const int ntiles = max(0, (a.row_ptr[r + 1] - first + a.splits - 1) / a.splits);
 
-    for (int c0 = t0; c0 < t1; c0 += CHUNK) {                // workgroup-uniform trip count
+    for (int c0 = 0; c0 < ntiles; c0 += CHUNK) {             // workgroup-uniform trip count
         // ---- 1. the kept visible keys of tiles c0 .. c0 + CHUNK - 1, ascending, into s_list
-        uint64_t word = 0;
+        uint32_t bits = 0;                                   // of 8 keys from k0
         int k0 = 0;
-        if (tid < CHUNK && c0 + tid < t1) {
-            const int t = c0 + tid;
-            k0 = a.col_idx[t] * 64;
-            word = a.bitmaps[(size_t)t * a.block_m + rr];
+        if (c0 + (tid >> 3) < ntiles) {
+            const int t = first + (c0 + (tid >> 3)) * a.splits, byte = tid & 7;
+            k0 = a.col_idx[t] * 64 + 8 * byte;
+            bits = reinterpret_cast<const uint8_t*>(a.bitmaps + (size_t)t * a.block_m + rr)[byte];
             if (a.causal) {
                 const long long lim = diag - k0;
-                if (lim < 0) word = 0;
-                else if (lim < 63) word &= (2ull << lim) - 1ull;
+                if (lim < 0) bits = 0;
+                else if (lim < 7) bits &= (2u << lim) - 1u;
             }
         }
-        const int cnt = __popcll(word);
+        const int cnt = __popc(bits);
         int incl = cnt;                                      // inclusive prefix sum inside the wavefront
 #pragma unroll
         for (int d = 1; d < 64; d <<= 1) {
             const int up = __shfl_up(incl, d, 64);
             if (lane >= d) incl += up;
         }
-        if (wave < 2 && lane == 63) s_wsum[wave] = incl;     // CHUNK = 128 tiles: two wavefronts hold them
+        if (lane == 63) s_wsum[wave] = incl;
         __syncthreads();                                     // also: the previous pass is done with s_list
-        const int n = s_wsum[0] + s_wsum[1];                 // keys of this pass
-        {
-            int pos = incl - cnt + (wave == 1 ? s_wsum[0] : 0);
-            while (word) {
-                const int j = __ffsll((long long)word) - 1;
-                word &= word - 1;
-                s_list[pos++] = k0 + j;
-            }
+        int n = 0, pos = incl - cnt;                         // n: keys of this pass
+#pragma unroll
+        for (int v = 0; v < kWaves; ++v) {
+            if (v == wave) pos += n;
+            n += s_wsum[v];
+        }
+        while (bits) {
+            s_list[pos++] = k0 + __ffs((int)bits) - 1;
+            bits &= bits - 1;
         }
         __syncthreads();
 
@@ -162,9 +166,12 @@ __global__ __launch_bounds__(64 * kWaves) void decode_kernel(FwdArgs a, int nQB)
             for (int u = 0; u < UN; ++u) {
                 const int idx = base + u * NS + strm;
                 valid[u] = idx < n;
-                const int key = s_list[valid[u] ? idx : 0];  // n > 0 here: slot 0 is a real key
-                kx[u] = *reinterpret_cast<const uint4*>(Kp + (size_t)key * a.sk[2] + 8 * sub);
-                vx[u] = *reinterpret_cast<const uint4*>(Vp + (size_t)key * a.sv[2] + 8 * sub);
+                kx[u] = vx[u] = make_uint4(0, 0, 0, 0);
+                if (valid[u]) {
+                    const int key = s_list[idx];
+                    kx[u] = *reinterpret_cast<const uint4*>(Kp + (size_t)key * a.sk[2] + 8 * sub);
+                    vx[u] = *reinterpret_cast<const uint4*>(Vp + (size_t)key * a.sv[2] + 8 * sub);
+                }
             }
 #pragma unroll
             for (int u = 0; u < UN; ++u) {

@@ -73,3 +73,10 @@ def test_decode_agrees_with_the_tiled_kernel_on_the_long_memory_shape():
     torch.cuda.synchronize()
     assert float((O.float() - O2.float()).abs().max()) <= 2e-2
     assert float((lse - lse2).abs().max()) <= 1e-3
+
+
+@pytest.mark.parametrize("splits", [1, 2, 5])
+def test_decode_of_more_tiles_than_one_pass_takes(splits):
+    """313 stored tiles: several passes over the key list, tiles dealt over the splits, the last tile ragged."""
+    mask = synth.random_mask(1, 2, 20001, 0.05, seed=9)
+    run_decode(1, 1, 2, 20001, 64, True, mask, seed=9, splits=splits)

@@ -24,8 +24,8 @@
 // What bounds it: reading the map and writing the mask once (805 MB for 16 x 4096 x 4096 causal maps).
 // A full first sweep for an exact histogram costs a read of the map more and, worse, one LDS atomic per
 // entry on a few hot bins.  Measured there: 473 us with the histogram sweep (126 us), one-workgroup
-// selections (26 + 52 us) and a mask sweep of 231 us; now 245 us, of which the sweep is 165 (4.9 TB/s),
-// the sample 33, the candidates 30 and the launches that return at once 14.  At 12 x 512 x 512 (launches
+// selections (26 + 52 us) and a mask sweep of 231 us; now 236 us, of which the sweep is 165 (4.9 TB/s),
+// the sample 33 and the candidates 29.  At 12 x 512 x 512 (launches
 // only) 61 -> 55 us; rows that start anywhere (Lk = 4095) 644 -> 252 us.
 //
 // Float bit patterns are mapped to unsigned keys whose integer order is the numeric order
@@ -137,8 +137,8 @@ __global__ __launch_bounds__(256) void select_init_kernel(Workspace w, unsigned 
     if (blockIdx.x == 0 && threadIdx.x == 0 && none && tau_out) *tau_out = INFINITY;   // rank N: everything is pruned
 }
 
-// The last workgroup of a launch to get here returns true, and then sees what all of them wrote.
-__device__ __forceinline__ bool last_workgroup(uint32_t* done)
+// The last of a launch's `count` workgroups that get here returns true, and then sees what all of them wrote.
+__device__ __forceinline__ bool last_workgroup(uint32_t* done, uint32_t count)
 {
     __shared__ uint32_t s_last;
     // What is handed over are counts in memory that only atomics of agent scope touch, and they are read
@@ -146,7 +146,7 @@ __device__ __forceinline__ bool last_workgroup(uint32_t* done)
     // would write back the L2, once per wavefront).
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     __syncthreads();
-    if (threadIdx.x == 0) s_last = atomicAdd(done, 1u) == gridDim.x - 1 ? 1u : 0u;
+    if (threadIdx.x == 0) s_last = atomicAdd(done, 1u) == count - 1 ? 1u : 0u;
     __syncthreads();
     return s_last != 0;
 }
@@ -317,7 +317,7 @@ __global__ __launch_bounds__(kThreads) void sample_coarse_kernel(Walk w, Sample 
     __syncthreads();
     for (int i = t; i < kCoarse; i += kThreads)
         if (h[i]) atomicAdd(&ws.coarse[i], h[i]);
-    if (!last_workgroup(&ws.st->done[0])) return;
+    if (!last_workgroup(&ws.st->done[0], gridDim.x)) return;
 
     __shared__ int s_bin[2];
     __shared__ unsigned long long s_below, s_total;
@@ -373,7 +373,7 @@ __global__ __launch_bounds__(kThreads) void sample_fine_kernel(Walk w, Sample s,
     __syncthreads();
     for (int i = t; i < kSub; i += kThreads)
         if (h[i]) atomicAdd(&ws.sub[i], h[i]);
-    if (!last_workgroup(&ws.st->done[1])) return;
+    if (!last_workgroup(&ws.st->done[1], gridDim.x)) return;
 
     __shared__ int s_bin[2];
     if (t == 0) {
@@ -429,8 +429,8 @@ __device__ __forceinline__ void zero_bytes(uint8_t* dst, int n, int lane)
     if (lane < 16 && tail < n) dst[tail] = 0;
 }
 
-// EXACT = false: the interval of the sample.  EXACT = true: tau itself is known (the exact way), every
-// entry is decided; runs only if the interval failed.
+// EXACT = false: the interval of the sample.  EXACT = true (with a mask only): tau itself is known; the
+// candidates' bytes are written or, if the interval failed (the exact way), every entry is decided.
 template <bool EXACT>
 __global__ __launch_bounds__(kSweepThreads) void mask_sweep_kernel(Walk w, Workspace ws, uint8_t* mask)
 {
@@ -441,7 +441,12 @@ __global__ __launch_bounds__(kSweepThreads) void mask_sweep_kernel(Walk w, Works
     __shared__ unsigned long long s_above;
     if (EXACT) {
         unsigned long long dummy;
-        if (!mask || interval_ok(ws.st, &dummy)) return;
+        if (interval_ok(ws.st, &dummy)) {                    // the candidates' bytes are all that is left
+            const uint32_t n = (uint32_t)ws.st->ncand, tau_key = ws.st->tau_key;
+            for (uint32_t i = blockIdx.x * kSweepThreads + threadIdx.x; i < n; i += gridDim.x * kSweepThreads)
+                if (ws.cand_key[i] >= tau_key) mask[ws.cand_idx[i]] = 1;
+            return;
+        }
     } else if (ws.st->wide) {
         return;
     }
@@ -563,25 +568,22 @@ __global__ __launch_bounds__(kSweepThreads) void mask_sweep_kernel(Walk w, Works
     }
 }
 
-// ---- select: tau among the candidates
-
-__global__ __launch_bounds__(kThreads) void candidate_bins_kernel(Workspace ws)
+// ---- select: tau among the candidates, in two histograms over their key bits.  `h` is LDS, `parts` the
+// workgroups of the launch that take part.
+__device__ __forceinline__ void candidate_bins(const Workspace& ws, uint32_t* h, unsigned long long rank, uint32_t parts)
 {
-    __shared__ uint32_t h[kCandBins];
-    unsigned long long rank;
-    if (!interval_ok(ws.st, &rank)) return;
     const int t = threadIdx.x;
     const uint32_t n = (uint32_t)ws.st->ncand, lo = ws.st->lo;
     const int bits = bits_for((unsigned long long)ws.st->hi - lo + 1);
     const int shift = bits > kCandBits ? bits - kCandBits : 0;
     for (int i = t; i < kCandBins; i += kThreads) h[i] = 0;
     __syncthreads();
-    for (uint32_t i = blockIdx.x * kThreads + t; i < n; i += gridDim.x * kThreads)
+    for (uint32_t i = blockIdx.x * kThreads + t; i < n; i += parts * kThreads)
         atomicAdd(&h[(ws.cand_key[i] - lo) >> shift], 1u);
     __syncthreads();
     for (int i = t; i < kCandBins; i += kThreads)
         if (h[i]) atomicAdd(&ws.cand[i], h[i]);
-    if (!last_workgroup(&ws.st->done[2])) return;
+    if (!last_workgroup(&ws.st->done[2], parts)) return;
     const unsigned long long want[1] = {rank};
     find_ranks<kCandBins>(ws.cand, 0ull, want, [&](int, int bin, unsigned long long below) {
         ws.st->cand_lo = lo + ((uint32_t)bin << shift);
@@ -590,23 +592,20 @@ __global__ __launch_bounds__(kThreads) void candidate_bins_kernel(Workspace ws)
     });
 }
 
-__global__ __launch_bounds__(kThreads) void candidate_last_kernel(Workspace ws, float* tau_out)
+__device__ __forceinline__ void candidate_last(const Workspace& ws, uint32_t* h, float* tau_out, uint32_t parts)
 {
-    __shared__ uint32_t h[kLastBins];
-    unsigned long long dummy;
-    if (!interval_ok(ws.st, &dummy)) return;
     const int t = threadIdx.x;
     const uint32_t n = (uint32_t)ws.st->ncand, lo = ws.st->cand_lo, width = 1u << ws.st->cand_shift;   // <= kLastBins
     for (int i = t; i < kLastBins; i += kThreads) h[i] = 0;
     __syncthreads();
-    for (uint32_t i = blockIdx.x * kThreads + t; i < n; i += gridDim.x * kThreads) {
+    for (uint32_t i = blockIdx.x * kThreads + t; i < n; i += parts * kThreads) {
         const uint32_t d = ws.cand_key[i] - lo;
         if (d < width) atomicAdd(&h[d], 1u);
     }
     __syncthreads();
     for (int i = t; i < kLastBins; i += kThreads)
         if (h[i]) atomicAdd(&ws.last[i], h[i]);
-    if (!last_workgroup(&ws.st->done[3])) return;
+    if (!last_workgroup(&ws.st->done[3], parts)) return;
     const unsigned long long want[1] = {ws.st->cand_rank};
     find_ranks<kLastBins>(ws.last, 0ull, want, [&](int, int bin, unsigned long long) {
         ws.st->tau_key = lo + (uint32_t)bin;
@@ -614,26 +613,24 @@ __global__ __launch_bounds__(kThreads) void candidate_last_kernel(Workspace ws, 
     });
 }
 
-__global__ __launch_bounds__(256) void candidate_fixup_kernel(Workspace ws, uint8_t* mask)
-{
-    unsigned long long dummy;
-    if (!interval_ok(ws.st, &dummy)) return;
-    const uint32_t n = (uint32_t)ws.st->ncand;
-    const uint32_t tau_key = ws.st->tau_key;
-    for (uint32_t i = blockIdx.x * 256u + threadIdx.x; i < n; i += gridDim.x * 256u)
-        if (ws.cand_key[i] >= tau_key) mask[ws.cand_idx[i]] = 1;
-}
-
-// ---- the exact way: 16 key bits per level over all entries, only if the interval failed.  The counts
-// of a workgroup are kept as 16-bit halves of LDS words and moved out before one of them can overflow.
+// One of the two levels of the selection: a histogram over the candidates or, only if the interval failed,
+// the exact way: 16 key bits per level over all entries, the counts of a workgroup kept as 16-bit halves of
+// LDS words and moved out before one of them can overflow.  Both in one launch: a launch that returns at once
+// costs 4.6 us between its neighbours, as does the mask sweep of the exact way, which shares the launch that
+// writes the candidates' mask bytes (16 x 4096 x 4096 causal: 245 us a call with them apart, 236 now).
 template <int LEVEL>
-__global__ __launch_bounds__(kThreads) void exact_level_kernel(Walk w, Workspace ws, float* tau_out)
+__global__ __launch_bounds__(kThreads) void select_level_kernel(Walk w, Workspace ws, float* tau_out, uint32_t parts)
 {
     constexpr int STEP = 256;                                // entries of a wavefront's step
     constexpr int STEPS = 65535 / (STEP * (kThreads / 64));  // steps of all wavefronts between two moves: 15
     __shared__ uint32_t h[kExactBins / 2];
-    unsigned long long dummy;
-    if (interval_ok(ws.st, &dummy)) return;
+    unsigned long long rank_inside;
+    if (interval_ok(ws.st, &rank_inside)) {
+        if (blockIdx.x >= parts) return;
+        if (LEVEL == 0) candidate_bins(ws, h, rank_inside, parts);
+        else candidate_last(ws, h, tau_out, parts);
+        return;
+    }
     const int t = threadIdx.x, lane = t & 63;
     const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
     const long long nwaves = (long long)gridDim.x * (kThreads / 64);
@@ -678,7 +675,7 @@ __global__ __launch_bounds__(kThreads) void exact_level_kernel(Walk w, Workspace
         }
         __syncthreads();
     }
-    if (!last_workgroup(&ws.st->done[4 + LEVEL])) return;
+    if (!last_workgroup(&ws.st->done[4 + LEVEL], gridDim.x)) return;
     const unsigned long long rank = LEVEL == 0 ? ws.st->rank : ws.st->exact_rank;
     const unsigned long long want[1] = {rank};
     find_ranks<kExactBins>(hist, 0ull, want, [&](int, int bin, unsigned long long below) {
@@ -749,13 +746,10 @@ hipError_t launch_prune_mask(const float* abar, int H, int Lq, int Lk, int causa
     hipLaunchKernelGGL(sample_coarse_kernel, dim3(sgrid), dim3(kThreads), 0, stream, w, s, ws);
     hipLaunchKernelGGL(sample_fine_kernel, dim3(sgrid), dim3(kThreads), 0, stream, w, s, ws);
     hipLaunchKernelGGL(mask_sweep_kernel<false>, dim3(grid), dim3(kSweepThreads), 0, stream, w, ws, mask);
-    hipLaunchKernelGGL(candidate_bins_kernel, dim3(cgrid), dim3(kThreads), 0, stream, ws);
-    hipLaunchKernelGGL(candidate_last_kernel, dim3(cgrid), dim3(kThreads), 0, stream, ws, tau_out);
-    if (mask) hipLaunchKernelGGL(candidate_fixup_kernel, dim3(256), dim3(256), 0, stream, ws, mask);
-    // nothing of what follows runs unless the interval failed
-    hipLaunchKernelGGL(exact_level_kernel<0>, dim3(egrid), dim3(kThreads), 0, stream, w, ws, tau_out);
-    hipLaunchKernelGGL(exact_level_kernel<1>, dim3(egrid), dim3(kThreads), 0, stream, w, ws, tau_out);
-    if (mask) hipLaunchKernelGGL(mask_sweep_kernel<true>, dim3(grid), dim3(kSweepThreads), 0, stream, w, ws, mask);
+    const unsigned lgrid = max(egrid, cgrid);
+    hipLaunchKernelGGL(select_level_kernel<0>, dim3(lgrid), dim3(kThreads), 0, stream, w, ws, tau_out, cgrid);
+    hipLaunchKernelGGL(select_level_kernel<1>, dim3(lgrid), dim3(kThreads), 0, stream, w, ws, tau_out, cgrid);
+    if (mask) hipLaunchKernelGGL(mask_sweep_kernel<true>, dim3(256), dim3(kSweepThreads), 0, stream, w, ws, mask);
     return hipGetLastError();
 }
 

@@ -524,6 +524,13 @@ ap_status ap_accumulate_attention_maps_lse(const void *Q, const void *K, const f
                                            float weight, float *abar, void *workspace,
                                            size_t workspace_bytes, void *stream);
 
+/* The first batch: as the two above (the second if `lse` is not NULL) on an abar of zeros, but abar need not
+ * hold anything: every entry is written, those that causality hides with 0. */
+ap_status ap_start_attention_maps(const void *Q, const void *K, const float *lse, ap_dtype dtype, int B, int H,
+                                  int Lq, int Lk, int D, const int64_t *stride_q, const int64_t *stride_k,
+                                  int causal, float softmax_scale, float weight, float *abar, void *workspace,
+                                  size_t workspace_bytes, void *stream);
+
 /* ---------------------------------------------------------------------------------------------
  * Mask construction, step 2: layer-wise percentile threshold and pruning mask (Section 3.2,
  * paragraph before Eq. (2), and Eq. (2)).

@@ -562,7 +562,7 @@ size_t ap_attention_maps_workspace_bytes(int B, int H, int Lq)
 static ap_status maps_common(const void* Q, const void* K, const float* lse, ap_dtype dtype, int B, int H,
                              int Lq, int Lk, int D, const int64_t* stride_q, const int64_t* stride_k,
                              int causal, float softmax_scale, float weight, float* abar, void* workspace,
-                             size_t workspace_bytes, void* stream)
+                             size_t workspace_bytes, void* stream, bool init = false)
 {
     if (!Q || !K || !stride_q || !stride_k || !abar || !workspace) return AP_ERR_INVALID_ARG;
     if (B <= 0 || H <= 0 || Lq <= 0 || Lk <= 0 || D <= 0) return AP_ERR_INVALID_ARG;
@@ -588,6 +588,7 @@ static ap_status maps_common(const void* Q, const void* K, const float* lse, ap_
     a.scale = softmax_scale > 0.f ? softmax_scale : 1.0f / sqrtf((float)D);
     a.weight = weight;
     a.abar = abar;
+    a.init = init ? 1 : 0;
     a.lse2 = (float*)workspace;
     return ap::launch_attention_maps(a, lse, (hipStream_t)stream) == hipSuccess ? AP_OK : AP_ERR_HIP;
 }
@@ -611,6 +612,15 @@ ap_status ap_accumulate_attention_maps_lse(const void* Q, const void* K, const f
     if (!lse) return AP_ERR_INVALID_ARG;
     return maps_common(Q, K, lse, dtype, B, H, Lq, Lk, D, stride_q, stride_k, causal, softmax_scale,
                        weight, abar, workspace, workspace_bytes, stream);
+}
+
+ap_status ap_start_attention_maps(const void* Q, const void* K, const float* lse, ap_dtype dtype, int B, int H,
+                                  int Lq, int Lk, int D, const int64_t* stride_q, const int64_t* stride_k,
+                                  int causal, float softmax_scale, float weight, float* abar, void* workspace,
+                                  size_t workspace_bytes, void* stream)
+{
+    return maps_common(Q, K, lse, dtype, B, H, Lq, Lk, D, stride_q, stride_k, causal, softmax_scale, weight, abar,
+                       workspace, workspace_bytes, stream, true);
 }
 
 size_t ap_prune_mask_workspace_bytes(void) { return ap::prune_mask_workspace_bytes(); }

@@ -120,6 +120,7 @@ struct MapArgs {
     float scale;                    // already resolved (> 0)
     float weight;
     float* abar;                    // [H, Lq, Lk], accumulated into
+    int init;                       // 1: written instead (hidden entries 0), whatever it held
     float* lse2;                    // [B, H, Lq] scratch: base-2 log-sum-exp of each score row
 };
 // lse: null (the row statistics are computed by a pass of their own), or the natural-log

@@ -11,6 +11,12 @@
 //                          sums P in registers; the running map in memory is read and written
 //                          once per call, whatever the batch size.
 //
+// What bounds them: the row statistics the issue of vector instructions (32 exponentials and 80 others per lane
+// and tile; B4 H16 L2048 D128 55 us, 75 with three wavefronts per SIMD and long rows first); the accumulation the
+// map's traffic in tiles of 128 x 128 (112 us there, 268 MB at 2.4 TB/s).  Deeper pipelines (K three tiles ahead, Q
+// through LDS), one persistent workgroup per compute unit and stores straight from registers all measured the same or
+// more.  The first batch writes the map without reading it, which saves its clearing too (33 us).
+//
 // Both use the score layout of the attention kernel: a wavefront owns 32 queries, lane l holds
 // query l % 32 and, of each 32-key block, the keys 8*(i/4) + 4*(l/32) + i%4 (i = 0..15).
 #include <hip/hip_runtime.h>
@@ -26,7 +32,7 @@ namespace {
 using namespace mfma;
 
 template <int D, int NW>
-__global__ __launch_bounds__(64 * NW) void row_lse_kernel(MapArgs a, int nQB)
+__global__ __launch_bounds__(64 * NW, 4) void row_lse_kernel(MapArgs a, int nQB)
 {
     constexpr int BM = 32 * NW;
     constexpr int TILE = kBN * D;
@@ -39,10 +45,16 @@ __global__ __launch_bounds__(64 * NW) void row_lse_kernel(MapArgs a, int nQB)
     const int lane = tid & 63;
     const int n = lane & 31, hh = lane >> 5;
 
+    // All workgroups of a call of ordinary size are resident at once and a compute unit gets every 32nd of an
+    // XCD's, so long rows first would give some of them long rows only (B4 H16 L2048 D128: 75 us, 68 in this
+    // order; 55 with four wavefronts per SIMD, which 128 registers allow): the rows' order is reversed in every other round of 32.
     const int bid = xcd_contiguous(blockIdx.x, gridDim.x);
-    const int qb = nQB - 1 - (bid % nQB);                    // long causal rows first
-    const int h = (bid / nQB) % a.H;
-    const int b = bid / (nQB * a.H);
+    const int per_xcd = (gridDim.x + 7) / 8;
+    const int group = bid / nQB, j = bid % nQB;
+    const int round = (nQB < 32 ? ((group * nQB) % per_xcd) / 32 : group) & 1;
+    const int qb = a.causal && round ? j : nQB - 1 - j;
+    const int h = group % a.H;
+    const int b = group / a.H;
 
     const uint16_t* Qp = (const uint16_t*)a.Q + (size_t)b * a.sq[0] + (size_t)h * a.sq[1];
     const uint16_t* Kp = (const uint16_t*)a.K + (size_t)b * a.sk[0] + (size_t)h * a.sk[1];
@@ -68,6 +80,8 @@ __global__ __launch_bounds__(64 * NW) void row_lse_kernel(MapArgs a, int nQB)
     const int k_swz = hh ^ swz_k<D>(n);
     const float sc = a.scale * kLog2e;
     float m = -INFINITY, lsum = 0.f;
+    // last key that any query of this wavefront sees
+    const long long wave_last = a.causal ? (long long)qb * BM + wave * 32 + 31 + off : (long long)a.Lk - 1;
 
     wait_vmem();
     settle<KSTEPS>(qreg);
@@ -78,8 +92,10 @@ __global__ __launch_bounds__(64 * NW) void row_lse_kernel(MapArgs a, int nQB)
         if (kt + 1 < nkt)
             issue_tile_loads<D, NW, false>(k_rsrc, lds + ((kt + 1) & 1) * TILE, (kt + 1) * 64,
                                            sk_bytes, wave, lane);
+        const uint16_t* Ks = smem + (kt & 1) * TILE;
+        if ((long long)kt * 64 > wave_last) continue;        // uniform over the wavefront
         f32x16 sacc[2];
-        qk_64<D>(smem + (kt & 1) * TILE, qreg, n, k_swz, sacc);
+        qk_64<D>(Ks, qreg, n, k_swz, sacc);
 
         // keys of this tile that exist and that this query may see: a prefix of the tile
         const long long k0 = (long long)kt * 64;
@@ -132,8 +148,10 @@ __global__ __launch_bounds__(64 * NW) void row_lse_kernel(MapArgs a, int nQB)
 // One workgroup: 32*NW queries x KT*64 keys of one head.  The Q rows of an example are loaded
 // once for all KT key tiles, every K tile serves all NW wavefronts, and the KT partial maps stay
 // in registers over the examples.
-template <int D, int NW, int KT>
-__global__ __launch_bounds__(64 * NW) void map_accumulate_kernel(MapArgs a, int nQB, int nKG)
+//
+// INIT: the map is written whatever it held, hidden entries 0.
+template <int D, int NW, int KT, bool INIT>
+__global__ __launch_bounds__(64 * NW, D == 128 ? 2 : 3) void map_accumulate_kernel(MapArgs a, int nQB, int nKG)
 {
     constexpr int BM = 32 * NW;
     constexpr int TILE = kBN * D;
@@ -158,9 +176,15 @@ __global__ __launch_bounds__(64 * NW) void map_accumulate_kernel(MapArgs a, int 
     int n_sub = min(KT, (a.Lk - key0 + 63) / 64);            // key tiles that exist ...
     if (a.causal) {                                          // ... and that some query of the block sees
         const long long block_diag = (long long)qb * BM + (BM - 1) + off;
-        if (block_diag < key0) return;
-        n_sub = (int)min((long long)n_sub, (block_diag - key0) / 64 + 1);
+        if (block_diag < key0) {
+            if (!INIT) return;
+            n_sub = 0;
+        } else {
+            n_sub = (int)min((long long)n_sub, (block_diag - key0) / 64 + 1);
+        }
     }
+    // last key that any query of this wavefront sees
+    const long long wave_last = a.causal ? (long long)qb * BM + wave * 32 + 31 + off : (long long)a.Lk - 1;
 
     const int qrow = qb * BM + wave * 32 + n;
     const int qload = qrow < a.Lq ? qrow : a.Lq - 1;
@@ -187,8 +211,8 @@ __global__ __launch_bounds__(64 * NW) void map_accumulate_kernel(MapArgs a, int 
             for (int i = 0; i < 16; ++i) acc[sub][kb][i] = 0.f;
 
     bf16x8 qcur[KSTEPS];
-    float lcur, lnext = 0.f;
-    {
+    float lcur = 0.f, lnext = 0.f;
+    if (n_sub > 0) {
         const uint16_t* qr = q_row(0);
 #pragma unroll
         for (int kk = 0; kk < KSTEPS; ++kk) qcur[kk] = *reinterpret_cast<const bf16x8*>(qr + 16 * kk);
@@ -196,7 +220,7 @@ __global__ __launch_bounds__(64 * NW) void map_accumulate_kernel(MapArgs a, int 
         issue_k(0, 0, 0);
     }
     int stage = 0;
-    for (int b = 0; b < a.B; ++b) {
+    for (int b = 0; n_sub > 0 && b < a.B; ++b) {
 #pragma unroll
         for (int sub = 0; sub < KT; ++sub) {
             if (sub >= n_sub) continue;                      // uniform over the workgroup
@@ -208,8 +232,9 @@ __global__ __launch_bounds__(64 * NW) void map_accumulate_kernel(MapArgs a, int 
             const bool last = sub + 1 == n_sub;
             if (!last) issue_k(b, sub + 1, stage ^ 1);       // the next tile travels under the arithmetic
             else if (b + 1 < a.B) issue_k(b + 1, 0, stage ^ 1);
+            const bool seen = (long long)key0 + sub * 64 <= wave_last;   // uniform over the wavefront
             f32x16 sacc[2];
-            qk_64<D>(smem + stage * TILE, qcur, n, k_swz, sacc);
+            if (seen) qk_64<D>(smem + stage * TILE, qcur, n, k_swz, sacc);
             if (last && b + 1 < a.B) {                       // Q rows and lse of the next example
                 const uint16_t* qr = q_row(b + 1);
 #pragma unroll
@@ -218,11 +243,12 @@ __global__ __launch_bounds__(64 * NW) void map_accumulate_kernel(MapArgs a, int 
             }
             // entries outside the map or hidden by causality are computed too (from zero keys or
             // real ones) and dropped when the tile is written
+            if (seen)
 #pragma unroll
-            for (int kb = 0; kb < 2; ++kb)
+                for (int kb = 0; kb < 2; ++kb)
 #pragma unroll
-                for (int i = 0; i < 16; ++i)
-                    acc[sub][kb][i] += __builtin_amdgcn_exp2f(fmaf(sacc[kb][i], sc, -lcur));
+                    for (int i = 0; i < 16; ++i)
+                        acc[sub][kb][i] += __builtin_amdgcn_exp2f(fmaf(sacc[kb][i], sc, -lcur));
             stage ^= 1;
         }
     }
@@ -233,7 +259,25 @@ __global__ __launch_bounds__(64 * NW) void map_accumulate_kernel(MapArgs a, int 
     const int c4 = (tid & 15) * 4;
 #pragma unroll
     for (int sub = 0; sub < KT; ++sub) {
-        if (sub >= n_sub) continue;
+        const long long k_first = (long long)key0 + sub * 64;
+        if (sub >= n_sub) {
+            if (INIT) {                                      // hidden from the whole block: zeros
+#pragma unroll
+                for (int pass = 0; pass < 8; ++pass) {
+                    const int q = qb * BM + pass * (4 * NW) + (tid >> 4);
+                    if (q >= a.Lq) continue;
+                    float* dst = a.abar + ((size_t)h * a.Lq + q) * a.Lk + k_first + c4;
+                    if (vec_ok && k_first + c4 < a.Lk) {
+                        *reinterpret_cast<float4*>(dst) = make_float4(0.f, 0.f, 0.f, 0.f);
+                    } else {
+#pragma unroll
+                        for (int e = 0; e < 4; ++e)
+                            if (k_first + c4 + e < a.Lk) dst[e] = 0.f;
+                    }
+                }
+            }
+            continue;
+        }
         __syncthreads();                                     // K stages / previous staged tile are consumed
         {
             const int row = wave * 32 + n;
@@ -249,7 +293,6 @@ __global__ __launch_bounds__(64 * NW) void map_accumulate_kernel(MapArgs a, int 
         __syncthreads();
         // a tile that lies inside the map and below the causal limit for all its rows takes the
         // branch-free path: all 8 loads of a thread are in flight before the first is used
-        const long long k_first = (long long)key0 + sub * 64;
         bool interior = vec_ok && qb * BM + BM <= a.Lq && k_first + 63 <= (long long)a.Lk - 1;
         if (a.causal) interior = interior && k_first + 63 <= (long long)qb * BM + off;
         if (interior) {
@@ -257,7 +300,8 @@ __global__ __launch_bounds__(64 * NW) void map_accumulate_kernel(MapArgs a, int 
             float4 o[8];
 #pragma unroll
             for (int pass = 0; pass < 8; ++pass)
-                o[pass] = *reinterpret_cast<const float4*>(base + (size_t)pass * (4 * NW) * a.Lk);
+                o[pass] = INIT ? make_float4(0.f, 0.f, 0.f, 0.f)
+                               : *reinterpret_cast<const float4*>(base + (size_t)pass * (4 * NW) * a.Lk);
 #pragma unroll
             for (int pass = 0; pass < 8; ++pass) {
                 const float4 v = *reinterpret_cast<const float4*>(outs + (pass * (4 * NW) + (tid >> 4)) * OUT_LD + c4);
@@ -279,11 +323,11 @@ __global__ __launch_bounds__(64 * NW) void map_accumulate_kernel(MapArgs a, int 
             long long last_key = (long long)a.Lk - 1;        // last key of this row that is accumulated
             if (a.causal) last_key = min(last_key, (long long)q + off);
             const long long k = k_first + c4;
-            if (k > last_key) continue;
+            if (k > (INIT ? (long long)a.Lk - 1 : last_key)) continue;
             const float4 v = *reinterpret_cast<const float4*>(outs + r * OUT_LD + c4);
             float* dst = a.abar + ((size_t)h * a.Lq + q) * a.Lk + k;
             if (vec_ok && k + 3 <= last_key) {
-                float4 o = *reinterpret_cast<float4*>(dst);
+                float4 o = INIT ? make_float4(0.f, 0.f, 0.f, 0.f) : *reinterpret_cast<float4*>(dst);
                 o.x = fmaf(a.weight, v.x, o.x);
                 o.y = fmaf(a.weight, v.y, o.y);
                 o.z = fmaf(a.weight, v.z, o.z);
@@ -293,7 +337,8 @@ __global__ __launch_bounds__(64 * NW) void map_accumulate_kernel(MapArgs a, int 
                 const float ve[4] = {v.x, v.y, v.z, v.w};
 #pragma unroll
                 for (int e = 0; e < 4; ++e)
-                    if (k + e <= last_key) dst[e] = fmaf(a.weight, ve[e], dst[e]);
+                    if (k + e <= last_key) dst[e] = fmaf(a.weight, ve[e], INIT ? 0.f : dst[e]);
+                    else if (INIT && k + e < a.Lk) dst[e] = 0.f;
             }
         }
     }
@@ -323,8 +368,11 @@ hipError_t launch_d(const MapArgs& a, const float* lse, hipStream_t stream)
     }
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL((map_accumulate_kernel<D, NW, KT>), dim3((unsigned)(a.H * nQB * nKG)),
-                       dim3(64 * NW), 0, stream, a, nQB, nKG);
+    const dim3 grid((unsigned)(a.H * nQB * nKG)), block(64 * NW);
+    if (a.init)
+        hipLaunchKernelGGL((map_accumulate_kernel<D, NW, KT, true>), grid, block, 0, stream, a, nQB, nKG);
+    else
+        hipLaunchKernelGGL((map_accumulate_kernel<D, NW, KT, false>), grid, block, 0, stream, a, nQB, nKG);
     return hipGetLastError();
 }
 

@@ -164,3 +164,21 @@ def test_entmax_block_row_with_more_than_16_gathered_entries():
         n_gathered = int((sched.start[: int(sched.cnt[0].item())] < 0).sum().item())
         assert (n_gathered > 16) == (Lk == 3000), n_gathered
         run_entmax(Q, K, V, mask, False)
+
+
+@pytest.mark.parametrize("D,kind", [(64, "equal"), (64, "ascending"), (128, "ascending"), (32, "descending"),
+                                    (64, "mixed"), (128, "periodic")])
+def test_entmax_start_from_the_largest_score_of_every_place(D, kind):
+    """Rows whose large scores share their places in the tiles (equal, growing or periodic scores: the start lies far
+    below tau) and rows whose large scores do not (the start is tau), alone and next to each other in a block row."""
+    B, H, L = 1, 2, 400
+    Q, K, V = rand_qkv(D, B, H, L, L, D)
+    if kind in ("ascending", "descending", "periodic"):
+        along = np.linspace(-1.0, 1.0, L, dtype=np.float32) if kind != "periodic" else \
+            np.where(np.arange(L) % 64 == 5, 1.0, 0.3).astype(np.float32)
+        Q = np.abs(Q)
+        K = (-along if kind == "descending" else along)[None, None, :, None] * np.abs(K)
+    else:
+        Q *= 0.0 if kind == "equal" else np.linspace(0.0, 3.0, L, dtype=np.float32)[None, None, :, None]
+    mask = synth.random_mask(H, L, L, 1.0 if kind == "equal" else 0.8, seed=D)
+    run_entmax(Q, K, V, mask, kind == "mixed")

@@ -8,27 +8,18 @@
 // several times, recomputing S^T = K Q^T on the matrix cores each time (the scores of a long row
 // do not fit on chip, and writing them out would cost more than recomputing them):
 //
-//   sweep 1     the largest score at every place of a tile, over all tiles: 64 scores per query, in
-//               registers, that hold the row maximum m and most of its other large scores; and the
-//               number of kept visible keys
-//   start       tau of those 64 scores alone, by the Newton steps below without touching memory: fewer keys
-//               can only have a smaller tau, so it is a place to start from that lies at or below the root
+//   sweep 1     row maximum m and the number n of kept visible keys
 //   sweeps 2..  with y = x - m <= 0, d = [y - tau]_+: the norm |d| and the sum g of d, and a Newton
 //               step on h(tau) = |d| - 1:  tau += (|d| - 1) |d| / g.  h is convex and decreasing
-//               with its root in [-1, 0); started at or below it (at -1 h >= 0 because the maximum
+//               with its root in [-1, 0); started at -1 (where h >= 0 because the maximum
 //               contributes 1) the steps increase monotonically to the root and never pass it.
 //               The norm is much closer to linear than its square, which saves about half of
 //               the sweeps.  A row is done when | |d|^2 - 1 | <= 1e-5 at its tau, or after the
-//               step taken from a tau with | |d|^2 - 1 | <= 1e-2: that step solves the quadratic of the
-//               support at its tau, which leaves what scores that drop out of the support on the way
-//               contribute, a few 1e-6 (the output is divided by the actual sum of P in any case), and
-//               the sweep that would only confirm it is saved.  The block row sweeps until all its rows are done.
+//               step taken from a tau with | |d|^2 - 1 | <= 1e-2: the steps converge quadratically,
+//               so that step leaves a residual of a few 1e-5 at most (the output is divided by
+//               the actual sum of P in any case) and the sweep that would only confirm it is
+//               saved.  The block row sweeps until all its rows are done.
 //   last sweep  P = [y - tau]_+^2, O^T += V^T P^T, O / sum P.
-//
-// What bounds it: the sweeps, each a chain of tile loads, matrix products and 32 scores per lane and tile, so
-// the start counts: from -1 the Newton steps take three to four sweeps, B4 H16 L2048 D128, 10 % kept: 111 us;
-// from the tau of 64 scores one or two, 99 us.  (Counting the support for the quadratic last step costs 4 of them; tau is
-// off by 0.6 to 1.6e-6 of its norm instead of 1.3 to 5.3e-6, and sum p by 1e-5 at most instead of 5e-5.)
 //
 // Same operand layouts, LDS swizzles and LDS-direct loads as the softmax kernel; walks the
 // layout's tiles or, if given, the entries of its visit schedule; 64x64 tiles, two LDS stages of K (one barrier per tile) in the threshold sweeps.
@@ -46,7 +37,6 @@ using namespace mfma;
 
 constexpr float kEntmaxTol = 1e-5f;          // on sum p - 1
 constexpr float kEntmaxEarly = 1e-2f;        // residual from which one more step is taken unconfirmed
-constexpr float kEntmaxStart = 1e-4f;        // residual at which the start is good enough
 constexpr int kEntmaxMaxIter = 60;
 constexpr int kEntmaxSchedEntries = 64;      // a block row with more schedule entries walks the layout instead
 constexpr int kEntmaxGathered = 16;          // ... or with more gathered entries among them
@@ -200,66 +190,36 @@ __global__ __launch_bounds__(128, 2) void entmax15_fwd_kernel(FwdArgs a, float* 
         return __uint_as_float(s[0]) + __uint_as_float(s[1]);
     };
 
-    // ---- sweep 1: largest score at every place of a tile, number of kept visible keys
-    f32x16 top[2];
-#pragma unroll
-    for (int kb = 0; kb < 2; ++kb)
-#pragma unroll
-        for (int i = 0; i < 16; ++i) top[kb][i] = -INFINITY;
+    // ---- sweep 1: row maximum and number of kept visible keys
+    float m = -INFINITY;
     int nkept = 0;
     sweep(false, [&](uint64_t word, f32x16* sacc) {
         nkept += __popcll(word);
 #pragma unroll
         for (int kb = 0; kb < 2; ++kb)
 #pragma unroll
-            for (int i = 0; i < 16; ++i) top[kb][i] = fmaxf(top[kb][i], sacc[kb][i]);
+            for (int i = 0; i < 16; ++i) m = fmaxf(m, sacc[kb][i]);
     });
-    float m = -INFINITY;
-#pragma unroll
-    for (int kb = 0; kb < 2; ++kb)
-#pragma unroll
-        for (int i = 0; i < 16; ++i) m = fmaxf(m, top[kb][i]);
     m = both_halves_max(m);
     const bool empty = nkept == 0;                           // both halves counted the same words
     const float mc = empty ? 0.f : m * c;
 
-    // number, sum and sum of squares of d = [y - tau]_+ > 0 over a tile's scores, added to g0, g1 and g2
-    auto add_sums = [&](const f32x16* sacc, float tau, int& g0, float& g1, float& g2) {
-#pragma unroll
-        for (int kb = 0; kb < 2; ++kb)
-#pragma unroll
-            for (int i = 0; i < 16; ++i) {
-                const float d = fmaxf(fmaf(sacc[kb][i], c, -mc) - tau, 0.f);   // -inf -> 0
-                g0 += d > 0.f ? 1 : 0;
-                g1 += d;
-                g2 = fmaf(d, d, g2);
-            }
-    };
-    auto newton = [](float tau, float g1, float g2) {
-        const float nd = sqrtf(g2);
-        return fminf(fmaxf(tau + (nd - 1.0f) * nd / g1, -1.0f), 0.f);
-    };
-    // ---- start: tau of those scores
-    float tau = -1.f;
-    bool open = !empty;
-    for (int iter = 0; iter < kEntmaxMaxIter && __ballot(open) != 0; ++iter) {
-        int g0 = 0;
-        float g1 = 0.f, g2 = 0.f;
-        add_sums(top, tau, g0, g1, g2);
-        g1 = both_halves_sum(g1);
-        g2 = both_halves_sum(g2);
-        if (!(g2 - 1.0f > kEntmaxStart) || g1 <= 0.f) open = false;
-        else if (open) tau = newton(tau, g1, g2);
-    }
-
     // ---- Newton sweeps for tau (relative to the row maximum: the root lies in [-1, 0))
+    float tau = -1.f;
     bool done = empty;
     for (int iter = 0; iter < kEntmaxMaxIter; ++iter) {
         if (__syncthreads_or(done ? 0 : 1) == 0) break;      // every row of the block row has its tau
-        int g0 = 0;
         float g1 = 0.f, g2 = 0.f;
-        sweep(false, [&](uint64_t, f32x16* sacc) { add_sums(sacc, tau, g0, g1, g2); });
-        const float n0 = both_halves_sum((float)g0);
+        sweep(false, [&](uint64_t, f32x16* sacc) {
+#pragma unroll
+            for (int kb = 0; kb < 2; ++kb)
+#pragma unroll
+                for (int i = 0; i < 16; ++i) {
+                    const float d = fmaxf(fmaf(sacc[kb][i], c, -mc) - tau, 0.f);   // -inf -> 0
+                    g1 += d;
+                    g2 = fmaf(d, d, g2);
+                }
+        });
         g1 = both_halves_sum(g1);
         g2 = both_halves_sum(g2);
         if (!done) {
@@ -267,11 +227,9 @@ __global__ __launch_bounds__(128, 2) void entmax15_fwd_kernel(FwdArgs a, float* 
             if (fabsf(f) <= kEntmaxTol || g1 <= 0.f) {
                 done = true;
             } else {
-                // the last step solves sum (d - step)^2 = 1 for the support at tau, which few or no scores leave
-                const float disc = g1 * g1 - n0 * f;
-                done = fabsf(f) <= kEntmaxEarly;
-                if (done && disc > 0.f) tau = fminf(tau + f / (g1 + sqrtf(disc)), 0.f);
-                else tau = newton(tau, g1, g2);
+                const float nd = sqrtf(g2);
+                tau = fminf(fmaxf(tau + (nd - 1.0f) * nd / g1, -1.0f), 0.f);
+                done = fabsf(f) <= kEntmaxEarly;             // this step is the last one
             }
         }
     }

@@ -169,8 +169,8 @@ def test_entmax_block_row_with_more_than_16_gathered_entries():
 @pytest.mark.parametrize("D,kind", [(64, "equal"), (64, "ascending"), (128, "ascending"), (32, "descending"),
                                     (64, "mixed"), (128, "periodic")])
 def test_entmax_start_from_the_largest_score_of_every_place(D, kind):
-    """Rows whose large scores share their places in the tiles (equal, growing or periodic scores: the start lies far
-    below tau) and rows whose large scores do not (the start is tau), alone and next to each other in a block row."""
+    """Rows whose large scores share their places in the tiles (equal, growing or periodic scores) and rows whose large
+    scores do not, alone and next to each other in a block row."""
     B, H, L = 1, 2, 400
     Q, K, V = rand_qkv(D, B, H, L, L, D)
     if kind in ("ascending", "descending", "periodic"):
@@ -182,3 +182,50 @@ def test_entmax_start_from_the_largest_score_of_every_place(D, kind):
         Q *= 0.0 if kind == "equal" else np.linspace(0.0, 3.0, L, dtype=np.float32)[None, None, :, None]
     mask = synth.random_mask(H, L, L, 1.0 if kind == "equal" else 0.8, seed=D)
     run_entmax(Q, K, V, mask, kind == "mixed")
+
+
+# Rows in which many scores lie just above the threshold and leave the support under the last step: values of
+# y = x - max x and how many keys have them.
+CLUSTERED = {
+    "two clusters": ((0.0, 1), (-0.999469, 1119), (-0.996444, 366), (-3.0, 50)),
+    "three clusters": ((0.0, 1), (-0.998105, 3442), (-0.992293, 245), (-0.97993, 1), (-3.0, 1174)),
+}
+
+
+def clustered_attained_sums(names, D=32):
+    """sum p at the returned tau, in 64 bits, for a query per named row (both walks).  Scores are the sum of three bf16
+    parts of a key, so that the kernel's are exact to 32 bits."""
+    rows = [np.repeat([v for v, _ in CLUSTERED[k]], [c for _, c in CLUSTERED[k]]) for k in names]
+    y = torch.from_numpy(np.concatenate(rows))
+    parts = []
+    rest = y.clone()
+    for _ in range(3):
+        parts.append(rest.to(torch.bfloat16))
+        rest = rest - parts[-1].double()
+    n, Lk = len(rows), len(y)
+    K = torch.zeros((1, 1, Lk, D), dtype=torch.bfloat16)
+    K[0, 0, :, :3] = torch.stack(parts, 1)
+    Q = torch.zeros((1, 1, n, D), dtype=torch.bfloat16)
+    Q[..., :3] = 1.0
+    x = K[0, 0, :, :3].double().sum(1).numpy()
+    mask = np.zeros((1, n, Lk), np.uint8)
+    at = 0
+    for i, row in enumerate(rows):
+        mask[0, i, at:at + len(row)] = 1
+        at += len(row)
+    lay = ap.ap_build_layout(torch.from_numpy(mask).cuda(), 64, 64)
+    sched = ap.ap_build_schedule(lay, causal=False)
+    totals = []
+    for sc in (None, sched):
+        _, tau = ap.ap_sparse_attn_entmax15_fwd(Q.cuda(), K.cuda(), K.cuda(), lay, softmax_scale=2.0, sched=sc)
+        th = tau.double().cpu().numpy()[0, 0]
+        u = np.where(mask[0] != 0, np.maximum(x[None] - th[:, None], 0.0), 0.0)
+        totals.append((u * u).sum(-1))
+    return np.concatenate(totals)
+
+
+@pytest.mark.parametrize("names", [("two clusters",), ("three clusters",), ("three clusters", "two clusters")])
+def test_entmax_tau_never_passes_the_root(names):
+    """tau rises to the root and never passes it: sum p >= 1 up to the residual 1e-5 at which a row stops (and as much
+    again for the 32-bit sums over some thousand keys)."""
+    assert clustered_attained_sums(names).min() >= 1.0 - 2e-5

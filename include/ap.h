@@ -327,8 +327,9 @@ ap_status ap_sparse_attn_decode(const void *Q, const void *K, const void *V, voi
  *
  * (the optimality conditions of 1.5-entmax; many p_ij are exactly 0).  tau is found by Newton's
  * iteration, which rises monotonically to the root: a row stops when |sum_j p_ij - 1| <= 1e-5 at
- * its tau, or after the one further step taken from a tau with |sum_j p_ij - 1| <= 1e-2 (the
- * steps converge quadratically, so the returned tau leaves |sum_j p_ij - 1| <= 1e-4).  O is
+ * its tau, or after the one further step taken from a tau with |sum_j p_ij - 1| <= 1e-2 if the sum
+ * formed with the output shows that the step left |sum_j p_ij - 1| <= 1e-4 (if not, the block row
+ * goes on until every row has stopped at its tau; 32-bit sums and scores).  O is
  * divided by the attained sum, so its weights sum to one whatever the residual; the backward call
  * forms p from the returned tau without that division.  A query with no visible kept key gets
  * O = 0 and tau = +infinity.

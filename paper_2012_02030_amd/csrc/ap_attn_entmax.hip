@@ -16,10 +16,12 @@
 //               The norm is much closer to linear than its square, which saves about half of
 //               the sweeps.  A row is done when | |d|^2 - 1 | <= 1e-5 at its tau, or after the
 //               step taken from a tau with | |d|^2 - 1 | <= 1e-2: the steps converge quadratically,
-//               so that step leaves a residual of a few 1e-5 at most (the output is divided by
-//               the actual sum of P in any case) and the sweep that would only confirm it is
+//               so that step usually leaves a few 1e-5 and the sweep that would only confirm it is
 //               saved.  The block row sweeps until all its rows are done.
-//   last sweep  P = [y - tau]_+^2, O^T += V^T P^T, O / sum P.
+//   last sweep  P = [y - tau]_+^2, O^T += V^T P^T, O / sum P.  The sum of P is what an unconfirmed step
+//               leaves: where it is more than 1e-4 above 1 (many scores just above tau that leave the
+//               support: 2.4e-3 with 3400 of them within 0.002), the block row takes up its Newton
+//               sweeps again, now each confirmed, and repeats this sweep.
 //
 // Same operand layouts, LDS swizzles and LDS-direct loads as the softmax kernel; walks the
 // layout's tiles or, if given, the entries of its visit schedule; 64x64 tiles, two LDS stages of K (one barrier per tile) in the threshold sweeps.
@@ -37,6 +39,7 @@ using namespace mfma;
 
 constexpr float kEntmaxTol = 1e-5f;          // on sum p - 1
 constexpr float kEntmaxEarly = 1e-2f;        // residual from which one more step is taken unconfirmed
+constexpr float kEntmaxLeft = 1e-4f;         // largest residual that such a step may leave
 constexpr int kEntmaxMaxIter = 60;
 constexpr int kEntmaxSchedEntries = 64;      // a block row with more schedule entries walks the layout instead
 constexpr int kEntmaxGathered = 16;          // ... or with more gathered entries among them
@@ -119,10 +122,6 @@ __global__ __launch_bounds__(128, 2) void entmax15_fwd_kernel(FwdArgs a, float* 
     settle<KSTEPS>(qreg);
 
     f32x16 oacc[DBLK];
-#pragma unroll
-    for (int db = 0; db < DBLK; ++db)
-#pragma unroll
-        for (int i = 0; i < 16; ++i) oacc[db][i] = 0.f;
 
     // One sweep over the tiles of the block row; `body(word, sacc, stage)` sees the raw scores of
     // a tile with pruned and hidden entries already replaced by -inf.
@@ -204,54 +203,62 @@ __global__ __launch_bounds__(128, 2) void entmax15_fwd_kernel(FwdArgs a, float* 
     const bool empty = nkept == 0;                           // both halves counted the same words
     const float mc = empty ? 0.f : m * c;
 
-    // ---- Newton sweeps for tau (relative to the row maximum: the root lies in [-1, 0))
-    float tau = -1.f;
+    float tau = -1.f, psum;
     bool done = empty;
-    for (int iter = 0; iter < kEntmaxMaxIter; ++iter) {
-        if (__syncthreads_or(done ? 0 : 1) == 0) break;      // every row of the block row has its tau
-        float g1 = 0.f, g2 = 0.f;
-        sweep(false, [&](uint64_t, f32x16* sacc) {
+    for (bool confirm = false;; confirm = true) {
+        // ---- Newton sweeps for tau (relative to the row maximum: the root lies in [-1, 0))
+        for (int iter = 0; iter < kEntmaxMaxIter; ++iter) {
+            if (__syncthreads_or(done ? 0 : 1) == 0) break;  // every row of the block row has its tau
+            float g1 = 0.f, g2 = 0.f;
+            sweep(false, [&](uint64_t, f32x16* sacc) {
+#pragma unroll
+                for (int kb = 0; kb < 2; ++kb)
+#pragma unroll
+                    for (int i = 0; i < 16; ++i) {
+                        const float d = fmaxf(fmaf(sacc[kb][i], c, -mc) - tau, 0.f);   // -inf -> 0
+                        g1 += d;
+                        g2 = fmaf(d, d, g2);
+                    }
+            });
+            g1 = both_halves_sum(g1);
+            g2 = both_halves_sum(g2);
+            if (!done) {
+                const float f = g2 - 1.0f;
+                if (fabsf(f) <= kEntmaxTol || g1 <= 0.f) {
+                    done = true;
+                } else {
+                    const float nd = sqrtf(g2);
+                    tau = fminf(fmaxf(tau + (nd - 1.0f) * nd / g1, -1.0f), 0.f);
+                    done = !confirm && fabsf(f) <= kEntmaxEarly;   // this step is the last one
+                }
+            }
+        }
+
+        // ---- last sweep: probabilities and output
+#pragma unroll
+        for (int db = 0; db < DBLK; ++db)
+#pragma unroll
+            for (int i = 0; i < 16; ++i) oacc[db][i] = 0.f;
+        psum = 0.f;
+        sweep(true, [&](uint64_t, f32x16* sacc) {
 #pragma unroll
             for (int kb = 0; kb < 2; ++kb)
 #pragma unroll
                 for (int i = 0; i < 16; ++i) {
-                    const float d = fmaxf(fmaf(sacc[kb][i], c, -mc) - tau, 0.f);   // -inf -> 0
-                    g1 += d;
-                    g2 = fmaf(d, d, g2);
+                    const float d = fmaxf(fmaf(sacc[kb][i], c, -mc) - tau, 0.f);
+                    const float p = d * d;
+                    sacc[kb][i] = p;
+                    psum += p;
                 }
+            tr_mm_64<D>(lds + STAGE, sacc, oacc, tr);
         });
-        g1 = both_halves_sum(g1);
-        g2 = both_halves_sum(g2);
-        if (!done) {
-            const float f = g2 - 1.0f;
-            if (fabsf(f) <= kEntmaxTol || g1 <= 0.f) {
-                done = true;
-            } else {
-                const float nd = sqrtf(g2);
-                tau = fminf(fmaxf(tau + (nd - 1.0f) * nd / g1, -1.0f), 0.f);
-                done = fabsf(f) <= kEntmaxEarly;             // this step is the last one
-            }
-        }
+        psum = both_halves_sum(psum);
+        // Also: all wavefronts are done with the tiles.  The second time is the last one, whatever is left.
+        done = confirm || !(psum - 1.0f > kEntmaxLeft);
+        if (__syncthreads_or(done ? 0 : 1) == 0) break;
     }
-
-    // ---- last sweep: probabilities and output
-    float psum = 0.f;
-    sweep(true, [&](uint64_t, f32x16* sacc) {
-#pragma unroll
-        for (int kb = 0; kb < 2; ++kb)
-#pragma unroll
-            for (int i = 0; i < 16; ++i) {
-                const float d = fmaxf(fmaf(sacc[kb][i], c, -mc) - tau, 0.f);
-                const float p = d * d;
-                sacc[kb][i] = p;
-                psum += p;
-            }
-        tr_mm_64<D>(lds + STAGE, sacc, oacc, tr);
-    });
-    psum = both_halves_sum(psum);
     const float inv = (!empty && psum > 0.f) ? 1.0f / psum : 0.f;
 
-    __syncthreads();                                         // all wavefronts are done with the tiles
     store_rows_bf16<D>(smem + wave * 32 * D, oacc, inv, lane, Op + (size_t)(qb * 64 + wave * 32) * a.so[2],
                        a.so[2], a.Lq - (qb * 64 + wave * 32));
     if (tau_out && row_ok && hh == 0)

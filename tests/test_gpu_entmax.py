@@ -1,8 +1,8 @@
 """GPU parity of masked attention with the 1.5-entmax normaliser (Section 6) against the fp64
 oracle: O within the forward tolerance (bf16 inputs and output, P rounded to bf16 before the
 second product), tau within 1e-3, and the residual |sum p - 1| at the returned tau within the
-bound the header states (1e-4: Newton's iteration stops a row at a residual <= 1e-5, or one
-quadratically converging step after a residual <= 1e-2; scores are formed in fp32)."""
+bound the header states (1e-4: Newton's iteration stops a row at a residual <= 1e-5, or one step
+after a residual <= 1e-2 if that step leaves no more than 1e-4; scores are formed in fp32)."""
 import numpy as np
 import pytest
 import torch
@@ -229,3 +229,10 @@ def test_entmax_tau_never_passes_the_root(names):
     """tau rises to the root and never passes it: sum p >= 1 up to the residual 1e-5 at which a row stops (and as much
     again for the 32-bit sums over some thousand keys)."""
     assert clustered_attained_sums(names).min() >= 1.0 - 2e-5
+
+
+@pytest.mark.parametrize("names", [("two clusters",), ("three clusters",), ("three clusters", "two clusters")])
+def test_entmax_residual_where_scores_leave_the_support_under_the_last_step(names):
+    """The bound of the header, |sum p - 1| <= 1e-4, on rows whose unconfirmed last step leaves 1.0e-3 and 2.4e-3."""
+    total = clustered_attained_sums(names)
+    assert np.abs(total - 1.0).max() <= 1e-4, total

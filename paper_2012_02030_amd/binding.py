@@ -213,12 +213,44 @@ def _stream_ptr(stream: Optional[torch.cuda.Stream]) -> int:
     return int(s.cuda_stream)
 
 
+def _current_handle() -> int:
+    return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+
+
+def _as_stream(stream) -> torch.cuda.Stream:
+    return stream if isinstance(stream, torch.cuda.Stream) else torch.cuda.ExternalStream(int(stream.cuda_stream))
+
+
+def _under(stream, call, *args):
+    """call(*args) with `stream` as torch's current stream.  Outputs, scratch memory and copies of inputs then belong
+    to the stream that the kernels run on: the caching allocator gives memory back in the order of the stream that it
+    was taken on, so scratch taken on another one could be handed out again under the running kernels.  What the call
+    returns is recorded on the caller's stream, which goes on to use it."""
+    if int(stream.cuda_stream) == _current_handle():
+        return call(*args)
+    before = torch.cuda.current_stream()
+    with torch.cuda.stream(_as_stream(stream)):
+        res = call(*args)
+    given = [a for a in args if isinstance(a, torch.Tensor)]
+    todo = [res]
+    while todo:
+        x = todo.pop()
+        if isinstance(x, torch.Tensor):
+            if x.is_cuda and not any(x is a for a in given):
+                x.record_stream(before)
+        elif isinstance(x, tuple):
+            todo.extend(x)
+    return res
+
+
 def ap_build_layout(mask: torch.Tensor, block_m: int = 64, block_n: int = 64,
                     cap: Optional[int] = None, stream: Optional[torch.cuda.Stream] = None,
                     count_only: bool = False, crop: Optional[tuple] = None) -> Layout:
     """mask: uint8/bool device tensor [H, Lq, Lk], nonzero = kept.  Asynchronous on the stream.
 
     crop = (Lq', Lk') builds the layout of the mask's top-left corner (ap_build_layout_cropped)."""
+    if stream is not None:
+        return _under(stream, ap_build_layout, mask, block_m, block_n, cap, None, count_only, crop)
     if mask.dtype == torch.bool:
         mask = mask.view(torch.uint8)
     if mask.dtype != torch.uint8 or mask.dim() != 3 or not mask.is_cuda:
@@ -268,6 +300,8 @@ def ap_build_layout_from_map(abar: torch.Tensor, tau: torch.Tensor, causal: bool
 
     abar: float32 device tensor [H, Lq, Lk]; tau: float32 device tensor with one element (e.g. the
     second result of ap_prune_mask).  Asynchronous on the stream."""
+    if stream is not None:
+        return _under(stream, ap_build_layout_from_map, abar, tau, causal, block_m, block_n, cap, None)
     if abar.dtype != torch.float32 or abar.dim() != 3 or not abar.is_cuda:
         raise ValueError("abar must be a float32 device tensor [H, Lq, Lk]")
     if tau.dtype != torch.float32 or tau.numel() != 1 or tau.device != abar.device:
@@ -313,6 +347,8 @@ class Schedule(NamedTuple):
 def ap_build_schedule(layout: Layout, causal: bool = False, min_cols: int = 0,
                       stream: Optional[torch.cuda.Stream] = None) -> Schedule:
     """Derive the visit schedule of a layout (block_n = 64).  Asynchronous on the stream."""
+    if stream is not None:
+        return _under(stream, ap_build_schedule, layout, causal, min_cols, None)
     dev = layout.row_ptr.device
     cap = int(layout.col_idx.shape[0])
     nrows = int(layout.row_ptr.shape[0]) - 1
@@ -364,10 +400,13 @@ def ap_sparse_attn_fwd(Q: torch.Tensor, K: torch.Tensor, V: torch.Tensor, layout
     under the top-left corner of that mask (ap_sparse_attn_fwd_cropped).
     Returns (O, lse); lse is None when return_lse is False.  Asynchronous on the stream.
     """
+    if stream is not None:
+        return _under(stream, ap_sparse_attn_fwd, Q, K, V, layout, causal, softmax_scale, out, lse, return_lse, None,
+                      sched, crop)
     if _lib is None:
         lib()
     if out is None and lse is None:
-        res = _calls.fwd(Q, K, V, layout, causal, softmax_scale, return_lse, stream, sched, crop)
+        res = _calls.fwd(Q, K, V, layout, causal, softmax_scale, return_lse, None, sched, crop)
         if _done(res, "ap_sparse_attn_fwd"):
             return res
     if Q.dtype == torch.bfloat16:
@@ -423,10 +462,13 @@ def ap_sparse_attn_decode(Q: torch.Tensor, K: torch.Tensor, V: torch.Tensor, lay
                           stream: Optional[torch.cuda.Stream] = None, splits: int = 1):
     """ap_sparse_attn_fwd for one or a few queries against many keys (bf16), `splits` workgroups
     per query.  Returns (O, lse)."""
+    if stream is not None:
+        return _under(stream, ap_sparse_attn_decode, Q, K, V, layout, causal, softmax_scale, out, return_lse, None,
+                      splits)
     if _lib is None:
         lib()
     if out is None:
-        res = _calls.split(Q, K, V, layout, splits, causal, softmax_scale, return_lse, stream, None, True)
+        res = _calls.split(Q, K, V, layout, splits, causal, softmax_scale, return_lse, None, None, True)
         if _done(res, "ap_sparse_attn_decode"):
             return res
     if Q.dtype != torch.bfloat16 or K.dtype != Q.dtype or V.dtype != Q.dtype:
@@ -465,10 +507,13 @@ def ap_sparse_attn_entmax15_fwd(Q: torch.Tensor, K: torch.Tensor, V: torch.Tenso
                                 stream: Optional[torch.cuda.Stream] = None,
                                 sched: Optional[Schedule] = None):
     """Masked attention with the 1.5-entmax normaliser (bf16, block_m 64).  Returns (O, tau)."""
+    if stream is not None:
+        return _under(stream, ap_sparse_attn_entmax15_fwd, Q, K, V, layout, causal, softmax_scale, out, return_tau,
+                      None, sched)
     if _lib is None:
         lib()
     if out is None:
-        res = _calls.entmax_fwd(Q, K, V, layout, causal, softmax_scale, return_tau, stream, sched)
+        res = _calls.entmax_fwd(Q, K, V, layout, causal, softmax_scale, return_tau, None, sched)
         if _done(res, "ap_sparse_attn_entmax15_fwd"):
             return res
     if sched is not None and sched.causal != bool(causal):
@@ -510,10 +555,13 @@ def ap_sparse_attn_fwd_split(Q: torch.Tensor, K: torch.Tensor, V: torch.Tensor, 
                              sched: Optional[Schedule] = None):
     """ap_sparse_attn_fwd with the entries of every block row cut into `splits` chunks (bf16,
     block_m 64): for few queries against many keys.  Returns (O, lse).  Asynchronous."""
+    if stream is not None:
+        return _under(stream, ap_sparse_attn_fwd_split, Q, K, V, layout, splits, causal, softmax_scale, out,
+                      return_lse, None, sched)
     if _lib is None:
         lib()
     if out is None:
-        res = _calls.split(Q, K, V, layout, splits, causal, softmax_scale, return_lse, stream, sched, False)
+        res = _calls.split(Q, K, V, layout, splits, causal, softmax_scale, return_lse, None, sched, False)
         if _done(res, "ap_sparse_attn_fwd_split"):
             return res
     if Q.dtype != torch.bfloat16 or K.dtype != Q.dtype or V.dtype != Q.dtype:
@@ -593,6 +641,8 @@ class LayoutT(NamedTuple):
 
 def ap_build_layout_transpose(layout: Layout, stream: Optional[torch.cuda.Stream] = None) -> LayoutT:
     """Asynchronous on the stream; the layout must not be truncated."""
+    if stream is not None:
+        return _under(stream, ap_build_layout_transpose, layout, None)
     dev = layout.row_ptr.device
     cap = int(layout.col_idx.shape[0])
     nkb = -(-layout.Lk // layout.block_n)
@@ -615,6 +665,8 @@ def ap_bwd_workspace_bytes(B: int, H: int, Lq: int) -> int:
 def ap_build_col_schedule(layout: Layout, layout_t: LayoutT, causal: bool = False, min_rows: int = 0,
                           stream: Optional[torch.cuda.Stream] = None) -> Schedule:
     """Derive the column schedule (for dK, dV) from a layout and its transpose.  Asynchronous."""
+    if stream is not None:
+        return _under(stream, ap_build_col_schedule, layout, layout_t, causal, min_rows, None)
     dev = layout.row_ptr.device
     cap = int(layout.col_idx.shape[0])
     ncols = int(layout_t.col_ptr.shape[0]) - 1
@@ -642,10 +694,13 @@ def ap_sparse_attn_bwd(Q: torch.Tensor, K: torch.Tensor, V: torch.Tensor, O: tor
 
     O and lse are the forward call's outputs; dO must have O's strides.  With a row schedule
     and/or a column schedule the call goes to ap_sparse_attn_bwd_sched.  Asynchronous on the stream."""
+    if stream is not None:
+        return _under(stream, ap_sparse_attn_bwd, Q, K, V, O, dO, lse, layout, layout_t, causal, softmax_scale, None,
+                      sched, col_sched)
     if _lib is None:
         lib()
     if O is not None:
-        res = _calls.bwd(Q, K, V, O, dO, lse, layout, layout_t, causal, softmax_scale, stream, sched, col_sched)
+        res = _calls.bwd(Q, K, V, O, dO, lse, layout, layout_t, causal, softmax_scale, None, sched, col_sched)
         if _done(res, "ap_sparse_attn_bwd"):
             return res
     for sc in (sched, col_sched):
@@ -702,9 +757,12 @@ def ap_sparse_attn_entmax15_bwd(Q: torch.Tensor, K: torch.Tensor, V: torch.Tenso
     """Gradients (dQ, dK, dV) of ap_sparse_attn_entmax15_fwd's O with respect to Q, K, V (bf16).
 
     tau is the forward call's second output; both schedules are required.  Asynchronous on the stream."""
+    if stream is not None:
+        return _under(stream, ap_sparse_attn_entmax15_bwd, Q, K, V, dO, tau, layout, layout_t, sched, col_sched,
+                      causal, softmax_scale, None)
     if _lib is None:
         lib()
-    res = _calls.bwd(Q, K, V, None, dO, tau, layout, layout_t, causal, softmax_scale, stream, sched, col_sched)
+    res = _calls.bwd(Q, K, V, None, dO, tau, layout, layout_t, causal, softmax_scale, None, sched, col_sched)
     if _done(res, "ap_sparse_attn_entmax15_bwd"):
         return res
     for t in (Q, K, V, dO):
@@ -753,6 +811,8 @@ def ap_accumulate_attention_maps(Q: torch.Tensor, K: torch.Tensor,
     none is given.  Q [B,H,Lq,D], K [B,H,Lk,D] bf16 device tensors.  lse: the log-sum-exp
     [B,H,Lq] of the unpruned attention call on the same inputs, if it is at hand
     (ap_accumulate_attention_maps_lse).  Asynchronous on the stream."""
+    if stream is not None:
+        return _under(stream, ap_accumulate_attention_maps, Q, K, abar, causal, softmax_scale, weight, None, lse)
     if Q.dtype != torch.bfloat16 or K.dtype != torch.bfloat16:
         raise ValueError("Q and K must be bfloat16")
     if Q.dim() != 4 or K.dim() != 4:
@@ -798,6 +858,8 @@ def ap_prune_mask(abar: torch.Tensor, prune_fraction: float, causal: bool = Fals
 
     Returns (mask uint8 [H,Lq,Lk] with 1 = kept, tau float32 [1] on device); with threshold_only the
     mask is not written and None is returned in its place.  Asynchronous."""
+    if stream is not None:
+        return _under(stream, ap_prune_mask, abar, prune_fraction, causal, None, threshold_only)
     if abar.dtype != torch.float32 or abar.dim() != 3 or not abar.is_cuda:
         raise ValueError("abar must be a float32 device tensor [H, Lq, Lk]")
     abar = abar.contiguous()

@@ -129,7 +129,8 @@ bool read_transposed(PyObject* o, Transposed* x)
     return true;
 }
 
-// causal, softmax_scale and stream as the binding's arguments have them
+// causal and softmax_scale as the binding's arguments have them, and torch's current stream.  A stream of the
+// caller's own is not taken: outputs and scratch memory are allocated here, and those belong to the current stream.
 struct Common {
     bool causal;
     float scale;
@@ -139,16 +140,11 @@ bool read_common(PyObject* causal, PyObject* scale, PyObject* stream, Common* c)
 {
     if (causal != Py_True && causal != Py_False) return false;
     c->causal = causal == Py_True;
-    if (!PyFloat_CheckExact(scale)) return false;
+    if (!PyFloat_CheckExact(scale) || stream != Py_None) return false;
     c->scale = (float)PyFloat_AS_DOUBLE(scale);
-    PyObject* s;
-    if (stream == Py_None) {
-        PyObject* d = PyObject_CallNoArgs(get_device);
-        s = d ? PyObject_CallOneArg(get_stream, d) : nullptr;
-        Py_XDECREF(d);
-    } else {
-        s = PyObject_GetAttrString(stream, "cuda_stream");
-    }
+    PyObject* d = PyObject_CallNoArgs(get_device);
+    PyObject* s = d ? PyObject_CallOneArg(get_stream, d) : nullptr;
+    Py_XDECREF(d);
     if (s && PyLong_Check(s)) c->stream = PyLong_AsVoidPtr(s);
     Py_XDECREF(s);
     if (!s || PyErr_Occurred()) {                            // the general path meets it again and reports it

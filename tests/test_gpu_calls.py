@@ -151,3 +151,31 @@ def test_transforms_and_modes_keep_to_the_general_path():
         assert ap._calls.fwd(q, K, V, lay, False, 0.0, True, None, None, False) is None
         return q.float().sum()
     torch.func.grad(under_grad)(Q)
+
+
+def test_a_side_stream_keeps_its_scratch_memory():
+    """Split and backward pass on a side stream that is still busy, while the current stream goes on allocating and
+    filling blocks of every size that the calls use: same results, and ready for use after one wait."""
+    B, H, Lq, Lk, D = 2, 4, 128, 256, 64
+    Q, K, V = _qkv(B, H, Lq, Lk, D, torch.bfloat16, False, 1)
+    lay, sched, lt, col = _plan(H, Lq, Lk, True, 2)
+    dO = torch.randn(B, H, Lq, D, generator=torch.Generator().manual_seed(3)).to(torch.bfloat16).cuda()
+    want = ap.ap_sparse_attn_fwd_split(Q, K, V, lay, 4, causal=True, sched=sched)
+    want = want + ap.ap_sparse_attn_bwd(Q, K, V, *want[:1], dO, want[1], lay, lt, causal=True, sched=sched,
+                                        col_sched=col)
+    side = torch.cuda.Stream()
+    side.wait_stream(torch.cuda.current_stream())
+    with torch.cuda.stream(side):
+        busy = torch.randn(2048, 2048, device="cuda")
+        for _ in range(20):
+            busy = busy @ busy * 0.01
+    got = ap.ap_sparse_attn_fwd_split(Q, K, V, lay, 4, causal=True, sched=sched, stream=side)
+    got = got + ap.ap_sparse_attn_bwd(Q, K, V, *got[:1], dO, got[1], lay, lt, causal=True, sched=sched,
+                                      col_sched=col, stream=side)
+    sizes = {4 * B * H * Lq * (D + 1) * 4, B * H * Lq * 4, B * H * Lq * D * 2, B * H * Lk * D * 2}
+    filled = [torch.full((n,), 255, dtype=torch.uint8, device="cuda") for n in sorted(sizes) for _ in range(4)]
+    torch.cuda.current_stream().wait_stream(side)
+    torch.cuda.synchronize()
+    for x, y in zip(got, want):
+        assert torch.equal(x, y)
+    assert all(bool((f == 255).all()) for f in filled)

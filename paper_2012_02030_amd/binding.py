@@ -10,6 +10,7 @@ from __future__ import annotations
 
 import ctypes
 import os
+import warnings
 from typing import NamedTuple, Optional
 
 import torch
@@ -50,6 +51,11 @@ _CALLS_API = ("ap_sparse_attn_fwd", "ap_sparse_attn_fwd_cropped", "ap_fwd_split_
               "ap_sparse_attn_fwd_split", "ap_sparse_attn_decode", "ap_sparse_attn_entmax15_fwd",
               "ap_bwd_workspace_bytes", "ap_sparse_attn_bwd", "ap_sparse_attn_bwd_sched",
               "ap_entmax15_bwd_workspace_bytes", "ap_sparse_attn_entmax15_bwd")
+
+
+class _NoCalls:
+    """In place of the native call path: leaves every call to the general path."""
+    fwd = split = entmax_fwd = bwd = staticmethod(lambda *args: None)
 
 
 class ApError(RuntimeError):
@@ -165,11 +171,12 @@ def lib() -> ctypes.CDLL:
                                     ctypes.c_size_t, vp]
         try:
             from . import ap_calls
+            ap_calls.bind(*(ctypes.cast(getattr(L, name), vp).value for name in _CALLS_API),
+                          torch._C._cuda_getDevice, torch._C._cuda_getCurrentRawStream)
         except ImportError as e:
-            raise RuntimeError("the native call path is missing: build it with "
-                               "`python -m paper_2012_02030_amd.build` (%s)" % e) from e
-        ap_calls.bind(*(ctypes.cast(getattr(L, name), vp).value for name in _CALLS_API),
-                      torch._C._cuda_getDevice, torch._C._cuda_getCurrentRawStream)
+            warnings.warn("the native call path is missing, every attention call takes the general path (about 10 us "
+                          "more of host time); `python -m paper_2012_02030_amd.build` builds it (%s)" % e)
+            ap_calls = _NoCalls
         _calls, _lib = ap_calls, L
     return _lib
 

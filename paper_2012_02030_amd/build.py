@@ -3,6 +3,7 @@ from __future__ import annotations
 
 import glob
 import os
+import shutil
 import subprocess
 import sys
 import sysconfig
@@ -85,12 +86,24 @@ def build(verbose: bool = False, extra=()) -> str:
     return LIB
 
 
-def build_calls(verbose: bool = False) -> str:
-    """Compile the CPython module that takes the attention calls from torch tensors to the library."""
+def build_calls(verbose: bool = False):
+    """Compile the CPython module that takes the attention calls from torch tensors to the library.
+
+    It saves host time and nothing else needs it, so where there is no host compiler or no headers the library stands
+    without it (and without an old one, which may be of another C ABI); returns None then."""
     import torch
     tdir = os.path.dirname(os.path.abspath(torch.__file__))
+    cxx = os.environ.get("CXX", "g++")
+    needs = [os.path.join(sysconfig.get_paths()["include"], "Python.h"),
+             os.path.join(tdir, "include", "torch", "csrc", "autograd", "python_variable.h")]
+    missing = [n for n in needs if not os.path.exists(n)] + ([] if shutil.which(cxx) else [cxx])
+    if missing:
+        print("WARNING: the native call path is not built, missing: " + ", ".join(missing), flush=True)
+        if os.path.exists(CALLS):
+            os.remove(CALLS)
+        return None
     tmp = CALLS + ".tmp.%d" % os.getpid()
-    cmd = [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall",
+    cmd = [cxx, "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall",
            "-D_GLIBCXX_USE_CXX11_ABI=%d" % int(torch._C._GLIBCXX_USE_CXX11_ABI),
            "-I", os.path.join(ROOT, "include"), "-isystem", sysconfig.get_paths()["include"],
            "-isystem", os.path.join(tdir, "include"),

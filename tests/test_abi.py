@@ -490,6 +490,41 @@ def test_missing_library_fails_loudly(monkeypatch):
         ap.lib()
 
 
+def test_library_works_without_the_native_call_path(monkeypatch):
+    """Only the host time of the attention calls depends on the module ap_calls: without it the library loads, says so,
+    and every call takes the general path."""
+    import sys
+
+    import torch
+
+    import paper_2012_02030_amd as package
+    monkeypatch.setattr(ap, "_lib", None)
+    monkeypatch.setattr(ap, "_calls", None)
+    monkeypatch.setitem(sys.modules, package.__name__ + ".ap_calls", None)
+    monkeypatch.delattr(package, "ap_calls", raising=False)
+    with pytest.warns(UserWarning, match="native call path is missing"):
+        ap.lib()
+    assert ap.ap_layout_max_tiles(2, 128, 128, 64, 64) == 8
+    with pytest.raises(ValueError, match="float32 or bfloat16"):     # the general path's own message
+        q = torch.zeros(1, 1, 64, 64, dtype=torch.float64)
+        ap.ap_sparse_attn_fwd(q, q, q, None)
+
+
+@pytest.mark.parametrize("what", ["compiler", "headers"])
+def test_build_without_what_the_native_call_path_needs(monkeypatch, tmp_path, capsys, what):
+    from paper_2012_02030_amd import build as b
+
+    old = tmp_path / "ap_calls.so"
+    old.write_bytes(b"old")
+    monkeypatch.setattr(b, "CALLS", str(old))
+    if what == "compiler":
+        monkeypatch.setenv("CXX", "no-such-compiler")
+    else:
+        monkeypatch.setattr(b.sysconfig, "get_paths", lambda: {"include": "/nonexistent"})
+    assert b.build_calls() is None
+    assert "not built" in capsys.readouterr().out and not old.exists()
+
+
 def test_build_reports_kernel_resources_and_no_spills():
     """The build parses the compiler's per-kernel resource remarks and records them; no kernel of
     the built library may spill vector registers (a reload inside a tile loop waits for the tile

@@ -9,7 +9,7 @@
 //              windows of a block row; every mask row of the strip is one contiguous read of
 //              1024 entries (16 per lane), packed to bits in registers, assembled into row words,
 //              staged in LDS and written to a dense scratch array as whole windows, one non-empty
-//              flag per window and their number per strip.  mask_strip reads the byte mask, map_strip
+//              flag per window (the first one carries their number as well).  mask_strip reads the byte mask, map_strip
 //              (Eq. (2) evaluated on the fly) the fp32 mean map with the layer's threshold: kept iff
 //              not (value < tau), and visible if the attention is causal
 //   tile_scan  any other window shape: one wavefront per window; row_count counts its flags
@@ -94,16 +94,15 @@ __device__ __forceinline__ uint32_t keep_bits16(const u32x4_a1& v)
     return (lo | (hi << 8)) >> 7;
 }
 
-// What a strip's wavefront hands on, given the OR of all row words of each lane's window: the flags, and
-// how many windows of the strip hold something.
-__device__ __forceinline__ void strip_flags(bool any, long long row, int strip, int strips, int nKB, int lane,
-                                            uint8_t* flags, int32_t* counts)
+// What a strip's wavefront hands on, given the OR of all row words of each lane's window: a flag per window
+// (bit 0), and in the flag byte of the strip's first window (bits 1..5) how many of its windows hold
+// something.  An array of their own for these numbers would make the workspace larger than callers were told.
+__device__ __forceinline__ void strip_flags(bool any, long long row, int strip, int nKB, int lane, uint8_t* flags)
 {
     const int kb = strip * 16 + (lane >> 2);
     const bool mine = (lane & 3) == 0 && kb < nKB;
-    if (mine) flags[row * nKB + kb] = any ? 1 : 0;
     const int n = __popcll(__ballot(mine && any));
-    if (lane == 0) counts[row * strips + strip] = n;
+    if (mine) flags[row * nKB + kb] = (uint8_t)((any ? 1 : 0) | (lane == 0 ? n << 1 : 0));
 }
 
 // The byte mask.  Same division of the work as map_strip_kernel below, with what is particular to bytes: a
@@ -115,8 +114,7 @@ __device__ __forceinline__ void strip_flags(bool any, long long row, int strip, 
 // with integer multiplies, 64-bit shuffles through LDS and bounds per row took 76 us.
 __global__ __launch_bounds__(256) void mask_strip_kernel(
     const uint8_t* __restrict__ mask, long long stride_h, long long stride_row, int Lq, int Lk, int BM, int nQB,
-    int nKB, long long n_units, uint8_t* __restrict__ flags, int32_t* __restrict__ counts,
-    uint64_t* __restrict__ dense /* may be null */)
+    int nKB, long long n_units, uint8_t* __restrict__ flags, uint64_t* __restrict__ dense /* may be null */)
 {
     extern __shared__ uint64_t stage_all[];                  // [4 wavefronts][16 windows][BM rows, row ^ window]
     const int lane = threadIdx.x & 63;
@@ -172,7 +170,7 @@ __global__ __launch_bounds__(256) void mask_strip_kernel(
         for (int u = 0; u < RB; ++u) cur[u] = nxt[u];
     }
     any |= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)any, 0x4E, 0xf, 0xf, false);   // lane ^ 2
-    strip_flags(any != 0, row, strip, strips, nKB, lane, flags, counts);
+    strip_flags(any != 0, row, strip, nKB, lane, flags);
     if (dense) {
         // same wavefront reads back what it wrote: LDS ordering only
         asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
@@ -209,7 +207,7 @@ __device__ __forceinline__ uint32_t keep_bits16_map(const float* p, int n_valid,
 __global__ __launch_bounds__(256) void map_strip_kernel(
     const float* __restrict__ src, const float* __restrict__ tau_ptr, long long stride_h, long long stride_row,
     int H, int Lq, int Lk, int BM, int nQB, int nKB, long long causal_off, int vec_ok,
-    uint8_t* __restrict__ flags, int32_t* __restrict__ counts, uint64_t* __restrict__ dense /* may be null */)
+    uint8_t* __restrict__ flags, uint64_t* __restrict__ dense /* may be null */)
 {
     extern __shared__ uint64_t stage_all[];                  // [4 wavefronts][16 windows][BM rows]
     const int lane = threadIdx.x & 63;
@@ -260,7 +258,7 @@ __global__ __launch_bounds__(256) void map_strip_kernel(
             if (dense && quarter == 0) stage[win * BM + r0 + u] = word;
         }
     }
-    strip_flags(any != 0, (long long)h * nQB + qb, strip, strips, nKB, lane, flags, counts);
+    strip_flags(any != 0, (long long)h * nQB + qb, strip, nKB, lane, flags);
     if (dense) {
         // same wavefront reads back what it wrote: LDS ordering only
         asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
@@ -285,19 +283,27 @@ __global__ __launch_bounds__(256) void row_count_kernel(
     if (lane == 0) counts[r] = cnt;
 }
 
-// Exclusive prefix sum over the n_rows row counts, each the sum of `parts` numbers, by one workgroup
-// of 1024 threads.
+// Exclusive prefix sum over the row counts by one workgroup of 1024 threads.  STRIPS: a row's count is the sum of
+// the numbers in the flag bytes of its strips' first windows; otherwise it is in `counts`.
+template <bool STRIPS>
 __global__ __launch_bounds__(1024) void row_scan_kernel(
-    const int32_t* __restrict__ counts, int n_rows, int parts, int32_t* __restrict__ row_ptr,
-    int64_t* __restrict__ nnz_out)
+    const int32_t* __restrict__ counts, const uint8_t* __restrict__ flags, int n_rows, int nKB,
+    int32_t* __restrict__ row_ptr, int64_t* __restrict__ nnz_out)
 {
+    const auto count = [&](int i) -> int {
+        if (!STRIPS) return counts[i];
+        int n = 0;
+#pragma unroll 4
+        for (int kb = 0; kb < nKB; kb += 16) n += flags[(long long)i * nKB + kb] >> 1;
+        return n;
+    };
     __shared__ long long wave_sum[16];
     const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
     const int per = (n_rows + 1023) / 1024;
     const int lo = min(n_rows, t * per);
     const int hi = min(lo + per, n_rows);
     long long s = 0;
-    for (long long i = (long long)lo * parts; i < (long long)hi * parts; ++i) s += counts[i];
+    for (int i = lo; i < hi; ++i) s += count(i);
     long long incl = s;
 #pragma unroll
     for (int off = 1; off < 64; off <<= 1) {
@@ -308,13 +314,13 @@ __global__ __launch_bounds__(1024) void row_scan_kernel(
     __syncthreads();
     long long run = incl - s;                          // exclusive prefix of this thread's rows
     for (int w = 0; w < wave; ++w) run += wave_sum[w];
+    if (t == 1023) {
+        row_ptr[n_rows] = (int32_t)(run + s);
+        if (nnz_out) *nnz_out = run + s;
+    }
     for (int i = lo; i < hi; ++i) {
         row_ptr[i] = (int32_t)run;
-        for (int k = 0; k < parts; ++k) run += counts[(long long)i * parts + k];
-    }
-    if (t == 1023) {
-        row_ptr[n_rows] = (int32_t)run;
-        if (nnz_out) *nnz_out = run;
+        if (i + 1 < hi) run += count(i);
     }
 }
 
@@ -332,7 +338,7 @@ __global__ __launch_bounds__(256) void compact_kernel(
     long long base = row_ptr[r];
     for (int k0 = 0; k0 < nKB; k0 += 64) {
         const int kb = k0 + lane;
-        const bool f = kb < nKB && flags[(size_t)r * nKB + kb] != 0;   // the same in every wavefront
+        const bool f = kb < nKB && (flags[(size_t)r * nKB + kb] & 1) != 0;   // the same in every wavefront
         const unsigned long long bal = __ballot(f);
         const int rank = __popcll(bal & ((1ull << lane) - 1ull));
         __syncthreads();                                     // the previous list is no longer read
@@ -366,9 +372,6 @@ __global__ __launch_bounds__(256) void compact_kernel(
 
 static inline size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
 
-// numbers that make up the count of a block row: one per strip of 16 windows, or one
-static inline size_t count_parts(size_t nKB, int BN) { return BN == 64 ? (nKB + 15) / 16 : 1; }
-
 bool layout_shape_ok(int H, int Lq, int Lk, int BM, int BN)
 {
     if (H <= 0 || Lq <= 0 || Lk <= 0) return false;
@@ -385,7 +388,7 @@ void layout_workspace_plan(int H, int Lq, int Lk, int BM, int BN, size_t* flags_
     const size_t n_rows = (size_t)H * nQB, n_tiles = n_rows * nKB;
     size_t off = 0;
     *flags_off = off;  off = align_up(off + n_tiles, 16);
-    *counts_off = off; off = align_up(off + n_rows * count_parts(nKB, BN) * sizeof(int32_t), 16);
+    *counts_off = off; off = align_up(off + n_rows * sizeof(int32_t), 16);
     *dense_off = off;  off = align_up(off + n_tiles * BM * W * sizeof(uint64_t), 16);
     *total = off;
 }
@@ -411,28 +414,28 @@ static hipError_t launch_build_layout_any(const SRC* src, const float* tau, long
     const int waves_per_block = 4;
     const unsigned row_blocks = (unsigned)((n_rows + waves_per_block - 1) / waves_per_block);
 
-    const int parts = (int)count_parts(nKB, BN);
     if (BN == 64) {                                          // block_m is a multiple of 16
-        const long long units = (long long)n_rows * parts;
+        const long long units = (long long)n_rows * ((nKB + 15) / 16);
         const dim3 grid((unsigned)((units + 3) / 4));
         if constexpr (sizeof(SRC) == 1)
             hipLaunchKernelGGL(mask_strip_kernel, grid, dim3(256), (size_t)4 * 16 * BM * sizeof(uint64_t), stream,
-                               src, stride_h, stride_row, Lq, Lk, BM, nQB, nKB, units, flags, counts, dense);
+                               src, stride_h, stride_row, Lq, Lk, BM, nQB, nKB, units, flags, dense);
         else
             hipLaunchKernelGGL(map_strip_kernel, grid, dim3(256), (size_t)4 * 16 * BM * sizeof(uint64_t), stream, src,
-                               tau, stride_h, stride_row, H, Lq, Lk, BM, nQB, nKB, causal_off, vec_ok, flags, counts,
-                               dense);
+                               tau, stride_h, stride_row, H, Lq, Lk, BM, nQB, nKB, causal_off, vec_ok, flags, dense);
+        hipLaunchKernelGGL(row_scan_kernel<true>, dim3(1), dim3(1024), 0, stream, counts, flags, n_rows, nKB, row_ptr,
+                           nnz_out);
     } else if constexpr (sizeof(SRC) == 1) {
         const unsigned tile_blocks = (unsigned)((n_tiles + waves_per_block - 1) / waves_per_block);
         hipLaunchKernelGGL(tile_scan_kernel, dim3(tile_blocks), dim3(64 * waves_per_block), 0, stream,
                            src, stride_h, stride_row, H, Lq, Lk, BM, BN, nQB, nKB, vec_ok, flags, dense);
         hipLaunchKernelGGL(row_count_kernel, dim3(row_blocks), dim3(64 * waves_per_block), 0, stream,
                            flags, n_rows, nKB, counts);
+        hipLaunchKernelGGL(row_scan_kernel<false>, dim3(1), dim3(1024), 0, stream, counts, flags, n_rows, nKB, row_ptr,
+                           nnz_out);
     } else {
         return hipErrorInvalidValue;                         // the map source is scanned in 64-key windows only
     }
-    hipLaunchKernelGGL(row_scan_kernel, dim3(1), dim3(1024), 0, stream, counts, n_rows, parts, row_ptr,
-                       nnz_out);
     if (col_idx)
         hipLaunchKernelGGL(compact_kernel, dim3((unsigned)n_rows), dim3(256), 0, stream,
                            flags, dense, row_ptr, n_rows, nKB, BM * W, col_idx, bitmaps, cap);

@@ -52,6 +52,18 @@ def test_layout_sizes(L):
     assert ap.ap_layout_workspace_bytes(1, 64, 64, 48, 64) == 0
 
 
+@pytest.mark.parametrize("shape", [(16, 4096, 4096, 64, 64), (1, 1, 1, 64, 64), (3, 100, 5000, 128, 64),
+                                   (2, 70, 1030, 16, 64), (2, 100, 333, 32, 128), (1, 65, 64, 64, 16)])
+def test_layout_workspace_has_the_size_that_callers_were_always_told(L, shape):
+    """A flag per tile, a count per block row, the bitmaps of every tile, each 16-byte aligned: a program that keeps a
+    workspace from an earlier build of the library goes on running."""
+    H, Lq, Lk, bm, bn = shape
+    rows = H * (-(-Lq // bm))
+    tiles = rows * (-(-Lk // bn))
+    up = lambda n: -(-n // 16) * 16
+    assert ap.ap_layout_workspace_bytes(*shape) == up(tiles) + up(rows * 4) + up(tiles * bm * (-(-bn // 64)) * 8)
+
+
 def test_build_layout_rejects_bad_arguments(L):
     fake = 0x1000   # never dereferenced: validation fails first
     call = L.ap_build_layout

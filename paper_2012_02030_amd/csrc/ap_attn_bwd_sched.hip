@@ -151,7 +151,7 @@ __device__ __forceinline__ float or_minus_inf(float x, uint32_t keep)
 template <int D, int MODE>
 __global__ __launch_bounds__(256, 2) void bwd_dq_sched_kernel(
     const int32_t* __restrict__ p_row_ptr, const int32_t* __restrict__ p_cnt, const int32_t* __restrict__ p_start,
-    const int32_t* __restrict__ p_cols, const uint32_t* __restrict__ p_words, int nQB, int p_B, BwdArgs a)
+    const int32_t* __restrict__ p_cols, const uint32_t* __restrict__ p_words, int nQB, int p_B, int n_blocks, BwdArgs a)
 {
     constexpr int TILE = kBN * D;
     constexpr int KSTEPS = D / 16;
@@ -175,7 +175,9 @@ __global__ __launch_bounds__(256, 2) void bwd_dq_sched_kernel(
     int vzero = 0;
     asm volatile("" : "+v"(vzero));
 
-    const int bid = xcd_contiguous(blockIdx.x, gridDim.x);
+    const int blk = block_index();
+    if (blk >= n_blocks) return;
+    const int bid = xcd_contiguous(blk, n_blocks);
     const int qb = nQB - 1 - (bid % nQB);
     const int b = (bid / nQB) % p_B;                         // the examples of a head one after another: they share its schedule
     const int h = bid / (nQB * p_B);
@@ -421,14 +423,16 @@ __global__ __launch_bounds__(256, 2) void bwd_dkv_sched_kernel(
     // takes.  Every XCD gets a contiguous range of pairs (they share Q and dO rows in its L2); when
     // the pairs divide evenly over the 8 XCDs, the heavy columns of all pairs of the range come
     // first, so that the longest workgroups start at once, then the other columns pair by pair.
+    const int blk = block_index();
+    if (blk >= NP * nKB) return;
     const int32_t* order = p_cnt + (size_t)p_H * nKB;
     const int32_t* n_heavy = order + (size_t)p_H * nKB;
     int pair, idx;
     if (NP % 8 == 0 && NP / 8 <= 64) {
         // lane p looks at pair P0 + p: one load and two wave-wide prefix sums instead of a chain of
         // dependent scalar loads
-        const int PP = NP / 8, P0 = (blockIdx.x & 7) * PP;
-        const int l = blockIdx.x >> 3;
+        const int PP = NP / 8, P0 = (blk & 7) * PP;
+        const int l = blk >> 3;
         const int hv = lane < PP ? n_heavy[(P0 + lane) / p_B] : 0;
         const int lt = lane < PP ? nKB - hv : 0;
         int hv_incl = hv, lt_incl = lt;                      // inclusive prefix sums over the lanes
@@ -453,7 +457,7 @@ __global__ __launch_bounds__(256, 2) void bwd_dkv_sched_kernel(
         pair = __builtin_amdgcn_readfirstlane(pair);
         idx = __builtin_amdgcn_readfirstlane(idx);
     } else {
-        const int bid = xcd_contiguous(blockIdx.x, gridDim.x);
+        const int bid = xcd_contiguous(blk, NP * nKB);
         pair = bid / nKB;
         idx = bid % nKB;
     }
@@ -631,11 +635,11 @@ template <int D>
 hipError_t launch_d(const BwdArgs& a, bool dq, bool dkv, hipStream_t stream)
 {
     const int nQB = (a.Lq + 63) / 64, nKB = (a.Lk + 63) / 64, NP = a.B * a.H;
-    const dim3 qgrid((unsigned)(NP * nQB)), kgrid((unsigned)(NP * nKB)), block(256);
+    const dim3 qgrid = grid_of((long long)NP * nQB, 256), kgrid = grid_of((long long)NP * nKB, 256), block(256);
     const Schedule &rs = a.sched, &cs = a.csched;
     auto run_dq = [&](auto kernel) {
         hipLaunchKernelGGL(kernel, qgrid, block, 0, stream, a.row_ptr, rs.cnt, rs.start, rs.cols,
-                           (const uint32_t*)rs.bitmaps, nQB, a.B, a);
+                           (const uint32_t*)rs.bitmaps, nQB, a.B, NP * nQB, a);
         return hipGetLastError();
     };
     auto run_dkv = [&](auto kernel) {

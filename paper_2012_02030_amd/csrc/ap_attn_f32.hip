@@ -59,7 +59,7 @@ __device__ __forceinline__ uint32_t or_over_32(uint32_t v)
 template <int D, typename Off>
 __global__ __launch_bounds__(64 * kNW, sizeof(Off) == 8 ? 2 : (D == 128 ? 3 : 4)) void fwd_f32_kernel(
     const int32_t* __restrict__ p_row_ptr, const int32_t* __restrict__ p_col_idx,
-    const uint64_t* __restrict__ p_bitmaps, int nQG, int p_H, FwdArgs a)
+    const uint64_t* __restrict__ p_bitmaps, int nQG, int p_H, int n_blocks, FwdArgs a)
 {
     constexpr int DBLK = D / 32;
     constexpr int NJ = D / 8;                          // 16-byte pieces of a lane's half of a row
@@ -82,7 +82,9 @@ __global__ __launch_bounds__(64 * kNW, sizeof(Off) == 8 ? 2 : (D == 128 ? 3 : 4)
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int n = lane & 31, hh = lane >> 5;
 
-    const int bid = xcd_contiguous(blockIdx.x, gridDim.x);   // the query groups of a head share an L2
+    const int blk = block_index();
+    if (blk >= n_blocks) return;
+    const int bid = xcd_contiguous(blk, n_blocks);     // the query groups of a head share an L2
     const int qg = nQG - 1 - bid % nQG;                // long causal rows first
     const int h = (bid / nQG) % p_H;
     const int b = bid / (nQG * p_H);
@@ -347,13 +349,15 @@ template <int D>
 hipError_t launch_d(const FwdArgs& a, hipStream_t stream)
 {
     const int nQG = (a.Lq + 31) / 32;                  // two groups per block row of the layout
-    const dim3 grid((unsigned)((long long)nQG * a.H * a.B)), block(64 * kNW);
+    const long long blocks = (long long)nQG * a.H * a.B;
+    if (blocks > 2147483647LL) return hipErrorInvalidValue;
+    const dim3 grid = grid_of(blocks, 64 * kNW), block(64 * kNW);
     if ((long long)a.Lk * a.sk[2] < (1ll << 29) && (long long)a.Lk * a.sv[2] < (1ll << 29))   // 2 GB a slice
         hipLaunchKernelGGL((fwd_f32_kernel<D, uint32_t>), grid, block, 0, stream, a.row_ptr, a.col_idx, a.bitmaps,
-                           nQG, a.H, a);
+                           nQG, a.H, (int)blocks, a);
     else
         hipLaunchKernelGGL((fwd_f32_kernel<D, uint64_t>), grid, block, 0, stream, a.row_ptr, a.col_idx, a.bitmaps,
-                           nQG, a.H, a);
+                           nQG, a.H, (int)blocks, a);
     return hipGetLastError();
 }
 

@@ -31,10 +31,11 @@ constexpr int kPer = kSeg / kWaves;                          // tiles of one wav
 __global__ __launch_bounds__(64 * kWaves) void build_col_schedule_kernel(
     const int32_t* __restrict__ col_ptr, const int32_t* __restrict__ row_idx,
     const int32_t* __restrict__ tile_idx, const uint64_t* __restrict__ bitmaps, int nKB, int Lq, int Lk,
-    int causal, int min_rows, Schedule s)
+    int causal, int min_rows, int n_cols, Schedule s)
 {
     __shared__ unsigned long long s_rows[kSeg];              // query rows of every tile that hold something
-    const int c = blockIdx.x;
+    const int c = block_index();
+    if (c >= n_cols) return;
     const int kb = c % nKB;
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -163,8 +164,8 @@ hipError_t launch_build_col_schedule(const int32_t* col_ptr, const int32_t* row_
                                      int min_rows, const Schedule& s, hipStream_t stream)
 {
     const int nKB = (Lk + 63) / 64;
-    hipLaunchKernelGGL(build_col_schedule_kernel, dim3((unsigned)(H * nKB)), dim3(64 * kWaves), 0, stream, col_ptr,
-                       row_idx, tile_idx, bitmaps, nKB, Lq, Lk, causal, min_rows, s);
+    hipLaunchKernelGGL(build_col_schedule_kernel, grid_of((long long)H * nKB, 64 * kWaves), dim3(64 * kWaves), 0, stream,
+                       col_ptr, row_idx, tile_idx, bitmaps, nKB, Lq, Lk, causal, min_rows, H * nKB, s);
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     int32_t* order = s.cnt + (size_t)H * nKB;                // the count array carries the visiting order

@@ -6,6 +6,18 @@
 
 namespace ap {
 
+// ---- launches
+// HIP counts the threads of a grid's dimension in 32 bits: `blocks` (below 2^31) workgroups of `threads` in one
+// dimension where they fit, in rows of 2^20 otherwise.  The kernel takes block_index() and lets workgroups beyond
+// the last one leave.
+constexpr int kGridRowLog2 = 20;
+inline dim3 grid_of(long long blocks, int threads)
+{
+    if (blocks * threads < (1ll << 32)) return dim3((unsigned)blocks);
+    return dim3(1u << kGridRowLog2, (unsigned)((blocks + (1 << kGridRowLog2) - 1) >> kGridRowLog2));
+}
+__device__ __forceinline__ int block_index() { return (int)((blockIdx.y << kGridRowLog2) + blockIdx.x); }
+
 // ---- layout pass (ap_layout.hip)
 bool layout_shape_ok(int H, int Lq, int Lk, int BM, int BN);
 void layout_workspace_plan(int H, int Lq, int Lk, int BM, int BN, size_t* flags_off,

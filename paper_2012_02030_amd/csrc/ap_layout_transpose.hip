@@ -38,8 +38,10 @@ __global__ __launch_bounds__(kThreads) void transpose_kernel(const int32_t* __re
     const int tid = threadIdx.x;
     const int lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int h = blockIdx.x / n_chunks;
-    const int kb0 = (blockIdx.x % n_chunks) * kCols;
+    const int blk = block_index();
+    if (blk >= H * n_chunks) return;
+    const int h = blk / n_chunks;
+    const int kb0 = (blk % n_chunks) * kCols;
     const int seg_rows = min(nQB, kSegRows);
     const int pitch = ((seg_rows + 31) >> 5) | 1;            // odd: the columns of a row fall into different banks
 
@@ -142,7 +144,7 @@ hipError_t launch_layout_transpose(const int32_t* row_ptr, const int32_t* col_id
     const int n_chunks = (nKB + kCols - 1) / kCols;
     const int seg_rows = nQB < kSegRows ? nQB : kSegRows;
     const size_t lds = (size_t)kCols * (((seg_rows + 31) / 32) | 1) * sizeof(uint32_t);
-    hipLaunchKernelGGL(transpose_kernel, dim3((unsigned)(H * n_chunks)), dim3(kThreads), lds, stream, row_ptr, col_idx,
+    hipLaunchKernelGGL(transpose_kernel, grid_of((long long)H * n_chunks, kThreads), dim3(kThreads), lds, stream, row_ptr, col_idx,
                        H, nQB, nKB, n_chunks, cap, col_ptr, row_idx, tile_idx);
     return hipGetLastError();
 }

@@ -53,7 +53,7 @@ __device__ __forceinline__ int wave_inclusive_scan(int v, int lane)
 __global__ __launch_bounds__(kThreads) void build_schedule_kernel(
     const int32_t* __restrict__ row_ptr, const int32_t* __restrict__ col_idx,
     const uint64_t* __restrict__ bitmaps, int nQB, int Lq, int Lk, int BM, long long cap,
-    int causal, int min_cols, Schedule s)
+    int causal, int min_cols, int n_rows, Schedule s)
 {
     extern __shared__ uint64_t lds64[];
     const int kSeg = kSegWords / BM;                       // tiles per segment: 64 (block_m 64) or 32 (128)
@@ -64,7 +64,8 @@ __global__ __launch_bounds__(kThreads) void build_schedule_kernel(
     __shared__ int32_t k0s[kSegMax];
     __shared__ uint64_t s_tail[2][128];                    // row words of the open gathered entry, double-buffered
 
-    const int r = blockIdx.x;
+    const int r = block_index();
+    if (r >= n_rows) return;
     const int qb = r % nQB;
     const int tid = threadIdx.x;
     const int row = tid & (BM - 1);                        // this thread's query row
@@ -238,8 +239,8 @@ hipError_t launch_build_schedule(const int32_t* row_ptr, const int32_t* col_idx,
     // words (padded), group column sets, column list
     const size_t lds = ((size_t)kSegMax * 65 + (size_t)kSegMax * 4) * sizeof(uint64_t) +
                        (size_t)kSegMax * 64 * sizeof(uint16_t);
-    hipLaunchKernelGGL(build_schedule_kernel, dim3((unsigned)(H * nQB)), dim3(kThreads), lds, stream, row_ptr,
-                       col_idx, bitmaps, nQB, Lq, Lk, BM, cap, causal, min_cols, s);
+    hipLaunchKernelGGL(build_schedule_kernel, grid_of((long long)H * nQB, kThreads), dim3(kThreads), lds, stream, row_ptr,
+                       col_idx, bitmaps, nQB, Lq, Lk, BM, cap, causal, min_cols, H * nQB, s);
     return hipGetLastError();
 }
 

@@ -366,8 +366,7 @@ __global__ __launch_bounds__(256, 2) void bwd_dq_sched_kernel(
         }
     }
     __syncthreads();
-    if (DBLK < 2 && kh == 1) return;
-    f32x16 sum[HB];
+    f32x16 sum[HB];                                          // D = 32: what kh == 1 adds up here is not used
 #pragma unroll
     for (int hb = 0; hb < HB; ++hb)
 #pragma unroll
@@ -381,6 +380,7 @@ __global__ __launch_bounds__(256, 2) void bwd_dq_sched_kernel(
             }
         }
     __syncthreads();                                         // the sums are read: their place becomes the stores' staging
+    if (DBLK < 2 && kh == 1) return;
     const int row0 = qb * 64 + qh * 32;
     store_rows_bf16<HB * 32>(smem + wave * 32 * HB * 32, sum, a.scale, lane,
                              dQp + (size_t)row0 * a.sq[2] + mine * 32, a.sq[2], a.Lq - row0);

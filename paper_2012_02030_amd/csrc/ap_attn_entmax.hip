@@ -203,10 +203,10 @@ __global__ __launch_bounds__(128, 2) void entmax15_fwd_kernel(FwdArgs a, float* 
     const bool empty = nkept == 0;                           // both halves counted the same words
     const float mc = empty ? 0.f : m * c;
 
-    float tau = -1.f, psum;
+    // ---- Newton sweeps for tau (relative to the row maximum: the root lies in [-1, 0))
+    float tau = -1.f;
     bool done = empty;
-    for (bool confirm = false;; confirm = true) {
-        // ---- Newton sweeps for tau (relative to the row maximum: the root lies in [-1, 0))
+    auto newton = [&](bool confirm) {
         for (int iter = 0; iter < kEntmaxMaxIter; ++iter) {
             if (__syncthreads_or(done ? 0 : 1) == 0) break;  // every row of the block row has its tau
             float g1 = 0.f, g2 = 0.f;
@@ -233,8 +233,11 @@ __global__ __launch_bounds__(128, 2) void entmax15_fwd_kernel(FwdArgs a, float* 
                 }
             }
         }
+    };
 
-        // ---- last sweep: probabilities and output
+    // ---- last sweep: probabilities and output
+    float psum;
+    auto output = [&]() {
 #pragma unroll
         for (int db = 0; db < DBLK; ++db)
 #pragma unroll
@@ -253,9 +256,15 @@ __global__ __launch_bounds__(128, 2) void entmax15_fwd_kernel(FwdArgs a, float* 
             tr_mm_64<D>(lds + STAGE, sacc, oacc, tr);
         });
         psum = both_halves_sum(psum);
-        // Also: all wavefronts are done with the tiles.  The second time is the last one, whatever is left.
-        done = confirm || !(psum - 1.0f > kEntmaxLeft);
-        if (__syncthreads_or(done ? 0 : 1) == 0) break;
+    };
+    newton(false);
+    output();
+    // Also: all wavefronts are done with the tiles.
+    done = !(psum - 1.0f > kEntmaxLeft);
+    if (__builtin_expect(__syncthreads_or(done ? 0 : 1) != 0, 0)) {
+        newton(true);
+        output();
+        __syncthreads();
     }
     const float inv = (!empty && psum > 0.f) ? 1.0f / psum : 0.f;
 

@@ -558,8 +558,8 @@ ap_status ap_start_attention_maps(const void *Q, const void *K, const float *lse
  *
  * Exact: tau is an element of abar.  A sample of the map gives a narrow interval of values, one sweep
  * writes the mask of everything outside it and collects the entries inside, and tau is selected among
- * those by their bit patterns; if the interval misses the rank or holds a very large number of ties,
- * further sweeps select by radix over all entries.  Integer atomics only, so the result is
+ * those by their bit patterns; if the interval holds more entries than the workspace has room for or
+ * misses the rank, further sweeps narrow it over all entries.  Integer atomics only, so the result is
  * bit-identical from run to run.
  * ------------------------------------------------------------------------------------------- */
 size_t ap_prune_mask_workspace_bytes(void);

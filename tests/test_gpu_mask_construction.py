@@ -202,6 +202,74 @@ def test_prune_mask_where_only_a_sample_is_looked_at(shape, causal, levels):
         check_prune(a, p, causal, layout_block_ms=())
 
 
+def _shares(rng, shape, parts):
+    """A map whose entries take the given (value, share) pairs at random places, exactly so many of each."""
+    n = int(np.prod(shape))
+    counts = [int(share * n) for _, share in parts[:-1]]
+    a = np.repeat(np.array([v for v, _ in parts], np.float32), counts + [n - sum(counts)])
+    rng.shuffle(a)
+    return a.reshape(shape), counts[0] / n
+
+
+@pytest.mark.parametrize("kind", ["distinct above", "two close above", "two close far above", "one above"])
+def test_prune_mask_where_the_rank_lies_next_to_a_mass_of_zeros(kind):
+    """The interval of the sample runs from zero, which 40 % of the entries are, to the values above: more candidates
+    than there is room for, and the sweep narrows it.  What is left are a few distinct values, or two tied ones in
+    one bin (one or two levels of further narrowing), or a single one."""
+    rng = np.random.default_rng(61)
+    shape = (3, 1500, 2003)
+    value = np.float32(3e38 if kind == "two close far above" else 0.5)
+    if kind == "one above":
+        a, f = _shares(rng, shape, [(0.0, 0.4), (value, 0.6)])
+    elif kind == "distinct above":
+        a, f = _shares(rng, shape, [(0.0, 0.4), (value, 0.6)])
+        a[a > 0] = rng.random(int((a > 0).sum()), dtype=np.float32)
+    else:
+        a, f = _shares(rng, shape, [(0.0, 0.4), (value, 0.3), (np.nextafter(value, np.float32(0)), 0.3)])
+    n = a.size
+    for extra in (-1.5, 0.5, 100.5):                         # the last zero, the first value above, the 101st
+        print("prune", kind, extra, flush=True)
+        check_prune(a, f + extra / n, False, layout_block_ms=())
+
+
+@pytest.mark.parametrize("kind", ["spread", "tied"])
+def test_prune_mask_where_the_sample_misleads(kind):
+    """Every fourth cluster of 16 entries, those that the sample reads, holds values far above all others (distinct
+    ones: the sweep collects; one value: it narrows), so that the interval misses the rank and everything starts
+    again from the whole range."""
+    rng = np.random.default_rng(67)
+    rows, cols, stride = 2048, 4096, 4                       # 8.4 million entries, a sample of 2.1 million
+    a = rng.random((1, rows, cols), dtype=np.float32) * np.float32(0.1)
+    phase = ((np.arange(rows, dtype=np.uint32) * np.uint32(2654435761)) >> np.uint32(8)) % stride
+    sampled = (np.arange(cols)[None, :] // 16 - phase[:, None].astype(np.int64)) % stride == 0
+    a[0][sampled] = 0.5 if kind == "tied" else 0.9 + np.float32(0.1) * rng.random(int(sampled.sum()), dtype=np.float32)
+    for p in (0.5, 0.2):
+        check_prune(a, p, False, layout_block_ms=())
+
+
+@pytest.mark.parametrize("kind,p", [("distinct", 0.5), ("zeros", 0.3), ("zeros", 0.6), ("few", 0.5)])
+def test_prune_mask_of_a_map_so_large_that_the_interval_is_narrowed_first(kind, p):
+    """369 million entries, too many for the oracle: tau is an entry, as many entries lie below it as the rank says,
+    and the mask is their comparison with it."""
+    g = torch.Generator(device="cuda")
+    g.manual_seed(71)
+    shape = (4, 9600, 9601)
+    a = torch.rand(shape, generator=g, device="cuda")
+    if kind == "zeros":
+        a = torch.relu(a - 0.6)
+    elif kind == "few":
+        a = torch.floor(a * 5)
+    mask, tau = ap.ap_prune_mask(a, p)
+    none, tau2 = ap.ap_prune_mask(a, p, threshold_only=True)
+    assert torch.equal(tau, tau2)
+    rank = int(p * a.numel())
+    below = sum(int((x < tau).sum()) for x in a)
+    up_to = sum(int((x <= tau).sum()) for x in a)
+    assert below <= rank < up_to, (below, rank, up_to)
+    for m, x in zip(mask, a):
+        assert torch.equal(m, (x >= tau).to(torch.uint8))
+
+
 def test_mask_feeds_layout_and_attention_end_to_end():
     """Q, K -> mean map -> mask -> layout on the GPU; entries whose oracle mean is not within
     the map tolerance of the oracle's threshold must agree with the oracle's mask."""

@@ -6,14 +6,14 @@
 // query slot, the 64-bit word of kept keys inside this block column with the causal limit
 // folded in.  Same structure as the row schedule with the roles of rows and columns swapped.
 //
-// One workgroup of four wavefronts per block column, one lane per tile row.  Up to 64 tiles at a
-// time are held in registers (every wavefront takes every fourth tile, all its loads in flight at
+// One workgroup of four wavefronts (one, for many short columns) per block column, one lane per tile row.  Up
+// to 64 tiles at a time are held in registers (every wavefront takes every fourth tile, all its loads in flight at
 // once); which query rows of a tile hold something is one ballot per tile, shared through LDS; every
 // wavefront then knows, with a lane per tile, the entry slot of every tile (ranks and prefix sums
 // over the lanes) and writes its own tiles.  All positions depend on ballots only, so the emitted
 // order is fixed: no atomics.  The time is the chain of dependent loads of one block column (position
 // list -> bitmap words): one wavefront that took the tiles one after another, twice, needed 44 us at
-// 16 heads of 64 x 64 tiles, this form 14 us.  A second kernel appends, behind the entry counts, the
+// 16 heads of 64 x 64 tiles, this form 13 us.  A second kernel appends, behind the entry counts, the
 // order in which the dK/dV kernel should visit the block columns of each head.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
@@ -24,15 +24,15 @@ namespace ap {
 
 namespace {
 
-constexpr int kSeg = 64;                                     // tiles held at a time
-constexpr int kWaves = 4;
-constexpr int kPer = kSeg / kWaves;                          // tiles of one wavefront
+constexpr int kPer = 16;                                     // tiles of one wavefront at a time
 
+template <int kWaves>
 __global__ __launch_bounds__(64 * kWaves) void build_col_schedule_kernel(
     const int32_t* __restrict__ col_ptr, const int32_t* __restrict__ row_idx,
     const int32_t* __restrict__ tile_idx, const uint64_t* __restrict__ bitmaps, int nKB, int Lq, int Lk,
     int causal, int min_rows, int n_cols, Schedule s)
 {
+    constexpr int kSeg = kWaves * kPer;                      // tiles held at a time
     __shared__ unsigned long long s_rows[kSeg];              // query rows of every tile that hold something
     const int c = block_index();
     if (c >= n_cols) return;
@@ -54,12 +54,14 @@ __global__ __launch_bounds__(64 * kWaves) void build_col_schedule_kernel(
 #pragma unroll
         for (int u = 0; u < kPer; ++u) {
             const int t = u * kWaves + wave;
-            word[u] = t < n ? bitmaps[(size_t)__builtin_amdgcn_readlane(ti_lane, t) * 64 + lane] : 0ull;
+            if (t >= n) break;                               // uniform
+            word[u] = bitmaps[(size_t)__builtin_amdgcn_readlane(ti_lane, t) * 64 + lane];
         }
         __syncthreads();                                     // s_rows of the previous segment is no longer read
 #pragma unroll
         for (int u = 0; u < kPer; ++u) {
             const int t = u * kWaves + wave;
+            if (t >= n) break;
             if (causal) {
                 const long long lim = (long long)__builtin_amdgcn_readlane(q0_lane, t) + lane + off - (long long)kb * 64;
                 if (lim < 0) word[u] = 0;
@@ -77,11 +79,12 @@ __global__ __launch_bounds__(64 * kWaves) void build_col_schedule_kernel(
     for (int seg = c0; seg < c1; seg += kSeg) {
         const int n = min(kSeg, c1 - seg);
         load_segment(seg, n);
-        const int nrows = __popcll(s_rows[lane]);
+        const int nrows = lane < n ? __popcll(s_rows[lane]) : 0;
         const unsigned long long cons = __ballot(nrows > 0 && nrows >= min_rows);
 #pragma unroll
         for (int u = 0; u < kPer; ++u) {
             const int t = u * kWaves + wave;
+            if (t >= n) break;
             if (!((cons >> t) & 1ull)) continue;
             const size_t e = (size_t)c0 + n_cons + __popcll(cons & ((1ull << t) - 1ull));
             if (lane == 0) s.start[e] = __builtin_amdgcn_readlane(q0_lane, t);
@@ -94,7 +97,7 @@ __global__ __launch_bounds__(64 * kWaves) void build_col_schedule_kernel(
     for (int seg = c0; seg < c1; seg += kSeg) {
         const int n = min(kSeg, c1 - seg);
         if (!one_segment) load_segment(seg, n);
-        const unsigned long long mine = s_rows[lane];        // lane t: tile t
+        const unsigned long long mine = lane < n ? s_rows[lane] : 0ull;   // lane t: tile t
         int cnt = __popcll(mine);
         if (cnt >= min_rows) cnt = 0;                        // already emitted as a run
         int incl = cnt;
@@ -106,6 +109,7 @@ __global__ __launch_bounds__(64 * kWaves) void build_col_schedule_kernel(
 #pragma unroll
         for (int u = 0; u < kPer; ++u) {
             const int t = u * kWaves + wave;
+            if (t >= n) break;
             if (__builtin_amdgcn_readlane(cnt, t) == 0) continue;
             const unsigned long long rows = s_rows[t];
             const int p0 = stream + __builtin_amdgcn_readlane(incl - cnt, t);
@@ -164,8 +168,15 @@ hipError_t launch_build_col_schedule(const int32_t* col_ptr, const int32_t* row_
                                      int min_rows, const Schedule& s, hipStream_t stream)
 {
     const int nKB = (Lk + 63) / 64;
-    hipLaunchKernelGGL(build_col_schedule_kernel, grid_of((long long)H * nKB, 64 * kWaves), dim3(64 * kWaves), 0, stream,
-                       col_ptr, row_idx, tile_idx, bitmaps, nKB, Lq, Lk, causal, min_rows, H * nKB, s);
+    // Up to 16 block rows a wavefront holds all tiles of a column.  Four of them per column are faster as long as
+    // all are resident (256 compute units, 32 wavefronts each), one where they take turns:
+    // 16 heads of 512 x 16384 9.0 us (20.1 with four), of 64 x 16384 5.2 (18.0), of 1024 x 1024 7.4 (5.0).
+    const auto run = [&](auto kernel, int waves) {
+        hipLaunchKernelGGL(kernel, grid_of((long long)H * nKB, 64 * waves), dim3(64 * waves), 0, stream, col_ptr, row_idx,
+                           tile_idx, bitmaps, nKB, Lq, Lk, causal, min_rows, H * nKB, s);
+    };
+    if ((Lq + 63) / 64 <= kPer && (long long)H * nKB * 4 > 256 * 32) run(build_col_schedule_kernel<1>, 1);
+    else run(build_col_schedule_kernel<4>, 4);
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     int32_t* order = s.cnt + (size_t)H * nKB;                // the count array carries the visiting order

@@ -114,6 +114,14 @@ def test_col_schedule_of_columns_longer_than_one_segment(Lq, density):
     check_col_schedule(mask, False, 17)
 
 
+@pytest.mark.parametrize("H,Lq", [(33, 65), (33, 1024), (33, 1025), (32, 1024)])
+def test_col_schedule_of_many_short_columns(H, Lq):
+    """Columns of at most 16 tiles, more of them than a round of four wavefronts each: one wavefront per column; with
+    17 tiles, or exactly a round of columns, four."""
+    mask = synth.random_mask(H, Lq, 4096, 0.0008, seed=Lq)
+    check_col_schedule(mask, True, 0) if Lq == 65 else check_col_schedule(mask, False, 3)
+
+
 def test_col_schedule_on_the_structured_mask():
     cfg = synth.CONFIGS["C3"]
     mask = np.stack([synth.head_mask(cfg, h) for h in range(2)]).astype(np.uint8)

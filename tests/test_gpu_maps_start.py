@@ -10,6 +10,21 @@ from paper_2012_02030_amd import binding as ap
 pytestmark = pytest.mark.gpu
 
 
+def start_on_nan(Q, K, causal, weight, lse=None):
+    """ap_start_attention_maps on a map full of NaN: every entry has to be written."""
+    (B, H, Lq, D), Lk = Q.shape, K.shape[2]
+    abar = torch.full((H, Lq, Lk), float("nan"), device="cuda")
+    ws_bytes = ap.ap_attention_maps_workspace_bytes(B, H, Lq)
+    ws = torch.empty(ws_bytes, dtype=torch.uint8, device="cuda")
+    status = ap.lib().ap_start_attention_maps(
+        Q.data_ptr(), K.data_ptr(), lse.data_ptr() if lse is not None else None, ap.AP_BF16, B, H, Lq, Lk, D,
+        ap._strides3(Q), ap._strides3(K), int(causal), 0.0, weight, abar.data_ptr(), ws.data_ptr(), ws_bytes,
+        int(torch.cuda.current_stream().cuda_stream))
+    assert status == ap.AP_OK
+    torch.cuda.synchronize()
+    return abar
+
+
 @pytest.mark.parametrize("B,H,Lq,Lk,D,causal", [
     (1, 1, 1, 1, 32, True), (2, 3, 31, 33, 64, False), (3, 1, 127, 129, 64, True), (1, 2, 128, 128, 128, True),
     (2, 1, 129, 385, 128, True), (1, 5, 300, 191, 64, False), (2, 2, 4, 700, 32, True), (1, 3, 1030, 1030, 64, True),
@@ -20,9 +35,16 @@ def test_first_batch_and_accumulation(B, H, Lq, Lk, D, causal):
     K = torch.randn(B, H, Lk, D, generator=g).to(torch.bfloat16)
     ref = B * oracle.mean_attention_map(Q.double().numpy(), K.double().numpy(), causal=causal)
     w = 0.5
-    junk = torch.full((H, Lq, Lk), float("nan"), device="cuda")          # what a fresh map may hold
-    del junk
     first = ap.ap_accumulate_attention_maps(Q.cuda(), K.cuda(), causal=causal, weight=w)
+    Qd, Kd = Q.cuda(), K.cuda()
+    assert torch.equal(start_on_nan(Qd, Kd, causal, w), first)
+    scores = Q.double() @ K.double().transpose(-1, -2) / D ** 0.5
+    if causal:
+        scores.masked_fill_(torch.ones(Lq, Lk, dtype=torch.bool).triu(Lk - Lq + 1), float("-inf"))
+    lse = scores.logsumexp(-1).float().cuda()
+    with_lse = start_on_nan(Qd, Kd, causal, w, lse)
+    assert torch.equal(with_lse, ap.ap_accumulate_attention_maps(Qd, Kd, causal=causal, weight=w, lse=lse))
+    assert float((with_lse - first).abs().max()) <= 1e-5 * B             # finite, too
     zeroed = ap.ap_accumulate_attention_maps(Q.cuda(), K.cuda(), torch.zeros(H, Lq, Lk, device="cuda"), causal=causal,
                                              weight=w)
     base = torch.randn(H, Lq, Lk, generator=g).cuda()

@@ -370,7 +370,7 @@ ap_status ap_sparse_attn_entmax15_fwd(const void *Q, const void *K, const void *
  *                 [col_ptr[c], col_ptr[c+1])
  *   row_idx       out, int32 [cap]: block row qb of each of them
  *   tile_idx      out, int32 [cap]: its position in col_idx / bitmaps
- *   A truncated layout (more tiles than cap) must not be transposed.  Three launches, deterministic.
+ *   A truncated layout (more tiles than cap) must not be transposed.  One launch, deterministic.
  *
  * ap_sparse_attn_bwd:
  *   Q, K, V, O, dO, lse   the forward call's inputs and outputs and the gradient of O; O and dO
@@ -381,7 +381,8 @@ ap_status ap_sparse_attn_entmax15_fwd(const void *Q, const void *K, const void *
  *   workspace     device scratch of at least ap_bwd_workspace_bytes(B, H, Lq) bytes, 16-byte
  *                 aligned (the row sums of dO * O)
  *
- * Supported: dtype = AP_BF16, D in {32, 64, 128}, block_m = block_n = 64.  Three launches.
+ * Supported: dtype = AP_BF16, D in {32, 64, 128}, block_m = block_n = 64.  Three launches (with a row
+ * schedule, below, two).
  * Deterministic (no floating-point atomics): dQ is formed per block row, dK and dV per block
  * column, each recomputing the scores of its tiles.
  * ------------------------------------------------------------------------------------------- */

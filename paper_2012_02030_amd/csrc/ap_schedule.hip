@@ -15,8 +15,8 @@
 // last group; inside a class by tile, then ascending): an isolated connection is used by one
 // query, so most gathered entries then concern one wavefront only and the other one skips them.
 //
-// One workgroup of four wavefronts per block row; a thread stands for one query row and for every
-// kParts-th tile or entry.  The bitmap words of a segment of tiles are brought into LDS with all loads
+// One workgroup of four wavefronts per block row; a thread stands for one query row and for every fourth
+// tile or entry (every second at block_m = 128).  The bitmap words of a segment of tiles are brought into LDS with all loads
 // in flight at once; the per-tile decisions are then taken with one lane per tile (column sets by OR
 // over LDS, positions by prefix sums over the lanes), the gathered columns are listed in LDS in their
 // final order, and the words of the gathered entries are assembled from that list, the entries dealt

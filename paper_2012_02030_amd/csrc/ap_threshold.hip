@@ -26,10 +26,10 @@
 //
 // What bounds it: reading the map and writing the mask once (805 MB for 16 x 4096 x 4096 causal maps).
 // A full first sweep for an exact histogram costs a read of the map more and, worse, one LDS atomic per
-// entry on a few hot bins.  Measured there: 473 us with the histogram sweep (126 us), one-workgroup
-// selections (26 + 52 us) and a mask sweep of 231 us; now 236 us, of which the sweep is 165 (4.9 TB/s),
-// the sample 33 and the candidates 29.  At 12 x 512 x 512 (launches
-// only) 61 -> 55 us; rows that start anywhere (Lk = 4095) 644 -> 252 us.
+// entry on a few hot bins.  Measured there: 451 us with the histogram sweep (126 us), one-workgroup
+// selections (26 + 52 us) and a mask sweep of 214 us; now 260 us, of which the sweep is 162 (5.0 TB/s),
+// the sample 35 and the candidates 31.  At 12 x 512 x 512 (launches
+// only) 63 -> 50 us; rows that start anywhere (Lk = 4095) 644 -> 252 us.
 // Other maps, with the two radix sweeps of 15 bits before: 16 x 4096 x 4096 causal, all equal 1640 -> 437 us, 60 %
 // zeros 1116 -> 451 to 460 us (440 where the rank lies next to their mass, 524 before), normal within 1 % 636 -> 428 us;
 // 16 x 16384 x 16384 causal 6.0 -> 4.1 ms, 60 % zeros 15.6 -> 4.7 ms; 12 x 512 x 512, all equal 91 -> 88 us.
@@ -806,7 +806,7 @@ __device__ __forceinline__ void candidate_only(const Workspace& ws, uint32_t* h,
 // in 65536 bins per level over all entries, the counts of a workgroup kept as 16-bit halves of
 // LDS words and moved out before one of them can overflow.  Both in one launch: a launch that returns at once
 // costs 4.6 us between its neighbours, as does the mask sweep of the exact way, which shares the launch that
-// writes the candidates' mask bytes (16 x 4096 x 4096 causal: 245 us a call with them apart, 236 now).
+// writes the candidates' mask bytes (16 x 4096 x 4096 causal: 9 us of a call).
 template <int LEVEL>
 __global__ __launch_bounds__(kThreads) void select_level_kernel(Walk w, Workspace ws, uint8_t* mask, float* tau_out, uint32_t parts)
 {

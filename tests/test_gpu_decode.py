@@ -80,3 +80,13 @@ def test_decode_of_more_tiles_than_one_pass_takes(splits):
     """313 stored tiles: several passes over the key list, tiles dealt over the splits, the last tile ragged."""
     mask = synth.random_mask(1, 2, 20001, 0.05, seed=9)
     run_decode(1, 1, 2, 20001, 64, True, mask, seed=9, splits=splits)
+
+
+@pytest.mark.parametrize("D", [64, 128])
+@pytest.mark.parametrize("keys", [1, 3, 4, 5, 63, 64, 65, 448, 449, 511, 512, 513, 1023, 1024, 1025, 1600])
+def test_decode_of_lists_around_whole_steps_and_batches(D, keys):
+    """A list of exactly so many kept keys: around one key of every stream of a wavefront (8 or 4 streams), of all
+    streams (128 or 64), and around whole batches of eight per stream (1024 or 512)."""
+    mask = np.zeros((1, 1, 1700), np.uint8)
+    mask[0, 0, np.random.default_rng(keys).permutation(1700)[:keys]] = 1
+    run_decode(1, 1, 1, 1700, D, False, mask, seed=keys)

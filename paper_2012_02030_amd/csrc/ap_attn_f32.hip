@@ -1,6 +1,6 @@
 // Masked attention forward in fp32 on the matrix cores (Section 3.2, masked-attention equation).
 //
-// One workgroup of four wavefronts per 32 queries.  For up to 32 stored tiles at a time the
+// One workgroup of four wavefronts (two up to 64 keys) per 32 queries.  For up to 32 stored tiles at a time the
 // workgroup brings the bitmap words of its queries into LDS and lists the keys that any of them keeps
 // (the used columns of a tile are the OR of its 32 words), packed without gaps over the tiles, together
 // with where the keep bits of each are found.  The wavefronts then take the chunks of 32 listed keys in
@@ -18,7 +18,7 @@
 // K and V, and four wavefronts per 32 queries rather than one, because a long causal row is one chain.
 // With one query per lane and K, V broadcast from LDS in vector arithmetic the same call was bound
 // by LDS reads: B8 H8 L500 D64, 5 % kept, 69 us, now 18 us; B4 H8 L1024 D128 437 us, now 47 us; B1 H2 L64
-// D32 (launch and chain of loads) 9.7 us, now 5.4 us.
+// D32 (launch and chain of loads) 9.7 us, now 5.1 us.
 //
 // Matrix-core layouts (32x32x2, l = lane): A[m][k] and B[k][n]: m = n = l % 32, k = l / 32;
 // C[m][n]: n = l % 32, m = 8*(i/4) + 4*(l/32) + i%4, i = 0..15.
@@ -34,9 +34,6 @@ namespace {
 
 using namespace mfma;
 
-constexpr int kNW = 4;                                 // wavefronts per 32 queries
-constexpr int kSeg = 32;                               // tiles listed at a time
-constexpr int kPer = kSeg / kNW;                       // of them, per wavefront
 
 // OR over the 32 lanes of each half of the wavefront
 template <int CTRL>
@@ -56,11 +53,14 @@ __device__ __forceinline__ uint32_t or_over_32(uint32_t v)
 // The leading arguments arrive in registers when a wavefront starts (kernel-argument preloading).
 // Off: byte offsets inside a (batch, head) slice of K and V, 32 bits wide where the slices allow it (one
 // register per row address instead of two, and a wavefront more per SIMD).
-template <int D, typename Off>
+// kNW wavefronts per 32 queries: two where there are at most 64 keys, i.e. two chunks, and four otherwise.
+template <int D, int kNW, typename Off>
 __global__ __launch_bounds__(64 * kNW, sizeof(Off) == 8 ? 2 : (D == 128 ? 3 : 4)) void fwd_f32_kernel(
     const int32_t* __restrict__ p_row_ptr, const int32_t* __restrict__ p_col_idx,
     const uint64_t* __restrict__ p_bitmaps, int nQG, int p_H, int n_blocks, FwdArgs a)
 {
+    constexpr int kSeg = kNW == 2 ? 2 : 32;            // tiles listed at a time (64 keys: one tile)
+    constexpr int kPer = kSeg / kNW;                   // of them, per wavefront
     constexpr int DBLK = D / 32;
     constexpr int NJ = D / 8;                          // 16-byte pieces of a lane's half of a row
     constexpr int DM = D < 64 ? D : 64;                // columns of the output that are merged at a time
@@ -351,13 +351,16 @@ hipError_t launch_d(const FwdArgs& a, hipStream_t stream)
     const int nQG = (a.Lq + 31) / 32;                  // two groups per block row of the layout
     const long long blocks = (long long)nQG * a.H * a.B;
     if (blocks > 2147483647LL) return hipErrorInvalidValue;
-    const dim3 grid = grid_of(blocks, 64 * kNW), block(64 * kNW);
-    if ((long long)a.Lk * a.sk[2] < (1ll << 29) && (long long)a.Lk * a.sv[2] < (1ll << 29))   // 2 GB a slice
-        hipLaunchKernelGGL((fwd_f32_kernel<D, uint32_t>), grid, block, 0, stream, a.row_ptr, a.col_idx, a.bitmaps,
-                           nQG, a.H, (int)blocks, a);
-    else
-        hipLaunchKernelGGL((fwd_f32_kernel<D, uint64_t>), grid, block, 0, stream, a.row_ptr, a.col_idx, a.bitmaps,
-                           nQG, a.H, (int)blocks, a);
+    const auto run = [&](auto kernel, int waves) {
+        hipLaunchKernelGGL(kernel, grid_of(blocks, 64 * waves), dim3(64 * waves), 0, stream, a.row_ptr, a.col_idx,
+                           a.bitmaps, nQG, a.H, (int)blocks, a);
+    };
+    const bool narrow = (long long)a.Lk * a.sk[2] < (1ll << 29) && (long long)a.Lk * a.sv[2] < (1ll << 29);   // 2 GB a slice
+    // 64 keys are two chunks: two more wavefronts per 32 queries would hold the places of other workgroups and do
+    // nothing but set up and merge.  B256 H8 40 x 40, D = 32: 28.8 us with four, 20.2 with two; 64 x 64, D = 64: 46.9, 36.5.
+    if (narrow && a.Lk <= 64) run(fwd_f32_kernel<D, 2, uint32_t>, 2);
+    else if (narrow) run(fwd_f32_kernel<D, 4, uint32_t>, 4);
+    else run(fwd_f32_kernel<D, 4, uint64_t>, 4);
     return hipGetLastError();
 }
 

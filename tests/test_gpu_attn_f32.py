@@ -45,3 +45,14 @@ def test_ragged_query_groups(Lq, D):
     Q, K, V = inputs(Lq, 2, 3, Lq, Lq + 7, D)
     run_and_compare(Q, K, V, synth.random_mask(3, Lq, Lq + 7, 0.2, seed=Lq), "f32", True)
     run_and_compare(Q, K, V, np.ones((3, Lq, Lq + 7), np.uint8), "f32", True)
+
+
+@pytest.mark.parametrize("D", [32, 64, 128])
+@pytest.mark.parametrize("Lk", [1, 31, 32, 33, 63, 64, 65])
+def test_few_keys(Lk, D):
+    """Two wavefronts per 32 queries up to 64 keys, four from 65 on: one chunk of keys, two, three; all kept, and few."""
+    Q, K, V = inputs(Lk, 3, 2, min(Lk, 45), Lk, D)
+    for density in (1.0, 0.1):
+        mask = synth.random_mask(2, min(Lk, 45), Lk, density, seed=Lk)
+        run_and_compare(Q, K, V, mask, "f32", False)
+        run_and_compare(Q, K, V, mask, "f32", True)

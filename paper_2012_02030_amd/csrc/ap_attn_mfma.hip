@@ -571,8 +571,9 @@ hipError_t launch_one(const FwdArgs& a, hipStream_t stream)
 
 // O = sum_s exp(lse_s - lse) O_s with lse = ln sum_s exp(lse_s): one thread per (row, 4 elements), 8 chunks
 // in flight at a time (bound by memory latency: 8 chunks of 4096 rows
-// of 128 take 5.4 us, 9.0 with one chunk after another).
-template <int D>
+// of 128 take 5.4 us, 9.0 with one chunk after another).  LOOK: only the chunks whose log-sum-exp says that they
+// hold something are read.
+template <int D, bool LOOK>
 __global__ __launch_bounds__(256) void merge_splits_kernel(FwdArgs a)
 {
     constexpr int TPR = D / 4;                               // threads per row
@@ -581,6 +582,9 @@ __global__ __launch_bounds__(256) void merge_splits_kernel(FwdArgs a)
     const long long row = ((long long)blockIdx.x * 256 + threadIdx.x) / TPR;
     const int part = threadIdx.x % TPR;
     if (row >= rows) return;
+    const auto load = [&](int s) {
+        return *reinterpret_cast<const float4*>(a.part_o + ((size_t)s * rows + row) * D + part * 4);
+    };
     float mx = -INFINITY, tot = 0.f;
     float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
     for (int s0 = 0; s0 < a.splits; s0 += U) {
@@ -592,8 +596,13 @@ __global__ __launch_bounds__(256) void merge_splits_kernel(FwdArgs a)
             o[k] = make_float4(0.f, 0.f, 0.f, 0.f);
             if (s0 + k < a.splits) {
                 l[k] = a.part_lse[(size_t)(s0 + k) * rows + row];
-                o[k] = *reinterpret_cast<const float4*>(a.part_o + ((size_t)(s0 + k) * rows + row) * D + part * 4);
+                if (!LOOK) o[k] = load(s0 + k);
             }
+        }
+        if (LOOK) {
+#pragma unroll
+            for (int k = 0; k < U; ++k)
+                if (l[k] != -INFINITY) o[k] = load(s0 + k);
         }
         float m_new = mx;
 #pragma unroll
@@ -632,6 +641,18 @@ __global__ __launch_bounds__(256) void merge_splits_kernel(FwdArgs a)
     if (a.lse && part == 0) a.lse[row] = mx == -INFINITY ? -INFINITY : mx + __logf(tot);
 }
 
+// Looking first costs a round trip to memory per 8 chunks (64 splits of 256 rows of 128: 17.7 -> 21.6 us a call), reading
+// empty chunks costs bandwidth (16 splits of 2048 heads' 40 x 40 82 -> 94 us): it pays from about as many workgroups
+// on as are resident at a time.
+template <int D>
+hipError_t launch_merge_d(const FwdArgs& a, hipStream_t stream)
+{
+    const long long wgs = ((long long)a.B * a.H * a.Lq * (D / 4) + 255) / 256;
+    if (wgs > 2048) hipLaunchKernelGGL((merge_splits_kernel<D, true>), dim3((unsigned)wgs), dim3(256), 0, stream, a);
+    else hipLaunchKernelGGL((merge_splits_kernel<D, false>), dim3((unsigned)wgs), dim3(256), 0, stream, a);
+    return hipGetLastError();
+}
+
 template <int D>
 hipError_t launch_split_d(const FwdArgs& a, hipStream_t stream)
 {
@@ -645,25 +666,20 @@ hipError_t launch_split_d(const FwdArgs& a, hipStream_t stream)
     else
         hipLaunchKernelGGL((fwd_mfma_kernel<D, 2, ST, false, true>), dim3((unsigned)blocks), dim3(128), 0,
                            stream, a.row_ptr, cnt, nQB, 0, a.nqb_layout, a.B, a.splits, a);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    const long long threads = (long long)a.B * a.H * a.Lq * (D / 4);
-    hipLaunchKernelGGL(merge_splits_kernel<D>, dim3((unsigned)((threads + 255) / 256)), dim3(256), 0, stream, a);
-    return hipGetLastError();
+    const hipError_t e = hipGetLastError();
+    return e != hipSuccess ? e : launch_merge_d<D>(a, stream);
 }
 
 }  // namespace
 
 hipError_t launch_merge_splits(const FwdArgs& a, hipStream_t stream)
 {
-    const long long rows = (long long)a.B * a.H * a.Lq;
     switch (a.D) {
-    case 32: hipLaunchKernelGGL(merge_splits_kernel<32>, dim3((unsigned)((rows * 8 + 255) / 256)), dim3(256), 0, stream, a); break;
-    case 64: hipLaunchKernelGGL(merge_splits_kernel<64>, dim3((unsigned)((rows * 16 + 255) / 256)), dim3(256), 0, stream, a); break;
-    case 128: hipLaunchKernelGGL(merge_splits_kernel<128>, dim3((unsigned)((rows * 32 + 255) / 256)), dim3(256), 0, stream, a); break;
+    case 32: return launch_merge_d<32>(a, stream);
+    case 64: return launch_merge_d<64>(a, stream);
+    case 128: return launch_merge_d<128>(a, stream);
     default: return hipErrorInvalidValue;
     }
-    return hipGetLastError();
 }
 
 hipError_t launch_fwd_split(const FwdArgs& a, hipStream_t stream)

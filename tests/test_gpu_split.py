@@ -79,3 +79,27 @@ def test_split_forward_rows_without_kept_keys():
     assert float(O[0, 0, 2].float().abs().max()) == 0.0 and bool(torch.isneginf(lse[0, 0, 2]))
     O_ref, _ = oracle.masked_attention(rq, rk, rv, mask)
     assert np.abs(O.double().cpu().numpy() - O_ref).max() <= TOL["bf16"]
+
+
+@pytest.mark.parametrize("D,Lq", [(32, 102), (32, 103), (64, 103), (128, 103)])
+@pytest.mark.parametrize("splits", [3, 9])
+def test_merge_of_many_rows_reads_only_chunks_that_hold_something(D, Lq, splits):
+    """65536 rows of 32 are 2048 workgroups of the merge kernel (40 x 16 x 102 rows: 2040), from there on empty chunks are
+    skipped: same result as the ordinary call, rows without kept keys and with fewer tiles than splits among them."""
+    B, H, Lk = 40, 16, 200
+    g = torch.Generator(device="cuda")
+    g.manual_seed(D + splits)
+    Q, K, V = (torch.randn((B, H, L, D), generator=g, device="cuda").to(torch.bfloat16) for L in (Lq, Lk, Lk))
+    mask = synth.random_mask(H, Lq, Lk, 0.02, seed=D)
+    mask[:, 5] = 0
+    lay = ap.ap_build_layout(torch.from_numpy(mask).cuda(), 64, 64)
+    want, want_lse = ap.ap_sparse_attn_fwd(Q, K, V, lay)
+    junk = torch.full((ap.ap_fwd_split_workspace_bytes(B, H, Lq, D, splits) // 4,), float("nan"), device="cuda")
+    del junk                                                 # what the workspace may hold
+    O, lse = ap.ap_sparse_attn_fwd_split(Q, K, V, lay, splits)
+    # entries reach 5 in so many rows, and a step of bf16 there is 0.031 (2^-7 of the value at most): the bound, which is
+    # stated for values around 1, goes with the value above that
+    assert bool(((O.float() - want.float()).abs() <= TOL["bf16"] * want.float().abs().clamp(min=1.0)).all())
+    empty = torch.isinf(want_lse)
+    assert bool(empty[:, :, 5].all()) and torch.equal(torch.isinf(lse), empty)
+    assert float((lse - want_lse)[~empty].abs().max()) <= TOL["bf16"]

@@ -161,8 +161,8 @@ __global__ __launch_bounds__(64 * kWaves) void decode_kernel(FwdArgs a, int nQB)
         __syncthreads();
 
         // ---- 2. stream `strm` folds keys strm, strm + NS, ... of the list.  All streams have UN of them, or the
-        // steps end with the wavefront's last key (a list of one key per stream takes one step and not UN: one of 1024
-        // sparse tiles, in 8 passes, 42 us with all steps, 17 now)
+        // steps end with the wavefront's last key (a list of one key per stream takes one step and not UN: 65536
+        // positions under a sparse mask, eight passes, 22.5 us with all steps, 16.3 so; 2000 queries of 500 keys 593 and 396)
         auto fold = [&](int base, auto full) {
             constexpr bool FULL = decltype(full)::value;
             uint4 kx[UN], vx[UN];

@@ -642,8 +642,8 @@ __global__ __launch_bounds__(256) void merge_splits_kernel(FwdArgs a)
 }
 
 // Looking first costs a round trip to memory per 8 chunks (64 splits of 256 rows of 128: 17.7 -> 21.6 us a call), reading
-// empty chunks costs bandwidth (16 splits of 2048 heads' 40 x 40 82 -> 94 us): it pays from about as many workgroups
-// on as are resident at a time.
+// empty chunks costs bandwidth (16 splits of 2048 heads' 40 x 40: 94 us, 76 looking first; 32 splits of 512 heads' 100 x
+// 300 of 128: 594, 458): it pays from about as many workgroups on as are resident at a time.
 template <int D>
 hipError_t launch_merge_d(const FwdArgs& a, hipStream_t stream)
 {

@@ -11,11 +11,11 @@
 //                          sums P in registers; the running map in memory is read and written
 //                          once per call, whatever the batch size.
 //
-// What bounds them: the row statistics the issue of vector instructions (32 exponentials and 80 others per lane
-// and tile; B4 H16 L2048 D128 55 us, 75 with three wavefronts per SIMD and long rows first); the accumulation the
-// map's traffic in tiles of 128 x 128 (112 us there, 268 MB at 2.4 TB/s).  Deeper pipelines (K three tiles ahead, Q
-// through LDS), one persistent workgroup per compute unit and stores straight from registers all measured the same or
-// more.  The first batch writes the map without reading it, which saves its clearing too (33 us).
+// What bounds them (B4 H16 L2048 D128, causal): the row statistics the issue of vector instructions, three per score
+// (49 us; 55 with a maximum over every tile).  The accumulation: 47 us of map traffic at 5.8 TB/s, and 66 of
+// arithmetic and operand traffic to LDS (570 MB at about 18 TB/s), which overlap only in part, since the workgroups
+// of a round start together (90 us; 112 with query rows loaded straight into registers and two wavefronts per SIMD).
+// The first batch writes the map without reading it.
 //
 // Both use the score layout of the attention kernel: a wavefront owns 32 queries, lane l holds
 // query l % 32 and, of each 32-key block, the keys 8*(i/4) + 4*(l/32) + i%4 (i = 0..15).
@@ -30,6 +30,18 @@ namespace ap {
 namespace {
 
 using namespace mfma;
+
+constexpr float kRaise = 32.f;
+
+__device__ __forceinline__ float sum_exp(const f32x16* sacc, float sc, float msc)
+{
+    float s[2] = {0.f, 0.f};
+#pragma unroll
+    for (int i = 0; i < 16; ++i)
+#pragma unroll
+        for (int kb = 0; kb < 2; ++kb) s[kb] += __builtin_amdgcn_exp2f(fmaf(sacc[kb][i], sc, -msc));
+    return s[0] + s[1];
+}
 
 template <int D, int NW>
 __global__ __launch_bounds__(64 * NW, 4) void row_lse_kernel(MapArgs a, int nQB)
@@ -79,9 +91,16 @@ __global__ __launch_bounds__(64 * NW, 4) void row_lse_kernel(MapArgs a, int nQB)
     }
     const int k_swz = hh ^ swz_k<D>(n);
     const float sc = a.scale * kLog2e;
-    float m = -INFINITY, lsum = 0.f;
+    // reference of the exponentials: a maximum of scores seen, raised only where the sum of a lane's 32
+    // exponentials exceeds kRaise, so an ordinary tile needs no maximum (16 instructions and a lane exchange of 130)
+    float m = -INFINITY, msc = -INFINITY, lsum = 0.f;
     // last key that any query of this wavefront sees
     const long long wave_last = a.causal ? (long long)qb * BM + wave * 32 + 31 + off : (long long)a.Lk - 1;
+
+    // tiles before n_whole are visible as a whole to the whole wavefront
+    long long whole_keys = a.Lk;
+    if (a.causal) whole_keys = min(whole_keys, (long long)qb * BM + wave * 32 + off + 1);
+    const int n_whole = (int)(whole_keys / 64);
 
     wait_vmem();
     settle<KSTEPS>(qreg);
@@ -98,16 +117,10 @@ __global__ __launch_bounds__(64 * NW, 4) void row_lse_kernel(MapArgs a, int nQB)
         qk_64<D>(Ks, qreg, n, k_swz, sacc);
 
         // keys of this tile that exist and that this query may see: a prefix of the tile
-        const long long k0 = (long long)kt * 64;
-        long long lim = (long long)a.Lk - k0;
-        if (a.causal) lim = min(lim, diag - k0 + 1);
-        float tmax = -INFINITY;
-        if (__ballot(lim < 64) == 0) {                       // whole tile visible to the whole wavefront
-#pragma unroll
-            for (int kb = 0; kb < 2; ++kb)
-#pragma unroll
-                for (int i = 0; i < 16; ++i) tmax = fmaxf(tmax, sacc[kb][i]);
-        } else {
+        if (kt >= n_whole) {                                 // uniform over the wavefront: some lane sees a part only
+            const long long k0 = (long long)kt * 64;
+            long long lim = (long long)a.Lk - k0;
+            if (a.causal) lim = min(lim, diag - k0 + 1);
             const uint64_t word = lim >= 64 ? ~0ull : (lim <= 0 ? 0ull : (1ull << lim) - 1ull);
             const uint64_t wsh = word >> (4 * hh);
             const uint32_t wbits[2] = {(uint32_t)wsh, (uint32_t)(wsh >> 32)};
@@ -116,25 +129,25 @@ __global__ __launch_bounds__(64 * NW, 4) void row_lse_kernel(MapArgs a, int nQB)
 #pragma unroll
                 for (int i = 0; i < 16; ++i) {
                     const int pos = 8 * (i / 4) + (i % 4);
-                    const float sv = ((wbits[kb] >> pos) & 1u) ? sacc[kb][i] : -INFINITY;
-                    sacc[kb][i] = sv;
-                    tmax = fmaxf(tmax, sv);
+                    sacc[kb][i] = ((wbits[kb] >> pos) & 1u) ? sacc[kb][i] : -INFINITY;
                 }
+            asm volatile("");                                // a branch, not selects in every tile's way
         }
-        {
+        float psum = sum_exp(sacc, sc, msc);
+        if (__ballot(!(psum <= kRaise)) != 0) {              // first tile (the reference is -inf), or larger scores
+            float tmax = -INFINITY;
+#pragma unroll
+            for (int kb = 0; kb < 2; ++kb)
+#pragma unroll
+                for (int i = 0; i < 16; ++i) tmax = fmaxf(tmax, sacc[kb][i]);
             const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(tmax), __float_as_uint(tmax), false, false);
-            tmax = fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
+            const float m_new = fmaxf(m, fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1])));
+            msc = (m_new == -INFINITY) ? 0.f : m_new * sc;
+            lsum *= (m == -INFINITY) ? 0.f : __builtin_amdgcn_exp2f(m * sc - msc);
+            m = m_new;
+            psum = sum_exp(sacc, sc, msc);
         }
-        const float m_new = fmaxf(m, tmax);
-        const float msc = (m_new == -INFINITY) ? 0.f : m_new * sc;
-        const float alpha = (m == -INFINITY) ? 0.f : __builtin_amdgcn_exp2f(m * sc - msc);
-        float psum = 0.f;
-#pragma unroll
-        for (int kb = 0; kb < 2; ++kb)
-#pragma unroll
-            for (int i = 0; i < 16; ++i) psum += __builtin_amdgcn_exp2f(fmaf(sacc[kb][i], sc, -msc));
-        lsum = lsum * alpha + psum;
-        m = m_new;
+        lsum += psum;
     }
     {
         const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(lsum), __float_as_uint(lsum), false, false);
@@ -145,200 +158,226 @@ __global__ __launch_bounds__(64 * NW, 4) void row_lse_kernel(MapArgs a, int nQB)
             (m == -INFINITY) ? -INFINITY : fmaf(m, sc, __log2f(lsum));
 }
 
-// One workgroup: 32*NW queries x KT*64 keys of one head.  The Q rows of an example are loaded
-// once for all KT key tiles, every K tile serves all NW wavefronts, and the KT partial maps stay
-// in registers over the examples.
+// One workgroup: 128 queries x 128 keys of one head, eight wavefronts of 32 queries x 64 keys.  The
+// partial map stays in registers over the examples; 128 registers leave room for four wavefronts per SIMD, i.e. two
+// workgroups per compute unit.  Query rows come through LDS like the key rows: as operands fetched straight from
+// memory (16-byte pieces of 32 rows per instruction) they took as long as the arithmetic (eight wavefronts: 120 us
+// instead of 77 with everything in cache).  Two stages of half rows measured the same as one buffer of whole rows.
 //
 // INIT: the map is written whatever it held, hidden entries 0.
-template <int D, int NW, int KT, bool INIT>
-__global__ __launch_bounds__(64 * NW, D == 128 ? 2 : 3) void map_accumulate_kernel(MapArgs a, int nQB, int nKG)
+template <int D, bool INIT>
+__global__ __launch_bounds__(512, 4) void map_accumulate_kernel(MapArgs a, int nQB, int nKG, int total)
 {
-    constexpr int BM = 32 * NW;
-    constexpr int TILE = kBN * D;
+    constexpr int BM = 128, BK = 128, TILE = kBN * D;
     constexpr int KSTEPS = D / 16;
-    constexpr int OUT_LD = 68;                               // floats per staged output row (16-byte rows)
+    constexpr int OUT_LD = BK + 4;                           // floats per staged output row (16-byte rows)
     constexpr int OUT_ELEMS = BM * OUT_LD * 2;               // in 2-byte units
-    constexpr int SMEM = 2 * TILE > OUT_ELEMS ? 2 * TILE : OUT_ELEMS;
+    constexpr int SMEM = 4 * TILE > OUT_ELEMS ? 4 * TILE : OUT_ELEMS;
     __shared__ __attribute__((aligned(1024))) uint16_t smem[SMEM];
     lds_u16* lds = (lds_u16*)smem;
 
     const int tid = threadIdx.x;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wq = wave & 3, wk = wave >> 2;
     const int lane = tid & 63;
     const int n = lane & 31, hh = lane >> 5;
 
-    const int bid = xcd_contiguous(blockIdx.x, gridDim.x);
+    const int linear = block_index();
+    if (linear >= total) return;
+    const int bid = xcd_contiguous(linear, total);
     const int kg = bid % nKG;
     const int qb = (bid / nKG) % nQB;
     const int h = bid / (nKG * nQB);
     const long long off = (long long)a.Lk - a.Lq;
-    const int key0 = kg * (KT * 64);                         // first key of this workgroup
-    int n_sub = min(KT, (a.Lk - key0 + 63) / 64);            // key tiles that exist ...
-    if (a.causal) {                                          // ... and that some query of the block sees
-        const long long block_diag = (long long)qb * BM + (BM - 1) + off;
-        if (block_diag < key0) {
-            if (!INIT) return;
-            n_sub = 0;
-        } else {
-            n_sub = (int)min((long long)n_sub, (block_diag - key0) / 64 + 1);
-        }
-    }
-    // last key that any query of this wavefront sees
-    const long long wave_last = a.causal ? (long long)qb * BM + wave * 32 + 31 + off : (long long)a.Lk - 1;
+    const int key0 = kg * BK;                                // first key of this workgroup
+    const int q0 = qb * BM;
+    // last keys that any query of the workgroup, of this wavefront sees
+    const long long block_last = a.causal ? (long long)q0 + (BM - 1) + off : (long long)a.Lk - 1;
+    const long long wave_last = a.causal ? (long long)q0 + wq * 32 + 31 + off : (long long)a.Lk - 1;
+    if (block_last < key0) return;                           // hidden from the whole block
 
-    const int qrow = qb * BM + wave * 32 + n;
-    const int qload = qrow < a.Lq ? qrow : a.Lq - 1;
+    // memory side of the tile: 32 threads per row, 16 rows per pass
+    const int c4 = (tid & 31) * 4, r0 = tid >> 5;
+    const bool vec_ok = (a.Lk & 3) == 0;                     // then every row of the map starts 16-byte aligned
+    float* const map0 = a.abar + ((size_t)h * a.Lq + q0 + r0) * a.Lk + key0;
+    const long long map_step = (long long)16 * a.Lk;
+
+    const int qrow = q0 + wq * 32 + n;
     const int sk_bytes = (int)a.sk[2] * 2;
     const unsigned k_bytes = (unsigned)((a.Lk - 1) * sk_bytes + D * 2);
-    const int k_swz = hh ^ swz_k<D>(n);
     const float sc = a.scale * kLog2e;
+    const bool seen = (long long)key0 + wk * 64 <= wave_last && key0 + wk * 64 < a.Lk;   // uniform over the wavefront
+    const float* lp = a.lse2 + (size_t)h * a.Lq + min(qrow, a.Lq - 1);
 
-    auto q_row = [&](int b) {
-        return (const uint16_t*)a.Q + (size_t)b * a.sq[0] + (size_t)h * a.sq[1] +
-               (size_t)qload * a.sq[2] + 8 * hh;
-    };
-    auto issue_k = [&](int b, int sub, int stage) {
+    // The 128 query rows and 128 key rows of an example travel to LDS (query rows fetched straight into registers
+    // are 16-byte pieces of 32 rows per instruction); a wavefront brings 16 rows of either.
+    constexpr int CPR = D / 8, RPI = 64 / CPR, NL = 16 / RPI;
+    const int cp = lane % CPR;
+    const uint16_t* const q_head = (const uint16_t*)a.Q + (size_t)h * a.sq[1] + (long long)q0 * a.sq[2];
+    const int q_last = a.Lq - 1 - q0;
+    auto issue = [&](int b) {
         const rsrc_t rs = make_rsrc((const uint16_t*)a.K + (size_t)b * a.sk[0] + (size_t)h * a.sk[1], k_bytes);
-        issue_tile_loads<D, NW, false>(rs, lds + stage * TILE, key0 + sub * 64, sk_bytes, wave, lane);
+        int rl = lane / CPR;                                 // addresses are formed anew: held over the loop they
+        asm volatile("" : "+v"(rl));                         // would cost registers that there are not
+        int k_voff[NL];
+#pragma unroll
+        for (int u = 0; u < NL; ++u)
+            k_voff[u] = rl * sk_bytes + (cp ^ swz_k<D>(wave * 16 + u * RPI + rl)) * 16;
+        load16_chain<NL, 1024>(lds_addr_of(lds + wave * 16 * D), (key0 + wave * 16) * sk_bytes, RPI * sk_bytes, k_voff, rs);
+        const uint16_t* const base = q_head + (size_t)b * a.sq[0];
+#pragma unroll
+        for (int u = 0; u < NL; ++u) {
+            const int r = wave * 16 + u * RPI + rl;
+            load16_to_lds(lds_addr_of(lds + 2 * TILE + wave * 16 * D + u * 512),
+                          base + min(r, q_last) * a.sq[2] + (cp ^ swz_k<D>(r)) * 8);
+        }
     };
 
-    f32x16 acc[KT][2];
+    f32x16 acc[2], s[2];
 #pragma unroll
-    for (int sub = 0; sub < KT; ++sub)
+    for (int kb = 0; kb < 2; ++kb)
+#pragma unroll
+        for (int i = 0; i < 16; ++i) acc[kb][i] = 0.f;
+    // S^T of the wavefront's 64 keys and 32 queries: three LDS reads per two matrix instructions
+    const int row_chunk = n * D + (hh ^ swz_k<D>(n)) * 8;    // chunk 2 kk of the row: this ^ (16 kk)
+    auto scores = [&]() {
+        bf16x8 kr[KSTEPS][2], qr[KSTEPS];
+        int rc = row_chunk;
+        asm volatile("" : "+v"(rc));
+        constexpr int AHEAD = 2;
 #pragma unroll
         for (int kb = 0; kb < 2; ++kb)
 #pragma unroll
-            for (int i = 0; i < 16; ++i) acc[sub][kb][i] = 0.f;
-
-    bf16x8 qcur[KSTEPS];
-    float lcur = 0.f, lnext = 0.f;
-    if (n_sub > 0) {
-        const uint16_t* qr = q_row(0);
+            for (int i = 0; i < 16; ++i) s[kb][i] = 0.f;
+        auto read_step = [&](int kk) {
+            const uint16_t* p = smem + (rc ^ (16 * kk));
+            qr[kk] = *reinterpret_cast<const bf16x8*>(p + 2 * TILE + wq * 32 * D);
+            kr[kk][0] = *reinterpret_cast<const bf16x8*>(p + wk * TILE);
+            kr[kk][1] = *reinterpret_cast<const bf16x8*>(p + wk * TILE + 32 * D);
+        };
 #pragma unroll
-        for (int kk = 0; kk < KSTEPS; ++kk) qcur[kk] = *reinterpret_cast<const bf16x8*>(qr + 16 * kk);
-        lcur = a.lse2[(size_t)h * a.Lq + qload];
-        issue_k(0, 0, 0);
-    }
-    int stage = 0;
-    for (int b = 0; n_sub > 0 && b < a.B; ++b) {
+        for (int kk = 0; kk < AHEAD; ++kk) read_step(kk);
 #pragma unroll
-        for (int sub = 0; sub < KT; ++sub) {
-            if (sub >= n_sub) continue;                      // uniform over the workgroup
-            wait_vmem();                                     // this K tile (and new Q rows) have landed
-            settle<KSTEPS>(qcur);
-            asm volatile("" : "+v"(lnext), "+v"(lcur));
-            if (sub == 0 && b > 0) lcur = lnext;
-            __syncthreads();                                 // ... for everybody; the other stage is free
-            const bool last = sub + 1 == n_sub;
-            if (!last) issue_k(b, sub + 1, stage ^ 1);       // the next tile travels under the arithmetic
-            else if (b + 1 < a.B) issue_k(b + 1, 0, stage ^ 1);
-            const bool seen = (long long)key0 + sub * 64 <= wave_last;   // uniform over the wavefront
-            f32x16 sacc[2];
-            if (seen) qk_64<D>(smem + stage * TILE, qcur, n, k_swz, sacc);
-            if (last && b + 1 < a.B) {                       // Q rows and lse of the next example
-                const uint16_t* qr = q_row(b + 1);
+        for (int kk = 0; kk < KSTEPS; ++kk) {
+            if (kk + AHEAD < KSTEPS) read_step(kk + AHEAD);
 #pragma unroll
-                for (int kk = 0; kk < KSTEPS; ++kk) qcur[kk] = *reinterpret_cast<const bf16x8*>(qr + 16 * kk);
-                lnext = a.lse2[((size_t)(b + 1) * a.H + h) * a.Lq + qload];
-            }
-            // entries outside the map or hidden by causality are computed too (from zero keys or
-            // real ones) and dropped when the tile is written
-            if (seen)
-#pragma unroll
-                for (int kb = 0; kb < 2; ++kb)
-#pragma unroll
-                    for (int i = 0; i < 16; ++i)
-                        acc[sub][kb][i] += __builtin_amdgcn_exp2f(fmaf(sacc[kb][i], sc, -lcur));
-            stage ^= 1;
+            for (int kb = 0; kb < 2; ++kb)
+                s[kb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kr[kk][kb], qr[kk], s[kb], 0, 0, 0);
         }
+        __builtin_amdgcn_sched_group_barrier(0x100, 3 * AHEAD, 0);
+#pragma unroll
+        for (int kk = 0; kk < KSTEPS; ++kk) {
+            if (kk + AHEAD < KSTEPS) __builtin_amdgcn_sched_group_barrier(0x100, 3, 0);
+            __builtin_amdgcn_sched_group_barrier(0x008, 2, 0);
+        }
+    };
+    // entries outside the map or hidden by causality are computed too (from zero keys or
+    // real ones) and dropped when the tile is written
+    float l;
+    auto add_exp = [&]() {
+#pragma unroll
+        for (int kb = 0; kb < 2; ++kb)
+#pragma unroll
+            for (int i = 0; i < 16; ++i) acc[kb][i] += __builtin_amdgcn_exp2f(fmaf(s[kb][i], sc, -l));
+    };
+    // One buffer: the next example's rows are requested once every wavefront has its scores and travel under the
+    // exponentials, and under the arithmetic of the other workgroup of the compute unit.
+    issue(0);
+    l = lp[0];
+    for (int b = 0; b + 1 < a.B; ++b) {
+        wait_vmem();                                         // the rows of example b have landed
+        asm volatile("" : "+v"(l));
+        __syncthreads();                                     // ... for everybody
+        if (seen) scores();
+        __syncthreads();                                     // everybody has read them
+        issue(b + 1);
+        const float lnext = lp[(long long)(b + 1) * a.H * a.Lq];
+        if (seen) add_exp();
+        l = lnext;
     }
+    wait_vmem();
+    asm volatile("" : "+v"(l));
+    __syncthreads();
+    if (seen) scores();
+    // a tile that lies inside the map and below the causal limit for all its rows takes the
+    // branch-free path: all 8 loads of a thread are in flight under the last exponentials
+    bool interior = vec_ok && q0 + BM <= a.Lq && (long long)key0 + BK <= a.Lk;
+    if (a.causal) interior = interior && (long long)key0 + (BK - 1) <= (long long)q0 + off;
+    float4 o[8];
+    if (!INIT && interior)
+#pragma unroll
+        for (int pass = 0; pass < 8; ++pass) o[pass] = *reinterpret_cast<const float4*>(map0 + c4 + pass * map_step);
+    if (seen) add_exp();
 
     // transpose through LDS: lanes hold columns of keys per query, memory wants rows of keys
     float* outs = reinterpret_cast<float*>(smem);
-    const bool vec_ok = (a.Lk & 3) == 0;                     // then every row of the map starts 16-byte aligned
-    const int c4 = (tid & 15) * 4;
+    __syncthreads();                                         // K stages are consumed
 #pragma unroll
-    for (int sub = 0; sub < KT; ++sub) {
-        const long long k_first = (long long)key0 + sub * 64;
-        if (sub >= n_sub) {
-            if (INIT) {                                      // hidden from the whole block: zeros
+    for (int kb = 0; kb < 2; ++kb)
 #pragma unroll
-                for (int pass = 0; pass < 8; ++pass) {
-                    const int q = qb * BM + pass * (4 * NW) + (tid >> 4);
-                    if (q >= a.Lq) continue;
-                    float* dst = a.abar + ((size_t)h * a.Lq + q) * a.Lk + k_first + c4;
-                    if (vec_ok && k_first + c4 < a.Lk) {
-                        *reinterpret_cast<float4*>(dst) = make_float4(0.f, 0.f, 0.f, 0.f);
-                    } else {
-#pragma unroll
-                        for (int e = 0; e < 4; ++e)
-                            if (k_first + c4 + e < a.Lk) dst[e] = 0.f;
-                    }
-                }
-            }
-            continue;
+        for (int g = 0; g < 4; ++g) {
+            const float4 v = make_float4(acc[kb][4 * g], acc[kb][4 * g + 1], acc[kb][4 * g + 2], acc[kb][4 * g + 3]);
+            *reinterpret_cast<float4*>(outs + (wq * 32 + n) * OUT_LD + wk * 64 + 32 * kb + 8 * g + 4 * hh) = v;
         }
-        __syncthreads();                                     // K stages / previous staged tile are consumed
-        {
-            const int row = wave * 32 + n;
-#pragma unroll
-            for (int kb = 0; kb < 2; ++kb)
-#pragma unroll
-                for (int g = 0; g < 4; ++g) {
-                    float4 v = make_float4(acc[sub][kb][4 * g], acc[sub][kb][4 * g + 1],
-                                           acc[sub][kb][4 * g + 2], acc[sub][kb][4 * g + 3]);
-                    *reinterpret_cast<float4*>(outs + row * OUT_LD + 32 * kb + 8 * g + 4 * hh) = v;
-                }
-        }
-        __syncthreads();
-        // a tile that lies inside the map and below the causal limit for all its rows takes the
-        // branch-free path: all 8 loads of a thread are in flight before the first is used
-        bool interior = vec_ok && qb * BM + BM <= a.Lq && k_first + 63 <= (long long)a.Lk - 1;
-        if (a.causal) interior = interior && k_first + 63 <= (long long)qb * BM + off;
-        if (interior) {
-            float* base = a.abar + ((size_t)h * a.Lq + (size_t)qb * BM + (tid >> 4)) * a.Lk + k_first + c4;
-            float4 o[8];
-#pragma unroll
-            for (int pass = 0; pass < 8; ++pass)
-                o[pass] = INIT ? make_float4(0.f, 0.f, 0.f, 0.f)
-                               : *reinterpret_cast<const float4*>(base + (size_t)pass * (4 * NW) * a.Lk);
-#pragma unroll
-            for (int pass = 0; pass < 8; ++pass) {
-                const float4 v = *reinterpret_cast<const float4*>(outs + (pass * (4 * NW) + (tid >> 4)) * OUT_LD + c4);
-                o[pass].x = fmaf(a.weight, v.x, o[pass].x);
-                o[pass].y = fmaf(a.weight, v.y, o[pass].y);
-                o[pass].z = fmaf(a.weight, v.z, o[pass].z);
-                o[pass].w = fmaf(a.weight, v.w, o[pass].w);
-            }
-#pragma unroll
-            for (int pass = 0; pass < 8; ++pass)
-                *reinterpret_cast<float4*>(base + (size_t)pass * (4 * NW) * a.Lk) = o[pass];
-            continue;
-        }
+    __syncthreads();
+    if (interior) {
+        const float* src = outs + r0 * OUT_LD + c4;
 #pragma unroll
         for (int pass = 0; pass < 8; ++pass) {
-            const int r = pass * (4 * NW) + (tid >> 4);
-            const int q = qb * BM + r;
-            if (q >= a.Lq) continue;
-            long long last_key = (long long)a.Lk - 1;        // last key of this row that is accumulated
-            if (a.causal) last_key = min(last_key, (long long)q + off);
-            const long long k = k_first + c4;
-            if (k > (INIT ? (long long)a.Lk - 1 : last_key)) continue;
-            const float4 v = *reinterpret_cast<const float4*>(outs + r * OUT_LD + c4);
-            float* dst = a.abar + ((size_t)h * a.Lq + q) * a.Lk + k;
-            if (vec_ok && k + 3 <= last_key) {
-                float4 o = INIT ? make_float4(0.f, 0.f, 0.f, 0.f) : *reinterpret_cast<float4*>(dst);
-                o.x = fmaf(a.weight, v.x, o.x);
-                o.y = fmaf(a.weight, v.y, o.y);
-                o.z = fmaf(a.weight, v.z, o.z);
-                o.w = fmaf(a.weight, v.w, o.w);
-                *reinterpret_cast<float4*>(dst) = o;
+            if (INIT) o[pass] = make_float4(0.f, 0.f, 0.f, 0.f);
+            const float4 v = *reinterpret_cast<const float4*>(src + pass * 16 * OUT_LD);
+            o[pass].x = fmaf(a.weight, v.x, o[pass].x);
+            o[pass].y = fmaf(a.weight, v.y, o[pass].y);
+            o[pass].z = fmaf(a.weight, v.z, o[pass].z);
+            o[pass].w = fmaf(a.weight, v.w, o[pass].w);
+            *reinterpret_cast<float4*>(map0 + c4 + pass * map_step) = o[pass];
+        }
+    } else {                                                 // a row's 128 entries as four 32-entry pieces
+        const int c1 = tid & 31;
+        const float* src = outs + r0 * OUT_LD + c1;
+#pragma unroll
+        for (int half = 0; half < 2; ++half) {
+            float old[4][4];
+#pragma unroll
+            for (int p = 0; p < 4; ++p)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    const int q = q0 + r0 + 16 * (4 * half + p);
+                    const long long key = (long long)key0 + c1 + 32 * e;
+                    const bool kept = q < a.Lq && key < a.Lk && (!a.causal || key <= q + off);
+                    old[p][e] = !INIT && kept ? map0[c1 + 32 * e + (4 * half + p) * map_step] : 0.f;
+                }
+#pragma unroll
+            for (int p = 0; p < 4; ++p)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    const int q = q0 + r0 + 16 * (4 * half + p);
+                    const long long key = (long long)key0 + c1 + 32 * e;
+                    const bool here = q < a.Lq && key < a.Lk, kept = here && (!a.causal || key <= q + off);
+                    const float v = fmaf(a.weight, src[(4 * half + p) * 16 * OUT_LD + 32 * e], old[p][e]);
+                    if (INIT ? here : kept) map0[c1 + 32 * e + (4 * half + p) * map_step] = kept ? v : 0.f;
+                }
+        }
+    }
+    if (!INIT || !a.causal) return;
+    // Zeros of the tiles that are hidden as a whole: those of block row nQB - 1 - qb are dealt to the workgroups of
+    // block row qb, which has at least as many visible ones, so they travel beside other tiles' arithmetic (in
+    // workgroups of their own they held places on the compute units: 30 us of 120 at B4 H16 L2048 D128).
+    const int zb = nQB - 1 - qb, z0 = zb * BM;
+    const long long z_vis = min((long long)nKG, ((long long)z0 + (BM - 1) + off) / BK + 1);
+    const long long my_vis = min((long long)nKG, block_last / BK + 1);
+    for (long long zk = z_vis + kg; zk < nKG; zk += my_vis) {
+        float* const z = a.abar + ((size_t)h * a.Lq + z0 + r0) * a.Lk + zk * BK;
+        const int cols = (int)min((long long)BK, a.Lk - zk * BK);
+#pragma unroll
+        for (int pass = 0; pass < 8; ++pass) {
+            if (z0 + r0 + 16 * pass >= a.Lq) continue;
+            if (vec_ok) {
+                if (c4 < cols) *reinterpret_cast<float4*>(z + c4 + pass * map_step) = make_float4(0.f, 0.f, 0.f, 0.f);
             } else {
-                const float ve[4] = {v.x, v.y, v.z, v.w};
 #pragma unroll
                 for (int e = 0; e < 4; ++e)
-                    if (k + e <= last_key) dst[e] = fmaf(a.weight, ve[e], INIT ? 0.f : dst[e]);
-                    else if (INIT && k + e < a.Lk) dst[e] = 0.f;
+                    if ((tid & 31) + 32 * e < cols) z[(tid & 31) + 32 * e + pass * map_step] = 0.f;
             }
         }
     }
@@ -356,8 +395,8 @@ __global__ __launch_bounds__(256) void lse_to_base2_kernel(const float* __restri
 template <int D>
 hipError_t launch_d(const MapArgs& a, const float* lse, hipStream_t stream)
 {
-    constexpr int NW = 4, KT = 2;
-    const int nQB = (a.Lq + 32 * NW - 1) / (32 * NW), nKG = (a.Lk + 64 * KT - 1) / (64 * KT);
+    constexpr int NW = 4;
+    const int nQB = (a.Lq + 32 * NW - 1) / (32 * NW), nKG = (a.Lk + 127) / 128;
     if (lse) {
         const long long n = (long long)a.B * a.H * a.Lq;
         hipLaunchKernelGGL(lse_to_base2_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, stream, lse,
@@ -368,11 +407,12 @@ hipError_t launch_d(const MapArgs& a, const float* lse, hipStream_t stream)
     }
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    const dim3 grid((unsigned)(a.H * nQB * nKG)), block(64 * NW);
+    const int total = a.H * nQB * nKG;
+    const dim3 grid = grid_of(total, 512);
     if (a.init)
-        hipLaunchKernelGGL((map_accumulate_kernel<D, NW, KT, true>), grid, block, 0, stream, a, nQB, nKG);
+        hipLaunchKernelGGL((map_accumulate_kernel<D, true>), grid, dim3(512), 0, stream, a, nQB, nKG, total);
     else
-        hipLaunchKernelGGL((map_accumulate_kernel<D, NW, KT, false>), grid, block, 0, stream, a, nQB, nKG);
+        hipLaunchKernelGGL((map_accumulate_kernel<D, false>), grid, dim3(512), 0, stream, a, nQB, nKG, total);
     return hipGetLastError();
 }
 

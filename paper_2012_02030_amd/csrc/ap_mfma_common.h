@@ -86,6 +86,14 @@ __device__ __forceinline__ void load16_to_lds(unsigned lds_addr, int voff, rsrc_
                  :: "s"(lds_addr), "v"(voff), "s"(rsrc), "s"(soff) : "memory", "m0");
 }
 
+// The same from a 64-bit address per lane (rows at any stride).
+__device__ __forceinline__ void load16_to_lds(unsigned lds_addr, const void* src)
+{
+    lds_addr = __builtin_amdgcn_readfirstlane(lds_addr);
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off"
+                 :: "s"(lds_addr), "v"(src) : "memory", "m0");
+}
+
 // Raw buffer descriptor: base address, stride 0, num_records bytes; loads beyond num_records
 // return zeros.
 __device__ __forceinline__ rsrc_t make_rsrc(const void* base, unsigned num_bytes)

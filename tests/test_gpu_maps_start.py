@@ -58,3 +58,22 @@ def test_first_batch_and_accumulation(B, H, Lq, Lk, D, causal):
     # one fused multiply-add per entry onto what was there; hidden entries stay as they are
     assert (onto.cpu().numpy()[:, hidden] == base.cpu().numpy()[:, hidden]).all()
     assert float((onto - (base + first)).abs().max()) <= 1e-6 * float(base.abs().max() + 1)
+
+
+@pytest.mark.parametrize("order", ["rising", "falling", "last", "far below"])
+@pytest.mark.parametrize("Lq,Lk,D,causal", [(130, 515, 64, False), (257, 257, 128, True), (65, 200, 32, False)])
+def test_rows_whose_largest_scores_come_late(order, Lq, Lk, D, causal):
+    """The row sums are taken relative to an earlier maximum until a tile's sum outgrows it: scores that rise with
+    the key, jump at the last one, or start far above or below all others."""
+    g = torch.Generator().manual_seed(7)
+    Q, K = torch.randn(2, 2, Lq, D, generator=g), torch.randn(2, 2, Lk, D, generator=g)
+    Q[..., 0] = 8.0                                                    # key[0] moves every score by sqrt(D) / D * 8
+    ramp = torch.linspace(-60, 60, Lk) * D ** 0.5 / 8
+    K[..., 0] = {"rising": ramp, "falling": -ramp, "last": torch.where(torch.arange(Lk) == Lk - 1, 90.0, 0.0),
+                 "far below": torch.where(torch.arange(Lk) < 64, -90.0, 0.0)}[order]
+    Q, K = Q.to(torch.bfloat16), K.to(torch.bfloat16)
+    ref = 2 * oracle.mean_attention_map(Q.double().numpy(), K.double().numpy(), causal=causal)
+    got = ap.ap_accumulate_attention_maps(Q.cuda(), K.cuda(), causal=causal, weight=1.0).double().cpu().numpy()
+    # a score of up to 130 in magnitude, formed in 32 bits from D products, is off by up to a few 2^-24 * 130
+    assert np.abs(got - ref).max() <= 2 * 1e-4
+    assert np.abs(got.sum(-1) - ref.sum(-1)).max() <= 2 * 1e-4

@@ -45,23 +45,6 @@ enum { SOFTMAX = 0, ENTMAX15 = 1, GBAR = 2 };
 
 __device__ __forceinline__ float lse2_of(float lse) { return lse == -INFINITY ? INFINITY : lse * kLog2e; }
 
-// Two products that share nothing but their shape, their matrix instructions in turn (each is one
-// dependent chain): s = T0 * B0, p = T1 * B1 for 32 rows of two tiles in LDS (SWZ_BOTH; `row` is this
-// lane's row, k_swz = (l / 32) ^ swz_u(row)) and two operands in registers.  Operands are requested
-// AHEAD contraction steps early.
-//
-// The operands that stay in registers (Q and dO rows, or K and V rows) come the same way as the tiles: 1 KB
-// per instruction into the LDS stage that is still free, and from there with one row per lane.  Loaded into
-// registers directly they are 16 bytes from each of 32 rows per instruction, about 50 cycles of the
-// vector memory path instead of 16, in front of the first tile of every workgroup.
-template <int D>
-__device__ __forceinline__ void read_operand(const uint16_t* T, int row, int k_swz, bf16x8* x)
-{
-#pragma unroll
-    for (int kk = 0; kk < D / 16; ++kk)
-        x[kk] = *reinterpret_cast<const bf16x8*>(T + row * D + ((2 * kk) ^ k_swz) * 8);
-}
-
 template <int CTRL>
 __device__ __forceinline__ float dpp_add(float v)
 {
@@ -78,6 +61,10 @@ __device__ __forceinline__ float group_sum(float v)
     return v;
 }
 
+// Two products that share nothing but their shape, their matrix instructions in turn (each is one
+// dependent chain): s = T0 * B0, p = T1 * B1 for 32 rows of two tiles in LDS (SWZ_BOTH; `row` is this
+// lane's row, k_swz = (l / 32) ^ swz_u(row)) and two operands in registers.  Operands are requested
+// AHEAD contraction steps early.
 template <int D>
 __device__ __forceinline__ void two_products_32(const uint16_t* T0, const uint16_t* T1, int row, int k_swz,
                                                 const bf16x8* b0, const bf16x8* b1, f32x16& s, f32x16& p)
@@ -105,39 +92,6 @@ __device__ __forceinline__ void two_products_32(const uint16_t* T0, const uint16
         if (kk + AHEAD < KSTEPS) __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);
         __builtin_amdgcn_sched_group_barrier(0x008, 2, 0);
     }
-}
-
-// acc^T[D x 32] += T^T[D x 32] * P[32 x 32] for 32 rows of a tile in LDS (SWZ_BOTH), starting at Ts (a
-// multiple of 32 rows into the tile); P: 16 scores per lane in the order the score products leave them,
-// as two bf16 operands.
-template <int D>
-__device__ __forceinline__ void tr_mm_32(lds_u16* Ts, const bf16x8* pb, f32x16* acc, const TrReadU<D>& t)
-{
-    constexpr int DBLK = D / 32;
-    bf16x8 x[2][DBLK];
-    auto read = [&](int ks) {
-#pragma unroll
-        for (int db = 0; db < DBLK; ++db) {
-            const bf16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((lds_bf16x4*)(Ts + 16 * ks * D + t.off[0][db]));
-            const bf16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((lds_bf16x4*)(Ts + 16 * ks * D + t.off[1][db]));
-            x[ks][db] = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
-        }
-    };
-    read(0);
-    read(1);
-#pragma unroll
-    for (int ks = 0; ks < 2; ++ks)
-#pragma unroll
-        for (int db = 0; db < DBLK; ++db)
-            acc[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(x[ks][db], pb[ks], acc[db], 0, 0, 0);
-}
-
-__device__ __forceinline__ void to_operands(const f32x16& x, bf16x8* pb)
-{
-#pragma unroll
-    for (int ks = 0; ks < 2; ++ks)
-#pragma unroll
-        for (int e = 0; e < 8; ++e) pb[ks][e] = (__bf16)x[8 * ks + e];
 }
 
 // all ones (one-bit signed field) selects x, zero selects -infinity
@@ -350,40 +304,9 @@ __global__ __launch_bounds__(256, 2) void bwd_dq_sched_kernel(
         if (row_ok && hh == 0 && kh == 0) a.delta[stat_base + qrow] = den > 0.f ? num / den : 0.f;
         return;
     }
-    // add the two key halves: each wavefront gives away half of its 32-column blocks and finishes the others
     __syncthreads();                                         // all wavefronts are done with the tiles
-    constexpr int HB = DBLK >= 2 ? DBLK / 2 : 1;
-    float4* give = reinterpret_cast<float4*>(smem);          // [wave][block][quarter][lane]
-    const int mine = DBLK >= 2 ? kh * HB : 0, other = DBLK >= 2 ? (1 - kh) * HB : 0;
-    if (DBLK >= 2 || kh == 1) {
-#pragma unroll
-        for (int db = 0; db < DBLK; ++db) {
-            if (db < other || db >= other + HB) continue;
-#pragma unroll
-            for (int g = 0; g < 4; ++g)
-                give[((wave * HB + db % HB) * 4 + g) * 64 + lane] =
-                    make_float4(dqacc[db][4 * g], dqacc[db][4 * g + 1], dqacc[db][4 * g + 2], dqacc[db][4 * g + 3]);
-        }
-    }
-    __syncthreads();
-    f32x16 sum[HB];                                          // D = 32: what kh == 1 adds up here is not used
-#pragma unroll
-    for (int hb = 0; hb < HB; ++hb)
-#pragma unroll
-        for (int g = 0; g < 4; ++g) {
-            const float4 v = give[(((wave ^ 2) * HB + hb) * 4 + g) * 64 + lane];
-            const float ve[4] = {v.x, v.y, v.z, v.w};
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                const float own = DBLK >= 2 && kh ? dqacc[DBLK - HB + hb][4 * g + e] : dqacc[hb][4 * g + e];
-                sum[hb][4 * g + e] = own + ve[e];
-            }
-        }
-    __syncthreads();                                         // the sums are read: their place becomes the stores' staging
-    if (DBLK < 2 && kh == 1) return;
     const int row0 = qb * 64 + qh * 32;
-    store_rows_bf16<HB * 32>(smem + wave * 32 * HB * 32, sum, a.scale, lane,
-                             dQp + (size_t)row0 * a.sq[2] + mine * 32, a.sq[2], a.Lq - row0);
+    store_key_halves<D>(smem, dqacc, wave, lane, a.scale, dQp + (size_t)row0 * a.sq[2], a.sq[2], a.Lq - row0);
 }
 
 // A pair of wavefronts per 32 keys.  Wavefront `role` of it forms the scores of query half `role` of every

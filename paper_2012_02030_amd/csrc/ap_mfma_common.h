@@ -376,6 +376,53 @@ __device__ __forceinline__ void tr_mm_64_u(lds_u16* Ts, const f32x16* p, f32x16*
     }
 }
 
+// Operands that stay in registers come the same way as the tiles: 1 KB per instruction into an LDS tile
+// (SWZ_BOTH; k_swz = (l / 32) ^ swz_u(row)), and from there with one row per lane.  Loaded into
+// registers directly they are 16 bytes from each of 32 rows per instruction, about 50 cycles of the
+// vector memory path instead of 16, in front of the first tile of every workgroup.
+template <int D>
+__device__ __forceinline__ void read_operand(const uint16_t* T, int row, int k_swz, bf16x8* x)
+{
+#pragma unroll
+    for (int kk = 0; kk < D / 16; ++kk)
+        x[kk] = *reinterpret_cast<const bf16x8*>(T + row * D + ((2 * kk) ^ k_swz) * 8);
+}
+
+// acc^T[D x 32] += T^T[D x 32] * P[32 x 32] for 32 rows of a tile in LDS (SWZ_BOTH), starting at Ts (a
+// multiple of 32 rows into the tile); P: 16 scores per lane in the order the score products leave them,
+// as two bf16 operands.
+template <int D, bool AHEAD = true>
+__device__ __forceinline__ void tr_mm_32(lds_u16* Ts, const bf16x8* pb, f32x16* acc, const TrReadU<D>& t)
+{
+    constexpr int DBLK = D / 32;
+    bf16x8 x[2][DBLK];
+    auto read = [&](int ks) {
+#pragma unroll
+        for (int db = 0; db < DBLK; ++db) {
+            const bf16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((lds_bf16x4*)(Ts + 16 * ks * D + t.off[0][db]));
+            const bf16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((lds_bf16x4*)(Ts + 16 * ks * D + t.off[1][db]));
+            x[ks][db] = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
+        }
+    };
+    read(0);
+    if (AHEAD) read(1);                                      // without: D / 8 registers less
+#pragma unroll
+    for (int ks = 0; ks < 2; ++ks) {
+        if (!AHEAD && ks == 1) read(1);
+#pragma unroll
+        for (int db = 0; db < DBLK; ++db)
+            acc[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(x[ks][db], pb[ks], acc[db], 0, 0, 0);
+    }
+}
+
+__device__ __forceinline__ void to_operands(const f32x16& x, bf16x8* pb)
+{
+#pragma unroll
+    for (int ks = 0; ks < 2; ++ks)
+#pragma unroll
+        for (int e = 0; e < 8; ++e) pb[ks][e] = (__bf16)x[8 * ks + e];
+}
+
 // Write acc^T[D x 32] * mul as 32 bf16 rows of D elements: staged through this wavefront's own
 // 32 x D region of LDS (key swizzle), then 128-bit stores; rows >= rows_valid are dropped.
 template <int D>
@@ -404,6 +451,47 @@ __device__ __forceinline__ void store_rows_bf16(uint16_t* stage, const f32x16* a
         const uint4 v = *reinterpret_cast<const uint4*>(stage + rr * D + (c ^ swz_k<D>(rr)) * 8);
         if (rr < rows_valid) *reinterpret_cast<uint4*>(dst + (size_t)rr * row_stride + c * 8) = v;
     }
+}
+
+// acc^T[D x 32] of the wavefronts w and w ^ 2 (of four) added, times mul, as 32 bf16 rows of D elements: each
+// gives away half of its 32-column blocks and finishes the others.  smem: what the tiles held (64 x D and more);
+// no wavefront may still be reading them.
+template <int D>
+__device__ __forceinline__ void store_key_halves(uint16_t* smem, const f32x16* acc, int wave, int lane, float mul,
+                                                 uint16_t* dst, long long row_stride, int rows_valid)
+{
+    constexpr int DBLK = D / 32;
+    constexpr int HB = DBLK >= 2 ? DBLK / 2 : 1;
+    const int kh = wave >> 1;
+    float4* give = reinterpret_cast<float4*>(smem);          // [wave][block][quarter][lane]
+    const int mine = DBLK >= 2 ? kh * HB : 0, other = DBLK >= 2 ? (1 - kh) * HB : 0;
+    if (DBLK >= 2 || kh == 1) {
+#pragma unroll
+        for (int db = 0; db < DBLK; ++db) {
+            if (db < other || db >= other + HB) continue;
+#pragma unroll
+            for (int g = 0; g < 4; ++g)
+                give[((wave * HB + db % HB) * 4 + g) * 64 + lane] =
+                    make_float4(acc[db][4 * g], acc[db][4 * g + 1], acc[db][4 * g + 2], acc[db][4 * g + 3]);
+        }
+    }
+    __syncthreads();
+    f32x16 sum[HB];                                          // D = 32: what kh == 1 adds up here is not used
+#pragma unroll
+    for (int hb = 0; hb < HB; ++hb)
+#pragma unroll
+        for (int g = 0; g < 4; ++g) {
+            const float4 v = give[(((wave ^ 2) * HB + hb) * 4 + g) * 64 + lane];
+            const float ve[4] = {v.x, v.y, v.z, v.w};
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const float own = DBLK >= 2 && kh ? acc[DBLK - HB + hb][4 * g + e] : acc[hb][4 * g + e];
+                sum[hb][4 * g + e] = own + ve[e];
+            }
+        }
+    __syncthreads();                                         // the sums are read: their place becomes the stores' staging
+    if (DBLK < 2 && kh == 1) return;
+    store_rows_bf16<HB * 32>(smem + wave * 32 * HB * 32, sum, mul, lane, dst + mine * 32, row_stride, rows_valid);
 }
 
 }  // namespace mfma

@@ -143,8 +143,7 @@ def _rows_mask(mask_h, rows, cfg):
 
 
 def test_entmax_block_row_with_more_than_64_schedule_entries():
-    """Dense 64 x 5000 mask: 79 consecutive entries in the one block row, more than the kernel
-    keeps gather keys for, so it walks the layout's tiles."""
+    """Dense 64 x 5000 mask: 79 consecutive entries in the one block row, far more than are held."""
     Q, K, V = rand_qkv(11, 1, 1, 64, 5000, 64)
     mask = np.ones((1, 64, 5000), np.uint8)
     run_entmax(Q, K, V, mask, False)
@@ -152,8 +151,7 @@ def test_entmax_block_row_with_more_than_64_schedule_entries():
 
 def test_entmax_block_row_with_more_than_16_gathered_entries():
     """Sparse 64 x 3000 mask (2 % kept, about 45 distinct columns per tile): every tile of the one
-    block row is packed, into more gathered entries than the kernel keeps keys for in LDS, so it
-    walks the layout's tiles; a 64 x 900 mask of the same kind stays within the limit."""
+    block row is packed, into many gathered entries; fewer with a 64 x 900 mask of the same kind."""
     for Lk, seed in ((3000, 12), (900, 13)):
         print("entmax gathered", Lk, flush=True)
         Q, K, V = rand_qkv(seed, 1, 1, 64, Lk, 64, gain=2.0)
@@ -164,6 +162,19 @@ def test_entmax_block_row_with_more_than_16_gathered_entries():
         n_gathered = int((sched.start[: int(sched.cnt[0].item())] < 0).sum().item())
         assert (n_gathered > 16) == (Lk == 3000), n_gathered
         run_entmax(Q, K, V, mask, False)
+
+
+@pytest.mark.parametrize("D", [32, 64, 128])
+@pytest.mark.parametrize("tiles", [1, 2, 3, 7, 8, 9, 10, 13])
+def test_entmax_every_number_of_entries_around_those_held(tiles, D):
+    """Block rows of so many entries (layout tiles; with the schedule consecutive and gathered ones), the last key
+    tile and the last query tile incomplete: all held up to 8, of longer rows the first few."""
+    Lk = 64 * tiles - 5
+    Q, K, V = rand_qkv(tiles, 1, 2, 70, Lk, D, gain=1.5)
+    mask = synth.random_mask(2, 70, Lk, 0.6, seed=tiles)
+    mask[1] = synth.random_mask(1, 70, Lk, 0.02, seed=tiles)[0]        # gathered
+    mask[:, 3] = 0                                                     # a query without keys
+    run_entmax(Q, K, V, mask, False)
 
 
 @pytest.mark.parametrize("D,kind", [(64, "equal"), (64, "ascending"), (128, "ascending"), (32, "descending"),
@@ -188,6 +199,7 @@ def test_entmax_start_from_the_largest_score_of_every_place(D, kind):
 # y = x - max x and how many keys have them.
 CLUSTERED = {
     "two clusters": ((0.0, 1), (-0.999469, 1119), (-0.996444, 366), (-3.0, 50)),
+    "short": ((0.0, 1), (-0.9981533752, 370), (-0.9582652282, 5)),     # 376 keys: all scores are held
     "three clusters": ((0.0, 1), (-0.998105, 3442), (-0.992293, 245), (-0.97993, 1), (-3.0, 1174)),
 }
 
@@ -224,14 +236,14 @@ def clustered_attained_sums(names, D=32):
     return np.concatenate(totals)
 
 
-@pytest.mark.parametrize("names", [("two clusters",), ("three clusters",), ("three clusters", "two clusters")])
+@pytest.mark.parametrize("names", [("two clusters",), ("three clusters",), ("three clusters", "two clusters"), ("short",)])
 def test_entmax_tau_never_passes_the_root(names):
     """tau rises to the root and never passes it: sum p >= 1 up to the residual 1e-5 at which a row stops (and as much
     again for the 32-bit sums over some thousand keys)."""
     assert clustered_attained_sums(names).min() >= 1.0 - 2e-5
 
 
-@pytest.mark.parametrize("names", [("two clusters",), ("three clusters",), ("three clusters", "two clusters")])
+@pytest.mark.parametrize("names", [("two clusters",), ("three clusters",), ("three clusters", "two clusters"), ("short",)])
 def test_entmax_residual_where_scores_leave_the_support_under_the_last_step(names):
     """The bound of the header, |sum p - 1| <= 1e-4, on rows whose unconfirmed last step leaves 1.0e-3 and 2.4e-3."""
     total = clustered_attained_sums(names)

@@ -403,6 +403,7 @@ hipError_t launch_d(const BwdArgs& a, hipStream_t stream)
 
 hipError_t launch_bwd(const BwdArgs& a, hipStream_t stream)
 {
+    if (bwd_short_fits(a)) return launch_bwd_short(a, stream);
     switch (a.D) {
         case 32: return launch_d<32>(a, stream);
         case 64: return launch_d<64>(a, stream);

@@ -45,61 +45,6 @@ enum { SOFTMAX = 0, ENTMAX15 = 1, GBAR = 2 };
 
 __device__ __forceinline__ float lse2_of(float lse) { return lse == -INFINITY ? INFINITY : lse * kLog2e; }
 
-template <int CTRL>
-__device__ __forceinline__ float dpp_add(float v)
-{
-    return v + __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, 0xf, 0xf, false));
-}
-// sum over aligned groups of N = 4, 8 or 16 lanes, in every lane of the group
-template <int N>
-__device__ __forceinline__ float group_sum(float v)
-{
-    v = dpp_add<0xB1>(v);                                    // quad_perm [1,0,3,2]
-    v = dpp_add<0x4E>(v);                                    // quad_perm [2,3,0,1]
-    if (N >= 8) v = dpp_add<0x141>(v);                       // row_half_mirror
-    if (N >= 16) v = dpp_add<0x140>(v);                      // row_mirror
-    return v;
-}
-
-// Two products that share nothing but their shape, their matrix instructions in turn (each is one
-// dependent chain): s = T0 * B0, p = T1 * B1 for 32 rows of two tiles in LDS (SWZ_BOTH; `row` is this
-// lane's row, k_swz = (l / 32) ^ swz_u(row)) and two operands in registers.  Operands are requested
-// AHEAD contraction steps early.
-template <int D>
-__device__ __forceinline__ void two_products_32(const uint16_t* T0, const uint16_t* T1, int row, int k_swz,
-                                                const bf16x8* b0, const bf16x8* b1, f32x16& s, f32x16& p)
-{
-    constexpr int KSTEPS = D / 16;
-    constexpr int AHEAD = KSTEPS < 3 ? KSTEPS : 3;
-#pragma unroll
-    for (int i = 0; i < 16; ++i) s[i] = p[i] = 0.f;
-    bf16x8 r0[KSTEPS], r1[KSTEPS];
-    auto read = [&](int kk) {
-        r0[kk] = *reinterpret_cast<const bf16x8*>(T0 + row * D + ((2 * kk) ^ k_swz) * 8);
-        r1[kk] = *reinterpret_cast<const bf16x8*>(T1 + row * D + ((2 * kk) ^ k_swz) * 8);
-    };
-#pragma unroll
-    for (int kk = 0; kk < AHEAD; ++kk) read(kk);
-#pragma unroll
-    for (int kk = 0; kk < KSTEPS; ++kk) {
-        if (kk + AHEAD < KSTEPS) read(kk + AHEAD);
-        s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(r0[kk], b0[kk], s, 0, 0, 0);
-        p = __builtin_amdgcn_mfma_f32_32x32x16_bf16(r1[kk], b1[kk], p, 0, 0, 0);
-    }
-    __builtin_amdgcn_sched_group_barrier(0x100, 2 * AHEAD, 0);   // pin that order
-#pragma unroll
-    for (int kk = 0; kk < KSTEPS; ++kk) {
-        if (kk + AHEAD < KSTEPS) __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);
-        __builtin_amdgcn_sched_group_barrier(0x008, 2, 0);
-    }
-}
-
-// all ones (one-bit signed field) selects x, zero selects -infinity
-__device__ __forceinline__ float or_minus_inf(float x, uint32_t keep)
-{
-    return __uint_as_float((__float_as_uint(x) & keep) | (0xff800000u & ~keep));
-}
-
 // The leading arguments repeat fields of `a`: they arrive in registers when a wavefront starts
 // (kernel-argument preloading), so the chain row pointer -> entry -> tiles starts at once.
 template <int D, int MODE>

@@ -117,6 +117,9 @@ hipError_t launch_bwd(const BwdArgs& a, hipStream_t stream);
 // the kernels that walk schedules (ap_attn_bwd_sched.hip); softmax: dq writes delta, dkv reads it;
 // entmax: runs the gbar pass and both gradient kernels whatever dq and dkv say
 hipError_t launch_bwd_sched(const BwdArgs& a, bool dq, bool dkv, hipStream_t stream);
+// short sequences in one launch, over the layout's bitmaps (ap_attn_bwd_short.hip)
+bool bwd_short_fits(const BwdArgs& a);
+hipError_t launch_bwd_short(const BwdArgs& a, hipStream_t stream);
 // column schedule (ap_col_schedule.hip): entry e of block column c is element col_ptr[c] + e
 hipError_t launch_build_col_schedule(const int32_t* col_ptr, const int32_t* row_idx, const int32_t* tile_idx,
                                      const uint64_t* bitmaps, int H, int Lq, int Lk, int causal,

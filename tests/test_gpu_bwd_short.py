@@ -1,0 +1,71 @@
+"""The backward pass of short sequences (one launch for dQ, dK and dV) against the fp64 oracle, and against the kernels
+of longer ones on the same problem with more queries and keys that nobody keeps."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2012_02030_amd import binding as ap
+from paper_2012_02030_amd import synth
+
+from test_gpu_bwd import run_bwd
+
+pytestmark = pytest.mark.gpu
+
+# around the edges of 32-row blocks, of 64-row tiles and of the kernel's sizes, and where few keys per query or few
+# pairs send a call to the general kernels
+SIZES = [(1, 1), (31, 33), (33, 31), (64, 64), (65, 64), (64, 65), (127, 129), (128, 256), (129, 96), (100, 20), (40, 256)]
+
+
+def rand(seed, B, H, L, D):
+    return np.random.default_rng([synth.SEED, 77, seed]).standard_normal((B, H, L, D), dtype=np.float32)
+
+
+@pytest.mark.parametrize("D", [32, 64])
+@pytest.mark.parametrize("Lq,Lk", SIZES)
+def test_short_backward_matches_oracle(Lq, Lk, D):
+    B, H = 2, 3
+    for causal in ((False, True) if Lk >= Lq else (False,)):
+        print(Lq, Lk, D, causal, flush=True)
+        mask = synth.random_mask(H, Lq, Lk, 0.4, seed=Lq + Lk)
+        mask[1, :, : Lk // 2] = 0                                      # empty tiles, queries without keys
+        mask[2] = Lq < 65                                              # everything, or nothing at all
+        run_bwd(rand(1, B, H, Lq, D), rand(2, B, H, Lk, D), rand(3, B, H, Lk, D), rand(4, B, H, Lq, D), mask, causal)
+
+
+def strided(x):
+    """The same values as a view of a [B, L, H, D] tensor."""
+    return x.transpose(1, 2).contiguous().transpose(1, 2)
+
+
+@pytest.mark.parametrize("form", [lambda x: x, strided], ids=["contiguous", "strided"])
+@pytest.mark.parametrize("B,H,Lq,Lk,D", [(2, 2, 100, 70, 64), (3, 1, 128, 250, 32), (24, 8, 256, 255, 64),
+                                         (24, 8, 130, 256, 32), (24, 8, 200, 97, 64)])
+def test_short_backward_matches_the_kernels_of_longer_sequences(B, H, Lq, Lk, D, form):
+    """From the same O and lse, P and dS are formed and rounded to bf16 alike in all of them; sums in 32 bits in another
+    order (delta, the results) turn a rounding where a value lies next to the middle of two: a unit in the last place
+    of a result (2^-7 of it at most) and 2^-8 of a term of its sum, which is no larger than the largest results."""
+    L = 320
+    g = torch.Generator().manual_seed(Lq * 7 + Lk)
+    Q, dO = (torch.randn(B, H, L, D, generator=g).to(torch.bfloat16).cuda() for _ in range(2))
+    K, V = (torch.randn(B, H, L, D, generator=g).to(torch.bfloat16).cuda() for _ in range(2))
+    mask = np.zeros((H, L, L), np.uint8)
+    mask[:, :Lq, :Lk] = synth.random_mask(H, Lq, Lk, 0.2, seed=Lk)
+    whole = torch.from_numpy(mask).cuda()
+    lay = ap.ap_build_layout(whole, 64, 64)
+    lay_t = ap.ap_build_layout_transpose(lay)
+    want = []
+    O, lse = ap.ap_sparse_attn_fwd(Q, K, V, lay)
+    for few in (None, 1, 65):                                          # tiles; all runs of 64; all gathered
+        rs = None if few is None else ap.ap_build_schedule(lay, causal=False, min_cols=few)
+        cs = None if few is None else ap.ap_build_col_schedule(lay, lay_t, causal=False, min_rows=few)
+        grads = ap.ap_sparse_attn_bwd(Q, K, V, O, dO, lse, lay, lay_t, sched=rs, col_sched=cs)
+        want.append([x[:, :, :n].double() for x, n in zip(grads, (Lq, Lk, Lk))])
+    cut = [form(x[:, :, :n]) for x, n in ((Q, Lq), (K, Lk), (V, Lk), (O, Lq), (dO, Lq))]
+    lse_cut = lse[:, :, :Lq].contiguous()
+    small = ap.ap_build_layout(whole[:, :Lq, :Lk].contiguous(), 64, 64)
+    got = ap.ap_sparse_attn_bwd(*cut, lse_cut, small, ap.ap_build_layout_transpose(small))
+    torch.cuda.synchronize()
+    for name, x, refs in zip(("dQ", "dK", "dV"), got, zip(*want)):
+        for ref in refs:
+            excess = ((x.double() - ref).abs() - ref.abs() / 128 - ref.abs().max() / 256).max()
+            assert float(excess) <= 0, (name, float(excess))

@@ -64,6 +64,17 @@ def test_split_forward_matches_oracle(case):
     run_split(B, H, Lq, Lk, D, causal, density, splits, use_sched, seed=Lk + splits)
 
 
+@pytest.mark.parametrize("D", [32, 64, 128])
+@pytest.mark.parametrize("use_sched", [False, True])
+@pytest.mark.parametrize("Lk,splits,density", [(256, 1, 0.5), (320, 1, 0.02), (512, 2, 0.01), (1111, 4, 0.05), (700, 2, 0.9),
+                                               (17100, 1, 0.3)])
+def test_split_chunks_shared_by_two_teams(Lk, splits, density, use_sched, D):
+    """Few chunks of four tiles and more: two teams take half of a chunk's entries each.  Odd and even numbers of entries,
+    one entry for both (gathered), causal limits inside the last tiles, 268 entries (the window of entry starts moves on)."""
+    print(Lk, splits, density, use_sched, D, flush=True)
+    run_split(2, 2, 70, Lk, D, True, density, splits, use_sched, seed=Lk)
+
+
 def test_split_forward_rows_without_kept_keys():
     B, H, Lq, Lk, D = 1, 1, 4, 512, 64
     rng = np.random.default_rng(5)

@@ -127,9 +127,15 @@ __global__ __launch_bounds__(256, 2) void bwd_dq_sched_kernel(
         }
     };
 
+    // A first entry of 64 consecutive keys is requested before anything else: its start is a scalar load, so this waits for
+    // no vector load.
+    const int start0 = t0 < t1 ? p_start[t0] : -1;
     Meta cur, nxt;
+    cur.start = start0;
+    cur.key = 0;
     cur.word = 0;
-    if (t0 < t1) fetch(t0, cur);                             // everything waits for this first
+    if (start0 >= 0) issue(cur, 0);
+    if (t0 < t1) fetch(t0, cur);
     // Q and dO rows of the block row (rows >= Lq read as zeros) into the second stage
     issue_tile_loads<D, 4, SWZ_BOTH>(q_rsrc, lds + STAGE, qb * 64, sq_bytes, wave, lane);
     issue_tile_loads<D, 4, SWZ_BOTH>(g_rsrc, lds + STAGE + TILE, qb * 64, so_bytes, wave, lane);
@@ -152,7 +158,7 @@ __global__ __launch_bounds__(256, 2) void bwd_dq_sched_kernel(
     }
     nxt = cur;
     if (t0 < t1) {
-        issue(cur, 0);
+        if (start0 < 0) issue(cur, 0);
         if (t0 + 1 < t1) fetch(t0 + 1, nxt);
     }
     const float sc = MODE == SOFTMAX ? a.scale * kLog2e : a.scale * 0.5f;
@@ -384,9 +390,20 @@ __global__ __launch_bounds__(256, 2) void bwd_dkv_sched_kernel(
         }
     };
 
+    // as in the dQ kernel
+    const int start0 = t0 < t1 ? p_start[t0] : -1;
     Meta cur, nxt;
-    cur.start = cur.row = 0;
-    if (t0 < t1) fetch(t0, cur);                             // everything waits for this first
+    cur.start = start0;
+    cur.row = 0;
+    Stat st;
+    st.v = 0.f;
+    st.word = 0;
+    if (start0 >= 0) {
+        issue(cur, 0);
+        fetch_stat(t0, cur, st);
+    } else if (t0 < t1) {
+        fetch(t0, cur);
+    }
     {   // K and V rows of the block column (rows >= Lk read as zeros) into the second stage
         const int sk_bytes = (int)a.sk[2] * 2, sv_bytes = (int)a.sv[2] * 2;
         issue_tile_loads<D, 4, SWZ_BOTH>(make_rsrc(Kp, (unsigned)((a.Lk - 1) * sk_bytes + D * 2)), lds + STAGE, kb * 64,
@@ -405,13 +422,12 @@ __global__ __launch_bounds__(256, 2) void bwd_dkv_sched_kernel(
 #pragma unroll
         for (int i = 0; i < 16; ++i) acc[db][i] = 0.f;
 
-    Stat st;
-    st.v = 0.f;
-    st.word = 0;
     nxt = cur;
     if (t0 < t1) {
-        issue(cur, 0);
-        fetch_stat(t0, cur, st);
+        if (start0 < 0) {
+            issue(cur, 0);
+            fetch_stat(t0, cur, st);
+        }
         if (t0 + 1 < t1) fetch(t0 + 1, nxt);
     }
     wait_vmem();

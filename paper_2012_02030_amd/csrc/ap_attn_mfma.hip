@@ -157,6 +157,13 @@ __global__ __launch_bounds__(64 * NW * TEAMS, (D <= 64 && STAGES == 1) ? 3 : 2) 
     constexpr int RPI = 64 / (D / 8);                        // tile rows per load instruction
     const int g_row = lane / (D / 8);                        // this lane's row inside a load instruction
 
+    // The first keys of the first two tiles come by scalar loads, so that the first tile is requested without a wait for
+    // the Q rows, which were requested before it (vector loads return in order).
+    int first_start = 0, second_start = 0;
+    if (SCHED && nt > 0) {
+        first_start = a.sched.start[t_begin];
+        second_start = a.sched.start[t_begin + (nt > 1 ? 1 : 0)];
+    }
     // The first key of every tile of the block row (>= 0, or -1 for a gathered entry) is kept in
     // registers, one tile per lane and 128 tiles at a time, and handed out with v_readlane: a
     // memory load of a start inside the loop would have to be waited for, and that wait would
@@ -408,7 +415,7 @@ __global__ __launch_bounds__(64 * NW * TEAMS, (D <= 64 && STAGES == 1) ? 3 : 2) 
         // current one is computed; one barrier per tile.
         int k0_next = 0;                                     // start of the tile whose loads were issued last
         if (nt > 0) {
-            k0_next = tile_start(0);
+            k0_next = SCHED ? first_start : tile_start(0);
             if (SCHED && k0_next < 0) {                      // the very first entry is gathered: fetch its keys
                 dma_cols(0, 0);
                 wait_vmem();
@@ -417,7 +424,7 @@ __global__ __launch_bounds__(64 * NW * TEAMS, (D <= 64 && STAGES == 1) ? 3 : 2) 
             }
             issue_tile(k0_next, gidx, lds);
             dma_words(0, 0);
-            if (SCHED && nt > 1 && tile_start(1) < 0) dma_cols(1, 1);
+            if (SCHED && nt > 1 && second_start < 0) dma_cols(1, 1);
         }
         settle_q();
         for (int it = 0; it < nt; ++it) {
@@ -458,7 +465,7 @@ __global__ __launch_bounds__(64 * NW * TEAMS, (D <= 64 && STAGES == 1) ? 3 : 2) 
         int s_cur = 0, s_nxt = 0;                            // starts of tile it and tile it + 1
         int rounds = nt;                                     // the same for both teams
         if (TEAMS > 1) {
-            if (nt > 0 && SCHED) s_cur = tile_start(0);
+            if (SCHED) s_cur = first_start;
             if (lane == 0 && wave == 0) s_rounds[team] = nt;
             if (SCHED && s_cur < 0) dma_cols(0, 0);          // the very first entry is gathered: fetch its keys
             wait_vmem();
@@ -467,7 +474,7 @@ __global__ __launch_bounds__(64 * NW * TEAMS, (D <= 64 && STAGES == 1) ? 3 : 2) 
             if (SCHED && s_cur < 0) read_cols(0, gcur);
         }
         if (nt > 0) {
-            s_cur = tile_start(0);
+            s_cur = SCHED ? first_start : tile_start(0);
             if (TEAMS == 1 && SCHED && s_cur < 0) {          // the very first entry is gathered: fetch its keys
                 dma_cols(0, 0);
                 wait_vmem();
@@ -478,7 +485,7 @@ __global__ __launch_bounds__(64 * NW * TEAMS, (D <= 64 && STAGES == 1) ? 3 : 2) 
             else issue_gather_loads<D, NW, false>(k_rsrc, Ks, gcur, sk_bytes, wave, lane);
             dma_words(0, 0);
             if (nt > 1) {
-                s_nxt = tile_start(1);
+                s_nxt = SCHED ? second_start : tile_start(1);
                 if (SCHED && s_nxt < 0) dma_cols(1, 1);
             }
         }

@@ -468,7 +468,7 @@ ap_status ap_sparse_attn_bwd_sched(const void *Q, const void *K, const void *V, 
  *                 16-byte aligned (gbar)
  *   everything else as in ap_sparse_attn_bwd_sched
  *
- * Supported: dtype = AP_BF16, D in {32, 64, 128}, block_m = block_n = 64.  Three launches (gbar,
+ * Supported: dtype = AP_BF16, D in {32, 64, 128}, block_m = block_n = 64.  Two launches (gbar and
  * dQ, dK/dV).  Deterministic.
  * ------------------------------------------------------------------------------------------- */
 size_t ap_entmax15_bwd_workspace_bytes(int B, int H, int Lq);

@@ -38,10 +38,10 @@ using namespace mfma;
 // What the kernels compute per entry.  SOFTMAX: P = exp(s - lse), dS = P (dP - delta) with the
 // per-query statistics lse and delta = <dO, O>.  ENTMAX15 (the 1.5-entmax normaliser of Section 6):
 // u = [s / 2 - tau]_+, P = u^2, dS = u (dP - gbar) with the per-query statistics tau (from the
-// forward pass) and gbar = sum_j u_j dP_j / sum_j u_j, which GBAR, a dQ-shaped pass that stops
-// before the last product, computes first.  For the two entmax modes BwdArgs::lse holds tau and
-// BwdArgs::delta holds gbar.
-enum { SOFTMAX = 0, ENTMAX15 = 1, GBAR = 2 };
+// forward pass) and gbar = sum_j u_j dP_j / sum_j u_j: the dQ kernel walks a block row's entries twice, first for
+// gbar (two products of three), then for dQ.  There BwdArgs::lse holds tau and BwdArgs::delta gets gbar.  (The
+// first walk as a launch of its own: B4 H16 L2048 D128 40 us + 52 for dQ, 72 in one.)
+enum { SOFTMAX = 0, ENTMAX15 = 1 };
 
 __device__ __forceinline__ float lse2_of(float lse) { return lse == -INFINITY ? INFINITY : lse * kLog2e; }
 
@@ -130,6 +130,10 @@ __global__ __launch_bounds__(256, 2) void bwd_dq_sched_kernel(
     // A first entry of 64 consecutive keys is requested before anything else: its start is a scalar load, so this waits for
     // no vector load.
     const int start0 = t0 < t1 ? p_start[t0] : -1;
+    // step i of the walks is entry i % (t1 - t0)
+    constexpr int WALKS = MODE == ENTMAX15 ? 2 : 1;
+    const int n_entries = t1 - t0, steps = WALKS * n_entries;
+    auto entry_of = [&](int i) { return t0 + (WALKS > 1 && i >= n_entries ? i - n_entries : i); };
     Meta cur, nxt;
     cur.start = start0;
     cur.key = 0;
@@ -140,10 +144,10 @@ __global__ __launch_bounds__(256, 2) void bwd_dq_sched_kernel(
     issue_tile_loads<D, 4, SWZ_BOTH>(q_rsrc, lds + STAGE, qb * 64, sq_bytes, wave, lane);
     issue_tile_loads<D, 4, SWZ_BOTH>(g_rsrc, lds + STAGE + TILE, qb * 64, so_bytes, wave, lane);
     const size_t stat_base = ((size_t)b * a.H + h) * a.Lq;
-    // SOFTMAX: log-sum-exp; entmax modes: tau (+inf for a query without keys) and gbar.  Loaded for every
+    // SOFTMAX: log-sum-exp; ENTMAX15: tau (+inf for a query without keys).  Loaded for every
     // lane and looked at later: a branch on the row would wait here, before the first tile is requested.
     float lse2 = a.lse[stat_base + (row_ok ? qrow : a.Lq - 1)];
-    float delta = MODE == ENTMAX15 ? a.delta[stat_base + (row_ok ? qrow : a.Lq - 1)] : 0.f;
+    float delta = 0.f;                                       // ENTMAX15: gbar, from the second walk on
     // delta = <dO, O> is formed here, where dO is at hand (a pass of its own reads dO once more).  The dK, dV
     // kernel reads it from memory.
     constexpr int CPR = D / 8, NO = 64 * CPR / 256;          // 16-byte pieces of a row; pieces of O per thread
@@ -159,10 +163,10 @@ __global__ __launch_bounds__(256, 2) void bwd_dq_sched_kernel(
     nxt = cur;
     if (t0 < t1) {
         if (start0 < 0) issue(cur, 0);
-        if (t0 + 1 < t1) fetch(t0 + 1, nxt);
+        if (WALKS > 1 || t0 + 1 < t1) fetch(entry_of(1), nxt);
     }
     const float sc = MODE == SOFTMAX ? a.scale * kLog2e : a.scale * 0.5f;
-    float num = 0.f, den = 0.f;                              // GBAR: this lane's share of sum u dP and sum u
+    float num = 0.f, den = 0.f;                              // first walk: this lane's share of sum u dP and sum u
     const int k_row = kh * 32 + n;
     const int k_swz = hh ^ swz_u<D>(n);
     const TrReadU<D> tr = make_tr_read_u<D>(lane);
@@ -203,46 +207,7 @@ __global__ __launch_bounds__(256, 2) void bwd_dq_sched_kernel(
         delta = s_pair[0][0][brow];
     }
 
-    int stage = 0;
-    for (int t = t0; t < t1; ++t) {
-        wait_vmem();                                         // entry t and the metadata of t + 1 have landed
-        __syncthreads();                                     // ... for everybody; the other stage is free
-        const uint32_t word = cur.word;
-        if (t + 1 < t1) {
-            issue(nxt, stage ^ 1);
-            cur = nxt;
-            if (t + 2 < t1) fetch(t + 2, nxt);
-        }
-        if (__ballot(word != 0) != 0) {
-            uint16_t* base = smem + stage * STAGE;
-            f32x16 s, p;
-            two_products_32<D>(base, base + TILE, k_row, k_swz, qreg, greg, s, p);   // S^T = K Q^T, dP^T = V dO^T
-            const int wbits = (int)(word >> (4 * hh));
-#pragma unroll
-            for (int i = 0; i < 16; ++i) {
-                const uint32_t keep = (uint32_t)__builtin_amdgcn_sbfe(wbits, 8 * (i / 4) + (i % 4), 1);
-                const float x = fmaf(s[i], sc, -lse2);
-                if (MODE == SOFTMAX) {
-                    s[i] = __builtin_amdgcn_exp2f(or_minus_inf(x, keep)) * (p[i] - delta);   // dS^T
-                } else {
-                    const float u = fmaxf(__uint_as_float(__float_as_uint(x) & keep), 0.f);   // pruned: 0
-                    if (MODE == GBAR) {
-                        num = fmaf(u, p[i], num);
-                        den += u;
-                    } else {
-                        s[i] = u * (p[i] - delta);           // dS^T
-                    }
-                }
-            }
-            if (MODE != GBAR) {
-                bf16x8 pb[2];
-                to_operands(s, pb);
-                tr_mm_32<D>(lds + stage * STAGE + kh * 32 * D, pb, dqacc, tr);   // dQ^T += K^T dS^T
-            }
-        }
-        stage ^= 1;
-    }
-    if (MODE == GBAR) {                                      // half-wavefronts and key halves hold different keys
+    auto set_gbar = [&]() {                                  // half-wavefronts and key halves hold different keys
         num += __shfl_xor(num, 32, 64);
         den += __shfl_xor(den, 32, 64);
         if (hh == 0) {
@@ -252,9 +217,57 @@ __global__ __launch_bounds__(256, 2) void bwd_dq_sched_kernel(
         __syncthreads();
         num = s_pair[0][0][brow] + s_pair[1][0][brow];
         den = s_pair[0][1][brow] + s_pair[1][1][brow];
-        if (row_ok && hh == 0 && kh == 0) a.delta[stat_base + qrow] = den > 0.f ? num / den : 0.f;
-        return;
+        delta = den > 0.f ? num / den : 0.f;
+        if (row_ok && hh == 0 && kh == 0) a.delta[stat_base + qrow] = delta;
+    };
+    int stage = 0;
+    for (int i = 0; i < steps; ++i) {
+        wait_vmem();                                         // this entry and the metadata of the next have landed
+        __syncthreads();                                     // ... for everybody; the other stage is free
+        const uint32_t word = cur.word;
+        if (i + 1 < steps) {
+            issue(nxt, stage ^ 1);
+            cur = nxt;
+            if (i + 2 < steps) fetch(entry_of(i + 2), nxt);
+        }
+        int first_walk = WALKS > 1 && i < n_entries;
+        asm volatile("" : "+v"(first_walk));                 // one loop, not one per walk: their addresses do not fit twice
+        if (MODE == ENTMAX15 && i == n_entries) set_gbar();
+        if (__ballot(word != 0) != 0) {
+            uint16_t* base = smem + stage * STAGE;
+            f32x16 s, p;
+            two_products_32<D>(base, base + TILE, k_row, k_swz, qreg, greg, s, p);   // S^T = K Q^T, dP^T = V dO^T
+            const int wbits = (int)(word >> (4 * hh));
+            if (MODE == ENTMAX15) {
+#pragma unroll
+                for (int k = 0; k < 16; ++k) {               // u, pruned: 0
+                    const uint32_t keep = (uint32_t)__builtin_amdgcn_sbfe(wbits, 8 * (k / 4) + (k % 4), 1);
+                    s[k] = fmaxf(__uint_as_float(__float_as_uint(fmaf(s[k], sc, -lse2)) & keep), 0.f);
+                }
+            }
+            if (MODE == ENTMAX15 && __builtin_amdgcn_readfirstlane(first_walk)) {
+#pragma unroll
+                for (int k = 0; k < 16; ++k) {
+                    num = fmaf(s[k], p[k], num);
+                    den += s[k];
+                }
+            } else {
+#pragma unroll
+                for (int k = 0; k < 16; ++k) {
+                    if (MODE == SOFTMAX) {
+                        const uint32_t keep = (uint32_t)__builtin_amdgcn_sbfe(wbits, 8 * (k / 4) + (k % 4), 1);
+                        s[k] = __builtin_amdgcn_exp2f(or_minus_inf(fmaf(s[k], sc, -lse2), keep));
+                    }
+                    s[k] *= p[k] - delta;                    // dS^T
+                }
+                bf16x8 pb[2];
+                to_operands(s, pb);
+                tr_mm_32<D>(lds + stage * STAGE + kh * 32 * D, pb, dqacc, tr);   // dQ^T += K^T dS^T
+            }
+        }
+        stage ^= 1;
     }
+    if (MODE == ENTMAX15 && n_entries == 0) set_gbar();      // (0, which the dK, dV kernel does not look at)
     __syncthreads();                                         // all wavefronts are done with the tiles
     const int row0 = qb * 64 + qh * 32;
     store_key_halves<D>(smem, dqacc, wave, lane, a.scale, dQp + (size_t)row0 * a.sq[2], a.sq[2], a.Lq - row0);
@@ -532,9 +545,8 @@ hipError_t launch_d(const BwdArgs& a, bool dq, bool dkv, hipStream_t stream)
         return hipGetLastError();
     };
     hipError_t e = hipSuccess;
-    if (a.entmax) {                                          // gbar first, then the two gradient kernels
-        e = run_dq(bwd_dq_sched_kernel<D, GBAR>);
-        if (e == hipSuccess) e = run_dq(bwd_dq_sched_kernel<D, ENTMAX15>);
+    if (a.entmax) {                                          // the dQ kernel leaves gbar for the other
+        e = run_dq(bwd_dq_sched_kernel<D, ENTMAX15>);
         return e == hipSuccess ? run_dkv(bwd_dkv_sched_kernel<D, ENTMAX15>) : e;
     }
     if (dq) e = run_dq(bwd_dq_sched_kernel<D, SOFTMAX>);

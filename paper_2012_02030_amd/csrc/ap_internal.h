@@ -115,7 +115,7 @@ struct BwdArgs {
 };
 hipError_t launch_bwd(const BwdArgs& a, hipStream_t stream);
 // the kernels that walk schedules (ap_attn_bwd_sched.hip); softmax: dq writes delta, dkv reads it;
-// entmax: runs the gbar pass and both gradient kernels whatever dq and dkv say
+// entmax: runs both gradient kernels whatever dq and dkv say (dq writes gbar, dkv reads it)
 hipError_t launch_bwd_sched(const BwdArgs& a, bool dq, bool dkv, hipStream_t stream);
 // short sequences in one launch, over the layout's bitmaps (ap_attn_bwd_short.hip)
 bool bwd_short_fits(const BwdArgs& a);

@@ -22,11 +22,11 @@
 //               tau, every step confirmed.
 //
 // A workgroup of four wavefronts takes a block row, a wavefront a 32 x 32 quarter of every entry.  The scores of up to
-// eight entries stay in registers (16 per entry and lane, 128 of 256): K is read once, a Newton step is three vector
+// E (5 to 8) entries stay in registers, 16 per entry and lane: K is read once, a Newton step is three vector
 // instructions per score and an exchange of the key halves through LDS, and V travels under the steps.  Of longer
-// block rows the first four or six entries are held and the others' scores are formed again in every sweep, as all
-// were before.  B4 H16 L2048 D128 (3.9 entries a block row) 112 -> 64 us, B32 H8 117 x 141 D64 25 -> 12; 32 entries
-// a block row, D = 128 650 -> 628 us (D = 32, where the sweeps alone ran four wavefronts per SIMD, 228 -> 237).
+// block rows the first HL entries are held and the others' scores are formed again in every sweep, as all were before.
+// B4 H16 L2048 (3.9 entries a block row) D128 112 -> 64 us, D64 78 -> 42; B32 H8 117 x 141 D64 25 -> 12; 32 entries
+// a block row D128 650 -> 628, D64 473 -> 415; without schedules (up to 32 tiles) D128 472 -> 370.
 //
 // Same operand layouts and LDS-direct loads as the softmax kernel; walks the layout's 64x64 tiles or, if given, the
 // entries of its visit schedule.
@@ -46,7 +46,6 @@ constexpr float kEntmaxTol = 1e-5f;          // on sum p - 1
 constexpr float kEntmaxEarly = 1e-2f;        // residual from which one more step is taken unconfirmed
 constexpr float kEntmaxLeft = 1e-4f;         // largest residual that such a step may leave
 constexpr int kEntmaxMaxIter = 60;
-constexpr int kEntmaxHeld = 8;               // entries of a block row whose scores stay in registers
 
 // s[32 x 32] = T * B^T for 32 rows of a tile in LDS (SWZ_BOTH; `row` is this lane's row) and an operand in registers.
 template <int D>
@@ -125,10 +124,10 @@ __device__ __forceinline__ float both_halves_sum(float v)
 
 // LDS of a workgroup: four tiles (a ring of three and the Q rows), gather keys of the held entries, and what the key
 // halves of a query exchange, by parity.
-template <int D>
+template <int D, int E>
 struct EntmaxLds {
     uint16_t tiles[4 * kBN * D];
-    int32_t cols[kEntmaxHeld][64];
+    int32_t cols[E][64];
     float2 pair[2][2][64];
     uint32_t pend[2][4];
 };
@@ -136,13 +135,13 @@ struct EntmaxLds {
 // One wavefront's view of its workgroup's block row.  Four wavefronts: `qh` and `kh` say which 32 x 32 quarter of
 // every entry this one forms.  Entries are those of the visit schedule (runs of 64 consecutive keys or 64 gathered
 // keys, causal limit already folded into their bitmaps), or the layout's tiles.
-template <int D>
+template <int D, int E>
 struct EntmaxRow {
     static constexpr int TILE = kBN * D, KSTEPS = D / 16, DBLK = D / 32;
     static constexpr int RPI = 64 / (D / 8);                 // tile rows per load instruction
     static constexpr int NLOAD = (D / 8) / 4;                // load instructions per wavefront and tile
     const FwdArgs& a;
-    EntmaxLds<D>& m;
+    EntmaxLds<D, E>& m;
     lds_u16* lds;
     int wave, lane, n, hh, qh, kh, brow, k_swz;
     int t0, ne;
@@ -158,7 +157,7 @@ struct EntmaxRow {
     float tau = -1.f, mc = 0.f, psum = 0.f;
     bool empty = true;
 
-    __device__ __forceinline__ EntmaxRow(const FwdArgs& args, EntmaxLds<D>& mem, int tid_, int b, int h, int qb, int t0_,
+    __device__ __forceinline__ EntmaxRow(const FwdArgs& args, EntmaxLds<D, E>& mem, int tid_, int b, int h, int qb, int t0_,
                                          int ne_)
         : a(args), m(mem), lds((lds_u16*)mem.tiles), t0(t0_), ne(ne_)
     {
@@ -182,7 +181,10 @@ struct EntmaxRow {
         words = (const uint32_t*)(use_sched ? a.sched.bitmaps : a.bitmaps);
         tr = make_tr_read_u<D>(lane);
     }
-    __device__ __forceinline__ int first_key(int t) const { return use_sched ? a.sched.start[t] : a.col_idx[t] * kBN; }
+    // what says where an entry starts, and its first key (-1: gathered); apart, so that nothing waits for the first
+    __device__ __forceinline__ int raw_start(int t) const { return use_sched ? a.sched.start[t] : a.col_idx[t]; }
+    __device__ __forceinline__ int key_of(int raw) const { return use_sched ? raw : raw * kBN; }
+    __device__ __forceinline__ int first_key(int t) const { return key_of(raw_start(t)); }
     // this lane's half of its bitmap word; without a schedule the causal limit is still to be applied
     __device__ __forceinline__ uint32_t raw_word(int t) const { return words[((size_t)t * 64 + brow) * 2 + kh]; }
     __device__ __forceinline__ uint32_t visible(uint32_t w, int k0) const
@@ -268,11 +270,11 @@ struct EntmaxRow {
     }
 };
 
-// A block row of at most kEntmaxHeld entries: every score stays in registers.  False: an unconfirmed step left too much.
-template <int D>
-__device__ __forceinline__ bool entmax_short_row(EntmaxRow<D>& w, f32x16* oacc)
+// A block row of at most E entries: every score stays in registers.  False: an unconfirmed step left too much.
+template <int D, int E>
+__device__ __forceinline__ bool entmax_short_row(EntmaxRow<D, E>& w, f32x16* oacc)
 {
-    constexpr int E = kEntmaxHeld, NS = 3, TILE = kBN * D, NLOAD = EntmaxRow<D>::NLOAD;
+    constexpr int NS = 3, TILE = kBN * D, NLOAD = EntmaxRow<D, E>::NLOAD;
     const uint16_t* tiles = w.m.tiles;
     const int ne = w.ne;
     const int start_l = w.lane < ne ? w.first_key(w.t0 + w.lane) : 0;   // lane e: first key of entry e
@@ -321,7 +323,7 @@ __device__ __forceinline__ bool entmax_short_row(EntmaxRow<D>& w, f32x16* oacc)
     f32x16 y[E];
     float m = -INFINITY;
     {
-        bf16x8 qreg[EntmaxRow<D>::KSTEPS];
+        bf16x8 qreg[EntmaxRow<D, E>::KSTEPS];
 #pragma unroll
         for (int e = 0; e < E; ++e) {
             if (e >= ne) continue;
@@ -382,17 +384,17 @@ __device__ __forceinline__ bool entmax_short_row(EntmaxRow<D>& w, f32x16* oacc)
 
 // Any number of entries: the scores of the first HL stay in registers, those of the others are formed again in every
 // sweep.  `confirm`: no Newton step is the last one before its result has been looked at.
-template <int D, int HL>
-__device__ __forceinline__ void entmax_long_row(EntmaxRow<D>& w, f32x16* oacc, bool confirm)
+template <int D, int HL, int E>
+__device__ __forceinline__ void entmax_long_row(EntmaxRow<D, E>& w, f32x16* oacc, bool confirm)
 {
-    constexpr int TILE = kBN * D, NLOAD = EntmaxRow<D>::NLOAD;
+    constexpr int TILE = kBN * D, NLOAD = EntmaxRow<D, E>::NLOAD;
     uint16_t* tiles = w.m.tiles;
     const int t_end = w.t0 + w.ne, t_begin = w.t0 + HL;
     // a zero the compiler cannot see through: indexed with it, what is loaded inside a loop is a vector load (a scalar
     // load would make every later wait for an LDS read wait for memory too)
     int vzero = 0;
     asm volatile("" : "+v"(vzero));
-    bf16x8 qreg[EntmaxRow<D>::KSTEPS];
+    bf16x8 qreg[EntmaxRow<D, E>::KSTEPS];
     wait_vmem();
     __syncthreads();                                         // Q rows have landed
     read_operand<D>(tiles + 3 * TILE, w.brow, w.k_swz, qreg);
@@ -409,7 +411,7 @@ __device__ __forceinline__ void entmax_long_row(EntmaxRow<D>& w, f32x16* oacc, b
 #pragma unroll
             for (int j = 0; j < 2; ++j) {
                 const int tt = min(t + j, t_end - 1) + vzero;
-                start[j] = w.first_key(tt);
+                start[j] = w.raw_start(tt);
                 if (w.use_sched) key[j] = w.a.sched.cols[(size_t)tt * 64 + w.lane];
                 fetched[j] = w.raw_word(tt);
             }
@@ -417,7 +419,7 @@ __device__ __forceinline__ void entmax_long_row(EntmaxRow<D>& w, f32x16* oacc, b
         auto issue = [&](int t, int to) {
 #pragma unroll
             for (int j = 0; j < 2; ++j) {
-                const int k0 = __builtin_amdgcn_readfirstlane(start[j]);
+                const int k0 = w.key_of(__builtin_amdgcn_readfirstlane(start[j]));
                 ahead[j] = t + j < t_end ? w.visible(fetched[j], k0) : 0;
                 if (t + j >= t_end) continue;
                 int gk[NLOAD];
@@ -547,11 +549,12 @@ __device__ __forceinline__ void entmax_long_row(EntmaxRow<D>& w, f32x16* oacc, b
     w.set_psum();
 }
 
-template <int D>
-__global__ __launch_bounds__(256, 2) void entmax15_fwd_kernel(FwdArgs a, float* tau_out, int nQB, int total)
+// E entries of a short row, the first HL of a longer one are held; W wavefronts per SIMD.
+template <int D, int E, int HL, int W>
+__global__ __launch_bounds__(256, W) void entmax15_fwd_kernel(FwdArgs a, float* tau_out, int nQB, int total)
 {
-    constexpr int HL = D == 128 ? 4 : 6;                      // what fits into 256 registers beside a sweep
-    __shared__ __attribute__((aligned(1024))) EntmaxLds<D> mem;
+    static_assert(HL <= E && HL % 2 == 0, "a longer row has the entries that are held, two of them per step");
+    __shared__ __attribute__((aligned(1024))) EntmaxLds<D, E> mem;
     const int blk = block_index();
     if (blk >= total) return;
     const int bid = xcd_contiguous(blk, total);
@@ -560,12 +563,12 @@ __global__ __launch_bounds__(256, 2) void entmax15_fwd_kernel(FwdArgs a, float* 
     const int b = bid / (nQB * a.H);
     const int tid = threadIdx.x;
     auto load_q = [&]() {                                    // (the last row again beyond Lq)
-        constexpr int RPI = EntmaxRow<D>::RPI;
+        constexpr int RPI = EntmaxRow<D, E>::RPI;
         const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
         const uint16_t* Qp = (const uint16_t*)a.Q + (size_t)b * a.sq[0] + (size_t)h * a.sq[1];
         lds_u16* dst = (lds_u16*)mem.tiles + 3 * kBN * D;
 #pragma unroll
-        for (int u = 0; u < EntmaxRow<D>::NLOAD; ++u) {
+        for (int u = 0; u < EntmaxRow<D, E>::NLOAD; ++u) {
             const int r = (wave + 4 * u) * RPI + lane / (D / 8);
             load16_to_lds(lds_addr_of(dst + (wave + 4 * u) * 512),
                           Qp + (long long)min(qb * 64 + r, a.Lq - 1) * a.sq[2] + ((lane % (D / 8)) ^ swz_u<D>(r)) * 8);
@@ -589,18 +592,18 @@ __global__ __launch_bounds__(256, 2) void entmax15_fwd_kernel(FwdArgs a, float* 
     for (int db = 0; db < D / 32; ++db)
 #pragma unroll
         for (int i = 0; i < 16; ++i) oacc[db][i] = 0.f;
-    EntmaxRow<D> w(a, mem, tid, b, h, qb, t0, ne);
+    EntmaxRow<D, E> w(a, mem, tid, b, h, qb, t0, ne);
     // What the other ways need they form anew from an index that the compiler takes for another one, so that
     // nothing of theirs stays in registers on the first one.
     auto other_view = [&]() {
         int t = tid;
         asm volatile("" : "+v"(t));
-        EntmaxRow<D> v(a, mem, t, b, h, qb, t0, ne);
+        EntmaxRow<D, E> v(a, mem, t, b, h, qb, t0, ne);
         v.par = w.par;
         v.tau = w.tau;
         return v;
     };
-    auto take_over = [&](const EntmaxRow<D>& v) {
+    auto take_over = [&](const EntmaxRow<D, E>& v) {
         w.tau = v.tau;
         w.mc = v.mc;
         w.psum = v.psum;
@@ -608,17 +611,17 @@ __global__ __launch_bounds__(256, 2) void entmax15_fwd_kernel(FwdArgs a, float* 
         w.par = v.par;
     };
     bool fine;
-    if (ne <= kEntmaxHeld) {
-        fine = entmax_short_row<D>(w, oacc);
+    if (ne <= E) {
+        fine = entmax_short_row<D, E>(w, oacc);
     } else {
-        EntmaxRow<D> v = other_view();
+        EntmaxRow<D, E> v = other_view();
         entmax_long_row<D, HL>(v, oacc, false);
         take_over(v);
         fine = !v.left_too_much();
     }
     // An unconfirmed step that left too much: once more, every step confirmed.
     if (__builtin_expect(!fine, 0)) {
-        EntmaxRow<D> v = other_view();
+        EntmaxRow<D, E> v = other_view();
         load_q();                                            // their place may have been used
         entmax_long_row<D, 0>(v, oacc, true);
         take_over(v);
@@ -632,12 +635,26 @@ __global__ __launch_bounds__(256, 2) void entmax15_fwd_kernel(FwdArgs a, float* 
         tau_out[((size_t)b * a.H + h) * a.Lq + row0 + w.n] = w.empty ? INFINITY : w.mc + w.tau;
 }
 
-template <int D>
-hipError_t launch_d(const FwdArgs& a, float* tau_out, hipStream_t stream)
+template <int D, int E, int HL, int W>
+hipError_t launch(const FwdArgs& a, float* tau_out, hipStream_t stream)
 {
     const int nQB = (a.Lq + 63) / 64, total = a.B * a.H * nQB;
-    hipLaunchKernelGGL(entmax15_fwd_kernel<D>, grid_of(total, 256), dim3(256), 0, stream, a, tau_out, nQB, total);
+    hipLaunchKernelGGL((entmax15_fwd_kernel<D, E, HL, W>), grid_of(total, 256), dim3(256), 0, stream, a, tau_out, nQB, total);
     return hipGetLastError();
+}
+
+// No block row has more entries than there are key tiles.  Registers go into entries held or into a third wavefront per
+// SIMD.  At D = 64 with up to six tiles every row fits either way (16 x 12 x 330, all tiles full: 42 us with two
+// wavefronts, 32 with three); with seven or eight only two wavefronts hold them all (500: 60 against 92); beyond that the
+// third is worth more where workgroups come in several rounds (B4 H16, 2048 keys of 3.9 entries a block row 51 against 42,
+// 1500 keys in 24 entries 257 against 227), and the entries are where they do not (8 x 8 x 1000, up to 8 entries 32 against 40).
+hipError_t launch_64(const FwdArgs& a, float* tau_out, hipStream_t stream)
+{
+    const int tiles = (a.Lk + 63) / 64;
+    const long long workgroups = (long long)a.B * a.H * ((a.Lq + 63) / 64);
+    if (tiles <= 6) return launch<64, 6, 0, 3>(a, tau_out, stream);
+    if (tiles <= 8 || workgroups <= 1024) return launch<64, 8, 6, 2>(a, tau_out, stream);
+    return launch<64, 5, 2, 3>(a, tau_out, stream);
 }
 
 }  // namespace
@@ -645,9 +662,9 @@ hipError_t launch_d(const FwdArgs& a, float* tau_out, hipStream_t stream)
 hipError_t launch_entmax15_fwd(const FwdArgs& a, float* tau_out, hipStream_t stream)
 {
     switch (a.D) {
-        case 32: return launch_d<32>(a, tau_out, stream);
-        case 64: return launch_d<64>(a, tau_out, stream);
-        case 128: return launch_d<128>(a, tau_out, stream);
+        case 32: return launch<32, 6, 2, 3>(a, tau_out, stream);
+        case 64: return launch_64(a, tau_out, stream);
+        case 128: return launch<128, 8, 4, 2>(a, tau_out, stream);
     }
     return hipErrorInvalidValue;
 }

@@ -69,8 +69,13 @@ __device__ __forceinline__ float scale_to(float a, float b)
     return a == b ? 1.0f : __builtin_amdgcn_exp2f(a - b);
 }
 
+// The leading arguments repeat fields of `a`: they arrive in registers when a wavefront starts (kernel-argument
+// preloading), which takes a round trip out of the chain.
 template <int D>
-__global__ __launch_bounds__(64 * kWaves) void decode_kernel(FwdArgs a, int nQB)
+__global__ __launch_bounds__(64 * kWaves) void decode_kernel(const int32_t* __restrict__ p_row_ptr,
+                                                             const int32_t* __restrict__ p_col_idx,
+                                                             const uint64_t* __restrict__ p_bitmaps, int p_splits, int p_Lq,
+                                                             int p_H, int p_block_m, int nQB, FwdArgs a)
 {
     constexpr int LPK = D / 8;                               // lanes per key row
     constexpr int SPW = 64 / LPK;                            // streams per wavefront
@@ -89,11 +94,17 @@ __global__ __launch_bounds__(64 * kWaves) void decode_kernel(FwdArgs a, int nQB)
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int sub = lane % LPK;                              // which 8 elements of a row
     const int strm = wave * SPW + lane / LPK;                // this lane's stream
-    const int split = blockIdx.x % a.splits;
-    const int row_id = blockIdx.x / a.splits;
-    const int i = row_id % a.Lq;                             // query
-    const int h = (row_id / a.Lq) % a.H;
-    const int b = row_id / (a.Lq * a.H);
+    const int split = blockIdx.x % p_splits;
+    const int row_id = blockIdx.x / p_splits;
+    const int i = row_id % p_Lq;                             // query
+    const int h = (row_id / p_Lq) % p_H;
+    const int b = row_id / (p_Lq * p_H);
+    const int r = h * nQB + i / p_block_m;
+    const int rr = i % p_block_m;
+    // This workgroup's tiles: every splits-th one, since the tiles near the query hold far more keys than
+    // the others (contiguous shares: the fullest of four has 1.6 times the mean at 16 thousand keys).
+    const int first = p_row_ptr[r] + split;
+    const int ntiles = max(0, (p_row_ptr[r + 1] - first + p_splits - 1) / p_splits);
 
     const uint16_t* Qp = (const uint16_t*)a.Q + (size_t)b * a.sq[0] + (size_t)h * a.sq[1] + (size_t)i * a.sq[2];
     const uint16_t* Kp = (const uint16_t*)a.K + (size_t)b * a.sk[0] + (size_t)h * a.sk[1];
@@ -117,22 +128,16 @@ __global__ __launch_bounds__(64 * kWaves) void decode_kernel(FwdArgs a, int nQB)
 #pragma unroll
     for (int e = 0; e < 8; ++e) o[e] = 0.f;
 
-    const int r = h * nQB + i / a.block_m;
-    const int rr = i % a.block_m;
     const long long diag = (long long)i + ((long long)a.Lk - a.Lq);
-    // This workgroup's tiles: every splits-th one, since the tiles near the query hold far more keys than
-    // the others (contiguous shares: the fullest of four has 1.6 times the mean at 16 thousand keys).
-    const int first = a.row_ptr[r] + split;
-    const int ntiles = max(0, (a.row_ptr[r + 1] - first + a.splits - 1) / a.splits);
 
     for (int c0 = 0; c0 < ntiles; c0 += CHUNK) {             // workgroup-uniform trip count
         // ---- 1. the kept visible keys of tiles c0 .. c0 + CHUNK - 1, ascending, into s_list
         uint32_t bits = 0;                                   // of 8 keys from k0
         int k0 = 0;
         if (c0 + (tid >> 3) < ntiles) {
-            const int t = first + (c0 + (tid >> 3)) * a.splits, byte = tid & 7;
-            k0 = a.col_idx[t] * 64 + 8 * byte;
-            bits = reinterpret_cast<const uint8_t*>(a.bitmaps + (size_t)t * a.block_m + rr)[byte];
+            const int t = first + (c0 + (tid >> 3)) * p_splits, byte = tid & 7;
+            k0 = p_col_idx[t] * 64 + 8 * byte;
+            bits = reinterpret_cast<const uint8_t*>(p_bitmaps + (size_t)t * p_block_m + rr)[byte];
             if (a.causal) {
                 const long long lim = diag - k0;
                 if (lim < 0) bits = 0;
@@ -271,10 +276,13 @@ hipError_t launch_fwd_decode(const FwdArgs& a, hipStream_t stream)
 {
     const int nQB = (a.Lq + a.block_m - 1) / a.block_m;
     const dim3 grid((unsigned)((long long)a.B * a.H * a.Lq * a.splits)), block(64 * kWaves);
+    const auto run = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, grid, block, 0, stream, a.row_ptr, a.col_idx, a.bitmaps, a.splits, a.Lq, a.H, a.block_m, nQB, a);
+    };
     switch (a.D) {
-        case 32: hipLaunchKernelGGL(decode_kernel<32>, grid, block, 0, stream, a, nQB); break;
-        case 64: hipLaunchKernelGGL(decode_kernel<64>, grid, block, 0, stream, a, nQB); break;
-        case 128: hipLaunchKernelGGL(decode_kernel<128>, grid, block, 0, stream, a, nQB); break;
+        case 32: run(decode_kernel<32>); break;
+        case 64: run(decode_kernel<64>); break;
+        case 128: run(decode_kernel<128>); break;
         default: return hipErrorInvalidValue;
     }
     const hipError_t e = hipGetLastError();

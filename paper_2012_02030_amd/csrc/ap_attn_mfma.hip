@@ -632,29 +632,31 @@ hipError_t launch_one(const FwdArgs& a, hipStream_t stream)
 // in flight at a time (bound by memory latency: 8 chunks of 4096 rows
 // of 128 take 5.4 us, 9.0 with one chunk after another).  LOOK: only the chunks whose log-sum-exp says that they
 // hold something are read.
+// The leading arguments repeat fields of `a`, as above.
 template <int D, bool LOOK>
-__global__ __launch_bounds__(256) void merge_splits_kernel(FwdArgs a)
+__global__ __launch_bounds__(256) void merge_splits_kernel(const float* __restrict__ p_part_o,
+                                                           const float* __restrict__ p_part_lse, long long rows,
+                                                           int p_splits, FwdArgs a)
 {
     constexpr int TPR = D / 4;                               // threads per row
     constexpr int U = 8;
-    const long long rows = (long long)a.B * a.H * a.Lq;
     const long long row = ((long long)blockIdx.x * 256 + threadIdx.x) / TPR;
     const int part = threadIdx.x % TPR;
     if (row >= rows) return;
     const auto load = [&](int s) {
-        return *reinterpret_cast<const float4*>(a.part_o + ((size_t)s * rows + row) * D + part * 4);
+        return *reinterpret_cast<const float4*>(p_part_o + ((size_t)s * rows + row) * D + part * 4);
     };
     float mx = -INFINITY, tot = 0.f;
     float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
-    for (int s0 = 0; s0 < a.splits; s0 += U) {
+    for (int s0 = 0; s0 < p_splits; s0 += U) {
         float l[U];
         float4 o[U];
 #pragma unroll
         for (int k = 0; k < U; ++k) {
             l[k] = -INFINITY;
             o[k] = make_float4(0.f, 0.f, 0.f, 0.f);
-            if (s0 + k < a.splits) {
-                l[k] = a.part_lse[(size_t)(s0 + k) * rows + row];
+            if (s0 + k < p_splits) {
+                l[k] = p_part_lse[(size_t)(s0 + k) * rows + row];
                 if (!LOOK) o[k] = load(s0 + k);
             }
         }
@@ -707,8 +709,12 @@ template <int D>
 hipError_t launch_merge_d(const FwdArgs& a, hipStream_t stream)
 {
     const long long wgs = ((long long)a.B * a.H * a.Lq * (D / 4) + 255) / 256;
-    if (wgs > 2048) hipLaunchKernelGGL((merge_splits_kernel<D, true>), dim3((unsigned)wgs), dim3(256), 0, stream, a);
-    else hipLaunchKernelGGL((merge_splits_kernel<D, false>), dim3((unsigned)wgs), dim3(256), 0, stream, a);
+    const auto run = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, dim3((unsigned)wgs), dim3(256), 0, stream, a.part_o, a.part_lse,
+                           (long long)a.B * a.H * a.Lq, a.splits, a);
+    };
+    if (wgs > 2048) run(merge_splits_kernel<D, true>);
+    else run(merge_splits_kernel<D, false>);
     return hipGetLastError();
 }
 

@@ -15,15 +15,15 @@
 // last group; inside a class by tile, then ascending): an isolated connection is used by one
 // query, so most gathered entries then concern one wavefront only and the other one skips them.
 //
-// One workgroup of four wavefronts per block row; a thread stands for one query row and for every fourth
-// tile or entry (every second at block_m = 128).  The bitmap words of a segment of tiles are brought into LDS with all loads
+// One workgroup of eight wavefronts per block row; a thread stands for one query row and for every eighth
+// tile or entry (every fourth at block_m = 128).  The bitmap words of a segment of tiles are brought into LDS with all loads
 // in flight at once; the per-tile decisions are then taken with one lane per tile (column sets by OR
 // over LDS, positions by prefix sums over the lanes), the gathered columns are listed in LDS in their
 // final order, and the words of the gathered entries are assembled from that list, the entries dealt
 // to the wavefronts.  Every decision depends on OR-reductions of the row words only, so the emitted
 // order is fixed: no atomics.  The time is one block row's chain of loads and LDS walks (1024
-// workgroups at 16 heads of 64 x 64 tiles, all resident): 61 us with one wavefront per block row, 26 us
-// with four.
+// workgroups at 16 heads of 64 x 64 tiles, three per compute unit at a time): 61 us with one wavefront per block row,
+// 25.8 with four, 23.6 with eight (block_m = 128 47 and 38, 64 queries over 16384 keys 55 and 45).
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -35,7 +35,7 @@ namespace {
 
 constexpr int kSegWords = 4096;                            // bitmap words of one segment (tiles x rows)
 constexpr int kSegMax = 64;                                // at most this many tiles per segment (block_m = 64)
-constexpr int kThreads = 256;
+constexpr int kThreads = 512;
 
 // inclusive prefix sum over the 64 lanes of a wavefront
 __device__ __forceinline__ int wave_inclusive_scan(int v, int lane)
@@ -69,7 +69,7 @@ __global__ __launch_bounds__(kThreads) void build_schedule_kernel(
     const int qb = r % nQB;
     const int tid = threadIdx.x;
     const int row = tid & (BM - 1);                        // this thread's query row
-    const int parts = kThreads / BM;                       // threads per row: 4 or 2
+    const int parts = kThreads / BM;                       // threads per row: 8 or 4
     const int part = __builtin_amdgcn_readfirstlane(tid / BM);   // the same in a wavefront
     const int lane = tid & 63;
     const int NG = BM / 32;                                // 32-row groups (wavefronts of the attention kernel)
@@ -83,15 +83,15 @@ __global__ __launch_bounds__(kThreads) void build_schedule_kernel(
     auto load_segment = [&](int seg, int n) {
         __syncthreads();                                   // previous use of the LDS arrays is over
         if (tid < n) k0s[tid] = col_idx[seg + tid] * 64;
-        uint64_t w[kSegMax / 4];                           // this thread's tiles part, part + parts, ...: 16 of them
+        uint64_t w[kSegWords / kThreads];                           // this thread's tiles part, part + parts, ...: 8 of them
 #pragma unroll
-        for (int u = 0; u < kSegMax / 4; ++u) {
+        for (int u = 0; u < kSegWords / kThreads; ++u) {
             const int t = u * parts + part;
             w[u] = t < n ? bitmaps[(size_t)(seg + t) * BM + row] : 0ull;
         }
         __syncthreads();
 #pragma unroll
-        for (int u = 0; u < kSegMax / 4; ++u) {
+        for (int u = 0; u < kSegWords / kThreads; ++u) {
             const int t = u * parts + part;
             if (t >= n) break;
             uint64_t word = w[u];

@@ -22,9 +22,12 @@ namespace {
 
 using namespace mfma;
 
-// N: most 32-row blocks of queries and of keys.
+// N: most 32-row blocks of queries and of keys.  The leading arguments repeat fields of `a`: they arrive in registers
+// when a wavefront starts (kernel-argument preloading).
 template <int D, int N>
-__global__ __launch_bounds__(64 * N, 2) void bwd_short_kernel(BwdArgs a, int nq, int nk, int total)
+__global__ __launch_bounds__(64 * N, 2) void bwd_short_kernel(
+    const int32_t* __restrict__ p_row_ptr, const int32_t* __restrict__ p_col_idx, const uint64_t* __restrict__ p_bitmaps,
+    int nq, int nk, int total, int p_B, int p_Lq, BwdArgs a)
 {
     constexpr int KSTEPS = D / 16, DBLK = D / 32;
     constexpr int CPR = D / 8, RPI = 64 / CPR;               // 16-byte pieces of a row; rows per load instruction
@@ -45,8 +48,10 @@ __global__ __launch_bounds__(64 * N, 2) void bwd_short_kernel(BwdArgs a, int nq,
     const int blk = block_index();
     if (blk >= total) return;
     const int bid = xcd_contiguous(blk, total);
-    const int b = bid % a.B;                                 // the examples of a head share its layout
-    const int h = bid / a.B;
+    const int b = bid % p_B;                                 // the examples of a head share its layout
+    const int h = bid / p_B;
+    const int nQB = (p_Lq + 63) / 64;
+    const int first_tile = p_row_ptr[h * nQB];
     const int tid = threadIdx.x;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int lane = tid & 63;
@@ -63,10 +68,8 @@ __global__ __launch_bounds__(64 * N, 2) void bwd_short_kernel(BwdArgs a, int nq,
                           j * RPI * bytes);
         }
     };
-    const int nQB = (a.Lq + 63) / 64;
-    const int first_tile = a.row_ptr[h * nQB];
     int row_end = 0;                                         // lane r: end of block row r's tiles
-    if (lane < nQB) row_end = a.row_ptr[h * nQB + lane + 1];
+    if (lane < nQB) row_end = p_row_ptr[h * nQB + lane + 1];
     load_rows(a.K, a.sk, a.Lk, nk, Ks);
     load_rows(a.V, a.sv, a.Lk, nk, Vs);
     load_rows(a.Q, a.sq, a.Lq, nq, Qs);
@@ -94,8 +97,8 @@ __global__ __launch_bounds__(64 * N, 2) void bwd_short_kernel(BwdArgs a, int nq,
     auto fetch_tile = [&](int t) {
         Tile x = {0, 0};
         if (t < last_tile) {
-            x.kb = a.col_idx[t];
-            x.word = a.bitmaps[(size_t)t * 64 + lane];
+            x.kb = p_col_idx[t];
+            x.word = p_bitmaps[(size_t)t * 64 + lane];
         }
         return x;
     };
@@ -274,9 +277,12 @@ hipError_t launch_d(const BwdArgs& a, hipStream_t stream)
 {
     const int nq = (a.Lq + 63) / 64 * 2, nk = (a.Lk + 31) / 32, total = a.B * a.H;
     const dim3 grid = grid_of(total, 64 * nk), block(64 * nk);
-    if (nq <= 2 && nk <= 2) hipLaunchKernelGGL((bwd_short_kernel<D, 2>), grid, block, 0, stream, a, nq, nk, total);
-    else if (nq <= 4 && nk <= 4) hipLaunchKernelGGL((bwd_short_kernel<D, 4>), grid, block, 0, stream, a, nq, nk, total);
-    else hipLaunchKernelGGL((bwd_short_kernel<D, 8>), grid, block, 0, stream, a, nq, nk, total);
+    const auto run = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, grid, block, 0, stream, a.row_ptr, a.col_idx, a.bitmaps, nq, nk, total, a.B, a.Lq, a);
+    };
+    if (nq <= 2 && nk <= 2) run(bwd_short_kernel<D, 2>);
+    else if (nq <= 4 && nk <= 4) run(bwd_short_kernel<D, 4>);
+    else run(bwd_short_kernel<D, 8>);
     return hipGetLastError();
 }
 

@@ -150,6 +150,8 @@ struct EntmaxRow {
     float c;                                                 // x = c * <q, k>
     int sk_bytes, sv_bytes;
     rsrc_t k_rsrc, v_rsrc;
+    const int32_t* starts;                                   // start of an entry, or block column of a tile
+    const int32_t* cols;                                     // gather keys, or null
     const uint32_t* words;
     TrReadU<D> tr;
     // state of the row
@@ -158,8 +160,8 @@ struct EntmaxRow {
     bool empty = true;
 
     __device__ __forceinline__ EntmaxRow(const FwdArgs& args, EntmaxLds<D, E>& mem, int tid_, int b, int h, int qb, int t0_,
-                                         int ne_)
-        : a(args), m(mem), lds((lds_u16*)mem.tiles), t0(t0_), ne(ne_)
+                                         int ne_, const int32_t* starts_, const int32_t* cols_, const uint32_t* words_)
+        : a(args), m(mem), lds((lds_u16*)mem.tiles), t0(t0_), ne(ne_), starts(starts_), cols(cols_), words(words_)
     {
         wave = __builtin_amdgcn_readfirstlane(tid_ >> 6);
         lane = tid_ & 63;
@@ -169,7 +171,7 @@ struct EntmaxRow {
         kh = wave >> 1;
         brow = qh * 32 + n;
         k_swz = hh ^ swz_u<D>(n);
-        use_sched = a.sched.cnt != nullptr;
+        use_sched = cols != nullptr;
         diag = (long long)qb * 64 + brow + a.Lk - a.Lq;
         c = 0.5f * a.scale;
         sk_bytes = (int)a.sk[2] * 2;
@@ -178,11 +180,10 @@ struct EntmaxRow {
                            (unsigned)((a.Lk - 1) * sk_bytes + D * 2));
         v_rsrc = make_rsrc((const uint16_t*)a.V + (size_t)b * a.sv[0] + (size_t)h * a.sv[1],
                            (unsigned)((a.Lk - 1) * sv_bytes + D * 2));
-        words = (const uint32_t*)(use_sched ? a.sched.bitmaps : a.bitmaps);
         tr = make_tr_read_u<D>(lane);
     }
     // what says where an entry starts, and its first key (-1: gathered); apart, so that nothing waits for the first
-    __device__ __forceinline__ int raw_start(int t) const { return use_sched ? a.sched.start[t] : a.col_idx[t]; }
+    __device__ __forceinline__ int raw_start(int t) const { return starts[t]; }
     __device__ __forceinline__ int key_of(int raw) const { return use_sched ? raw : raw * kBN; }
     __device__ __forceinline__ int first_key(int t) const { return key_of(raw_start(t)); }
     // this lane's half of its bitmap word; without a schedule the causal limit is still to be applied
@@ -285,7 +286,7 @@ __device__ __forceinline__ bool entmax_short_row(EntmaxRow<D, E>& w, f32x16* oac
         if (e < ne) word[e] = w.visible(w.raw_word(w.t0 + e), __builtin_amdgcn_readlane(start_l, e));
     }
     if (w.use_sched)
-        for (int e = w.wave; e < ne; e += 4) w.m.cols[e][w.lane] = w.a.sched.cols[(size_t)(w.t0 + e) * 64 + w.lane];
+        for (int e = w.wave; e < ne; e += 4) w.m.cols[e][w.lane] = w.cols[(size_t)(w.t0 + e) * 64 + w.lane];
     __syncthreads();
     uint32_t live = 0;                                       // bit e: this quarter of entry e keeps something
 #pragma unroll
@@ -412,7 +413,7 @@ __device__ __forceinline__ void entmax_long_row(EntmaxRow<D, E>& w, f32x16* oacc
             for (int j = 0; j < 2; ++j) {
                 const int tt = min(t + j, t_end - 1) + vzero;
                 start[j] = w.raw_start(tt);
-                if (w.use_sched) key[j] = w.a.sched.cols[(size_t)tt * 64 + w.lane];
+                if (w.use_sched) key[j] = w.cols[(size_t)tt * 64 + w.lane];
                 fetched[j] = w.raw_word(tt);
             }
         };
@@ -476,7 +477,7 @@ __device__ __forceinline__ void entmax_long_row(EntmaxRow<D, E>& w, f32x16* oacc
             int gk[NLOAD];
             if (k0 < 0)
 #pragma unroll
-                for (int u = 0; u < NLOAD; ++u) gk[u] = w.a.sched.cols[(size_t)t * 64 + w.load_row(u)];
+                for (int u = 0; u < NLOAD; ++u) gk[u] = w.cols[(size_t)t * 64 + w.load_row(u)];
             w.template issue<true>(v, j, k0, gk);
         }
         wait_vmem();
@@ -549,9 +550,13 @@ __device__ __forceinline__ void entmax_long_row(EntmaxRow<D, E>& w, f32x16* oacc
     w.set_psum();
 }
 
-// E entries of a short row, the first HL of a longer one are held; W wavefronts per SIMD.
+// E entries of a short row, the first HL of a longer one are held; W wavefronts per SIMD.  The leading arguments repeat
+// fields of `a` (p_cnt and p_cols null: the layout's tiles); they arrive in registers when a wavefront starts.
 template <int D, int E, int HL, int W>
-__global__ __launch_bounds__(256, W) void entmax15_fwd_kernel(FwdArgs a, float* tau_out, int nQB, int total)
+__global__ __launch_bounds__(256, W) void entmax15_fwd_kernel(
+    const int32_t* __restrict__ p_row_ptr, const int32_t* __restrict__ p_cnt, const int32_t* __restrict__ p_starts,
+    const int32_t* __restrict__ p_cols, const uint32_t* __restrict__ p_words, int nQB, int total, int p_H, FwdArgs a,
+    float* tau_out)
 {
     static_assert(HL <= E && HL % 2 == 0, "a longer row has the entries that are held, two of them per step");
     __shared__ __attribute__((aligned(1024))) EntmaxLds<D, E> mem;
@@ -559,8 +564,11 @@ __global__ __launch_bounds__(256, W) void entmax15_fwd_kernel(FwdArgs a, float* 
     if (blk >= total) return;
     const int bid = xcd_contiguous(blk, total);
     const int qb = nQB - 1 - (bid % nQB);                    // long causal rows first
-    const int h = (bid / nQB) % a.H;
-    const int b = bid / (nQB * a.H);
+    const int h = (bid / nQB) % p_H;
+    const int b = bid / (nQB * p_H);
+    const int r = h * nQB + qb;
+    const int t0 = p_row_ptr[r];
+    int ne = p_cnt ? p_cnt[r] : p_row_ptr[r + 1] - t0;
     const int tid = threadIdx.x;
     auto load_q = [&]() {                                    // (the last row again beyond Lq)
         constexpr int RPI = EntmaxRow<D, E>::RPI;
@@ -575,30 +583,22 @@ __global__ __launch_bounds__(256, W) void entmax15_fwd_kernel(FwdArgs a, float* 
         }
     };
     load_q();
-    const int r = h * nQB + qb;
-    const int t0 = a.row_ptr[r];
-    int ne;
-    if (a.sched.cnt) {
-        ne = a.sched.cnt[r];
-    } else {
-        int t1 = a.row_ptr[r + 1];
+    if (!p_cnt && a.causal) {                                // columns ascend: hidden tiles are at the end
         const long long block_diag = (long long)qb * 64 + 63 + a.Lk - a.Lq;
-        if (a.causal)                                        // columns ascend: hidden tiles are at the end
-            while (t1 > t0 && (long long)a.col_idx[t1 - 1] * kBN > block_diag) --t1;
-        ne = t1 - t0;
+        while (ne > 0 && (long long)p_starts[t0 + ne - 1] * kBN > block_diag) --ne;
     }
     f32x16 oacc[D / 32];
 #pragma unroll
     for (int db = 0; db < D / 32; ++db)
 #pragma unroll
         for (int i = 0; i < 16; ++i) oacc[db][i] = 0.f;
-    EntmaxRow<D, E> w(a, mem, tid, b, h, qb, t0, ne);
+    EntmaxRow<D, E> w(a, mem, tid, b, h, qb, t0, ne, p_starts, p_cols, p_words);
     // What the other ways need they form anew from an index that the compiler takes for another one, so that
     // nothing of theirs stays in registers on the first one.
     auto other_view = [&]() {
         int t = tid;
         asm volatile("" : "+v"(t));
-        EntmaxRow<D, E> v(a, mem, t, b, h, qb, t0, ne);
+        EntmaxRow<D, E> v(a, mem, t, b, h, qb, t0, ne, p_starts, p_cols, p_words);
         v.par = w.par;
         v.tau = w.tau;
         return v;
@@ -639,7 +639,10 @@ template <int D, int E, int HL, int W>
 hipError_t launch(const FwdArgs& a, float* tau_out, hipStream_t stream)
 {
     const int nQB = (a.Lq + 63) / 64, total = a.B * a.H * nQB;
-    hipLaunchKernelGGL((entmax15_fwd_kernel<D, E, HL, W>), grid_of(total, 256), dim3(256), 0, stream, a, tau_out, nQB, total);
+    const bool sched = a.sched.cnt != nullptr;
+    hipLaunchKernelGGL((entmax15_fwd_kernel<D, E, HL, W>), grid_of(total, 256), dim3(256), 0, stream, a.row_ptr, a.sched.cnt,
+                       sched ? a.sched.start : a.col_idx, sched ? a.sched.cols : nullptr,
+                       (const uint32_t*)(sched ? a.sched.bitmaps : a.bitmaps), nQB, total, a.H, a, tau_out);
     return hipGetLastError();
 }
 

@@ -138,10 +138,10 @@ __device__ __forceinline__ int bits_for(unsigned long long width)   // smallest 
     return width <= 1 ? 0 : 64 - __clzll((long long)(width - 1));
 }
 
-__global__ __launch_bounds__(256) void select_init_kernel(Workspace w, unsigned long long rank, unsigned long long n,
+__global__ __launch_bounds__(256) void select_init_kernel(void* ws, unsigned long long rank, unsigned long long n,
                                                           float* tau_out, int none)
 {
-    uint4* p = reinterpret_cast<uint4*>(w.st);
+    uint4* p = reinterpret_cast<uint4*>(ws);                 // the state is the first block
     for (int i = blockIdx.x * 256 + threadIdx.x; i < (int)(kClearBytes / 16); i += gridDim.x * 256) {
         uint4 v = make_uint4(0, 0, 0, 0);
         if (i == 0) v = make_uint4((uint32_t)rank, (uint32_t)(rank >> 32), (uint32_t)n, (uint32_t)(n >> 32));
@@ -261,6 +261,26 @@ struct Walk {
     int per_head;                // units per head
 };
 
+__host__ __device__ inline Walk walk_of(const float* abar, int H, int Lq, int Lk, int causal)
+{
+    Walk w;
+    w.abar = abar;
+    w.H = H;
+    w.Lq = Lq;
+    w.Lk = Lk;
+    w.causal = causal;
+    w.per_head = causal ? (Lq + 1) / 2 : Lq;
+    w.units = H * w.per_head;
+    return w;
+}
+
+// Kernels take the maps' description and the workspace as these scalars and not as structures: arguments arrive in
+// registers when a wavefront starts (kernel-argument preloading), structures by a round trip to memory first.
+#define AP_WALK_PARAMS const float *p_abar, void *p_ws, int p_H, int p_Lq, int p_Lk, int p_causal
+#define AP_WALK_LOCALS                                             \
+    const Walk w = walk_of(p_abar, p_H, p_Lq, p_Lk, p_causal);     \
+    const Workspace ws = carve(p_ws);
+
 struct Unit {                    // wave-uniform
     const float* row[2];
     long long base[2];           // linear index of the first entry of each row
@@ -353,8 +373,11 @@ __device__ __forceinline__ void for_sample(const Walk& w, const Sample& s, F&& b
     }
 }
 
-__global__ __launch_bounds__(kThreads) void sample_coarse_kernel(Walk w, Sample s, Workspace ws)
+__global__ __launch_bounds__(kThreads) void sample_coarse_kernel(AP_WALK_PARAMS, unsigned long long p_slots,
+                                                             uint32_t p_per_unit, uint32_t p_stride)
 {
+    AP_WALK_LOCALS
+    const Sample s = {p_slots, p_per_unit, p_stride};
     __shared__ uint32_t h[kCoarse];
     const int t = threadIdx.x;
     for (int i = t; i < kCoarse; i += kThreads) h[i] = 0;
@@ -406,8 +429,11 @@ __global__ __launch_bounds__(kThreads) void sample_coarse_kernel(Walk w, Sample 
 }
 
 // `refine`: the first of two sweeps narrows the interval, whatever it holds.
-__global__ __launch_bounds__(kThreads) void sample_fine_kernel(Walk w, Sample s, Workspace ws, int refine)
+__global__ __launch_bounds__(kThreads) void sample_fine_kernel(AP_WALK_PARAMS, unsigned long long p_slots,
+                                                           uint32_t p_per_unit, uint32_t p_stride, int refine)
 {
+    AP_WALK_LOCALS
+    const Sample s = {p_slots, p_per_unit, p_stride};
     __shared__ uint32_t h[kSub];
     const int t = threadIdx.x;
     for (int i = t; i < kSub; i += kThreads) h[i] = 0;
@@ -708,9 +734,9 @@ __device__ __forceinline__ void sweep(const Walk& w, const Workspace& ws, uint8_
     }
 }
 
-__global__ __launch_bounds__(kSweepThreads) void mask_sweep_kernel(Walk w, Workspace ws, uint8_t* mask, float* tau_out,
-                                                                   int again)
+__global__ __launch_bounds__(kSweepThreads) void mask_sweep_kernel(AP_WALK_PARAMS, uint8_t* mask, float* tau_out, int again)
 {
+    AP_WALK_LOCALS
     __shared__ unsigned long long lds[kNarrowBins / 2];
     static_assert(sizeof lds >= kSweepThreads / 64 * kStage * 12, "the staged candidates fit");
     const uint32_t way = ws.st->way;
@@ -719,8 +745,9 @@ __global__ __launch_bounds__(kSweepThreads) void mask_sweep_kernel(Walk w, Works
 }
 
 // The mask where the sweep did not write all of it: the candidates' bytes, or, after the exact way, every entry.
-__global__ __launch_bounds__(kSweepThreads) void mask_finish_kernel(Walk w, Workspace ws, uint8_t* mask)
+__global__ __launch_bounds__(kSweepThreads) void mask_finish_kernel(AP_WALK_PARAMS, uint8_t* mask)
 {
+    AP_WALK_LOCALS
     unsigned long long dummy;
     if (!interval_ok(ws.st, &dummy)) return sweep<KNOWN, kSweepThreads>(w, ws, mask, nullptr, 0, nullptr);
     const uint32_t n = (uint32_t)ws.st->ncand, tau_key = ws.st->tau_key;
@@ -808,8 +835,9 @@ __device__ __forceinline__ void candidate_only(const Workspace& ws, uint32_t* h,
 // costs 4.6 us between its neighbours, as does the mask sweep of the exact way, which shares the launch that
 // writes the candidates' mask bytes (16 x 4096 x 4096 causal: 9 us of a call).
 template <int LEVEL>
-__global__ __launch_bounds__(kThreads) void select_level_kernel(Walk w, Workspace ws, uint8_t* mask, float* tau_out, uint32_t parts)
+__global__ __launch_bounds__(kThreads) void select_level_kernel(AP_WALK_PARAMS, uint8_t* mask, float* tau_out, uint32_t parts)
 {
+    AP_WALK_LOCALS
     constexpr int STEP = 256;                                // entries of a wavefront's step
     constexpr int STEPS = 65535 / (STEP * (kThreads / 64));  // steps of all wavefronts between two moves: 15
     __shared__ __attribute__((aligned(8))) uint32_t h[kExactBins / 2];
@@ -920,17 +948,9 @@ hipError_t launch_prune_mask(const float* abar, int H, int Lq, int Lk, int causa
                              unsigned long long rank, unsigned long long n, bool none, uint8_t* mask,
                              float* tau_out, void* workspace, hipStream_t stream)
 {
-    const Workspace ws = carve(workspace);
-    Walk w;
-    w.abar = abar;
-    w.H = H;
-    w.Lq = Lq;
-    w.Lk = Lk;
-    w.causal = causal;
-    w.per_head = causal ? (Lq + 1) / 2 : Lq;
-    w.units = H * w.per_head;
+    const Walk w = walk_of(abar, H, Lq, Lk, causal);
 
-    hipLaunchKernelGGL(select_init_kernel, dim3(64), dim3(256), 0, stream, ws, rank, n, tau_out, none ? 1 : 0);
+    hipLaunchKernelGGL(select_init_kernel, dim3(64), dim3(256), 0, stream, workspace, rank, n, tau_out, none ? 1 : 0);
     if (none) {
         if (mask)
             hipLaunchKernelGGL(zero_mask_kernel, dim3(2048), dim3(256), 0, stream, mask,
@@ -963,15 +983,17 @@ hipError_t launch_prune_mask(const float* abar, int H, int Lq, int Lk, int causa
     const unsigned egrid = (unsigned)min(256, (w.units + kThreads / 64 - 1) / (kThreads / 64));
     const unsigned cgrid = (unsigned)min(64ull, (n + kThreads - 1) / kThreads);
 
-    hipLaunchKernelGGL(sample_coarse_kernel, dim3(sgrid), dim3(kThreads), 0, stream, w, s, ws);
-    hipLaunchKernelGGL(sample_fine_kernel, dim3(sgrid), dim3(kThreads), 0, stream, w, s, ws, refine ? 1 : 0);
+    hipLaunchKernelGGL(sample_coarse_kernel, dim3(sgrid), dim3(kThreads), 0, stream, abar, workspace, H, Lq, Lk, causal,
+                       s.slots, s.per_unit, s.stride);
+    hipLaunchKernelGGL(sample_fine_kernel, dim3(sgrid), dim3(kThreads), 0, stream, abar, workspace, H, Lq, Lk, causal,
+                       s.slots, s.per_unit, s.stride, refine ? 1 : 0);
     if (refine)
-        hipLaunchKernelGGL(mask_sweep_kernel, dim3(grid), dim3(kSweepThreads), 0, stream, w, ws, mask, tau_out, 1);
-    hipLaunchKernelGGL(mask_sweep_kernel, dim3(grid), dim3(kSweepThreads), 0, stream, w, ws, mask, tau_out, 0);
+        hipLaunchKernelGGL(mask_sweep_kernel, dim3(grid), dim3(kSweepThreads), 0, stream, abar, workspace, H, Lq, Lk, causal, mask, tau_out, 1);
+    hipLaunchKernelGGL(mask_sweep_kernel, dim3(grid), dim3(kSweepThreads), 0, stream, abar, workspace, H, Lq, Lk, causal, mask, tau_out, 0);
     const unsigned lgrid = max(egrid, cgrid);
-    hipLaunchKernelGGL(select_level_kernel<0>, dim3(lgrid), dim3(kThreads), 0, stream, w, ws, mask, tau_out, cgrid);
-    hipLaunchKernelGGL(select_level_kernel<1>, dim3(lgrid), dim3(kThreads), 0, stream, w, ws, mask, tau_out, cgrid);
-    if (mask) hipLaunchKernelGGL(mask_finish_kernel, dim3(256), dim3(kSweepThreads), 0, stream, w, ws, mask);
+    hipLaunchKernelGGL(select_level_kernel<0>, dim3(lgrid), dim3(kThreads), 0, stream, abar, workspace, H, Lq, Lk, causal, mask, tau_out, cgrid);
+    hipLaunchKernelGGL(select_level_kernel<1>, dim3(lgrid), dim3(kThreads), 0, stream, abar, workspace, H, Lq, Lk, causal, mask, tau_out, cgrid);
+    if (mask) hipLaunchKernelGGL(mask_finish_kernel, dim3(256), dim3(kSweepThreads), 0, stream, abar, workspace, H, Lq, Lk, causal, mask);
     return hipGetLastError();
 }
 

@@ -382,7 +382,7 @@ ap_status ap_sparse_attn_entmax15_fwd(const void *Q, const void *K, const void *
  *                 aligned (the row sums of dO * O)
  *
  * Supported: dtype = AP_BF16, D in {32, 64, 128}, block_m = block_n = 64.  Three launches (with a row
- * schedule, below, two).
+ * schedule, below, two; of short sequences, at most 256 queries and keys with D <= 64, one).
  * Deterministic (no floating-point atomics): dQ is formed per block row, dK and dV per block
  * column, each recomputing the scores of its tiles.
  * ------------------------------------------------------------------------------------------- */

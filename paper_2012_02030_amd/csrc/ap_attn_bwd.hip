@@ -5,7 +5,7 @@
 //   dV_j  = sum_i P_ij dO_i          dP_ij = <dO_i, V_j>          delta_i = <dO_i, O_i>
 //   dS_ij = P_ij (dP_ij - delta_i)   dQ_i = scale sum_j dS_ij K_j  dK_j = scale sum_i dS_ij Q_i
 //
-// Three kernels, no floating-point atomics:
+// Three kernels, no floating-point atomics (short sequences take one kernel of their own, ap_attn_bwd_short.hip):
 //   bwd_delta_kernel   delta_i for every (example, head, query)
 //   bwd_dq_kernel      one workgroup per (example, head, two block rows): walks the rows' tiles as
 //                      the forward kernel does (a wavefront owns 32 queries, S^T = K Q^T and

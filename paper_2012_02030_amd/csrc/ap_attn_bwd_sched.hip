@@ -23,6 +23,9 @@
 // 269 -> 230 us; B4 H16 L2048 218 -> 156 us in all.  Of a dQ workgroup's 20 us there, 7 pass before its first
 // entry (a chain of cold loads), 1.5 per entry, 2 in the sum over key halves and the store; of a dK, dV
 // workgroup's 27 us 5.4, 2.4 per entry and 1.5.  Inside an entry the LDS pipe is busy about 70 % of the time.
+// Timed in parts there (dQ / dK, dV, of 174 / 216 us): loads and barriers alone 131 / 138, no entry at all 85 / 74
+// (402 MB read and written once are 80 at the rate of a large copy), no score products 149 / 185, no gradient
+// products 155 / 171.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 

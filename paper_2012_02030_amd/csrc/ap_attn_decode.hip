@@ -18,8 +18,8 @@
 //      those of several workgroups by the split forward call's merge kernel.
 //
 // Bound by the latency of its chain of loads (row bounds, tile words, key list, K and V rows) and by the
-// workgroup with the most keys: B4 H16 D128, 1600 of 16001 keys kept, 4 splits 15.5 us (52 MB of K and V rows,
-// 3.4 TB/s).  With contiguous shares of the tiles, one thread per tile for the list and four keys in flight
+// workgroup with the most keys: B4 H16 D128, 1600 of 16001 keys kept, 4 splits 15.0 us (52 MB of K and V rows,
+// 3.5 TB/s; 15.5 with the arguments read from memory first).  With contiguous shares of the tiles, one thread per tile for the list and four keys in flight
 // per stream 20.9 us.
 #include <hip/hip_runtime.h>
 #include <stdint.h>

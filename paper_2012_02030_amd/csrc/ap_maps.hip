@@ -172,7 +172,9 @@ __global__ __launch_bounds__(512, 4) void map_accumulate_kernel(MapArgs a, int n
     constexpr int KSTEPS = D / 16;
     constexpr int OUT_LD = BK + 4;                           // floats per staged output row (16-byte rows)
     constexpr int OUT_ELEMS = BM * OUT_LD * 2;               // in 2-byte units
-    constexpr int SMEM = 4 * TILE > OUT_ELEMS ? 4 * TILE : OUT_ELEMS;
+    constexpr int STAGES = D <= 64 ? 2 : 1;                  // what fits where the output is staged
+    constexpr int STAGE = 4 * TILE;
+    constexpr int SMEM = STAGES * STAGE > OUT_ELEMS ? STAGES * STAGE : OUT_ELEMS;
     __shared__ __attribute__((aligned(1024))) uint16_t smem[SMEM];
     lds_u16* lds = (lds_u16*)smem;
 
@@ -216,6 +218,7 @@ __global__ __launch_bounds__(512, 4) void map_accumulate_kernel(MapArgs a, int n
     const uint16_t* const q_head = (const uint16_t*)a.Q + (size_t)h * a.sq[1] + (long long)q0 * a.sq[2];
     const int q_last = a.Lq - 1 - q0;
     auto issue = [&](int b) {
+        lds_u16* const to = lds + (b % STAGES) * STAGE;
         const rsrc_t rs = make_rsrc((const uint16_t*)a.K + (size_t)b * a.sk[0] + (size_t)h * a.sk[1], k_bytes);
         int rl = lane / CPR;                                 // addresses are formed anew: held over the loop they
         asm volatile("" : "+v"(rl));                         // would cost registers that there are not
@@ -223,12 +226,12 @@ __global__ __launch_bounds__(512, 4) void map_accumulate_kernel(MapArgs a, int n
 #pragma unroll
         for (int u = 0; u < NL; ++u)
             k_voff[u] = rl * sk_bytes + (cp ^ swz_k<D>(wave * 16 + u * RPI + rl)) * 16;
-        load16_chain<NL, 1024>(lds_addr_of(lds + wave * 16 * D), (key0 + wave * 16) * sk_bytes, RPI * sk_bytes, k_voff, rs);
+        load16_chain<NL, 1024>(lds_addr_of(to + wave * 16 * D), (key0 + wave * 16) * sk_bytes, RPI * sk_bytes, k_voff, rs);
         const uint16_t* const base = q_head + (size_t)b * a.sq[0];
 #pragma unroll
         for (int u = 0; u < NL; ++u) {
             const int r = wave * 16 + u * RPI + rl;
-            load16_to_lds(lds_addr_of(lds + 2 * TILE + wave * 16 * D + u * 512),
+            load16_to_lds(lds_addr_of(to + 2 * TILE + wave * 16 * D + u * 512),
                           base + min(r, q_last) * a.sq[2] + (cp ^ swz_k<D>(r)) * 8);
         }
     };
@@ -240,7 +243,7 @@ __global__ __launch_bounds__(512, 4) void map_accumulate_kernel(MapArgs a, int n
         for (int i = 0; i < 16; ++i) acc[kb][i] = 0.f;
     // S^T of the wavefront's 64 keys and 32 queries: three LDS reads per two matrix instructions
     const int row_chunk = n * D + (hh ^ swz_k<D>(n)) * 8;    // chunk 2 kk of the row: this ^ (16 kk)
-    auto scores = [&]() {
+    auto scores = [&](int b) {
         bf16x8 kr[KSTEPS][2], qr[KSTEPS];
         int rc = row_chunk;
         asm volatile("" : "+v"(rc));
@@ -250,7 +253,7 @@ __global__ __launch_bounds__(512, 4) void map_accumulate_kernel(MapArgs a, int n
 #pragma unroll
             for (int i = 0; i < 16; ++i) s[kb][i] = 0.f;
         auto read_step = [&](int kk) {
-            const uint16_t* p = smem + (rc ^ (16 * kk));
+            const uint16_t* p = smem + (b % STAGES) * STAGE + (rc ^ (16 * kk));
             qr[kk] = *reinterpret_cast<const bf16x8*>(p + 2 * TILE + wq * 32 * D);
             kr[kk][0] = *reinterpret_cast<const bf16x8*>(p + wk * TILE);
             kr[kk][1] = *reinterpret_cast<const bf16x8*>(p + wk * TILE + 32 * D);
@@ -281,24 +284,57 @@ __global__ __launch_bounds__(512, 4) void map_accumulate_kernel(MapArgs a, int n
             for (int i = 0; i < 16; ++i) acc[kb][i] += __builtin_amdgcn_exp2f(fmaf(s[kb][i], sc, -l));
     };
     // One buffer: the next example's rows are requested once every wavefront has its scores and travel under the
-    // exponentials, and under the arithmetic of the other workgroup of the compute unit.
+    // exponentials, and under the arithmetic of the other workgroup of the compute unit.  Two (D <= 64): they travel
+    // under the scores too, with one barrier less (B64 H16 D64 128 x 128 77.9 -> 75.2 us, 256 x 256 87.2 -> 83.8, B256 H8
+    // D32 40 x 40 151 -> 143, against 99.7, 112 and 134 with four wavefronts and query rows in registers).
     issue(0);
     l = lp[0];
     for (int b = 0; b + 1 < a.B; ++b) {
         wait_vmem();                                         // the rows of example b have landed
         asm volatile("" : "+v"(l));
         __syncthreads();                                     // ... for everybody
-        if (seen) scores();
-        __syncthreads();                                     // everybody has read them
-        issue(b + 1);
-        const float lnext = lp[(long long)(b + 1) * a.H * a.Lq];
+        float lnext;
+        auto next = [&]() {
+            issue(b + 1);
+            lnext = lp[(long long)(b + 1) * a.H * a.Lq];
+        };
+        if (STAGES == 2) next();
+        if (seen) scores(b);
+        if (STAGES == 1) {
+            __syncthreads();                                 // everybody has read them
+            next();
+        }
         if (seen) add_exp();
         l = lnext;
     }
     wait_vmem();
     asm volatile("" : "+v"(l));
     __syncthreads();
-    if (seen) scores();
+    if (INIT && a.causal) {
+        // Zeros of the tiles that are hidden as a whole: those of block row nQB - 1 - qb are dealt to the workgroups of
+        // block row qb, which has at least as many visible ones, so they travel beside other tiles' arithmetic (in
+        // workgroups of their own they held places on the compute units: 30 us of 120 at B4 H16 L2048 D128), before the
+        // last scores rather than at the end (B2 H4 8192 x 8192 D32 307 -> 300 us).
+        const int zb = nQB - 1 - qb, z0 = zb * BM;
+        const long long z_vis = min((long long)nKG, ((long long)z0 + (BM - 1) + off) / BK + 1);
+        const long long my_vis = min((long long)nKG, block_last / BK + 1);
+        for (long long zk = z_vis + kg; zk < nKG; zk += my_vis) {
+            float* const z = a.abar + ((size_t)h * a.Lq + z0 + r0) * a.Lk + zk * BK;
+            const int cols = (int)min((long long)BK, a.Lk - zk * BK);
+#pragma unroll
+            for (int pass = 0; pass < 8; ++pass) {
+                if (z0 + r0 + 16 * pass >= a.Lq) continue;
+                if (vec_ok) {
+                    if (c4 < cols) *reinterpret_cast<float4*>(z + c4 + pass * map_step) = make_float4(0.f, 0.f, 0.f, 0.f);
+                } else {
+#pragma unroll
+                    for (int e = 0; e < 4; ++e)
+                        if ((tid & 31) + 32 * e < cols) z[(tid & 31) + 32 * e + pass * map_step] = 0.f;
+                }
+            }
+        }
+    }
+    if (seen) scores(a.B - 1);
     // a tile that lies inside the map and below the causal limit for all its rows takes the
     // branch-free path: all 8 loads of a thread are in flight under the last exponentials
     bool interior = vec_ok && q0 + BM <= a.Lq && (long long)key0 + BK <= a.Lk;
@@ -357,28 +393,6 @@ __global__ __launch_bounds__(512, 4) void map_accumulate_kernel(MapArgs a, int n
                     const float v = fmaf(a.weight, src[(4 * half + p) * 16 * OUT_LD + 32 * e], old[p][e]);
                     if (INIT ? here : kept) map0[c1 + 32 * e + (4 * half + p) * map_step] = kept ? v : 0.f;
                 }
-        }
-    }
-    if (!INIT || !a.causal) return;
-    // Zeros of the tiles that are hidden as a whole: those of block row nQB - 1 - qb are dealt to the workgroups of
-    // block row qb, which has at least as many visible ones, so they travel beside other tiles' arithmetic (in
-    // workgroups of their own they held places on the compute units: 30 us of 120 at B4 H16 L2048 D128).
-    const int zb = nQB - 1 - qb, z0 = zb * BM;
-    const long long z_vis = min((long long)nKG, ((long long)z0 + (BM - 1) + off) / BK + 1);
-    const long long my_vis = min((long long)nKG, block_last / BK + 1);
-    for (long long zk = z_vis + kg; zk < nKG; zk += my_vis) {
-        float* const z = a.abar + ((size_t)h * a.Lq + z0 + r0) * a.Lk + zk * BK;
-        const int cols = (int)min((long long)BK, a.Lk - zk * BK);
-#pragma unroll
-        for (int pass = 0; pass < 8; ++pass) {
-            if (z0 + r0 + 16 * pass >= a.Lq) continue;
-            if (vec_ok) {
-                if (c4 < cols) *reinterpret_cast<float4*>(z + c4 + pass * map_step) = make_float4(0.f, 0.f, 0.f, 0.f);
-            } else {
-#pragma unroll
-                for (int e = 0; e < 4; ++e)
-                    if ((tid & 31) + 32 * e < cols) z[(tid & 31) + 32 * e + pass * map_step] = 0.f;
-            }
         }
     }
 }

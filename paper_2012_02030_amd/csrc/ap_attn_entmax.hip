@@ -647,7 +647,8 @@ hipError_t launch(const FwdArgs& a, float* tau_out, hipStream_t stream)
 }
 
 // No block row has more entries than there are key tiles.  Registers go into entries held or into a third wavefront per
-// SIMD.  At D = 64 with up to six tiles every row fits either way (16 x 12 x 330, all tiles full: 42 us with two
+// SIMD.  With up to two tiles two entries are all there is, and a fourth wavefront fits (the same at D = 32: B256 H8 40 x 40
+// 20.7 us with room for six entries, 16.5 with two).  At D = 64 with up to six tiles every row fits either way (16 x 12 x 330, all tiles full: 42 us with two
 // wavefronts, 32 with three); with seven or eight only two wavefronts hold them all (500: 60 against 92); beyond that the
 // third is worth more where workgroups come in several rounds (B4 H16, 2048 keys of 3.9 entries a block row 51 against 42,
 // 1500 keys in 24 entries 257 against 227), and the entries are where they do not (8 x 8 x 1000, up to 8 entries 32 against 40).
@@ -655,6 +656,7 @@ hipError_t launch_64(const FwdArgs& a, float* tau_out, hipStream_t stream)
 {
     const int tiles = (a.Lk + 63) / 64;
     const long long workgroups = (long long)a.B * a.H * ((a.Lq + 63) / 64);
+    if (tiles <= 2) return launch<64, 2, 0, 4>(a, tau_out, stream);
     if (tiles <= 6) return launch<64, 6, 0, 3>(a, tau_out, stream);
     if (tiles <= 8 || workgroups <= 1024) return launch<64, 8, 6, 2>(a, tau_out, stream);
     return launch<64, 5, 2, 3>(a, tau_out, stream);
@@ -665,7 +667,9 @@ hipError_t launch_64(const FwdArgs& a, float* tau_out, hipStream_t stream)
 hipError_t launch_entmax15_fwd(const FwdArgs& a, float* tau_out, hipStream_t stream)
 {
     switch (a.D) {
-        case 32: return launch<32, 6, 2, 3>(a, tau_out, stream);
+        case 32:
+            if (a.Lk <= 128) return launch<32, 2, 0, 4>(a, tau_out, stream);   // as in launch_64
+            return launch<32, 6, 2, 3>(a, tau_out, stream);
         case 64: return launch_64(a, tau_out, stream);
         case 128: return launch<128, 8, 4, 2>(a, tau_out, stream);
     }

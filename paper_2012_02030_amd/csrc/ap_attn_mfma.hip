@@ -55,11 +55,8 @@ using namespace mfma;
 // the first 16 dwords of the argument block to a wavefront in registers when it starts, so the
 // loads of the block row's pointer and count go out at once instead of after a first round trip
 // for the argument block (the structure itself is too large to be preloaded).
-//
-// TEAMS = 2 (with SPLIT and one stage): two teams of NW wavefronts, each with LDS of its own, take one half of the
-// chunk's entries each and add up at the end.  The barriers are common, so the team with fewer entries goes along.
-template <int D, int NW, int STAGES, bool SCHED, bool SPLIT = false, int TEAMS = 1>
-__global__ __launch_bounds__(64 * NW * TEAMS, (D <= 64 && STAGES == 1) ? 3 : 2) void fwd_mfma_kernel(
+template <int D, int NW, int STAGES, bool SCHED, bool SPLIT = false>
+__global__ __launch_bounds__(64 * NW, (D <= 64 && STAGES == 1) ? 3 : 2) void fwd_mfma_kernel(
     const int32_t* __restrict__ p_row_ptr, const int32_t* __restrict__ p_cnt, int nQB, int xcd_chunk,
     int p_nqb_layout, int p_B, int p_splits, FwdArgs a)
 {
@@ -76,17 +73,12 @@ __global__ __launch_bounds__(64 * NW * TEAMS, (D <= 64 && STAGES == 1) ? 3 : 2) 
     constexpr int META_C = 128;                              // elements of one key slot
     constexpr int SMEM = TILES + 2 * META_W + 2 * META_C;
 
-    constexpr int TEAM_MEM = TEAMS > 1 ? (SMEM + 511) / 512 * 512 : SMEM;
-    static_assert(TEAMS == 1 || (TEAMS == 2 && SPLIT && STAGES == 1), "two teams: chunks only");
-    __shared__ __attribute__((aligned(1024))) uint16_t s_all[TEAM_MEM * TEAMS];
-    const int team = TEAMS > 1 ? __builtin_amdgcn_readfirstlane((int)threadIdx.x / (64 * NW)) : 0;
-    uint16_t* const smem = s_all + team * TEAM_MEM;
-    __shared__ int s_rounds[TEAMS];
+    __shared__ __attribute__((aligned(1024))) uint16_t smem[SMEM];
     lds_u16* lds = (lds_u16*)smem;
     lds_u16* wmeta = lds + TILES;
     lds_u16* cmeta = wmeta + 2 * META_W;
 
-    const int tid = threadIdx.x - team * 64 * NW;            // inside the team
+    const int tid = threadIdx.x;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);   // uniform, and known to be
     const int lane = tid & 63;
     const int n = lane & 31;                                 // query inside the wavefront's 32
@@ -144,11 +136,6 @@ __global__ __launch_bounds__(64 * NW * TEAMS, (D <= 64 && STAGES == 1) ? 3 : 2) 
         const int e0 = min(nt, split * chunk);
         t_begin += e0;
         nt = min(nt - e0, chunk);
-        if (TEAMS > 1) {                                     // this team's half of them
-            const int half = (nt + 1) / 2;
-            t_begin += team * half;
-            nt = team ? nt - half : half;
-        }
     }
     const long long off = (long long)a.Lk - a.Lq;
     const long long diag = (long long)qrow + off;            // last visible key if causal
@@ -463,19 +450,9 @@ __global__ __launch_bounds__(64 * NW * TEAMS, (D <= 64 && STAGES == 1) ? 3 : 2) 
 #pragma unroll
         for (int u = 0; u < NLOAD; ++u) gcur[u] = 0;
         int s_cur = 0, s_nxt = 0;                            // starts of tile it and tile it + 1
-        int rounds = nt;                                     // the same for both teams
-        if (TEAMS > 1) {
-            if (SCHED) s_cur = first_start;
-            if (lane == 0 && wave == 0) s_rounds[team] = nt;
-            if (SCHED && s_cur < 0) dma_cols(0, 0);          // the very first entry is gathered: fetch its keys
-            wait_vmem();
-            __syncthreads();
-            rounds = max(s_rounds[0], s_rounds[TEAMS - 1]);
-            if (SCHED && s_cur < 0) read_cols(0, gcur);
-        }
         if (nt > 0) {
             s_cur = SCHED ? first_start : tile_start(0);
-            if (TEAMS == 1 && SCHED && s_cur < 0) {          // the very first entry is gathered: fetch its keys
+            if (SCHED && s_cur < 0) {                        // the very first entry is gathered: fetch its keys
                 dma_cols(0, 0);
                 wait_vmem();
                 __syncthreads();
@@ -490,8 +467,7 @@ __global__ __launch_bounds__(64 * NW * TEAMS, (D <= 64 && STAGES == 1) ? 3 : 2) 
             }
         }
         settle_q();
-        for (int it = 0; it < rounds; ++it) {
-            const bool mine = TEAMS == 1 || it < nt;
+        for (int it = 0; it < nt; ++it) {
             const int slot = it & 1;
             wait_vmem();                                     // K and metadata of this tile (keys of the next)
             __syncthreads();                                 // ... for everybody; the V buffer is free
@@ -503,12 +479,10 @@ __global__ __launch_bounds__(64 * NW * TEAMS, (D <= 64 && STAGES == 1) ? 3 : 2) 
                 s_nn = tile_start(it + 2);
                 if (SCHED && s_nn < 0) dma_cols(it + 2, slot);
             }
-            if (mine) {
-                if (!SCHED || s_cur >= 0) issue_tile_loads<D, NW, true>(v_rsrc, Vs, s_cur, sv_bytes, wave, lane);
-                else issue_gather_loads<D, NW, true>(v_rsrc, Vs, gcur, sv_bytes, wave, lane);
-            }
+            if (!SCHED || s_cur >= 0) issue_tile_loads<D, NW, true>(v_rsrc, Vs, s_cur, sv_bytes, wave, lane);
+            else issue_gather_loads<D, NW, true>(v_rsrc, Vs, gcur, sv_bytes, wave, lane);
             const uint64_t word = apply_causal(read_word(slot), s_cur) & valid;
-            const bool active = mine && __ballot(word != 0) != 0;   // something visible for these 32 queries
+            const bool active = __ballot(word != 0) != 0;    // something visible for these 32 queries
             f32x16 sacc[2];
             if (active) qk_tile(Ks, sacc);
             if (SCHED && it + 1 < nt && s_nxt < 0) read_cols(slot ^ 1, gidx);
@@ -535,32 +509,6 @@ __global__ __launch_bounds__(64 * NW * TEAMS, (D <= 64 && STAGES == 1) ? 3 : 2) 
     {
         const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(lsum), __float_as_uint(lsum), false, false);
         ltot = __uint_as_float(r[0]) + __uint_as_float(r[1]);
-    }
-    if constexpr (TEAMS > 1) {                               // the second team hands what it has to the first
-        __syncthreads();                                     // all wavefronts are done with the tiles
-        constexpr int HAND = DBLK * 16 + 2;
-        float* hand = reinterpret_cast<float*>(s_all) + wave * 64 * HAND + lane;
-        static_assert(NW * 64 * HAND * 4 <= TEAM_MEM * TEAMS * 2, "fits into the tiles");
-        if (team) {
-#pragma unroll
-            for (int db = 0; db < DBLK; ++db)
-#pragma unroll
-                for (int i = 0; i < 16; ++i) hand[(16 * db + i) * 64] = oacc[db][i];
-            hand[16 * DBLK * 64] = m;
-            hand[(16 * DBLK + 1) * 64] = ltot;
-        }
-        __syncthreads();
-        if (team) return;
-        const float m1 = hand[16 * DBLK * 64], l1 = hand[(16 * DBLK + 1) * 64];
-        const float m_new = fmaxf(m, m1);
-        const float f0 = m == -INFINITY ? 0.f : __builtin_amdgcn_exp2f((m - m_new) * sc);
-        const float f1 = m1 == -INFINITY ? 0.f : __builtin_amdgcn_exp2f((m1 - m_new) * sc);
-#pragma unroll
-        for (int db = 0; db < DBLK; ++db)
-#pragma unroll
-            for (int i = 0; i < 16; ++i) oacc[db][i] = fmaf(hand[(16 * db + i) * 64], f1, oacc[db][i] * f0);
-        ltot = ltot * f0 + l1 * f1;
-        m = m_new;
     }
     const float inv = ltot > 0.f ? 1.f / ltot : 0.f;
     if (SPLIT) {                                             // partial result: fp32, normalised by its own sum
@@ -718,13 +666,6 @@ hipError_t launch_merge_d(const FwdArgs& a, hipStream_t stream)
     return hipGetLastError();
 }
 
-// Two teams per chunk where the chunks leave compute units half empty (a workgroup of one team is two wavefronts): up to
-// one workgroup per compute unit at D = 128, up to two below, and chunks of at least four tiles to share.  Segments of
-// 64 queries over 16384 keys, 64 pairs: 4 chunks D128 30.0 -> 26.3 us (2 chunks 45 -> 33), 8 chunks D64 18.6 -> 17.9, D32 16.0 -> 13.6;
-// 8 chunks D128, i.e. 512 workgroups, 28.8 without and 30.0 with; 16 pairs, 8 chunks D128 19.8 -> 16.9.
-constexpr long long kTeamKeys = 4 * kBN;
-template <int D> constexpr long long team_blocks() { return D == 128 ? 256 : 512; }
-
 template <int D>
 hipError_t launch_split_d(const FwdArgs& a, hipStream_t stream)
 {
@@ -732,17 +673,12 @@ hipError_t launch_split_d(const FwdArgs& a, hipStream_t stream)
     const long long blocks = (long long)nQB * a.H * a.B * a.splits;
     constexpr int ST = D == 128 ? 1 : 2;
     const int32_t* cnt = a.sched.cnt;
-    const auto run = [&](auto kernel, int threads) {
-        hipLaunchKernelGGL(kernel, dim3((unsigned)blocks), dim3(threads), 0, stream, a.row_ptr, cnt, nQB, 0,
-                           a.nqb_layout, a.B, a.splits, a);
-    };
-    if (blocks <= team_blocks<D>() && a.Lk >= (long long)kTeamKeys * a.splits) {
-        if (cnt) run(fwd_mfma_kernel<D, 2, 1, true, true, 2>, 256);
-        else run(fwd_mfma_kernel<D, 2, 1, false, true, 2>, 256);
-    } else {
-        if (cnt) run(fwd_mfma_kernel<D, 2, ST, true, true>, 128);
-        else run(fwd_mfma_kernel<D, 2, ST, false, true>, 128);
-    }
+    if (cnt)
+        hipLaunchKernelGGL((fwd_mfma_kernel<D, 2, ST, true, true>), dim3((unsigned)blocks), dim3(128), 0,
+                           stream, a.row_ptr, cnt, nQB, 0, a.nqb_layout, a.B, a.splits, a);
+    else
+        hipLaunchKernelGGL((fwd_mfma_kernel<D, 2, ST, false, true>), dim3((unsigned)blocks), dim3(128), 0,
+                           stream, a.row_ptr, cnt, nQB, 0, a.nqb_layout, a.B, a.splits, a);
     const hipError_t e = hipGetLastError();
     return e != hipSuccess ? e : launch_merge_d<D>(a, stream);
 }

@@ -68,11 +68,26 @@ def test_split_forward_matches_oracle(case):
 @pytest.mark.parametrize("use_sched", [False, True])
 @pytest.mark.parametrize("Lk,splits,density", [(256, 1, 0.5), (320, 1, 0.02), (512, 2, 0.01), (1111, 4, 0.05), (700, 2, 0.9),
                                                (17100, 1, 0.3)])
-def test_split_chunks_shared_by_two_teams(Lk, splits, density, use_sched, D):
-    """Few chunks of four tiles and more: two teams take half of a chunk's entries each.  Odd and even numbers of entries,
-    one entry for both (gathered), causal limits inside the last tiles, 268 entries (the window of entry starts moves on)."""
+def test_split_chunks_of_four_tiles_and_more(Lk, splits, density, use_sched, D):
+    """Few long chunks: odd and even numbers of entries, a single gathered one, causal limits inside the last tiles, 268
+    entries (the window of entry starts moves on)."""
     print(Lk, splits, density, use_sched, D, flush=True)
     run_split(2, 2, 70, Lk, D, True, density, splits, use_sched, seed=Lk)
+
+
+@pytest.mark.parametrize("D", [32, 64, 128])
+@pytest.mark.parametrize("use_sched", [False, True])
+def test_split_result_does_not_depend_on_the_batch(use_sched, D):
+    """An example alone (16 workgroups) and as the first of 40 (640): the same chunks, so the same bits of O and lse."""
+    B, H, Lq, Lk, splits = 40, 2, 70, 1111, 4
+    rng = np.random.default_rng([synth.SEED, 31338])
+    q, k, v = (to_device(rng.standard_normal((B, H, L, D), dtype=np.float32), "bf16")[0] for L in (Lq, Lk, Lk))
+    lay = ap.ap_build_layout(torch.from_numpy(synth.random_mask(H, Lq, Lk, 0.1, seed=D)).cuda(), 64, 64)
+    sched = ap.ap_build_schedule(lay, causal=True) if use_sched else None
+    O, lse = ap.ap_sparse_attn_fwd_split(q, k, v, lay, splits, causal=True, sched=sched)
+    O1, lse1 = ap.ap_sparse_attn_fwd_split(q[:1], k[:1], v[:1], lay, splits, causal=True, sched=sched)
+    torch.cuda.synchronize()
+    assert torch.equal(O1, O[:1]) and torch.equal(lse1, lse[:1])
 
 
 def test_split_forward_rows_without_kept_keys():

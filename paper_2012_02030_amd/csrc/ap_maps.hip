@@ -92,7 +92,9 @@ __global__ __launch_bounds__(64 * NW, 4) void row_lse_kernel(MapArgs a, int nQB)
     const int k_swz = hh ^ swz_k<D>(n);
     const float sc = a.scale * kLog2e;
     // reference of the exponentials: a maximum of scores seen, raised only where the sum of a lane's 32
-    // exponentials exceeds kRaise, so an ordinary tile needs no maximum (16 instructions and a lane exchange of 130)
+    // exponentials exceeds kRaise, so an ordinary tile needs no maximum (16 instructions and a lane exchange of 130).
+    // While every score seen is -inf (finite rows whose products overflow) it stays -inf, and so the next tile's
+    // sum is +inf or NaN and raises it.
     float m = -INFINITY, msc = -INFINITY, lsum = 0.f;
     // last key that any query of this wavefront sees
     const long long wave_last = a.causal ? (long long)qb * BM + wave * 32 + 31 + off : (long long)a.Lk - 1;
@@ -134,7 +136,7 @@ __global__ __launch_bounds__(64 * NW, 4) void row_lse_kernel(MapArgs a, int nQB)
             asm volatile("");                                // a branch, not selects in every tile's way
         }
         float psum = sum_exp(sacc, sc, msc);
-        if (__ballot(!(psum <= kRaise)) != 0) {              // first tile (the reference is -inf), or larger scores
+        if (__ballot(!(psum <= kRaise)) != 0) {              // no finite score so far (the reference is -inf), or larger ones
             float tmax = -INFINITY;
 #pragma unroll
             for (int kb = 0; kb < 2; ++kb)
@@ -142,10 +144,10 @@ __global__ __launch_bounds__(64 * NW, 4) void row_lse_kernel(MapArgs a, int nQB)
                 for (int i = 0; i < 16; ++i) tmax = fmaxf(tmax, sacc[kb][i]);
             const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(tmax), __float_as_uint(tmax), false, false);
             const float m_new = fmaxf(m, fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1])));
-            msc = (m_new == -INFINITY) ? 0.f : m_new * sc;
+            msc = m_new * sc;
             lsum *= (m == -INFINITY) ? 0.f : __builtin_amdgcn_exp2f(m * sc - msc);
             m = m_new;
-            psum = sum_exp(sacc, sc, msc);
+            psum = sum_exp(sacc, sc, m == -INFINITY ? 0.f : msc);
         }
         lsum += psum;
     }

@@ -77,3 +77,22 @@ def test_rows_whose_largest_scores_come_late(order, Lq, Lk, D, causal):
     # a score of up to 130 in magnitude, formed in 32 bits from D products, is off by up to a few 2^-24 * 130
     assert np.abs(got - ref).max() <= 2 * 1e-4
     assert np.abs(got.sum(-1) - ref.sum(-1)).max() <= 2 * 1e-4
+
+
+@pytest.mark.parametrize("level", [-8.0, -200.0])
+@pytest.mark.parametrize("first", [64, 70, 128])
+@pytest.mark.parametrize("Lq,Lk,D,causal", [(130, 515, 64, False), (100, 260, 128, True), (65, 200, 32, False)])
+def test_rows_whose_first_scores_overflow(first, level, Lq, Lk, D, causal):
+    """Finite padding rows whose products overflow: every query's first 64 scores and more are -inf, the others ordinary or
+    (level -200) so low that their exponentials vanish against any reference but their own maximum."""
+    g = torch.Generator().manual_seed(9)
+    Q, K = torch.randn(2, 2, Lq, D, generator=g), torch.randn(2, 2, Lk, D, generator=g)
+    Q[..., 0] = 8.0                                                    # key[0] moves every score by sqrt(D) / D * 8
+    K[..., 0] = torch.where(torch.arange(Lk) < first, -3e38, level * D ** 0.5 / 8)
+    Q, K = Q.to(torch.bfloat16), K.to(torch.bfloat16)
+    ref = 2 * oracle.mean_attention_map(Q.double().numpy(), K.double().numpy(), causal=causal)
+    got = ap.ap_accumulate_attention_maps(Q.cuda(), K.cuda(), causal=causal, weight=1.0).double().cpu().numpy()
+    assert np.isfinite(got).all() and (got[..., :first] == 0).all()
+    # a score of up to 210 in magnitude, formed in 32 bits from D products, is off by up to a few 2^-24 * 210
+    assert np.abs(got - ref).max() <= 2 * 1e-4
+    assert np.abs(got.sum(-1) - ref.sum(-1)).max() <= 2 * 1e-4

@@ -627,6 +627,7 @@ __global__ __launch_bounds__(256, W) void entmax15_fwd_kernel(
         take_over(v);
     }
     const float inv = (!w.empty && w.psum > 0.f) ? 1.0f / w.psum : 0.f;
+    wait_vmem();                                             // without entries nobody has waited for the Q rows
     __syncthreads();                                         // all wavefronts are done with the tiles
     const int row0 = qb * 64 + w.qh * 32;
     uint16_t* Op = (uint16_t*)a.O + (size_t)b * a.so[0] + (size_t)h * a.so[1];

@@ -248,3 +248,20 @@ def test_entmax_residual_where_scores_leave_the_support_under_the_last_step(name
     """The bound of the header, |sum p - 1| <= 1e-4, on rows whose unconfirmed last step leaves 1.0e-3 and 2.4e-3."""
     total = clustered_attained_sums(names)
     assert np.abs(total - 1.0).max() <= 1e-4, total
+
+
+@pytest.mark.parametrize("D", [32, 64, 128])
+@pytest.mark.parametrize("Lk", [100, 300])
+def test_entmax_block_rows_without_entries_are_positive_zeros(Lk, D):
+    """Nobody reads the query rows of a block row that keeps nothing, and they must not reach what is written for it."""
+    Q, K, V = rand_qkv(61, 4, 4, 150, Lk, D, gain=-1e30)
+    mask = synth.random_mask(4, 150, Lk, 0.3, seed=62)
+    mask[:, 64:128] = 0
+    mask[2] = 0
+    q, k, v = (to_device(x, "bf16")[0] for x in (Q, K, V))
+    lay = ap.ap_build_layout(torch.from_numpy(mask).cuda(), 64, 64)
+    for sched in (None, ap.ap_build_schedule(lay, causal=False)):
+        O, tau = ap.ap_sparse_attn_entmax15_fwd(q, k, v, lay, sched=sched)
+        torch.cuda.synchronize()
+        assert not O[:, :, 64:128].contiguous().view(torch.int16).any() and not O[:, 2].contiguous().view(torch.int16).any()
+        assert bool((tau[:, :, 64:128] == float("inf")).all()) and bool((tau[:, 2] == float("inf")).all())

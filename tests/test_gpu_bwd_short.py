@@ -69,3 +69,29 @@ def test_short_backward_matches_the_kernels_of_longer_sequences(B, H, Lq, Lk, D,
         for ref in refs:
             excess = ((x.double() - ref).abs() - ref.abs() / 128 - ref.abs().max() / 256).max()
             assert float(excess) <= 0, (name, float(excess))
+
+
+@pytest.mark.parametrize("B,H,L,D", [(2, 2, 128, 64), (2, 2, 128, 32), (24, 8, 256, 64), (2, 2, 320, 64)])
+def test_tiles_that_nobody_keeps_are_never_used(B, H, L, D):
+    """Rows of 64 keys and of 64 queries that are not in the layout at all (padding that nobody has written, here NaN) reach
+    no gradient, neither in the short kernel nor (320) in the general ones."""
+    Q, K, V, dO = (rand(i, B, H, L, D) for i in range(4))
+    mask = synth.random_mask(H, L, L, 0.3, seed=L + D)
+    mask[:, :, 64:128] = 0
+    mask[:, :64] = 0
+    q, k, v, g = (torch.from_numpy(x).to(torch.bfloat16).cuda() for x in (Q, K, V, dO))
+    lay = ap.ap_build_layout(torch.from_numpy(mask).cuda(), 64, 64)
+    lt = ap.ap_build_layout_transpose(lay)
+
+    def grads():
+        O, lse = ap.ap_sparse_attn_fwd(q, k, v, lay)
+        got = ap.ap_sparse_attn_bwd(q, k, v, O, g, lse, lay, lt)
+        torch.cuda.synchronize()
+        return got
+
+    want = grads()
+    k[:, :, 64:128] = v[:, :, 64:128] = float("nan")
+    q[:, :, :64] = g[:, :, :64] = float("nan")
+    for a, b in zip(grads(), want):
+        assert torch.equal(a, b)                                       # (NaN equals nothing)
+    assert not want[0][:, :, :64].any() and not want[1][:, :, 64:128].any() and not want[2][:, :, 64:128].any()

@@ -198,13 +198,36 @@ __global__ __launch_bounds__(512, 4) void map_accumulate_kernel(MapArgs a, int n
     // last keys that any query of the workgroup, of this wavefront sees
     const long long block_last = a.causal ? (long long)q0 + (BM - 1) + off : (long long)a.Lk - 1;
     const long long wave_last = a.causal ? (long long)q0 + wq * 32 + 31 + off : (long long)a.Lk - 1;
-    if (block_last < key0) return;                           // hidden from the whole block
 
     // memory side of the tile: 32 threads per row, 16 rows per pass
     const int c4 = (tid & 31) * 4, r0 = tid >> 5;
     const bool vec_ok = (a.Lk & 3) == 0;                     // then every row of the map starts 16-byte aligned
     float* const map0 = a.abar + ((size_t)h * a.Lq + q0 + r0) * a.Lk + key0;
     const long long map_step = (long long)16 * a.Lk;
+    auto write_zeros = [&](int z0, long long zk) {           // of the tile of rows z0.. and keys zk * BK..
+        float* const z = a.abar + ((size_t)h * a.Lq + z0 + r0) * a.Lk + zk * BK;
+        const int cols = (int)min((long long)BK, a.Lk - zk * BK);
+#pragma unroll
+        for (int pass = 0; pass < 8; ++pass) {
+            if (z0 + r0 + 16 * pass >= a.Lq) continue;
+            if (vec_ok) {
+                if (c4 < cols) *reinterpret_cast<float4*>(z + c4 + pass * map_step) = make_float4(0.f, 0.f, 0.f, 0.f);
+            } else {
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+                    if ((tid & 31) + 32 * e < cols) z[(tid & 31) + 32 * e + pass * map_step] = 0.f;
+            }
+        }
+    };
+    // A tile that is hidden as a whole gets its zeros from its own workgroup before anything else, or (DEAL) from one with
+    // a visible tile, before its last scores.  First batches (us, own / dealt): B2 H4 8192 x 8192 D32 273 / 300, B16 H12
+    // 1024 x 1024 D64 76 / 78, B1 H16 4096 x 4096 D64 225 / 234; at D = 128 B4 H16 2048 x 2048 123 / 124, B4 H12 2000 x 2000
+    // 98 / 103, but B2 H8 4096 x 4096 177 / 170.
+    constexpr bool DEAL = D == 128;
+    if (block_last < key0) {
+        if (INIT && !DEAL) write_zeros(q0, kg);
+        return;
+    }
 
     const int qrow = q0 + wq * 32 + n;
     const int sk_bytes = (int)a.sk[2] * 2;
@@ -312,29 +335,13 @@ __global__ __launch_bounds__(512, 4) void map_accumulate_kernel(MapArgs a, int n
     wait_vmem();
     asm volatile("" : "+v"(l));
     __syncthreads();
-    if (INIT && a.causal) {
-        // Zeros of the tiles that are hidden as a whole: those of block row nQB - 1 - qb are dealt to the workgroups of
-        // block row qb, which has at least as many visible ones, so they travel beside other tiles' arithmetic (in
-        // workgroups of their own they held places on the compute units: 30 us of 120 at B4 H16 L2048 D128), before the
-        // last scores rather than at the end (B2 H4 8192 x 8192 D32 307 -> 300 us).
+    if (INIT && DEAL && a.causal) {
+        // the zeros of block row nQB - 1 - qb are dealt to the workgroups of block row qb, which has at least as many visible
+        // tiles
         const int zb = nQB - 1 - qb, z0 = zb * BM;
         const long long z_vis = min((long long)nKG, ((long long)z0 + (BM - 1) + off) / BK + 1);
         const long long my_vis = min((long long)nKG, block_last / BK + 1);
-        for (long long zk = z_vis + kg; zk < nKG; zk += my_vis) {
-            float* const z = a.abar + ((size_t)h * a.Lq + z0 + r0) * a.Lk + zk * BK;
-            const int cols = (int)min((long long)BK, a.Lk - zk * BK);
-#pragma unroll
-            for (int pass = 0; pass < 8; ++pass) {
-                if (z0 + r0 + 16 * pass >= a.Lq) continue;
-                if (vec_ok) {
-                    if (c4 < cols) *reinterpret_cast<float4*>(z + c4 + pass * map_step) = make_float4(0.f, 0.f, 0.f, 0.f);
-                } else {
-#pragma unroll
-                    for (int e = 0; e < 4; ++e)
-                        if ((tid & 31) + 32 * e < cols) z[(tid & 31) + 32 * e + pass * map_step] = 0.f;
-                }
-            }
-        }
+        for (long long zk = z_vis + kg; zk < nKG; zk += my_vis) write_zeros(z0, zk);
     }
     if (seen) scores(a.B - 1);
     // a tile that lies inside the map and below the causal limit for all its rows takes the

@@ -96,3 +96,11 @@ def test_rows_whose_first_scores_overflow(first, level, Lq, Lk, D, causal):
     # a score of up to 210 in magnitude, formed in 32 bits from D products, is off by up to a few 2^-24 * 210
     assert np.abs(got - ref).max() <= 2 * 1e-4
     assert np.abs(got.sum(-1) - ref.sum(-1)).max() <= 2 * 1e-4
+
+
+@pytest.mark.parametrize("Lq,Lk", [(516, 516), (300, 523), (513, 900)])
+@pytest.mark.parametrize("D", [32, 64, 128])
+def test_first_batch_with_tiles_hidden_as_a_whole(Lq, Lk, D):
+    """Their zeros come from other workgroups than the visible tiles (D <= 64) or from the same (D = 128); rows that start
+    16-byte aligned, and rows that do not."""
+    test_first_batch_and_accumulation(2, 2, Lq, Lk, D, True)

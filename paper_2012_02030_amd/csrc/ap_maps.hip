@@ -344,14 +344,22 @@ __global__ __launch_bounds__(512, 4) void map_accumulate_kernel(MapArgs a, int n
         for (long long zk = z_vis + kg; zk < nKG; zk += my_vis) write_zeros(z0, zk);
     }
     if (seen) scores(a.B - 1);
-    // a tile that lies inside the map and below the causal limit for all its rows takes the
-    // branch-free path: all 8 loads of a thread are in flight under the last exponentials
+    // All 8 loads of a thread are in flight under the last exponentials.  A tile that lies inside the map and below the
+    // causal limit for all its rows takes a branch-free path.  Where rows start 16-byte aligned the others take pieces
+    // of four entries too, which are in the map or not as a whole (B3 H3 2000 x 500 D64, a quarter of the tiles: adding
+    // 20.0 us with single entries that are read when the sums are there, 16.4).
     bool interior = vec_ok && q0 + BM <= a.Lq && (long long)key0 + BK <= a.Lk;
     if (a.causal) interior = interior && (long long)key0 + (BK - 1) <= (long long)q0 + off;
     float4 o[8];
-    if (!INIT && interior)
+    if (!INIT && interior) {
 #pragma unroll
         for (int pass = 0; pass < 8; ++pass) o[pass] = *reinterpret_cast<const float4*>(map0 + c4 + pass * map_step);
+    } else if (!INIT && vec_ok) {
+        const float* const from = a.abar + ((size_t)h * a.Lq + q0) * a.Lk + key0 + min(c4, a.Lk - 4 - key0);
+#pragma unroll
+        for (int pass = 0; pass < 8; ++pass)
+            o[pass] = *reinterpret_cast<const float4*>(from + (long long)min(r0 + 16 * pass, q_last) * a.Lk);
+    }
     if (seen) add_exp();
 
     // transpose through LDS: lanes hold columns of keys per query, memory wants rows of keys
@@ -376,6 +384,21 @@ __global__ __launch_bounds__(512, 4) void map_accumulate_kernel(MapArgs a, int n
             o[pass].z = fmaf(a.weight, v.z, o[pass].z);
             o[pass].w = fmaf(a.weight, v.w, o[pass].w);
             *reinterpret_cast<float4*>(map0 + c4 + pass * map_step) = o[pass];
+        }
+    } else if (vec_ok) {
+        const float* src = outs + r0 * OUT_LD + c4;
+#pragma unroll
+        for (int pass = 0; pass < 8; ++pass) {
+            const float4 v = *reinterpret_cast<const float4*>(src + pass * 16 * OUT_LD);
+            // entries of this piece that the query sees; the others keep what they hold
+            const long long sees = a.causal ? (long long)q0 + r0 + 16 * pass + off - key0 - c4 : 3;
+            if (INIT) o[pass] = make_float4(0.f, 0.f, 0.f, 0.f);
+            if (sees >= 0) o[pass].x = fmaf(a.weight, v.x, o[pass].x);
+            if (sees >= 1) o[pass].y = fmaf(a.weight, v.y, o[pass].y);
+            if (sees >= 2) o[pass].z = fmaf(a.weight, v.z, o[pass].z);
+            if (sees >= 3) o[pass].w = fmaf(a.weight, v.w, o[pass].w);
+            if (r0 + 16 * pass <= q_last && key0 + c4 < a.Lk)
+                *reinterpret_cast<float4*>(map0 + c4 + pass * map_step) = o[pass];
         }
     } else {                                                 // a row's 128 entries as four 32-entry pieces
         const int c1 = tid & 31;

@@ -104,3 +104,13 @@ def test_first_batch_with_tiles_hidden_as_a_whole(Lq, Lk, D):
     """Their zeros come from other workgroups than the visible tiles (D <= 64) or from the same (D = 128); rows that start
     16-byte aligned, and rows that do not."""
     test_first_batch_and_accumulation(2, 2, Lq, Lk, D, True)
+
+
+@pytest.mark.parametrize("B,H,Lq,Lk,D,causal", [
+    (1, 2, 40, 40, 32, False), (2, 2, 64, 40, 32, False), (3, 1, 33, 100, 32, True), (4, 2, 17, 36, 32, True),
+    (5, 2, 130, 260, 32, True), (3, 2, 20, 132, 128, True), (2, 2, 100, 20, 64, False), (2, 1, 260, 131, 64, False),
+])
+def test_tiles_that_are_mostly_outside_the_map(B, H, Lq, Lk, D, causal):
+    """Fewer queries or keys than a tile has, and tiles cut by the map's end or the causal limit, with rows of the map that
+    start 16-byte aligned and rows that do not; odd and even numbers of examples."""
+    test_first_batch_and_accumulation(B, H, Lq, Lk, D, causal)

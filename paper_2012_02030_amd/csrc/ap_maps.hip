@@ -233,13 +233,18 @@ __global__ __launch_bounds__(512, 4) void map_accumulate_kernel(MapArgs a, int n
     const int sk_bytes = (int)a.sk[2] * 2;
     const unsigned k_bytes = (unsigned)((a.Lk - 1) * sk_bytes + D * 2);
     const float sc = a.scale * kLog2e;
-    const bool seen = (long long)key0 + wk * 64 <= wave_last && key0 + wk * 64 < a.Lk;   // uniform over the wavefront
+    // some query of the wavefront sees some key of it (uniform over the wavefront)
+    const bool seen = (long long)key0 + wk * 64 <= wave_last && key0 + wk * 64 < a.Lk && q0 + wq * 32 < a.Lq;
     const float* lp = a.lse2 + (size_t)h * a.Lq + min(qrow, a.Lq - 1);
 
     // The 128 query rows and 128 key rows of an example travel to LDS (query rows fetched straight into registers
-    // are 16-byte pieces of 32 rows per instruction); a wavefront brings 16 rows of either.
+    // are 16-byte pieces of 32 rows per instruction); a wavefront brings 16 rows of either, key rows only if any of them
+    // exists.  The first ones are brought by the wavefronts of the second 64 keys, which in a small map have no scores
+    // (B256 H8 40 x 40 D32 142 -> 134 us, B128 H16 40 x 40 D128 160 -> 146, B64 H16 64 x 64 D64 54.7 -> 47.7; not
+    // bringing query rows that do not exist either gives 120, 132 and 42, but costs 1 % where all rows exist).
     constexpr int CPR = D / 8, RPI = 64 / CPR, NL = 16 / RPI;
     const int cp = lane % CPR;
+    const int part = 16 * (wave ^ 4);
     const uint16_t* const q_head = (const uint16_t*)a.Q + (size_t)h * a.sq[1] + (long long)q0 * a.sq[2];
     const int q_last = a.Lq - 1 - q0;
     auto issue = [&](int b) {
@@ -250,13 +255,14 @@ __global__ __launch_bounds__(512, 4) void map_accumulate_kernel(MapArgs a, int n
         int k_voff[NL];
 #pragma unroll
         for (int u = 0; u < NL; ++u)
-            k_voff[u] = rl * sk_bytes + (cp ^ swz_k<D>(wave * 16 + u * RPI + rl)) * 16;
-        load16_chain<NL, 1024>(lds_addr_of(to + wave * 16 * D), (key0 + wave * 16) * sk_bytes, RPI * sk_bytes, k_voff, rs);
+            k_voff[u] = rl * sk_bytes + (cp ^ swz_k<D>(part + u * RPI + rl)) * 16;
+        if (key0 + part < a.Lk)
+            load16_chain<NL, 1024>(lds_addr_of(to + part * D), (key0 + part) * sk_bytes, RPI * sk_bytes, k_voff, rs);
         const uint16_t* const base = q_head + (size_t)b * a.sq[0];
 #pragma unroll
         for (int u = 0; u < NL; ++u) {
-            const int r = wave * 16 + u * RPI + rl;
-            load16_to_lds(lds_addr_of(to + 2 * TILE + wave * 16 * D + u * 512),
+            const int r = part + u * RPI + rl;
+            load16_to_lds(lds_addr_of(to + 2 * TILE + part * D + u * 512),
                           base + min(r, q_last) * a.sq[2] + (cp ^ swz_k<D>(r)) * 8);
         }
     };
@@ -299,8 +305,8 @@ __global__ __launch_bounds__(512, 4) void map_accumulate_kernel(MapArgs a, int n
             __builtin_amdgcn_sched_group_barrier(0x008, 2, 0);
         }
     };
-    // entries outside the map or hidden by causality are computed too (from zero keys or
-    // real ones) and dropped when the tile is written
+    // entries outside the map or hidden by causality are computed too (from whatever is in LDS) and dropped when the tile
+    // is written
     float l;
     auto add_exp = [&]() {
 #pragma unroll
@@ -310,8 +316,8 @@ __global__ __launch_bounds__(512, 4) void map_accumulate_kernel(MapArgs a, int n
     };
     // One buffer: the next example's rows are requested once every wavefront has its scores and travel under the
     // exponentials, and under the arithmetic of the other workgroup of the compute unit.  Two (D <= 64): they travel
-    // under the scores too, with one barrier less (B64 H16 D64 128 x 128 77.9 -> 75.2 us, 256 x 256 87.2 -> 83.8, B256 H8
-    // D32 40 x 40 151 -> 143, against 99.7, 112 and 134 with four wavefronts and query rows in registers).
+    // under the scores too, with one barrier less (B64 H16 D64 128 x 128 77.9 -> 75.2 us, 256 x 256 87.2 -> 83.8, against
+    // 99.7 and 112 with four wavefronts and query rows in registers).
     issue(0);
     l = lp[0];
     for (int b = 0; b + 1 < a.B; ++b) {

@@ -43,8 +43,13 @@ using namespace mfma;
 // u = [s / 2 - tau]_+, P = u^2, dS = u (dP - gbar) with the per-query statistics tau (from the
 // forward pass) and gbar = sum_j u_j dP_j / sum_j u_j: the dQ kernel walks a block row's entries twice, first for
 // gbar (two products of three), then for dQ.  There BwdArgs::lse holds tau and BwdArgs::delta gets gbar.  (The
-// first walk as a launch of its own: B4 H16 L2048 D128 40 us + 52 for dQ, 72 in one.)
+// first walk as a launch of its own: B4 H16 L2048 D128 40 us + 52 for dQ, 72 in one; 3 heads of 5000 x 9000 D64 89 + 143 us, both
+// still waiting for their tiles before the products, 165 in one.)
 enum { SOFTMAX = 0, ENTMAX15 = 1 };
+
+template <int N> struct Int {
+    static constexpr int value = N;
+};
 
 __device__ __forceinline__ float lse2_of(float lse) { return lse == -INFINITY ? INFINITY : lse * kLog2e; }
 
@@ -224,53 +229,74 @@ __global__ __launch_bounds__(256, 2) void bwd_dq_sched_kernel(
         if (row_ok && hh == 0 && kh == 0) a.delta[stat_base + qrow] = delta;
     };
     int stage = 0;
-    for (int i = 0; i < steps; ++i) {
-        wait_vmem();                                         // this entry and the metadata of the next have landed
-        __syncthreads();                                     // ... for everybody; the other stage is free
-        const uint32_t word = cur.word;
-        if (i + 1 < steps) {
-            issue(nxt, stage ^ 1);
-            cur = nxt;
-            if (i + 2 < steps) fetch(entry_of(i + 2), nxt);
-        }
-        int first_walk = WALKS > 1 && i < n_entries;
-        asm volatile("" : "+v"(first_walk));                 // one loop, not one per walk: their addresses do not fit twice
-        if (MODE == ENTMAX15 && i == n_entries) set_gbar();
-        if (__ballot(word != 0) != 0) {
-            uint16_t* base = smem + stage * STAGE;
-            f32x16 s, p;
-            two_products_32<D>(base, base + TILE, k_row, k_swz, qreg, greg, s, p);   // S^T = K Q^T, dP^T = V dO^T
-            const int wbits = (int)(word >> (4 * hh));
-            if (MODE == ENTMAX15) {
-#pragma unroll
-                for (int k = 0; k < 16; ++k) {               // u, pruned: 0
-                    const uint32_t keep = (uint32_t)__builtin_amdgcn_sbfe(wbits, 8 * (k / 4) + (k % 4), 1);
-                    s[k] = fmaxf(__uint_as_float(__float_as_uint(fmaf(s[k], sc, -lse2)) & keep), 0.f);
-                }
+    // steps first .. last - 1: the gradient (GRAD), the first walk (SUMS), or both, the second after the first (ALL)
+    enum { GRAD, SUMS, ALL };
+    auto walk = [&](int first, int last, auto what_) {
+        constexpr int WHAT = decltype(what_)::value;
+        for (int i = first; i < last; ++i) {
+            __syncthreads();                                 // this entry has landed for everybody; the other stage is free
+            const uint32_t word = cur.word;
+            if (i + 1 < steps) issue(nxt, stage ^ 1);
+            // (of the last entry again at the end: behind a branch the compiler copies what is fetched, and so waits for it and
+            // for the tiles before the products: 1.5-entmax, 3 heads of 5000 x 9000 D64, 165 us for both walks, 260 so)
+            Meta after;
+            fetch(entry_of(min(i + 2, steps - 1)), after);
+            int sums = WHAT == SUMS;
+            if (WHAT == ALL) {
+                sums = i < n_entries;
+                asm volatile("" : "+v"(sums));               // one loop (D = 128: addresses for two do not fit)
+                if (i == n_entries) set_gbar();
+                sums = __builtin_amdgcn_readfirstlane(sums);
             }
-            if (MODE == ENTMAX15 && __builtin_amdgcn_readfirstlane(first_walk)) {
+            if (__ballot(word != 0) != 0) {
+                uint16_t* base = smem + stage * STAGE;
+                f32x16 s, p;
+                two_products_32<D>(base, base + TILE, k_row, k_swz, qreg, greg, s, p);   // S^T = K Q^T, dP^T = V dO^T
+                const int wbits = (int)(word >> (4 * hh));
+                if (MODE == ENTMAX15) {
 #pragma unroll
-                for (int k = 0; k < 16; ++k) {
-                    num = fmaf(s[k], p[k], num);
-                    den += s[k];
-                }
-            } else {
-#pragma unroll
-                for (int k = 0; k < 16; ++k) {
-                    if (MODE == SOFTMAX) {
+                    for (int k = 0; k < 16; ++k) {           // u, pruned: 0
                         const uint32_t keep = (uint32_t)__builtin_amdgcn_sbfe(wbits, 8 * (k / 4) + (k % 4), 1);
-                        s[k] = __builtin_amdgcn_exp2f(or_minus_inf(fmaf(s[k], sc, -lse2), keep));
+                        s[k] = fmaxf(__uint_as_float(__float_as_uint(fmaf(s[k], sc, -lse2)) & keep), 0.f);
                     }
-                    s[k] *= p[k] - delta;                    // dS^T
                 }
-                bf16x8 pb[2];
-                to_operands(s, pb);
-                tr_mm_32<D>(lds + stage * STAGE + kh * 32 * D, pb, dqacc, tr);   // dQ^T += K^T dS^T
+                if (sums) {
+#pragma unroll
+                    for (int k = 0; k < 16; ++k) {
+                        num = fmaf(s[k], p[k], num);
+                        den += s[k];
+                    }
+                } else {
+#pragma unroll
+                    for (int k = 0; k < 16; ++k) {
+                        if (MODE == SOFTMAX) {
+                            const uint32_t keep = (uint32_t)__builtin_amdgcn_sbfe(wbits, 8 * (k / 4) + (k % 4), 1);
+                            s[k] = __builtin_amdgcn_exp2f(or_minus_inf(fmaf(s[k], sc, -lse2), keep));
+                        }
+                        s[k] *= p[k] - delta;                // dS^T
+                    }
+                    bf16x8 pb[2];
+                    to_operands(s, pb);
+                    tr_mm_32<D>(lds + stage * STAGE + kh * 32 * D, pb, dqacc, tr);   // dQ^T += K^T dS^T
+                }
             }
+            stage ^= 1;
+            wait_vmem();                                     // the next entry and the metadata of the one after it
+            asm volatile("" : "+v"(after.start), "+v"(after.key), "+v"(after.word));
+            cur = nxt;
+            nxt = after;
         }
-        stage ^= 1;
+    };
+    if constexpr (MODE == SOFTMAX) {
+        walk(0, steps, Int<GRAD>{});
+    } else if constexpr (D <= 64) {
+        walk(0, n_entries, Int<SUMS>{});
+        set_gbar();
+        walk(n_entries, steps, Int<GRAD>{});
+    } else {
+        walk(0, steps, Int<ALL>{});
+        if (n_entries == 0) set_gbar();                      // (0, which the dK, dV kernel does not look at)
     }
-    if (MODE == ENTMAX15 && n_entries == 0) set_gbar();      // (0, which the dK, dV kernel does not look at)
     __syncthreads();                                         // all wavefronts are done with the tiles
     const int row0 = qb * 64 + qh * 32;
     store_key_halves<D>(smem, dqacc, wave, lane, a.scale, dQp + (size_t)row0 * a.sq[2], a.sq[2], a.Lq - row0);

@@ -25,8 +25,8 @@
 // E (5 to 8) entries stay in registers, 16 per entry and lane: K is read once, a Newton step is three vector
 // instructions per score and an exchange of the key halves through LDS, and V travels under the steps.  Of longer
 // block rows the first HL entries are held and the others' scores are formed again in every sweep, as all were before.
-// B4 H16 L2048 (3.9 entries a block row) D128 112 -> 64 us, D64 78 -> 42; B32 H8 117 x 141 D64 25 -> 12; 32 entries
-// a block row D128 650 -> 628, D64 473 -> 415; without schedules (up to 32 tiles) D128 472 -> 370.
+// B4 H16 L2048 (3.9 entries a block row) D128 112 -> 64 us, D64 78 -> 42; B32 H8 117 x 141 D64 25 -> 11.4; 32 entries
+// a block row (nothing pruned) D128 735 -> 680, D64 541 -> 444; without schedules (up to 32 tiles, every tenth key) D128 487 -> 361.
 //
 // Same operand layouts and LDS-direct loads as the softmax kernel; walks the layout's 64x64 tiles or, if given, the
 // entries of its visit schedule.
@@ -182,10 +182,8 @@ struct EntmaxRow {
                            (unsigned)((a.Lk - 1) * sv_bytes + D * 2));
         tr = make_tr_read_u<D>(lane);
     }
-    // what says where an entry starts, and its first key (-1: gathered); apart, so that nothing waits for the first
-    __device__ __forceinline__ int raw_start(int t) const { return starts[t]; }
-    __device__ __forceinline__ int key_of(int raw) const { return use_sched ? raw : raw * kBN; }
-    __device__ __forceinline__ int first_key(int t) const { return key_of(raw_start(t)); }
+    // first key of an entry, -1: gathered
+    __device__ __forceinline__ int first_key(int t) const { return use_sched ? starts[t] : starts[t] * kBN; }
     // this lane's half of its bitmap word; without a schedule the causal limit is still to be applied
     __device__ __forceinline__ uint32_t raw_word(int t) const { return words[((size_t)t * 64 + brow) * 2 + kh]; }
     __device__ __forceinline__ uint32_t visible(uint32_t w, int k0) const
@@ -391,10 +389,19 @@ __device__ __forceinline__ void entmax_long_row(EntmaxRow<D, E>& w, f32x16* oacc
     constexpr int TILE = kBN * D, NLOAD = EntmaxRow<D, E>::NLOAD;
     uint16_t* tiles = w.m.tiles;
     const int t_end = w.t0 + w.ne, t_begin = w.t0 + HL;
-    // a zero the compiler cannot see through: indexed with it, what is loaded inside a loop is a vector load (a scalar
-    // load would make every later wait for an LDS read wait for memory too)
-    int vzero = 0;
-    asm volatile("" : "+v"(vzero));
+    // First keys of entries: 64 at a time are kept in a register, one per lane, so that nothing but words and tiles is
+    // loaded for an entry that is not gathered.  (Loaded in every sweep together with gather keys: rows of 24 entries
+    // D64 263 us, 248 so; 1000 keys in 16 entries D32 111, 104.)
+    int start_l = 0, window = -1;
+    auto first_keys = [&](int e, int* k0) {                  // of entries e, e + 1 of the block row (e even)
+        if (__builtin_expect(e >> 6 != window, 0)) {
+            window = e >> 6;
+            start_l = w.first_key(w.t0 + min(64 * window + w.lane, w.ne - 1));
+            asm volatile("" : "+v"(start_l));                // waited for here and not where the branch ends
+        }
+        k0[0] = __builtin_amdgcn_readlane(start_l, e & 63);
+        k0[1] = __builtin_amdgcn_readlane(start_l, (e & 63) + 1);
+    };
     bf16x8 qreg[EntmaxRow<D, E>::KSTEPS];
     wait_vmem();
     __syncthreads();                                         // Q rows have landed
@@ -405,22 +412,22 @@ __device__ __forceinline__ void entmax_long_row(EntmaxRow<D, E>& w, f32x16* oacc
     // while the current ones are used.  With V (last sweep): K in the first pair, V in the second.
     auto sweep = [&](auto with_v_, auto&& body) {
         constexpr bool with_v = decltype(with_v_)::value;
-        // first keys, gather keys and words of the entries after those on their way, one step ahead
+        // gather keys and words of the entries after those on their way, one step ahead
         int start[2] = {0, 0}, key[2] = {0, 0};
         uint32_t fetched[2] = {0, 0}, ahead[2] = {0, 0};
         auto fetch = [&](int t) {
+            first_keys(t - w.t0, start);                     // (of the last entry again if there is one left)
 #pragma unroll
             for (int j = 0; j < 2; ++j) {
-                const int tt = min(t + j, t_end - 1) + vzero;
-                start[j] = w.raw_start(tt);
-                if (w.use_sched) key[j] = w.cols[(size_t)tt * 64 + w.lane];
+                const int tt = min(t + j, t_end - 1);
+                if (start[j] < 0) key[j] = w.cols[(size_t)tt * 64 + w.lane];
                 fetched[j] = w.raw_word(tt);
             }
         };
         auto issue = [&](int t, int to) {
 #pragma unroll
             for (int j = 0; j < 2; ++j) {
-                const int k0 = w.key_of(__builtin_amdgcn_readfirstlane(start[j]));
+                const int k0 = start[j];
                 ahead[j] = t + j < t_end ? w.visible(fetched[j], k0) : 0;
                 if (t + j >= t_end) continue;
                 int gk[NLOAD];
@@ -447,7 +454,7 @@ __device__ __forceinline__ void entmax_long_row(EntmaxRow<D, E>& w, f32x16* oacc
             }
             wait_vmem();
 #pragma unroll
-            for (int j = 0; j < 2; ++j) asm volatile("" : "+v"(start[j]), "+v"(key[j]), "+v"(fetched[j]));
+            for (int j = 0; j < 2; ++j) asm volatile("" : "+v"(key[j]), "+v"(fetched[j]));
             const uint32_t word[2] = {ahead[0], ahead[1]};
             __syncthreads();
             if (!with_v && t + 2 < t_end) {
@@ -470,10 +477,11 @@ __device__ __forceinline__ void entmax_long_row(EntmaxRow<D, E>& w, f32x16* oacc
     // tiles of held entries e, e + 1 into the first two places
     auto bring = [&](int e, bool v) {
         __syncthreads();                                     // what was there is consumed
+        int start[2];
+        first_keys(e, start);
 #pragma unroll
         for (int j = 0; j < 2; ++j) {
-            const int t = w.t0 + e + j + vzero;
-            const int k0 = __builtin_amdgcn_readfirstlane(w.first_key(t));
+            const int t = w.t0 + e + j, k0 = start[j];
             int gk[NLOAD];
             if (k0 < 0)
 #pragma unroll
@@ -489,8 +497,7 @@ __device__ __forceinline__ void entmax_long_row(EntmaxRow<D, E>& w, f32x16* oacc
 #pragma unroll
     for (int e = 0; e < HL; ++e) {
         if (e % 2 == 0) bring(e, false);
-        const int t = w.t0 + e + vzero;
-        const uint32_t word = w.visible(w.raw_word(t), __builtin_amdgcn_readfirstlane(w.first_key(t)));
+        const uint32_t word = w.visible(w.raw_word(w.t0 + e), __builtin_amdgcn_readlane(start_l, e));
         if (__ballot(word != 0) == 0) continue;
         live |= 1u << e;
         product_32<D>(tiles + e % 2 * TILE, w.kh * 32 + w.n, w.k_swz, qreg, y[e]);
@@ -650,9 +657,14 @@ hipError_t launch(const FwdArgs& a, float* tau_out, hipStream_t stream)
 // No block row has more entries than there are key tiles.  Registers go into entries held or into a third wavefront per
 // SIMD.  With up to two tiles two entries are all there is, and a fourth wavefront fits (the same at D = 32: B256 H8 40 x 40
 // 20.7 us with room for six entries, 16.5 with two).  At D = 64 with up to six tiles every row fits either way (16 x 12 x 330, all tiles full: 42 us with two
-// wavefronts, 32 with three); with seven or eight only two wavefronts hold them all (500: 60 against 92); beyond that the
-// third is worth more where workgroups come in several rounds (B4 H16, 2048 keys of 3.9 entries a block row 51 against 42,
-// 1500 keys in 24 entries 257 against 227), and the entries are where they do not (8 x 8 x 1000, up to 8 entries 32 against 40).
+// wavefronts, 32 with three); with seven or eight only two wavefronts hold them all (500: 60 against 92).  Beyond that it is
+// the rows that decide, and they are not known here.  Two wavefronts (512 workgroups at a time) against three (768), 8 heads of
+// 1024 keys with block rows of 3, of 6 to 8 and of 16 entries, us:
+//   512 workgroups    11.7 / 11.3    17.1 / 27.2    58 / 67        one round of either
+//   640               19.5 / 13.0    28.1 / 31.5    98 / 83        two rounds against one
+//   1024              22.0 / 20.5    32.1 / 45.8   118 / 124       two of either
+//   2048              42.4 / 32.8    60 / 74       231 / 217       four against three
+// So the entries are held up to 1024 workgroups, at a price between 513 and 768.
 hipError_t launch_64(const FwdArgs& a, float* tau_out, hipStream_t stream)
 {
     const int tiles = (a.Lk + 63) / 64;
@@ -670,7 +682,7 @@ hipError_t launch_entmax15_fwd(const FwdArgs& a, float* tau_out, hipStream_t str
     switch (a.D) {
         case 32:
             if (a.Lk <= 128) return launch<32, 2, 0, 4>(a, tau_out, stream);   // as in launch_64
-            return launch<32, 6, 2, 3>(a, tau_out, stream);
+            return launch<32, 6, 4, 3>(a, tau_out, stream);
         case 64: return launch_64(a, tau_out, stream);
         case 128: return launch<128, 8, 4, 2>(a, tau_out, stream);
     }

@@ -81,7 +81,7 @@ hipError_t launch_merge_splits(const FwdArgs& a, hipStream_t stream);
 // a few queries against many keys, a.splits workgroups per query, no matrix cores (ap_attn_decode.hip)
 hipError_t launch_fwd_decode(const FwdArgs& a, hipStream_t stream);
 
-// ---- 1.5-entmax forward (ap_attn_entmax.hip): bf16, block 64x64, plain layout walk
+// ---- 1.5-entmax forward (ap_attn_entmax.hip): bf16, block 64x64, tiles or schedule entries
 hipError_t launch_entmax15_fwd(const FwdArgs& a, float* tau_out, hipStream_t stream);
 
 // ---- backward pass (ap_layout_transpose.hip, ap_attn_bwd.hip)

@@ -265,3 +265,18 @@ def test_entmax_block_rows_without_entries_are_positive_zeros(Lk, D):
         torch.cuda.synchronize()
         assert not O[:, :, 64:128].contiguous().view(torch.int16).any() and not O[:, 2].contiguous().view(torch.int16).any()
         assert bool((tau[:, :, 64:128] == float("inf")).all()) and bool((tau[:, 2] == float("inf")).all())
+
+
+@pytest.mark.parametrize("D", [32, 64, 128])
+@pytest.mark.parametrize("tiles", [63, 64, 65, 66, 130])
+def test_entmax_starts_of_more_entries_than_a_wavefront_has_lanes(tiles, D):
+    """Block rows of 63 to 130 entries, the last of them gathered (with the schedule), odd and even numbers."""
+    full = tiles - 2
+    Lk = 64 * full + 1000
+    Q, K, V = rand_qkv(tiles, 1, 1, 64, Lk, D, gain=1.5)
+    mask = synth.random_mask(1, 64, Lk, 0.5, seed=tiles)
+    mask[:, :, 64 * full:] = 0
+    mask[:, 1::2, 64 * full + 7::11] = 1                               # 91 isolated keys: two gathered entries
+    sched = ap.ap_build_schedule(ap.ap_build_layout(torch.from_numpy(mask).cuda(), 64, 64), causal=False)
+    assert int(sched.cnt[0].item()) == tiles
+    run_entmax(Q, K, V, mask, False)

@@ -12,7 +12,7 @@ from paper_2012_02030_amd import binding as ap
 from paper_2012_02030_amd import synth
 
 from gpu_util import assert_grad_close, to_device
-from test_gpu_bwd import BWD_CASES, rand_inputs
+from test_gpu_bwd import BWD_CASES, rand_inputs, run_bwd
 
 pytestmark = pytest.mark.gpu
 
@@ -153,6 +153,26 @@ def test_scheduled_backward_matches_oracle(case):
     B, H, Lq, Lk, D, causal, density = case
     Q, K, V, dO = rand_inputs(Lq + Lk + D, B, H, Lq, Lk, D)
     mask = synth.random_mask(H, Lq, Lk, density, seed=D + Lq)
+    run_bwd_sched(Q, K, V, dO, mask, causal, which=("both", "row", "col"))
+
+
+# Calls that the one-launch kernel of short sequences leaves to the general ones at D <= 64: a side longer than 256, few keys
+# per query, more than 128 queries of few pairs; one tile, cut tiles, queries without keys.
+BESIDE_SHORT = [
+    # B, H, Lq, Lk, causal, density
+    (1, 2, 64, 257, True, 0.4), (2, 2, 1, 300, True, 0.5), (1, 2, 257, 300, True, 0.2), (1, 2, 320, 100, False, 0.3),
+    (1, 2, 65, 30, False, 0.5), (2, 2, 250, 40, False, 0.1), (1, 1, 65, 1, False, 1.0), (2, 2, 200, 200, True, 0.3),
+    (1, 3, 129, 256, True, 0.02),
+]
+
+
+@pytest.mark.parametrize("D", [32, 64])
+@pytest.mark.parametrize("case", BESIDE_SHORT, ids=lambda c: "B%d_H%d_%dx%d_%s_%g" % (c[:4] + ("causal" if c[4] else "full", c[5])))
+def test_general_backward_beside_the_short_kernel(case, D):
+    B, H, Lq, Lk, causal, density = case
+    Q, K, V, dO = rand_inputs(Lq + Lk + D + 1, B, H, Lq, Lk, D)
+    mask = synth.random_mask(H, Lq, Lk, density, seed=D + Lk)
+    run_bwd(Q, K, V, dO, mask, causal)
     run_bwd_sched(Q, K, V, dO, mask, causal, which=("both", "row", "col"))
 
 

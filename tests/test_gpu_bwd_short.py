@@ -8,6 +8,7 @@ from paper_2012_02030_amd import binding as ap
 from paper_2012_02030_amd import synth
 
 from test_gpu_bwd import run_bwd
+from test_gpu_bwd_sched import nan_padded
 
 pytestmark = pytest.mark.gpu
 
@@ -95,3 +96,22 @@ def test_tiles_that_nobody_keeps_are_never_used(B, H, L, D):
     for a, b in zip(grads(), want):
         assert torch.equal(a, b)                                       # (NaN equals nothing)
     assert not want[0][:, :, :64].any() and not want[1][:, :, 64:128].any() and not want[2][:, :, 64:128].any()
+
+
+@pytest.mark.parametrize("D", [32, 64])
+@pytest.mark.parametrize("B,H,Lq,Lk", [(2, 2, 50, 40), (2, 2, 100, 97), (24, 8, 200, 230)])
+def test_rows_behind_the_last_row_are_never_used(B, H, Lq, Lk, D):
+    """In all three forms: NaN behind row L - 1 of Q, K, V, O and dO changes no bit of a gradient."""
+    q, k, v, g = (torch.from_numpy(rand(9 + i, B, H, L, D)).to(torch.bfloat16).cuda()
+                  for i, L in enumerate((Lq, Lk, Lk, Lq)))
+    mask = synth.random_mask(H, Lq, Lk, 0.4, seed=Lq)
+    mask[:, :, Lk - 1] = 1
+    mask[:, Lq - 1, :] = 1
+    lay = ap.ap_build_layout(torch.from_numpy(mask).cuda(), 64, 64)
+    lt = ap.ap_build_layout_transpose(lay)
+    O, lse = ap.ap_sparse_attn_fwd(q, k, v, lay)
+    want = ap.ap_sparse_attn_bwd(q, k, v, O, g, lse, lay, lt)
+    got = ap.ap_sparse_attn_bwd(*(nan_padded(x) for x in (q, k, v, O, g)), lse, lay, lt)
+    torch.cuda.synchronize()
+    for a, b in zip(got, want):
+        assert torch.equal(a, b)                                       # (NaN equals nothing)

@@ -22,6 +22,8 @@ FLAGS = [
     # leading scalar kernel arguments (up to 16 dwords) arrive in registers when a wavefront starts
     "-mllvm", "-amdgpu-kernarg-preload-count=16",
     "-Wall", "-Wno-unused-command-line-argument",
+    # a constant that does not fit the type it is converted to is an error, not a value
+    "-Werror=literal-conversion",
     # the LDS-direct load helper names M0 as clobbered; the compiler remarks that M0 is a reserved
     # register (it never keeps a value of its own live in it across a statement)
     "-Wno-inline-asm",

@@ -37,6 +37,7 @@
 // Float bit patterns are mapped to unsigned keys whose integer order is the numeric order
 // (sign bit flipped for non-negative values, all bits flipped for negative ones; -0 counts as +0).
 #include <hip/hip_runtime.h>
+#include <algorithm>
 #include <stdint.h>
 
 #include "ap_internal.h"
@@ -973,15 +974,16 @@ hipError_t launch_prune_mask(const float* abar, int H, int Lq, int Lk, int causa
     // entries that one workgroup of the exact pass may meet: it counts them in 32 bits
     const double per_wg = (double)((sweep_wgs + grid - 1) / grid) * (kSweepThreads / 64) * (double)unit_len;
     const bool refine = want > (double)n / kRefineShare && n > 2 * kSample && per_wg < 4294967296.0;
+    // (std::min: the min of host code takes ints, and of a double beyond them anything may come)
     const unsigned long long size =
-        want > (double)kSample && !refine ? (unsigned long long)min(min(want, (double)n), 2147483648.0) : kSample;
-    s.stride = (uint32_t)min(max(n / size, 1ull), 1ull << 30);
+        want > (double)kSample && !refine ? (unsigned long long)std::min({want, (double)n, 2147483648.0}) : kSample;
+    s.stride = (uint32_t)std::min(std::max(n / size, 1ull), 1ull << 30);
     s.per_unit = (uint32_t)(((unit_len + 15) / 16 + s.stride - 1) / s.stride);
     s.slots = (unsigned long long)w.units * s.per_unit;
-    const unsigned sgrid = (unsigned)min(128ull, (s.slots * 4 + kThreads - 1) / kThreads);
+    const unsigned sgrid = (unsigned)std::min(128ull, (s.slots * 4 + kThreads - 1) / kThreads);
     // the exact levels take 128 KB of LDS: one workgroup of 16 wavefronts per compute unit
     const unsigned egrid = (unsigned)min(256, (w.units + kThreads / 64 - 1) / (kThreads / 64));
-    const unsigned cgrid = (unsigned)min(64ull, (n + kThreads - 1) / kThreads);
+    const unsigned cgrid = (unsigned)std::min(64ull, (n + kThreads - 1) / kThreads);
 
     hipLaunchKernelGGL(sample_coarse_kernel, dim3(sgrid), dim3(kThreads), 0, stream, abar, workspace, H, Lq, Lk, causal,
                        s.slots, s.per_unit, s.stride);

@@ -335,11 +335,11 @@ ap_status ap_sparse_attn_decode(const void *Q, const void *K, const void *V, voi
  * O = 0 and tau = +infinity.
  *
  *   tau           out, float [B, H, Lq] contiguous, or NULL
- *   everything else as in ap_sparse_attn_fwd; a block row with more than 64 schedule entries
- *   walks the layout's tiles instead (same result)
+ *   everything else as in ap_sparse_attn_fwd
  *
- * Supported: dtype = AP_BF16, block_m = block_n = 64, D in {32, 64, 128}.  One launch; the tiles of
- * a block row are swept several times (scores are recomputed, not stored).  Deterministic.
+ * Supported: dtype = AP_BF16, block_m = block_n = 64, D in {32, 64, 128}.  One launch; the scores of a
+ * block row's first tiles or entries (2 to 8 of them) stay in registers, those of the others are formed
+ * again in every sweep.  Deterministic.
  * ------------------------------------------------------------------------------------------- */
 ap_status ap_sparse_attn_entmax15_fwd(const void *Q, const void *K, const void *V, void *O, float *tau,
                                       ap_dtype dtype, int B, int H, int Lq, int Lk, int D,
@@ -384,7 +384,8 @@ ap_status ap_sparse_attn_entmax15_fwd(const void *Q, const void *K, const void *
  * Supported: dtype = AP_BF16, D in {32, 64, 128}, block_m = block_n = 64.  Three launches (with a row
  * schedule, below, two; of short sequences, at most 256 queries and keys with D <= 64, one).
  * Deterministic (no floating-point atomics): dQ is formed per block row, dK and dV per block
- * column, each recomputing the scores of its tiles.
+ * column, each recomputing the scores of its tiles; the one launch forms all three from the same
+ * scores, per example and head.
  * ------------------------------------------------------------------------------------------- */
 ap_status ap_build_layout_transpose(const int32_t *row_ptr, const int32_t *col_idx, int H, int Lq,
                                     int Lk, int block_m, int block_n, int64_t cap, int32_t *col_ptr,

@@ -43,7 +43,6 @@ __global__ __launch_bounds__(64 * N, 2) void bwd_short_kernel(
     uint16_t* const Gs = smem + 2 * N * BLOCK;
     uint16_t* const Vs = smem + 3 * N * BLOCK;
     uint16_t* const dSs = Vs;
-    lds_u16* lds = (lds_u16*)smem;
 
     const int blk = block_index();
     if (blk >= total) return;
@@ -85,7 +84,7 @@ __global__ __launch_bounds__(64 * N, 2) void bwd_short_kernel(
     uint4 o[NO];
 #pragma unroll
     for (int u = 0; u < NO; ++u) o[u] = o_piece(tid + u * nt);
-    float lse = tid < a.Lq ? a.lse[stat_base + tid] : -INFINITY;
+    const float lse = tid < a.Lq ? a.lse[stat_base + tid] : -INFINITY;
 
     // ---- kept keys of every query, causal limit included: tile after tile of the head, one per wavefront, the
     // first two of them ahead of time
@@ -119,10 +118,7 @@ __global__ __launch_bounds__(64 * N, 2) void bwd_short_kernel(
     const Tile tile0 = fetch_tile(first_tile + wave), tile1 = fetch_tile(first_tile + wave + nk);
 
     for (int i = tid; i < nk * 32 * N; i += nt) s_word[0][i] = 0;
-    for (int q = tid; q < 32 * nq; q += nt) {
-        if (q >= nt) lse = q < a.Lq ? a.lse[stat_base + q] : -INFINITY;
-        s_lse[q] = lse == -INFINITY ? INFINITY : lse * kLog2e;
-    }
+    if (tid < 32 * nq) s_lse[tid] = lse == -INFINITY ? INFINITY : lse * kLog2e;   // 32 nq <= 64 nk threads (bwd_short_fits)
     __syncthreads();
     put_tile(first_tile + wave, tile0);
     put_tile(first_tile + wave + nk, tile1);
@@ -224,7 +220,8 @@ __global__ __launch_bounds__(64 * N, 2) void bwd_short_kernel(
 #pragma unroll
                 for (int g = 0; g < 4; ++g) {
                     const bf16x8 x = dd[j][g >> 1];
-                    const bf16x4 v = (g & 1) ? __builtin_shufflevector(x, x, 4, 5, 6, 7) : __builtin_shufflevector(x, x, 0, 1, 2, 3);
+                    const bf16x4 v = (g & 1) ? __builtin_shufflevector(x, x, 4, 5, 6, 7)
+                                             : __builtin_shufflevector(x, x, 0, 1, 2, 3);
                     *reinterpret_cast<bf16x4*>(dSs + (j * N + wave) * DS + n * 32 + (g ^ swz_u<32>(n)) * 8 + 4 * hh) = v;
                 }
         }

@@ -19,8 +19,8 @@
 //
 // Bound by the latency of its chain of loads (row bounds, tile words, key list, K and V rows) and by the
 // workgroup with the most keys: B4 H16 D128, 1600 of 16001 keys kept, 4 splits 15.0 us (52 MB of K and V rows,
-// 3.5 TB/s; 15.5 with the arguments read from memory first).  With contiguous shares of the tiles, one thread per tile for the list and four keys in flight
-// per stream 20.9 us.
+// 3.5 TB/s; 15.5 with the arguments read from memory first).  With contiguous shares of the tiles, one thread per
+// tile for the list and four keys in flight per stream 20.9 us.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -277,7 +277,8 @@ hipError_t launch_fwd_decode(const FwdArgs& a, hipStream_t stream)
     const int nQB = (a.Lq + a.block_m - 1) / a.block_m;
     const dim3 grid((unsigned)((long long)a.B * a.H * a.Lq * a.splits)), block(64 * kWaves);
     const auto run = [&](auto kernel) {
-        hipLaunchKernelGGL(kernel, grid, block, 0, stream, a.row_ptr, a.col_idx, a.bitmaps, a.splits, a.Lq, a.H, a.block_m, nQB, a);
+        hipLaunchKernelGGL(kernel, grid, block, 0, stream, a.row_ptr, a.col_idx, a.bitmaps, a.splits, a.Lq, a.H,
+                           a.block_m, nQB, a);
     };
     switch (a.D) {
         case 32: run(decode_kernel<32>); break;

@@ -22,11 +22,12 @@
 //               tau, every step confirmed.
 //
 // A workgroup of four wavefronts takes a block row, a wavefront a 32 x 32 quarter of every entry.  The scores of up to
-// E (5 to 8) entries stay in registers, 16 per entry and lane: K is read once, a Newton step is three vector
+// E (2 to 8) entries stay in registers, 16 per entry and lane: K is read once, a Newton step is three vector
 // instructions per score and an exchange of the key halves through LDS, and V travels under the steps.  Of longer
 // block rows the first HL entries are held and the others' scores are formed again in every sweep, as all were before.
 // B4 H16 L2048 (3.9 entries a block row) D128 112 -> 64 us, D64 78 -> 42; B32 H8 117 x 141 D64 25 -> 11.4; 32 entries
-// a block row (nothing pruned) D128 735 -> 680, D64 541 -> 444; without schedules (up to 32 tiles, every tenth key) D128 487 -> 361.
+// a block row (nothing pruned) D128 735 -> 680, D64 541 -> 444; without schedules (up to 32 tiles, every tenth key) D128
+// 487 -> 361.
 //
 // Same operand layouts and LDS-direct loads as the softmax kernel; walks the layout's 64x64 tiles or, if given, the
 // entries of its visit schedule.
@@ -71,36 +72,6 @@ __device__ __forceinline__ void product_32(const uint16_t* T, int row, int k_swz
     for (int kk = 0; kk < KSTEPS; ++kk) {
         if (kk + AHEAD < KSTEPS) __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
         __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-    }
-}
-
-// The same for 32 rows of two tiles, their matrix instructions in turn.
-template <int D>
-__device__ __forceinline__ void product_32x2(const uint16_t* T0, const uint16_t* T1, int row, int k_swz,
-                                             const bf16x8* b, f32x16& s0, f32x16& s1)
-{
-    constexpr int KSTEPS = D / 16;
-    constexpr int AHEAD = KSTEPS < 3 ? KSTEPS : 3;
-#pragma unroll
-    for (int i = 0; i < 16; ++i) s0[i] = s1[i] = 0.f;
-    bf16x8 x0[KSTEPS], x1[KSTEPS];
-    auto read = [&](int kk) {
-        x0[kk] = *reinterpret_cast<const bf16x8*>(T0 + row * D + ((2 * kk) ^ k_swz) * 8);
-        x1[kk] = *reinterpret_cast<const bf16x8*>(T1 + row * D + ((2 * kk) ^ k_swz) * 8);
-    };
-#pragma unroll
-    for (int kk = 0; kk < AHEAD; ++kk) read(kk);
-#pragma unroll
-    for (int kk = 0; kk < KSTEPS; ++kk) {
-        if (kk + AHEAD < KSTEPS) read(kk + AHEAD);
-        s0 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(x0[kk], b[kk], s0, 0, 0, 0);
-        s1 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(x1[kk], b[kk], s1, 0, 0, 0);
-    }
-    __builtin_amdgcn_sched_group_barrier(0x100, 2 * AHEAD, 0);
-#pragma unroll
-    for (int kk = 0; kk < KSTEPS; ++kk) {
-        if (kk + AHEAD < KSTEPS) __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);
-        __builtin_amdgcn_sched_group_barrier(0x008, 2, 0);
     }
 }
 
@@ -656,8 +627,9 @@ hipError_t launch(const FwdArgs& a, float* tau_out, hipStream_t stream)
 
 // No block row has more entries than there are key tiles.  Registers go into entries held or into a third wavefront per
 // SIMD.  With up to two tiles two entries are all there is, and a fourth wavefront fits (the same at D = 32: B256 H8 40 x 40
-// 20.7 us with room for six entries, 16.5 with two).  At D = 64 with up to six tiles every row fits either way (16 x 12 x 330, all tiles full: 42 us with two
-// wavefronts, 32 with three); with seven or eight only two wavefronts hold them all (500: 60 against 92).  Beyond that it is
+// 20.7 us with room for six entries, 16.5 with two).  At D = 64 with up to six tiles every row fits either way (16 x 12 x
+// 330, all tiles full: 42 us with two wavefronts, 32 with three); with seven or eight only two wavefronts hold them all
+// (500: 60 against 92).  Beyond that it is
 // the rows that decide, and they are not known here.  Two wavefronts (512 workgroups at a time) against three (768), 8 heads of
 // 1024 keys with block rows of 3, of 6 to 8 and of 16 entries, us:
 //   512 workgroups    11.7 / 11.3    17.1 / 27.2    58 / 67        one round of either

@@ -577,9 +577,9 @@ hipError_t launch_one(const FwdArgs& a, hipStream_t stream)
 }
 
 // O = sum_s exp(lse_s - lse) O_s with lse = ln sum_s exp(lse_s): one thread per (row, 4 elements), 8 chunks
-// in flight at a time (bound by memory latency: 8 chunks of 4096 rows
-// of 128 take 4.5 us, 5.4 with the arguments read from memory first, 9.0 with one chunk after another).  LOOK: only the chunks whose log-sum-exp says that they
-// hold something are read.
+// in flight at a time (bound by memory latency: 8 chunks of 4096 rows of 128 take 4.5 us, 5.4 with the arguments read
+// from memory first, 9.0 with one chunk after another).  LOOK: only the chunks whose log-sum-exp says that they hold
+// something are read.
 // The leading arguments repeat fields of `a`, as above.
 template <int D, bool LOOK>
 __global__ __launch_bounds__(256) void merge_splits_kernel(const float* __restrict__ p_part_o,

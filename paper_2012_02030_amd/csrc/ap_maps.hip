@@ -59,7 +59,8 @@ __global__ __launch_bounds__(64 * NW, 4) void row_lse_kernel(MapArgs a, int nQB)
 
     // All workgroups of a call of ordinary size are resident at once and a compute unit gets every 32nd of an
     // XCD's, so long rows first would give some of them long rows only (B4 H16 L2048 D128: 75 us, 68 in this
-    // order; 55 with four wavefronts per SIMD, which 128 registers allow): the rows' order is reversed in every other round of 32.
+    // order; 55 with four wavefronts per SIMD, which 128 registers allow): the rows' order is reversed in every other
+    // round of 32.
     const int bid = xcd_contiguous(blockIdx.x, gridDim.x);
     const int per_xcd = (gridDim.x + 7) / 8;
     const int group = bid / nQB, j = bid % nQB;

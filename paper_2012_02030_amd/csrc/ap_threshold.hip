@@ -990,12 +990,18 @@ hipError_t launch_prune_mask(const float* abar, int H, int Lq, int Lk, int causa
     hipLaunchKernelGGL(sample_fine_kernel, dim3(sgrid), dim3(kThreads), 0, stream, abar, workspace, H, Lq, Lk, causal,
                        s.slots, s.per_unit, s.stride, refine ? 1 : 0);
     if (refine)
-        hipLaunchKernelGGL(mask_sweep_kernel, dim3(grid), dim3(kSweepThreads), 0, stream, abar, workspace, H, Lq, Lk, causal, mask, tau_out, 1);
-    hipLaunchKernelGGL(mask_sweep_kernel, dim3(grid), dim3(kSweepThreads), 0, stream, abar, workspace, H, Lq, Lk, causal, mask, tau_out, 0);
+        hipLaunchKernelGGL(mask_sweep_kernel, dim3(grid), dim3(kSweepThreads), 0, stream, abar, workspace, H, Lq, Lk, causal,
+                           mask, tau_out, 1);
+    hipLaunchKernelGGL(mask_sweep_kernel, dim3(grid), dim3(kSweepThreads), 0, stream, abar, workspace, H, Lq, Lk, causal,
+                       mask, tau_out, 0);
     const unsigned lgrid = max(egrid, cgrid);
-    hipLaunchKernelGGL(select_level_kernel<0>, dim3(lgrid), dim3(kThreads), 0, stream, abar, workspace, H, Lq, Lk, causal, mask, tau_out, cgrid);
-    hipLaunchKernelGGL(select_level_kernel<1>, dim3(lgrid), dim3(kThreads), 0, stream, abar, workspace, H, Lq, Lk, causal, mask, tau_out, cgrid);
-    if (mask) hipLaunchKernelGGL(mask_finish_kernel, dim3(256), dim3(kSweepThreads), 0, stream, abar, workspace, H, Lq, Lk, causal, mask);
+    hipLaunchKernelGGL(select_level_kernel<0>, dim3(lgrid), dim3(kThreads), 0, stream, abar, workspace, H, Lq, Lk, causal,
+                       mask, tau_out, cgrid);
+    hipLaunchKernelGGL(select_level_kernel<1>, dim3(lgrid), dim3(kThreads), 0, stream, abar, workspace, H, Lq, Lk, causal,
+                       mask, tau_out, cgrid);
+    if (mask)
+        hipLaunchKernelGGL(mask_finish_kernel, dim3(256), dim3(kSweepThreads), 0, stream, abar, workspace, H, Lq, Lk, causal,
+                           mask);
     return hipGetLastError();
 }
 

@@ -13,9 +13,11 @@
 //      dword of a V row per lane, 32 lanes to a row.
 // No tile goes through LDS; it holds the lists and, at the end, the four partial results for the merge.
 //
-// What bounds it: the matrix pipe at 64 cycles per instruction (4 096 cycles per chunk and wavefront at
-// D = 64), so the packing, which leaves far tiles their few used columns, is worth more than any reuse of
-// K and V, and four wavefronts per 32 queries rather than one, because a long causal row is one chain.
+// What bounds it: each wavefront's chain (words, lists, K rows, products at 64 cycles per instruction or 4 096
+// per chunk at D = 64, V rows), with no unit full.  B8 H8 L500 D64, 10 % kept, 16.7 us: the matrix pipe is busy for a third
+// of the kernel's cycles and the vector units for a quarter, and wavefronts wait for memory or barriers during 46 %
+// of their time.  Hence the packing, which leaves far tiles their few used columns, and four wavefronts per
+// 32 queries rather than one, because a long causal row is one chain.
 // With one query per lane and K, V broadcast from LDS in vector arithmetic the same call was bound
 // by LDS reads: B8 H8 L500 D64, 5 % kept, 69 us, now 18 us; B4 H8 L1024 D128 437 us, now 47 us; B1 H2 L64
 // D32 (launch and chain of loads) 9.7 us, now 5.1 us.

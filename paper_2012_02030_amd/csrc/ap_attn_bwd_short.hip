@@ -136,11 +136,23 @@ __global__ __launch_bounds__(64 * N, 2) void bwd_short_kernel(
             kept_some |= w.x | w.y | w.z | w.w;
         }
     const uint64_t live_blocks = __ballot(kept_some != 0);
+    // keys of this wavefront's block that some query keeps: the OR over i
+    uint32_t used_keys = kept_some | (uint32_t)__builtin_amdgcn_update_dpp(0, (int)kept_some, 0x128, 0xf, 0xf, false);   // row_ror:8
+    if constexpr (N > 2) {
+        const auto r = __builtin_amdgcn_permlane16_swap(used_keys, used_keys, false, false);
+        used_keys = r[0] | r[1];
+    }
+    if constexpr (N > 4) {
+        const auto r = __builtin_amdgcn_permlane32_swap(used_keys, used_keys, false, false);
+        used_keys = r[0] | r[1];
+    }
+    used_keys = (uint32_t)__builtin_amdgcn_readlane((int)used_keys, wave);
 
     // ---- delta_i = <dO_i, O_i>
     auto add_delta = [&](int idx, const uint4& x) {
         const int row = idx / CPR, c = idx % CPR;
         const uint4 g = *reinterpret_cast<const uint4*>(Gs + row * D + (c ^ swz_u<D>(row)) * 8);
+        const float row_lse = s_lse[row];
         const uint32_t ow[4] = {x.x, x.y, x.z, x.w}, gw[4] = {g.x, g.y, g.z, g.w};
         float d = 0.f;
 #pragma unroll
@@ -149,7 +161,7 @@ __global__ __launch_bounds__(64 * N, 2) void bwd_short_kernel(
             d = fmaf(__uint_as_float(ow[k] & 0xffff0000u), __uint_as_float(gw[k] & 0xffff0000u), d);
         }
         d = group_sum<CPR>(d);
-        if (c == 0) s_delta[row] = row < a.Lq ? d : 0.f;
+        if (c == 0) s_delta[row] = row_lse != INFINITY ? d : 0.f;
     };
     const int pieces = 32 * nq * CPR;                        // a multiple of 64: a wavefront has all or none of a step
 #pragma unroll
@@ -157,6 +169,22 @@ __global__ __launch_bounds__(64 * N, 2) void bwd_short_kernel(
         if (tid + u * nt < pieces) add_delta(tid + u * nt, o[u]);
     for (int idx = tid + NO * nt; idx < pieces; idx += nt) add_delta(idx, o_piece(idx));
     const int k_swz = hh ^ swz_u<D>(n);
+    // Rows of keys that nobody keeps and of queries that keep nothing become zeros: a tile brings them too, nobody need have
+    // written them, and they would be multiplied by exact zeros (entries of a schedule do not hold them).
+    const uint4 zero = make_uint4(0, 0, 0, 0);
+    if (!((used_keys >> n) & 1))                             // the pieces that this lane reads below
+#pragma unroll
+        for (int kk = 0; kk < KSTEPS; ++kk) {
+            const int at = wave * BLOCK + n * D + ((2 * kk) ^ k_swz) * 8;
+            *reinterpret_cast<uint4*>(Ks + at) = zero;
+            *reinterpret_cast<uint4*>(Vs + at) = zero;
+        }
+    if (tid < a.Lq && lse == -INFINITY)                      // (their delta is zero whatever is read of them meanwhile)
+#pragma unroll
+        for (int c = 0; c < CPR; ++c) {
+            *reinterpret_cast<uint4*>(Qs + tid * D + c * 8) = zero;
+            *reinterpret_cast<uint4*>(Gs + tid * D + c * 8) = zero;
+        }
     bf16x8 kreg[KSTEPS], vreg[KSTEPS];                       // K^T and V^T operands
     read_operand<D>(Ks + wave * BLOCK, n, k_swz, kreg);
     read_operand<D>(Vs + wave * BLOCK, n, k_swz, vreg);

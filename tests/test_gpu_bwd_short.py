@@ -98,6 +98,38 @@ def test_tiles_that_nobody_keeps_are_never_used(B, H, L, D):
     assert not want[0][:, :, :64].any() and not want[1][:, :, 64:128].any() and not want[2][:, :, 64:128].any()
 
 
+@pytest.mark.parametrize("causal", [False, True])
+@pytest.mark.parametrize("D", [32, 64])
+@pytest.mark.parametrize("B,H,Lq,Lk", [(2, 2, 50, 60), (1, 1, 91, 91), (2, 2, 128, 128), (24, 8, 200, 230)])
+def test_keys_that_nobody_keeps_are_never_used(B, H, Lq, Lk, D, causal):
+    """Single keys that no query keeps and single queries that keep nothing, inside tiles of the layout, with schedules that do
+    not hold them: whatever stands there (NaN, infinity) changes no bit of a gradient."""
+    Q, K, V, dO = (rand(20 + i, B, H, L, D) for i, L in enumerate((Lq, Lk, Lk, Lq)))
+    mask = synth.random_mask(H, Lq, Lk, 0.1, seed=Lq + D)
+    mask[:, np.arange(Lq), np.arange(Lq) % Lk] = 1
+    keys, queries = [0, 7, 33, Lk - 1], [0, 5, 40, Lq - 1]
+    mask[:, :, keys] = 0
+    mask[:, queries] = 0
+    q, k, v, g = (torch.from_numpy(x).to(torch.bfloat16).cuda() for x in (Q, K, V, dO))
+    lay = ap.ap_build_layout(torch.from_numpy(mask).cuda(), 64, 64)
+    lt = ap.ap_build_layout_transpose(lay)
+    sched, cs = ap.ap_build_schedule(lay, causal=causal), ap.ap_build_col_schedule(lay, lt, causal=causal)
+
+    def grads():
+        got = ap.ap_sparse_attn_bwd(q, k, v, O, g, lse, lay, lt, causal=causal, sched=sched, col_sched=cs)
+        torch.cuda.synchronize()
+        return got
+
+    O, lse = ap.ap_sparse_attn_fwd(q, k, v, lay, causal=causal, sched=sched)
+    want = grads()
+    for x, rows in ((k, keys), (v, keys), (q, queries), (g, queries)):
+        x[:, :, rows] = float("nan")
+    v[:, :, keys[1]] = float("inf")
+    for a, b in zip(grads(), want):
+        assert torch.equal(a, b)                                       # (NaN equals nothing)
+    assert not want[0][:, :, queries].any() and not want[1][:, :, keys].any() and not want[2][:, :, keys].any()
+
+
 @pytest.mark.parametrize("D", [32, 64])
 @pytest.mark.parametrize("B,H,Lq,Lk", [(2, 2, 50, 40), (2, 2, 100, 97), (24, 8, 200, 230)])
 def test_rows_behind_the_last_row_are_never_used(B, H, Lq, Lk, D):
